@@ -1,0 +1,166 @@
+// Exact dot products of fp16 rows on the integer matrix cores.
+//
+// The prompt phase needs q . k to fp64 precision (the scores decide which tokens are kept), and the
+// fp64 matrix instruction is the slowest way to it on this chip: 64 cycles per 16 x 16 x 4 block,
+// 32 times the time per multiply of v_mfma_i32_16x16x64_i8, and no vector instruction runs beside it.
+// A half is a multiple of 2^-24, so below kDigitMax a value times 2^24 is an integer of 31 bits
+// and sign, written here as four signed base-256 digits (each in [-128, 127]):
+//     x 2^24 = d0 + 256 d1 + 256^2 d2 + 256^3 d3,      |d3| <= 127.
+// A dot product is then sixteen dot products of digit planes, whose 32-bit integer sums are exact;
+// planes with the same weight share an accumulator (seven groups, group s = sum of di dj, i + j = s).
+// With D <= 128 the largest sums are
+//     |g6| <= 128 * 127^2, |g5| <= 128 * 2 * 127 * 128, |g4| <= 128 (2 * 127 * 128 + 128^2),
+//     |g3| <= 128 (2 * 127 * 128 + 2 * 128^2), |g2| <= 128 * 3 * 128^2,
+// so that 256 g6 + g5, 256 g3 + g2 and 256 g1 + g0 fit 32 bits (the tightest: 2145386496): four
+// integers per product, each exact in fp64, joined by four fused multiply-adds that also apply the
+// scale and the shift of the exponent.  Four roundings in all, against D / 4 and more in the
+// fp64 matrix sum.
+//
+// Layout of v_mfma_i32_16x16x64_i8 (wave64, lane = 16 g + c): A row / B column c takes the 16
+// consecutive k = 16 g .. 16 g + 15 of a 64-wide block from lane (g, c); result register w of lane
+// (g, c) is element [4 g + w][c].
+#pragma once
+
+#include "lessdec_common.h"
+
+namespace lessdec {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+// Values of this magnitude and above (infinities and NaN among them) have no digits: the tile that
+// holds one is multiplied in fp64 (dot_tile_f64).  127.0 as a half.
+constexpr unsigned kDigitMax = 0x57F0;
+
+// Joined sums of one lane's four elements of a tile.
+struct DotParts {
+  v4i p65, p4, p32, p10;
+};
+// weight of the least digit pair in a dot product
+constexpr double kDotUnit = 0x1p-48;
+
+// Digits of 4 halves (two dwords): plane p's dword holds digit p of the four.
+__device__ inline void digits_of4(unsigned h01, unsigned h23, unsigned (&plane)[4])
+{
+  auto digit_word = [](unsigned short h) {
+    const float f = fmaf((float)__builtin_bit_cast(_Float16, h), 0x1p24f, 0.f);   // exact
+    // adding 128 to every digit makes the digits the bytes of the sum; the sign bits flip back below
+    return (unsigned)(int)f + 0x80808080u;
+  };
+  const unsigned u0 = digit_word((unsigned short)h01), u1 = digit_word((unsigned short)(h01 >> 16));
+  const unsigned u2 = digit_word((unsigned short)h23), u3 = digit_word((unsigned short)(h23 >> 16));
+  const unsigned a = __builtin_amdgcn_perm(u1, u0, 0x05010400u), b = __builtin_amdgcn_perm(u1, u0, 0x07030602u);
+  const unsigned c = __builtin_amdgcn_perm(u3, u2, 0x05010400u), d = __builtin_amdgcn_perm(u3, u2, 0x07030602u);
+  plane[0] = __builtin_amdgcn_perm(c, a, 0x05040100u) ^ 0x80808080u;
+  plane[1] = __builtin_amdgcn_perm(c, a, 0x07060302u) ^ 0x80808080u;
+  plane[2] = __builtin_amdgcn_perm(d, b, 0x05040100u) ^ 0x80808080u;
+  plane[3] = __builtin_amdgcn_perm(d, b, 0x07060302u) ^ 0x80808080u;
+}
+
+// Whether any of the N dwords holds a half without digits.
+template <int N>
+__device__ inline bool without_digits(const unsigned (&w)[N])
+{
+  typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+  us2 m = {0, 0};
+#pragma unroll
+  for (int i = 0; i < N; ++i) m = __builtin_elementwise_max(m, __builtin_bit_cast(us2, w[i] & 0x7fff7fffu));
+  return m.x >= kDigitMax || m.y >= kDigitMax;
+}
+
+// A row of D halves in operand order: the lane's 16 elements of every 64-wide block, all planes.
+template <int D>
+struct RowDigits {
+  static constexpr int KC = D / 64;
+  v4i d[KC][4];
+  // returns whether the lane's elements all have digits
+  __device__ inline bool load(const __half *row, int g)
+  {
+    bool bad = false;
+#pragma unroll
+    for (int kc = 0; kc < KC; ++kc) {
+      const uint4 x = reinterpret_cast<const uint4 *>(row + 64 * kc + 16 * g)[0];
+      const uint4 y = reinterpret_cast<const uint4 *>(row + 64 * kc + 16 * g)[1];
+      const unsigned w[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+      bad |= without_digits(w);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        unsigned p[4];
+        digits_of4(w[2 * i], w[2 * i + 1], p);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) d[kc][q][i] = (int)p[q];
+      }
+    }
+    return !bad;
+  }
+};
+
+// One 64-wide block and one digit plane `pa` of the A operand against all planes of B.
+__device__ inline void dot_planes(const v4i a, const v4i (&b)[4], int pa, v4i (&s)[7])
+{
+#pragma unroll
+  for (int pb = 0; pb < 4; ++pb) s[pa + pb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b[pb], s[pa + pb], 0, 0, 0);
+}
+__device__ inline DotParts dot_join(const v4i (&s)[7])
+{
+  DotParts r;
+  r.p65 = (s[6] << 8) + s[5];
+  r.p4 = s[4];
+  r.p32 = (s[3] << 8) + s[2];
+  r.p10 = (s[1] << 8) + s[0];
+  return r;
+}
+// c (dot product of element w) + shift, c folded into the four weights
+__device__ inline double dot_affine(const DotParts &p, int w, double c, double shift)
+{
+  return fma((double)p.p65[w], c * (kDotUnit * 0x1p40),
+             fma((double)p.p4[w], c * (kDotUnit * 0x1p32),
+                 fma((double)p.p32[w], c * (kDotUnit * 0x1p16), fma((double)p.p10[w], c * kDotUnit, shift))));
+}
+
+// The same tile in fp64, for operands that have no digits: element w of lane (g, c) is
+// key[4 g + w] . query[c].  krow(i): row of the tile's key i (any readable row), qrow: the lane's query.
+template <int D, typename KRow>
+__device__ inline v4d dot_tile_f64(KRow krow, const __half *qrow, int g, int c)
+{
+  // result register v of v_mfma_f64_16x16x4 holds row g + 4 v, so matrix row i stands for key 4 (i % 4) + i / 4
+  const __half *kr = krow(4 * (c % 4) + c / 4);
+  v4d acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+  for (int s = 0; s < D / 4; ++s)
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)__half2float(kr[4 * s + g]),
+                                               (double)__half2float(qrow[4 * s + g]), acc, 0, 0, 0);
+  return acc;
+}
+
+// 2^y of N values in fp64, y <= a few: y = n + f with |f| <= 1/2, polynomial of degree 9 in f
+// (interpolated at Chebyshev points, 1.9e-14 relative), scaled by 2^n; 0 where that underflows.
+// Scores come in base-2 units, so no reduction by ln 2 is needed.  The N chains run side by
+// side: one alone would wait for every multiply-add.
+template <int N>
+__device__ inline void exp2_f64(const double (&y)[N], double (&e)[N])
+{
+  constexpr double kPoly[9] = {1.3259645242976312e-06, 1.5252672925061028e-05, 0.00015403433751260721,
+                               0.0013333558200794317,  0.009618129193934294,   0.05550410866465167,
+                               0.2402265069564034,     0.6931471805599462,     1.0000000000000135};
+  double f[N], p[N];
+  int n[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const double r = __builtin_rint(y[i]);
+    f[i] = y[i] - r;
+    n[i] = (int)r;
+    p[i] = 1.0205905366707709e-07;
+  }
+#pragma unroll
+  for (int k = 0; k < 9; ++k)
+#pragma unroll
+    for (int i = 0; i < N; ++i) p[i] = fma(p[i], f[i], kPoly[k]);
+#pragma unroll
+  for (int i = 0; i < N; ++i) e[i] = __builtin_ldexp(p[i], n[i]);
+}
+
+constexpr double kLog2E = 1.4426950408889634074;
+constexpr double kLn2 = 0.69314718055994530942;
+
+}  // namespace lessdec

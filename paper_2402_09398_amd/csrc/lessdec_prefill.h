@@ -1,0 +1,30 @@
+// What the prompt phase's kernel files share.
+#pragma once
+
+#include "lessdec_common.h"
+
+namespace lessdec {
+
+constexpr int kPrefillWaves = 4;   // waves per block of the prompt phase's passes
+constexpr int kXcds = 8;           // workgroups go to the chip's 8 dies round-robin by index
+
+// Workgroup -> (unit, group of tiles).  Causal sweeps have very different
+// lengths, so every die gets the same sequence of groups: die x works through units x, x + 8,
+// ..., each unit's groups in order.  The dies stay balanced and a unit's rows stay in one L2.
+// grid = ceil(U / 8) * 8 * ngrp.
+struct PrefillBlock { unsigned u; int grp; };
+__device__ inline PrefillBlock prefill_block(unsigned b, int ngrp)
+{
+  const unsigned xcd = b % kXcds, r = b / kXcds;
+  return PrefillBlock{(r / (unsigned)ngrp) * kXcds + xcd, (int)(r % (unsigned)ngrp)};
+}
+inline unsigned prefill_grid(unsigned U, unsigned ngrp) { return (U + kXcds - 1) / kXcds * kXcds * ngrp; }
+
+// fp16 storage, scores from digit products (lessdec_rows.hip)
+hipError_t launch_rows_f16(const void *Q, const void *K, const void *V, unsigned UG, int G, int P, int D, double *lse,
+                           void *out, hipStream_t st);
+// list == nullptr: every column
+hipError_t launch_columns_f16(const void *Q, const void *K, unsigned U, int G, int P, int D, const double *lse,
+                              const int32_t *list, const int32_t *count, int C, double *colsum, hipStream_t st);
+
+}  // namespace lessdec

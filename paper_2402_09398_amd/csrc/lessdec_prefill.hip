@@ -2,8 +2,9 @@
 // tokens (column sums of the attention matrix), one-shot cut to the budget, and the
 // low-rank state of everything cut away (Eq. 6).
 //
-// The scores decide which tokens are kept, so Q K^T runs in fp64 on the matrix cores
-// (v_mfma_f64_16x16x4_f64).  Operand layout of that instruction, wave64, lane = 16 * g + c:
+// The scores decide which tokens are kept, so Q K^T is needed to fp64 precision: with fp16 storage
+// as integer products of digit planes (lessdec_rows.hip), with fp32 storage and in the masked row pass
+// in fp64 on the matrix cores (v_mfma_f64_16x16x4_f64).  Operand layout of that instruction, wave64, lane = 16 * g + c:
 //   A[i][k] is taken from lane i + 16 k, B[k][j] from lane j + 16 k,
 //   result register v of lane (g, c) holds D[g + 4 v][c].
 // Both passes compute transposed tiles S^T[key][query] = K Q^T, so a lane always owns one
@@ -11,6 +12,7 @@
 // contiguous chunks of D / 4, chunk g supplying the k index of the instruction.
 #include "lessdec_common.h"
 #include "lessdec_internal.h"
+#include "lessdec_prefill.h"
 
 namespace lessdec {
 
@@ -51,20 +53,6 @@ __device__ inline v4d tile_kq(const double (&kd)[D / 4], const Chunk<T, D> &qraw
   for (int s = 0; s < D / 4; ++s)
     acc = __builtin_amdgcn_mfma_f64_16x16x4f64(kd[s], qraw.get(s), acc, 0, 0, 0);
   return acc;
-}
-
-constexpr int kPrefillWaves = 4;   // independent waves (16 queries or 16 keys each) per block
-constexpr int kXcds = 8;           // workgroups go to the chip's 8 dies round-robin by index
-
-// Workgroup -> (unit, group of kPrefillWaves tiles).  Causal sweeps have very different
-// lengths, so every die gets the same sequence of groups: die x works through units x, x + 8,
-// ..., each unit's groups in order.  The dies stay balanced and a unit's rows stay in one L2.
-// grid = ceil(U / 8) * 8 * ngrp.
-struct PrefillBlock { unsigned u; int grp; };
-__device__ inline PrefillBlock prefill_block(unsigned b, int ngrp)
-{
-  const unsigned xcd = b % kXcds, r = b / kXcds;
-  return PrefillBlock{(r / (unsigned)ngrp) * kXcds + xcd, (int)(r % (unsigned)ngrp)};
 }
 
 // p V^T for one tile of 16 keys, fp32 storage: v_mfma_f32_16x16x4_f32, one key group per
@@ -166,7 +154,7 @@ __device__ inline void store_out(__half *orow, int g, const v4f (&O)[D / 16], fl
 }
 
 // -------------------------------------------------------------------------------------
-// Row pass: one wave per block of 16 queries, kPrefillWaves consecutive query blocks per
+// Row pass, fp32 storage (fp16: lessdec_rows.hip): one wave per block of 16 queries, kPrefillWaves consecutive query blocks per
 // workgroup.  The workgroup sweeps the key tiles up to its last diagonal; every key tile is
 // fetched and widened to fp64 once, by all 256 threads, into the LDS (two buffers, one
 // barrier per tile) in the order the matrix instruction wants its operand, and each wave
@@ -185,7 +173,6 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
   // U counts query rows here: unit u's G query heads are rows u G .. u G + G - 1 of Q, out and
   // lse, and attend over unit u's keys and values
   constexpr int CH = D / 4, DB = D / 16;
-  constexpr bool kHalf = sizeof(T) == 2;
   constexpr int EPT = 16 * D / (64 * kPrefillWaves);      // tile elements widened per thread
   static_assert(EPT % 2 == 0 && CH % EPT == 0, "a thread's elements stay within one lane group");
   __shared__ double2 s_k[2][16 * D / 2];
@@ -242,10 +229,6 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
       buf[((wi + p) * 4 + wg) * 16 + wc] =
           double2{(double)Store<T>::to_float(raw[2 * p]), (double)Store<T>::to_float(raw[2 * p + 1])};
     fetch(jt < it_last ? jt + 1 : jt);
-    VTile<D> vt;
-    if constexpr (kHalf) {
-      if (out != nullptr) vt.load(reinterpret_cast<const __half *>(Vu), P, j0, g, c);
-    }
     // tile jt is complete, and nobody still reads the buffer that tile jt + 1 will go into
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
@@ -288,8 +271,7 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
     }
     L += esum;
     if (out != nullptr) {
-      if constexpr (kHalf) tile_pv<D>(vt, e, O);
-      else tile_pv<D>(reinterpret_cast<const float *>(Vu), P, j0, g, c, e, O);
+      tile_pv<D>(reinterpret_cast<const float *>(Vu), P, j0, g, c, e, O);
     }
   }
   L += __shfl_xor(L, 16);
@@ -660,7 +642,7 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
 }
 
 // -------------------------------------------------------------------------------------
-// Column pass: one wave per block of 16 keys.  Sweeps the query tiles from the diagonal
+// Column pass, fp32 storage (fp16: lessdec_rows.hip): one wave per block of 16 keys.  Sweeps the query tiles from the diagonal
 // down and sums a_ij = e^{s_ij - lse_i} over the queries: the accumulated attention
 // probability of each prompt token (H2O's score, Sec. 2.1).  No atomics: every column is
 // owned by one wave and reduced in a fixed order.
@@ -950,7 +932,7 @@ __global__ __launch_bounds__(256) void prefill_compact_kernel(const int32_t *__r
 }
 
 // -------------------------------------------------------------------------------------
-// Exact column sums of listed tokens only: the column pass with 16 listed keys per wave in
+// Exact column sums of listed tokens only, fp32 storage: the column pass with 16 listed keys per wave in
 // place of 16 consecutive ones.  The sweep starts at the query tile of the wave's earliest
 // key; a key takes part from its own position on.  The length of the list is only known on
 // the device: a unit gets enough blocks for a list a little longer than the budget, and its
@@ -1336,8 +1318,12 @@ static hipError_t launch_prefill_t(const PrefillArgs &a, hipStream_t st)
         (const T *)a.Q, (const T *)a.K, (const T *)a.V, U * G, G, P, a.phi_all, a.psi_all, a.psimax, a.hpre, a.zpre, d->rank,
         d->n_heavy, d->n_recent, (d->flags & LESSDEC_FLAG_SPARSE_DENOM) ? 1 : 0, a.lse, (T *)a.out);
   } else {
-    prefill_rowpass_kernel<T, D><<<(U * G + kXcds - 1) / kXcds * kXcds * tiles, 64 * kPrefillWaves, 0, st>>>(
-        (const T *)a.Q, (const T *)a.K, (const T *)a.V, U * G, G, P, a.lse, (T *)a.out);
+    if constexpr (sizeof(T) == 2) {
+      if ((e = launch_rows_f16(a.Q, a.K, a.V, U * G, G, P, D, a.lse, a.out, st)) != hipSuccess) return e;
+    } else {
+      prefill_rowpass_kernel<T, D><<<(U * G + kXcds - 1) / kXcds * kXcds * tiles, 64 * kPrefillWaves, 0, st>>>(
+          (const T *)a.Q, (const T *)a.K, (const T *)a.V, U * G, G, P, a.lse, (T *)a.out);
+    }
   }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -1366,18 +1352,28 @@ static hipError_t launch_prefill_t(const PrefillArgs &a, hipStream_t st)
     if ((e = hipGetLastError()) != hipSuccess) return e;
     prefill_compact_kernel<<<U, 256, 0, st>>>(a.slot_of, P, a.list, a.count);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    const int bpu = (C + 32 + 16 * kPrefillWaves - 1) / (16 * kPrefillWaves);
-    prefill_colexact_kernel<T, D><<<(U + kXcds - 1) / kXcds * kXcds * (unsigned)bpu, 64 * kPrefillWaves, 0, st>>>(
-        (const T *)a.Q, (const T *)a.K, U, P, a.lse, a.list, a.count, bpu, G, a.colsum);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if constexpr (sizeof(T) == 2) {
+      e = launch_columns_f16(a.Q, a.K, U, G, P, D, a.lse, a.list, a.count, C, a.colsum, st);
+    } else {
+      const int bpu = (C + 32 + 16 * kPrefillWaves - 1) / (16 * kPrefillWaves);
+      prefill_colexact_kernel<T, D><<<(U + kXcds - 1) / kXcds * kXcds * (unsigned)bpu, 64 * kPrefillWaves, 0, st>>>(
+          (const T *)a.Q, (const T *)a.K, U, P, a.lse, a.list, a.count, bpu, G, a.colsum);
+      e = hipGetLastError();
+    }
+    if (e != hipSuccess) return e;
     if (!lambda) {
       prefill_refine_kernel<<<U, 256, 0, st>>>(a.colsum, a.slot_of, P, d->n_heavy, d->n_recent, a.list);
       keep = a.list;
     }
   } else {
-    prefill_colpass_kernel<T, D><<<grid, 64 * kPrefillWaves, 0, st>>>((const T *)a.Q, (const T *)a.K, U, P,
-                                                                     a.lse, G, a.colsum);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if constexpr (sizeof(T) == 2) {
+      e = launch_columns_f16(a.Q, a.K, U, G, P, D, a.lse, nullptr, nullptr, C, a.colsum, st);
+    } else {
+      prefill_colpass_kernel<T, D><<<grid, 64 * kPrefillWaves, 0, st>>>((const T *)a.Q, (const T *)a.K, U, P,
+                                                                       a.lse, G, a.colsum);
+      e = hipGetLastError();
+    }
+    if (e != hipSuccess) return e;
     prefill_rank_kernel<<<rank_grid, 256, 0, st>>>(a.colsum, P, d->n_heavy, d->n_recent, lambda ? 1 : 0,
                                                    a.slot_of);
   }

@@ -1,0 +1,76 @@
+"""Prompt phase with fp16 storage: scores from digit planes of the halves (GPU, against the oracle).
+
+Sizes at the edges of the tiles (16 queries per wave, 32 keys per tile, 64 or 128 queries per
+workgroup), values that have no digits (|x| >= 127: those tiles are multiplied in fp64) and values that
+are not finite.  Tolerances: tests/harness.py.
+"""
+import numpy as np
+import pytest
+
+from paper_2402_09398_amd import workloads as wl
+from tests import harness as hz
+
+pytestmark = pytest.mark.gpu
+
+
+def shape(prompt, **kw):
+    d = dict(name=f"digits-{prompt}", batch=1, heads=3, head_dim=128, prompt=prompt, steps=2, n_heavy=4, n_recent=4,
+             rank=4, hidden=64, dtype="f16")
+    d.update(kw)
+    return wl.WORKLOADS[2].scaled(**d)
+
+
+def run(w, inp):
+    units = list(range(w.units))
+    res = hz.gpu_run(w, inp)
+    rep = hz.check_against_oracle(w, inp, units, res)
+    rep.failures.extend(hz.check_every_unit(w, res))
+    print("\n" + rep.summary(), flush=True)
+    assert rep.ok(), rep.failures[:10]
+    return res
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("prompt", [1, 9, 16, 17, 31, 32, 33, 48, 63, 64, 65, 97, 128, 129, 161])
+def test_tile_edges(prompt, head_dim):
+    w = shape(prompt, head_dim=head_dim)
+    run(w, wl.all_inputs(w))
+
+
+def test_wide_workgroup():
+    """Prompts of 4096 tokens and more take 128 queries per workgroup."""
+    w = shape(4096 + 37, heads=1)
+    run(w, wl.all_inputs(w))
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("which", ["K", "Q", "KQ"])
+def test_values_without_digits(which, head_dim):
+    """Some rows carry elements of 127 and more (and the largest that still has digits, 126.9)."""
+    w = shape(150, head_dim=head_dim, q_per_kv=2)
+    inp = wl.all_inputs(w)
+    rng = np.random.default_rng(5)
+    for name in which:
+        x = inp[name].reshape(w.units, -1, w.prompt, head_dim)
+        for value in (126.9375, -126.9375, 127.0, -300.0, 6e4 if which == "K" else 900.0):
+            for u in range(w.units):
+                for head in range(x.shape[1]):
+                    x[u, head, rng.integers(2, w.prompt), rng.integers(head_dim)] = value
+    # what the large channel meets is small, so that the rows stay soft
+    other = {"K": "Q", "Q": "K"}.get(which)
+    if other:
+        big = np.abs(inp[which].astype(np.float32)).reshape(-1, head_dim).max(axis=0) > 100
+        inp[other][..., big] *= np.float16(1 / 64)
+    run(w, inp)
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
+def test_rows_before_a_value_that_is_not_finite(value):
+    """Rows of earlier tiles neither see the key nor its value: bit for bit as without it."""
+    w = shape(100, steps=0)
+    clean = wl.all_inputs(w)
+    dirty = {k: v.copy() for k, v in clean.items()}
+    dirty["K"][:, 70, 5] = value
+    dirty["V"][:, 70, 7] = value
+    a, b = (hz.gpu_run(w, x)["prefill_out"] for x in (clean, dirty))
+    assert np.array_equal(a[:, :64].view(np.uint16), b[:, :64].view(np.uint16))
