@@ -8,6 +8,7 @@
 // order of the equations, the heads four at a time; a block first copies its unit's rows into the
 // LDS when they fit.  The discarded pair is folded into H, z within the step (nothing is left
 // pending).
+#include "lessdec_digits.h"
 #include "lessdec_wave.h"
 
 namespace lessdec {
@@ -57,11 +58,11 @@ struct LdsCopies {
   const int *pos = nullptr;                // [m]
 };
 
-// After the unit's last head, by the whole block of 256 threads: accumulated scores, eviction
+// After the unit's last head, by the whole block: accumulated scores, eviction
 // choice, fold of the discarded pair into H, z (Eq. 4, Eq. 5), in-place insert of the new pair
 // (Sec. 3.2).  s_inc holds the step's probabilities per pair summed over the heads; s_e is
-// scratch of the same size; s_cand 256 entries.
-template <typename T, int D>
+// scratch of the same size; s_cand THREADS entries.
+template <typename T, int D, int THREADS = 256>
 __device__ inline void gqa_finish_unit(const StepArgs &a, int u, int tid, double *s_e, const double *s_inc,
                                        Cand *s_cand, const LdsCopies<T> lds = LdsCopies<T>())
 {
@@ -79,7 +80,7 @@ __device__ inline void gqa_finish_unit(const StepArgs &a, int u, int tid, double
   // accumulated scores; eviction candidate of this thread's rows
   const bool lambda = (a.flags & LESSDEC_FLAG_LAMBDA) != 0;
   Cand best = cand_none();
-  for (int r = tid; r < rows; r += 256) {
+  for (int r = tid; r < rows; r += THREADS) {
     double na = s_inc[r];
     int pj = n;
     if (r < m) {
@@ -95,7 +96,7 @@ __device__ inline void gqa_finish_unit(const StepArgs &a, int u, int tid, double
   }
   s_cand[tid] = best;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
+  for (int o = THREADS / 2; o > 0; o >>= 1) {
     if (tid < o && cand_less(s_cand[tid + o], s_cand[tid])) s_cand[tid] = s_cand[tid + o];
     __syncthreads();
   }
@@ -130,7 +131,7 @@ __device__ inline void gqa_finish_unit(const StepArgs &a, int u, int tid, double
   }
   __syncthreads();
   // scores of the pairs that stay, and the new pair into its slot (Sec. 3.2: in place)
-  for (int r = tid; r < m; r += 256)
+  for (int r = tid; r < m; r += THREADS)
     if (r != ins_slot) a.acc[(size_t)u * C + r] = s_e[r];
   if (ins_slot >= 0) {
     if (tid < D) {
@@ -446,6 +447,235 @@ __global__ __launch_bounds__(256) void gqa_finish_kernel(const StepArgs a, int n
   gqa_finish_unit<T, D>(a, u, tid, s_e, s_inc, s_cand);
 }
 
+// -------------------------------------------------------------------------------------
+// Many query heads per unit (multi-query attention), fp16 storage: the heads sixteen at a time as the
+// columns of matrix tiles.  A block of eight waves per share of a unit's head groups; tile T of 16 cache
+// rows belongs to wave T mod 8, which keeps its scores in registers (NTW tiles).  Scores are exact
+// integer products of digit planes (lessdec_digits.h; fp64 matrix products where a value has no
+// digits), lane (g, c) holding rows 4 g + w of head c; softmax in fp64, maximum and sum through the LDS; a
+// pair's share of the accumulated scores is its row's sum over the lanes c; p V takes the fp32
+// weights to v_mfma_f32_16x16x4_f32, a row's values straight from memory (element d = D / 16 i + b
+// is operand row i of block b, so a lane reads one run per row), and the waves' partial outputs meet
+// in the LDS in wave order.  The vector form above (other shapes) scores a row for four heads at a time on the fp64
+// vector units: 52 us for 64 units x 71 heads x 204 slots, against 19 here (a step: 64 us before, 36 now).
+// Dynamic LDS: gqm_lds.
+// -------------------------------------------------------------------------------------
+constexpr int kGqmWaves = 8, kGqmHeads = 16, kGqmMaxRows = 1024;
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+template <int D, int NTW>
+__global__ __launch_bounds__(64 * kGqmWaves, D == 64 && NTW <= 2 ? 4 : 2) void gqm_step_kernel(const StepArgs a, int G, int nhb)
+{
+  using T = __half;
+  constexpr int KC = D / 64, DB = D / 16, NV = DB / 2, THREADS = 64 * kGqmWaves;
+  extern __shared__ __attribute__((aligned(16))) double dyn[];
+  __shared__ double s_mx[kGqmWaves][kGqmHeads], s_sum[kGqmWaves][kGqmHeads], s_hd[kGqmHeads][2];
+  const int C = a.C, R = a.R, rows_cap = C + 2;
+  double *s_inc = dyn;                               // [C+1] this step's probabilities per pair, summed over the heads
+  double *s_e = s_inc + rows_cap;                    // [C+1] scratch of the finish
+  double *s_z = s_e + rows_cap;                      // [R] z
+  double *s_f = s_z + LESSDEC_MAX_RANK;              // [16][R] phi(q) of the group
+  float *s_o = reinterpret_cast<float *>(s_f + kGqmHeads * LESSDEC_MAX_RANK);   // [8][16][D] partial outputs
+  Cand *s_cand = reinterpret_cast<Cand *>(s_o);      // after the last group
+  static_assert(sizeof(Cand) * THREADS <= sizeof(float) * kGqmWaves * kGqmHeads * D, "candidates overlay the partial outputs");
+  const int u = (int)blockIdx.x / nhb, hb = (int)blockIdx.x % nhb;
+  const int ngrp = (G + kGqmHeads - 1) / kGqmHeads;
+  const int grp0 = ngrp * hb / nhb, grp1 = ngrp * (hb + 1) / nhb;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64, g = l / 16, c = l % 16;
+  const int n = sane_n_seen(a.n_seen[u]);
+  const int m = n < C ? n : C;             // live slots are 0..m-1 (slots fill in order)
+  const int rows = m + 1;                  // + the appended pair (K', V' of Eq. 3)
+  const T *kc = reinterpret_cast<const T *>(a.k_cache) + (size_t)u * C * D;
+  const T *vc = reinterpret_cast<const T *>(a.v_cache) + (size_t)u * C * D;
+  const T *kn = reinterpret_cast<const T *>(a.k) + (size_t)u * D, *vn = reinterpret_cast<const T *>(a.v) + (size_t)u * D;
+  const float *Hu = a.H + (size_t)u * R * D;
+  const double cs = kLog2E / sqrt((double)D);        // q . k to base-2 units
+  const bool sparse_den = (a.flags & LESSDEC_FLAG_SPARSE_DENOM) != 0;
+  auto row_of = [&](const T *cache, const T *last, int r) { return r < m ? cache + (size_t)r * D : last; };   // rows past the appended one repeat it
+
+  for (int r = tid; r < rows; r += THREADS) s_inc[r] = 0.0;
+  if (tid < R) s_z[tid] = a.z[(size_t)u * R + tid];
+  for (int grp = grp0; grp < grp1; ++grp) {
+    const int h0 = grp * kGqmHeads;
+    const int hc = h0 + c < G ? h0 + c : G - 1;      // heads past the last repeat it: computed, never kept
+    const bool head = h0 + c < G;
+    __syncthreads();                                 // the group before is done with the LDS
+    for (int i = tid; i < kGqmHeads * R; i += THREADS) {
+      const int h = h0 + i / R < G ? h0 + i / R : G - 1;
+      const size_t at = ((size_t)u * G + h) * R + i % R;
+      s_f[i] = a.f_phi32 ? (double)a.f_phi32[at] : a.f_phi[at];
+    }
+    // scores of this wave's tiles, base-2 units
+    const T *qrow = reinterpret_cast<const T *>(a.q) + ((size_t)u * G + hc) * D;
+    RowDigits<D> qd;
+    const bool qbad = __any(!qd.load(qrow, g));
+    double e[NTW][4], mx = -__builtin_inf();
+#pragma unroll
+    for (int t = 0; t < NTW; ++t) {
+      const int r0 = 16 * (t * kGqmWaves + wave);
+#pragma unroll
+      for (int w = 0; w < 4; ++w) e[t][w] = -__builtin_inf();
+      if (r0 >= rows) continue;                      // wave-uniform
+      RowDigits<D> kd;
+      const bool kbad = __any(!kd.load(row_of(kc, kn, r0 + c), g));
+      if (!qbad && !kbad) {
+        v4i s[7];
+#pragma unroll
+        for (int i = 0; i < 7; ++i) s[i] = v4i{0, 0, 0, 0};
+#pragma unroll
+        for (int k = 0; k < KC; ++k)
+#pragma unroll
+          for (int pa = 0; pa < 4; ++pa) dot_planes(kd.d[k][pa], qd.d[k], pa, s);
+        const DotParts p = dot_join(s);
+#pragma unroll
+        for (int w = 0; w < 4; ++w) e[t][w] = dot_affine(p, w, cs, 0.0);
+      } else {
+        const v4d s = dot_tile_f64<D>([&](int i) { return row_of(kc, kn, r0 + i); }, qrow, g, c);
+#pragma unroll
+        for (int w = 0; w < 4; ++w) e[t][w] = s[w] * cs;
+      }
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        if (r0 + 4 * g + w >= rows) e[t][w] = -__builtin_inf();
+        mx = fmax(mx, e[t][w]);
+      }
+    }
+    // this wave's value rows are requested ahead of the exchange where the registers hold them
+    constexpr bool kAhead = NTW <= 4;
+    unsigned vraw[kAhead ? NTW : 1][4][NV];
+    auto load_values = [&](int t, unsigned (&v)[4][NV]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const T *src = row_of(vc, vn, 16 * (t * kGqmWaves + wave) + 4 * g + w) + DB * c;
+        if constexpr (NV == 4) {
+          const uint4 x = *reinterpret_cast<const uint4 *>(src);
+          v[w][0] = x.x; v[w][1] = x.y; v[w][2] = x.z; v[w][3] = x.w;
+        } else {
+          const uint2 x = *reinterpret_cast<const uint2 *>(src);
+          v[w][0] = x.x; v[w][1] = x.y;
+        }
+      }
+    };
+    if constexpr (kAhead) {
+#pragma unroll
+      for (int t = 0; t < NTW; ++t) load_values(t, vraw[t]);
+    }
+    mx = fmax(mx, __shfl_xor(mx, 16));
+    mx = fmax(mx, __shfl_xor(mx, 32));
+    if (g == 0) s_mx[wave][c] = mx;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kGqmWaves; ++w) mx = fmax(mx, s_mx[w][c]);
+    // m* = max(scores, exponent of phi(q) z^T) is the common shift (Eq. 3 times 2^{-m*}); den = phi(q) z^T
+    // 2^{-m*} + sum_j 2^{s_j - m*}
+    double fz = 0.0;
+    for (int r = 0; r < R; ++r) fz = fma(s_f[c * R + r], s_z[r], fz);
+    const double mstar = fz > 0.0 ? fmax(mx, (double)__builtin_amdgcn_frexp_exp(fz)) : mx;
+    double down[1] = {-mstar}, hs[1];
+    exp2_f64(down, hs);
+    if (!(fz > 0.0)) hs[0] = 0.0;
+    double part = 0.0;
+#pragma unroll
+    for (int t = 0; t < NTW; ++t) {
+      double y[4];
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {                  // no weight for rows past the last, -inf and what is not a number
+        y[w] = e[t][w] - mstar;
+        y[w] = y[w] > -5000.0 ? y[w] : -5000.0;
+      }
+      exp2_f64(y, e[t]);
+      part += (e[t][0] + e[t][1]) + (e[t][2] + e[t][3]);
+    }
+    part += __shfl_xor(part, 16);
+    part += __shfl_xor(part, 32);
+    if (g == 0) s_sum[wave][c] = part;
+    __syncthreads();
+    double sum = 0.0;
+#pragma unroll
+    for (int w = 0; w < kGqmWaves; ++w) sum += s_sum[w][c];
+    const double den = (fz > 0.0 ? fz * hs[0] : 0.0) + sum;
+    if (wave == 0 && g == 0) {
+      s_hd[c][0] = hs[0];
+      s_hd[c][1] = 1.0 / den;
+    }
+    const double ascale = head ? 1.0 / (sparse_den ? sum : den) : 0.0;
+    v4f O[DB];
+#pragma unroll
+    for (int b = 0; b < DB; ++b) O[b] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < NTW; ++t) {
+      const int r0 = 16 * (t * kGqmWaves + wave);
+      if (r0 >= rows) continue;                      // wave-uniform
+      if constexpr (!kAhead) load_values(t, vraw[0]);
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const double inc = row16_allreduce(e[t][w] * ascale, OpAdd{});
+        const int r = r0 + 4 * g + w;
+        if (c == 0 && r < rows) s_inc[r] += inc;     // the row is this wave's alone
+        const float pw = (float)e[t][w];
+#pragma unroll
+        for (int b = 0; b < DB; ++b) {
+          const __half2 h = __builtin_bit_cast(__half2, vraw[kAhead ? t : 0][w][b / 2]);
+          O[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(b % 2 ? __high2float(h) : __low2float(h), pw, O[b], 0, 0, 0);
+        }
+      }
+    }
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+#pragma unroll
+      for (int b = 0; b < DB; b += 4)
+        *reinterpret_cast<float4 *>(s_o + (wave * kGqmHeads + c) * D + DB * (4 * g + w) + b) =
+            float4{O[b][w], O[b + 1][w], O[b + 2][w], O[b + 3][w]};
+    __syncthreads();
+    // outputs, two adjacent columns of a head per thread: (phi(q) H 2^{-m*} + sum_j 2^{s_j - m*} V_j) / den
+    for (int i = tid; i < kGqmHeads * D / 2; i += THREADS) {
+      const int h = i / (D / 2), d = i % (D / 2) * 2;
+      if (h0 + h >= G) break;
+      double n0 = 0.0, n1 = 0.0;
+      if (s_hd[h][0] > 0.0) {
+#pragma unroll 4
+        for (int r = 0; r < R; ++r) {
+          const float2 h2 = *reinterpret_cast<const float2 *>(Hu + r * D + d);
+          n0 = fma(s_f[h * R + r], (double)h2.x, n0);
+          n1 = fma(s_f[h * R + r], (double)h2.y, n1);
+        }
+        n0 *= s_hd[h][0];
+        n1 *= s_hd[h][0];
+      }
+#pragma unroll
+      for (int w = 0; w < kGqmWaves; ++w) {
+        const float2 o = *reinterpret_cast<const float2 *>(s_o + (w * kGqmHeads + h) * D + d);
+        n0 += (double)o.x;
+        n1 += (double)o.y;
+      }
+      float f0 = (float)(n0 * s_hd[h][1]), f1 = (float)(n1 * s_hd[h][1]);
+      asm volatile("" : "+v"(f0), "+v"(f1));         // fp64 -> fp16 in one step would be a software sequence
+      *reinterpret_cast<__half2 *>(reinterpret_cast<T *>(a.out) + ((size_t)u * G + h0 + h) * D + d) = __floats2half2_rn(f0, f1);
+    }
+  }
+  __syncthreads();
+  if (nhb > 1) {
+    // the unit's heads are spread over nhb blocks: leave this block's sums for the finishing launch
+    double *sums = a.gqa_parts + ((size_t)u * nhb + hb) * rows_cap;
+    for (int r = tid; r < rows; r += THREADS) sums[r] = s_inc[r];
+    return;
+  }
+  gqa_finish_unit<T, D, THREADS>(a, u, tid, s_e, s_inc, s_cand);
+}
+
+// Dynamic LDS of gqm_step_kernel, in bytes.
+static size_t gqm_lds(int C, int D)
+{
+  return (size_t)(2 * (C + 2) + (1 + kGqmHeads) * LESSDEC_MAX_RANK) * sizeof(double) +
+         (size_t)kGqmWaves * kGqmHeads * D * sizeof(float);
+}
+
+// Sixteen heads to a matrix tile pay from nine heads on (up to eight the streaming kernel takes them).
+static bool gqm_supported(int dtype, int C, int G)
+{
+  return dtype == LESSDEC_DTYPE_F16 && G > 8 && C + 1 <= kGqmMaxRows;
+}
+
 // Blocks per unit: one when the units alone fill the chip, else the heads are spread over up
 // to kGqaMaxHeadBlocks blocks (the cache rows are then staged once per block).
 int gqa_head_blocks(long units, int G)
@@ -471,6 +701,31 @@ static size_t block_lds_limit()
   return limit;
 }
 
+int gqa_launches(int dtype, int C, long units, int G)
+{
+  int nhb = gqa_head_blocks(units, G);
+  const int most = gqm_supported(dtype, C, G) ? (G + kGqmHeads - 1) / kGqmHeads : (G + kGqaChunk - 1) / kGqaChunk;
+  if (nhb > most) nhb = most;                               // whole groups or chunks per block
+  return nhb > 1 ? 2 : 1;
+}
+
+template <int D>
+static hipError_t launch_step_gqm_t(const StepArgs &a, int G, hipStream_t st)
+{
+  const int ngrp = (G + kGqmHeads - 1) / kGqmHeads, tiles = (a.C + 1 + 15) / 16, ntw = (tiles + kGqmWaves - 1) / kGqmWaves;
+  int nhb = gqa_head_blocks(a.U, G);
+  if (nhb > ngrp) nhb = ngrp;
+  const size_t lds = gqm_lds(a.C, D);
+  if (lds > block_lds_limit()) return hipErrorInvalidValue;
+#define LESSDEC_GQM(NTW) gqm_step_kernel<D, NTW><<<a.U * nhb, 64 * kGqmWaves, lds, st>>>(a, G, nhb)
+  if (ntw <= 1) LESSDEC_GQM(1); else if (ntw <= 2) LESSDEC_GQM(2); else if (ntw <= 4) LESSDEC_GQM(4); else LESSDEC_GQM(8);
+#undef LESSDEC_GQM
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  if (nhb > 1) gqa_finish_kernel<__half, D><<<a.U, 256, (size_t)2 * (a.C + 2) * sizeof(double), st>>>(a, nhb);
+  return hipGetLastError();
+}
+
 template <typename T, int D>
 static hipError_t launch_step_gqa_t(const StepArgs &a, int G, hipStream_t st)
 {
@@ -492,6 +747,7 @@ static hipError_t launch_step_gqa_t(const StepArgs &a, int G, hipStream_t st)
 
 hipError_t launch_step_gqa(const StepArgs &a, int G, int dtype, int D, hipStream_t st)
 {
+  if (gqm_supported(dtype, a.C, G)) return D == 128 ? launch_step_gqm_t<128>(a, G, st) : launch_step_gqm_t<64>(a, G, st);
   if (dtype == LESSDEC_DTYPE_F16)
     return D == 128 ? launch_step_gqa_t<__half, 128>(a, G, st) : launch_step_gqa_t<__half, 64>(a, G, st);
   return D == 128 ? launch_step_gqa_t<float, 128>(a, G, st) : launch_step_gqa_t<float, 64>(a, G, st);

@@ -1,0 +1,62 @@
+"""Decode step with more than eight query heads per key/value head, fp16 storage: the heads as columns
+of matrix tiles (GPU, against the oracle).  Head counts around the groups of sixteen, cache sizes at the
+edges of the row tiles (16 rows, 8 waves, up to 1024 rows) and beyond them, a cache still filling, the other
+options, one block per unit and several.  Tolerances: tests/harness.py."""
+import numpy as np
+import pytest
+
+from paper_2402_09398_amd import workloads as wl
+from tests import harness as hz
+
+pytestmark = pytest.mark.gpu
+
+
+def shape(name, **kw):
+    d = dict(name=name, batch=2, heads=1, head_dim=64, prompt=60, steps=8, n_heavy=10, n_recent=10, rank=4, hidden=64,
+             dtype="f16", q_per_kv=17)
+    d.update(kw)
+    return wl.WORKLOADS[2].scaled(**d)
+
+
+CASES = [
+    (shape("heads-9", q_per_kv=9), 0),
+    (shape("heads-16-d128", q_per_kv=16, head_dim=128), 0),
+    (shape("heads-33-rank-20", q_per_kv=33, rank=20, hidden=48), 0),
+    (shape("heads-128", q_per_kv=128, steps=3), 0),
+    (shape("one-slot", n_heavy=0, n_recent=1), 0),
+    (shape("rows-16", n_heavy=8, n_recent=7), 0),
+    (shape("rows-17", n_heavy=8, n_recent=8), 0),
+    (shape("rows-128-d128", n_heavy=60, n_recent=67, head_dim=128, prompt=140), 0),
+    (shape("rows-129", n_heavy=64, n_recent=64, prompt=140), 0),
+    (shape("rows-257-d128", n_heavy=128, n_recent=128, head_dim=128, prompt=300), 0),
+    (shape("rows-513", n_heavy=256, n_recent=256, prompt=540, batch=1, steps=4), 0),
+    (shape("rows-1024-d128", n_heavy=500, n_recent=523, head_dim=128, prompt=1030, batch=1, steps=4), 0),
+    (shape("rows-1025", n_heavy=512, n_recent=512, prompt=1030, batch=1, steps=4), 0),
+    (shape("filling", prompt=0, steps=30), 0),
+    (shape("sparse-denominator"), 1),
+    (shape("lambda", n_heavy=4), 2),
+    (shape("one-block-per-unit", batch=130, heads=4, q_per_kv=18, prompt=30, steps=4), 0),
+]
+
+
+@pytest.mark.parametrize("w,flags", CASES, ids=lambda x: getattr(x, "name", None))
+def test_many_heads(w, flags):
+    rep = hz.run_workload(w, range(min(w.units, 24)), flags=flags)
+    print("\n" + rep.summary(), flush=True)
+    assert rep.ok(), rep.failures[:10]
+
+
+def test_values_without_digits():
+    """Cached keys and queries with elements of 127 and more: those tiles are multiplied in fp64."""
+    w = shape("no-digits", prompt=50, steps=6)
+    inp = wl.all_inputs(w)
+    inp["K"][:, 45::2, 3] = 300.0
+    inp["k"][::2, :, 3] = -150.0
+    inp["Q"][..., 3] *= np.float16(1 / 64)
+    inp["q"][..., 3] *= np.float16(1 / 64)
+    inp["q"][1::3, :, 5, 7] = 200.0
+    units = list(range(w.units))
+    res = hz.gpu_run(w, inp)
+    rep = hz.check_against_oracle(w, inp, units, res)
+    rep.failures.extend(hz.check_every_unit(w, res))
+    assert rep.ok(), rep.failures[:10]
