@@ -364,7 +364,7 @@ int lessdec_step_launches(const lessdec_desc *desc)
   if (gq_parts(desc, s) && gqs_fusable(desc->head_dim, (int)s.C, desc->hidden, desc->rank, (int)s.G)) return 1;
   if (s.G > 1)                                                              // feature maps, heads, (finishing launch)
     return gqs_supported(desc->dtype, desc->head_dim, (int)s.C, desc->rank, (int)s.G)
-               ? 2 : 1 + gqa_launches(desc->dtype, (int)s.C, (long)s.U, (int)s.G);
+               ? 2 : gqa_head_blocks((long)s.U, (int)s.G) > 1 ? 3 : 2;
   if (use_wpu(desc, s))
     return wpu_fusable(desc->batch, desc->heads, desc->head_dim, (int)s.C, desc->hidden, desc->rank) ? 1 : 2;
   return 3;                                                                 // phi, psi, step

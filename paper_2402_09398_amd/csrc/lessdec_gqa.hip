@@ -464,7 +464,7 @@ constexpr int kGqmWaves = 8, kGqmHeads = 16, kGqmMaxRows = 1024;
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 template <int D, int NTW>
-__global__ __launch_bounds__(64 * kGqmWaves, D == 64 && NTW <= 2 ? 4 : 2) void gqm_step_kernel(const StepArgs a, int G, int nhb)
+__global__ __launch_bounds__(64 * kGqmWaves, D == 64 && NTW <= 2 ? 4 : 2) void gqm_step_kernel(const StepArgs a, int G, int nhb, int finish)
 {
   using T = __half;
   constexpr int KC = D / 64, DB = D / 16, NV = DB / 2, THREADS = 64 * kGqmWaves;
@@ -654,8 +654,8 @@ __global__ __launch_bounds__(64 * kGqmWaves, D == 64 && NTW <= 2 ? 4 : 2) void g
     }
   }
   __syncthreads();
-  if (nhb > 1) {
-    // the unit's heads are spread over nhb blocks: leave this block's sums for the finishing launch
+  if (!finish) {
+    // the unit is finished by a launch of its own: leave this block's sums for it
     double *sums = a.gqa_parts + ((size_t)u * nhb + hb) * rows_cap;
     for (int r = tid; r < rows; r += THREADS) sums[r] = s_inc[r];
     return;
@@ -701,28 +701,21 @@ static size_t block_lds_limit()
   return limit;
 }
 
-int gqa_launches(int dtype, int C, long units, int G)
-{
-  int nhb = gqa_head_blocks(units, G);
-  const int most = gqm_supported(dtype, C, G) ? (G + kGqmHeads - 1) / kGqmHeads : (G + kGqaChunk - 1) / kGqaChunk;
-  if (nhb > most) nhb = most;                               // whole groups or chunks per block
-  return nhb > 1 ? 2 : 1;
-}
-
 template <int D>
 static hipError_t launch_step_gqm_t(const StepArgs &a, int G, hipStream_t st)
 {
   const int ngrp = (G + kGqmHeads - 1) / kGqmHeads, tiles = (a.C + 1 + 15) / 16, ntw = (tiles + kGqmWaves - 1) / kGqmWaves;
   int nhb = gqa_head_blocks(a.U, G);
+  const bool split = nhb > 1;                               // few units: the finish is spread thinner as a launch of its own
   if (nhb > ngrp) nhb = ngrp;
   const size_t lds = gqm_lds(a.C, D);
   if (lds > block_lds_limit()) return hipErrorInvalidValue;
-#define LESSDEC_GQM(NTW) gqm_step_kernel<D, NTW><<<a.U * nhb, 64 * kGqmWaves, lds, st>>>(a, G, nhb)
+#define LESSDEC_GQM(NTW) gqm_step_kernel<D, NTW><<<a.U * nhb, 64 * kGqmWaves, lds, st>>>(a, G, nhb, split ? 0 : 1)
   if (ntw <= 1) LESSDEC_GQM(1); else if (ntw <= 2) LESSDEC_GQM(2); else if (ntw <= 4) LESSDEC_GQM(4); else LESSDEC_GQM(8);
 #undef LESSDEC_GQM
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (nhb > 1) gqa_finish_kernel<__half, D><<<a.U, 256, (size_t)2 * (a.C + 2) * sizeof(double), st>>>(a, nhb);
+  if (split) gqa_finish_kernel<__half, D><<<a.U, 256, (size_t)2 * (a.C + 2) * sizeof(double), st>>>(a, nhb);
   return hipGetLastError();
 }
 

@@ -90,7 +90,6 @@ hipError_t launch_step(const StepArgs &a, int dtype, int D, hipStream_t st);
 hipError_t launch_step_gqa(const StepArgs &a, int G, int dtype, int D, hipStream_t st);
 constexpr int kGqaMaxHeadBlocks = 8;
 int gqa_head_blocks(long units, int G);
-int gqa_launches(int dtype, int C, long units, int G);          // launches of launch_step_gqa
 hipError_t launch_state_sync(const StepArgs &a, int dtype, int D, hipStream_t st);
 // several query heads per unit, streaming form: one block per unit, one wave per query head
 // (lessdec_gqs.hip); leaves the discarded pair pending like the single-head streaming path
