@@ -252,12 +252,12 @@ int step_features_impl(const lessdec_desc *desc, const void *q, const void *k, i
   fa.D = desc->head_dim; fa.Rp = desc->hidden; fa.R = desc->rank;
   fa.x = q; fa.W1 = desc->Wq1; fa.W2 = desc->Wq2; fa.W3 = nullptr;
   fa.out = reinterpret_cast<double *>(ws + w.off_fphi); fa.out_f64 = 1;
-  if (launch_featmap_generic(fa, desc->dtype, st) != hipSuccess) return LESSDEC_EHIP;
-  fa.Hh = desc->heads;
-  fa.x = k; fa.W1 = desc->Wk1; fa.W2 = desc->Wk2; fa.W3 = desc->Wk3;
-  fa.out = reinterpret_cast<float *>(ws + w.off_fpsi); fa.out_f64 = 0;
-  if (launch_featmap_generic(fa, desc->dtype, st) != hipSuccess) return LESSDEC_EHIP;
-  return LESSDEC_OK;
+  FeatmapArgs fk = fa;
+  fk.Hh = desc->heads;
+  fk.x = k; fk.W1 = desc->Wk1; fk.W2 = desc->Wk2; fk.W3 = desc->Wk3;
+  fk.out = reinterpret_cast<float *>(ws + w.off_fpsi); fk.out_f64 = 0;
+  return launch_featmap_step(fa, fk, desc->dtype, reinterpret_cast<double *>(ws + w.off_parts), w.off_gqa - w.off_parts,
+                             st) == hipSuccess ? LESSDEC_OK : LESSDEC_EHIP;
 }
 
 int step_attend_impl(const lessdec_desc *desc, const void *q, const void *k, const void *v, void *out,
@@ -367,7 +367,7 @@ int lessdec_step_launches(const lessdec_desc *desc)
                ? 2 : gqa_head_blocks((long)s.U, (int)s.G) > 1 ? 3 : 2;
   if (use_wpu(desc, s))
     return wpu_fusable(desc->batch, desc->heads, desc->head_dim, (int)s.C, desc->hidden, desc->rank) ? 1 : 2;
-  return 3;                                                                 // phi, psi, step
+  return 3;                                                                 // feature maps (two launches), step
 }
 
 int lessdec_step_static(const lessdec_desc *desc, const void *q, const void *k, const void *v, void *out,

@@ -5,113 +5,199 @@
 
 namespace lessdec {
 
+typedef double v4d __attribute__((ext_vector_type(4)));
+
 // =====================================================================================
-// Feature maps, generic path: any D, R', R, either storage type, fp64 accumulation in the
-// oracle's summation order.  One block evaluates TM rows that share a head, so the
-// head's weights are read once per TM rows.
+// Feature maps, generic path: any R', R, either storage type, fp64 throughout, on the fp64 matrix
+// cores (v_mfma_f64_16x16x4_f64; lane = 16 g + c: A[i][k] from lane i + 16 k, B[k][j] from lane
+// j + 16 k, result register v of lane (g, c) is element [g + 4 v][c]).
 //   x    : rows of D values; row (u * rpu + p) belongs to unit u = b * Hh + h
 //   out  : [rows, R] as double (out_f64) or float
 //   W3   : NULL for phi (Eq. 1), the R x R matrix for psi (Eq. 2)
-// grid = Hh * ceil(B * rpu / TM) (head fastest), block = 256, dynamic LDS = TM * (D + R' + R) doubles
+// A block of four waves evaluates 16 rows that share a head, over one of `parts` parts of the hidden
+// units.  Layer 1 is H1 = W1 X^T, a tile of 16 hidden units at a time, tiles dealt to the waves; lane group g
+// supplies the D / 4 elements from g D / 4 on, so a lane's operands are one run of its row.  Register v of the
+// activated tile is then directly the B operand of layer 2 (hidden units g + 4 v).  The waves' layer-2
+// sums meet in the LDS in wave order.  With one part the block finishes the map; a decode step, which has few
+// (head, 16 rows) pairs, spreads the hidden units over blocks that leave their sums (fp64) in the workspace, and
+// featmap_finish_kernel adds them in part order: the two launches that phi and psi took one each.
+// Bound by the fp64 matrix rate (66 cycles an instruction) and the erfc of the hidden units, about half and half.
+// 8 x 32 units, D = 128, R' = 512, fp32 storage: 16 us for both maps, against 82 with a hidden unit per
+// thread on the vector units and a block per (head, 8 rows).
 // =====================================================================================
-template <typename T, int TM>
-__global__ __launch_bounds__(256) void featmap_generic_kernel(
-    const T *__restrict__ x, const T *__restrict__ W1, const T *__restrict__ W2,
-    const T *__restrict__ W3, void *__restrict__ out, int out_f64,
-    int B, int Hh, int rpu, int D, int Rp, int R)
+constexpr int kFmWaves = 4;
+
+// gelu, the third matrix and the absolute value of one row's outputs: sum[r] -> f
+template <typename T>
+__device__ inline void featmap_store(const FeatmapArgs &a, int h, long row, int r, const double *h2)
 {
-  extern __shared__ double sm[];
-  double *xs = sm;                 // [TM][D]
-  double *hs = xs + TM * D;        // [TM][Rp]
-  double *h2 = hs + TM * Rp;       // [TM][R]
-  const int h = blockIdx.x % Hh;
-  const long rows_head = (long)B * rpu;
-  const long i0 = (long)(blockIdx.x / Hh) * TM;
-  const int tid = threadIdx.x;
-  const T *W1h = W1 + (size_t)h * D * Rp;
-  const T *W2h = W2 + (size_t)h * Rp * R;
+  double f;
+  if (a.W3 == nullptr) {
+    f = fabs(h2[r]);
+  } else {
+    const T *W3 = reinterpret_cast<const T *>(a.W3) + ((size_t)h * a.R + r) * a.R;
+    double s = 0.0;
+    for (int j = 0; j < a.R; ++j) s = fma(h2[j], (double)Store<T>::to_float(W3[j]), s);
+    f = fabs(s);
+  }
+  const size_t at = (size_t)row * a.R + r;
+  if (a.out_f64) reinterpret_cast<double *>(a.out)[at] = f;
+  else reinterpret_cast<float *>(a.out)[at] = (float)f;
+}
 
-  auto global_row = [&](long i) -> long {   // i-th row of this head -> row in x / out
-    long b = i / rpu, p = i % rpu;
-    return (b * Hh + h) * (long)rpu + p;
+// sums: [rows of a][parts][R], then b's; not used with one part.  grid = (blocks of a + blocks of b), block b of
+// a map = ((chunk * parts) + part) * Hh + head
+template <typename T, int D, int RT>
+__global__ __launch_bounds__(64 * kFmWaves) void featmap_generic_kernel(const FeatmapArgs a_, const FeatmapArgs b_,
+                                                                        unsigned na, int parts, double *__restrict__ sums)
+{
+  constexpr int CH = D / 4, EPV = Store<T>::kPerVec, NV = CH / EPV;
+  __shared__ double s_red[kFmWaves][16][17];               // a wave's sums of 16 outputs x 16 rows
+  __shared__ double s_h2[16][LESSDEC_MAX_RANK + 1];
+  const bool first = blockIdx.x < na;
+  const FeatmapArgs &a = first ? a_ : b_;
+  const int Hh = a.Hh, Rp = a.Rp, R = a.R, rpu = a.rpu;
+  unsigned bid = first ? blockIdx.x : blockIdx.x - na;
+  const int h = (int)(bid % (unsigned)Hh);
+  bid /= (unsigned)Hh;
+  const int part = (int)(bid % (unsigned)parts);
+  const long rows_head = (long)a.B * rpu, i0 = (long)(bid / (unsigned)parts) * 16;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64, g = l / 16, c = l % 16;
+  auto global_row = [&](long i) -> long {                  // i-th row of this head -> row in x / out
+    const long b = i / rpu, p = i % rpu;
+    return (b * Hh + h) * rpu + p;
   };
-
-  for (int idx = tid; idx < TM * D; idx += 256) {
-    int m = idx / D, d = idx % D;
-    long i = i0 + m;
-    xs[idx] = (i < rows_head) ? (double)Store<T>::to_float(x[global_row(i) * D + d]) : 0.0;
+  typename Store<T>::Vec xr[NV];
+  {
+    const long i = i0 + c < rows_head ? i0 + c : rows_head - 1;          // padding: any row
+    const T *x = reinterpret_cast<const T *>(a.x) + global_row(i) * D + g * CH;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) xr[k] = load_vec<T>(x + k * EPV);
   }
-  __syncthreads();
-
-  for (int i = tid; i < Rp; i += 256) {
-    double a[TM];
+  const T *W1 = reinterpret_cast<const T *>(a.W1) + (size_t)h * D * Rp;
+  const T *W2 = reinterpret_cast<const T *>(a.W2) + (size_t)h * Rp * R;
+  const int tiles = (Rp + 15) / 16, t0 = (int)((long)tiles * part / parts), t1 = (int)((long)tiles * (part + 1) / parts);
+  v4d c2[RT];
 #pragma unroll
-    for (int m = 0; m < TM; ++m) a[m] = 0.0;
-    for (int d = 0; d < D; ++d) {
-      double w = (double)Store<T>::to_float(W1h[(size_t)i * D + d]);
+  for (int t = 0; t < RT; ++t) c2[t] = v4d{0.0, 0.0, 0.0, 0.0};
+  for (int tile = t0 + wave; tile < t1; tile += kFmWaves) {
+    const int hid = 16 * tile;
+    const T *w1 = W1 + (size_t)(hid + c < Rp ? hid + c : Rp - 1) * D + g * CH;
+    v4d acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int m = 0; m < TM; ++m) a[m] = fma(xs[m * D + d], w, a[m]);
+    for (int k = 0; k < NV; ++k) {
+      const typename Store<T>::Vec w = load_vec<T>(w1 + k * EPV);
+#pragma unroll
+      for (int e = 0; e < EPV; ++e)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)Store<T>::get(w, e), (double)Store<T>::get(xr[k], e), acc, 0, 0, 0);
     }
 #pragma unroll
-    for (int m = 0; m < TM; ++m) hs[m * Rp + i] = gelu_f64(a[m]);
-  }
-  __syncthreads();
-
-  for (int pr = tid; pr < TM * R; pr += 256) {
-    int m = pr / R, r = pr % R;
-    double a = 0.0;
-    for (int i = 0; i < Rp; ++i)
-      a = fma(hs[m * Rp + i], (double)Store<T>::to_float(W2h[(size_t)r * Rp + i]), a);
-    h2[pr] = gelu_f64(a);
-  }
-  __syncthreads();
-
-  for (int pr = tid; pr < TM * R; pr += 256) {
-    int m = pr / R, r = pr % R;
-    long i = i0 + m;
-    if (i >= rows_head) continue;
-    double g;
-    if (W3 == nullptr) {
-      g = fabs(h2[pr]);
-    } else {
-      const T *W3h = W3 + (size_t)h * R * R;
-      double a = 0.0;
-      for (int j = 0; j < R; ++j)
-        a = fma(h2[m * R + j], (double)Store<T>::to_float(W3h[(size_t)r * R + j]), a);
-      g = fabs(a);
+    for (int v = 0; v < 4; ++v) {
+      const int j = hid + g + 4 * v;
+      const double act = j < Rp ? gelu_f64(acc[v]) : 0.0;
+#pragma unroll
+      for (int t = 0; t < RT; ++t) {
+        const int r = 16 * t + c;
+        const double w2 = (double)Store<T>::to_float(W2[(size_t)(r < R ? r : R - 1) * Rp + (j < Rp ? j : Rp - 1)]);
+        c2[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(w2, act, c2[t], 0, 0, 0);
+      }
     }
-    const size_t o = (size_t)global_row(i) * R + r;
-    if (out_f64) reinterpret_cast<double *>(out)[o] = g;
-    else reinterpret_cast<float *>(out)[o] = (float)g;
+  }
+#pragma unroll
+  for (int t = 0; t < RT; ++t) {
+    if (t > 0) __syncthreads();
+#pragma unroll
+    for (int v = 0; v < 4; ++v) s_red[wave][g + 4 * v][c] = c2[t][v];
+    __syncthreads();
+    const int r = tid % 16, row = tid / 16;
+    double sum = 0.0;
+#pragma unroll
+    for (int w = 0; w < kFmWaves; ++w) sum += s_red[w][r][row];
+    if (16 * t + r < R) {
+      if (parts == 1) {
+        s_h2[row][16 * t + r] = gelu_f64(sum);
+      } else if (i0 + row < rows_head) {
+        const size_t at = (first ? 0 : (size_t)a_.B * a_.Hh * a_.rpu) + (size_t)global_row(i0 + row);
+        sums[(at * parts + part) * R + 16 * t + r] = sum;
+      }
+    }
+  }
+  if (parts > 1) return;
+  __syncthreads();
+  for (int o = tid; o < 16 * R; o += 64 * kFmWaves) {
+    const int row = o / R, r = o % R;
+    if (i0 + row >= rows_head) break;
+    featmap_store<T>(a, h, global_row(i0 + row), r, s_h2[row]);
   }
 }
 
+// The parts' sums of a decode step's rows (rpu = 1) added in part order, and the rest of the maps.  A wave per row,
+// a lane per output.  grid = ceil((rows of a + rows of b) / 4), block = 256.
 template <typename T>
-static hipError_t launch_featmap_generic_t(const FeatmapArgs &a, hipStream_t st)
+__global__ __launch_bounds__(256) void featmap_finish_kernel(const FeatmapArgs a_, const FeatmapArgs b_, int parts,
+                                                             const double *__restrict__ sums)
 {
-  const long rows_head = (long)a.B * a.rpu;
-  if (a.Rp <= 512) {
-    constexpr int TM = 8;
-    const unsigned grid = (unsigned)(a.Hh * ((rows_head + TM - 1) / TM));
-    size_t lds = sizeof(double) * TM * (size_t)(a.D + a.Rp + a.R);
-    featmap_generic_kernel<T, TM><<<grid, 256, lds, st>>>(
-        (const T *)a.x, (const T *)a.W1, (const T *)a.W2, (const T *)a.W3, a.out, a.out_f64,
-        a.B, a.Hh, a.rpu, a.D, a.Rp, a.R);
-  } else {
-    constexpr int TM = 2;
-    const unsigned grid = (unsigned)(a.Hh * ((rows_head + TM - 1) / TM));
-    size_t lds = sizeof(double) * TM * (size_t)(a.D + a.Rp + a.R);
-    featmap_generic_kernel<T, TM><<<grid, 256, lds, st>>>(
-        (const T *)a.x, (const T *)a.W1, (const T *)a.W2, (const T *)a.W3, a.out, a.out_f64,
-        a.B, a.Hh, a.rpu, a.D, a.Rp, a.R);
+  __shared__ double s_h2[4][LESSDEC_MAX_RANK];
+  const long na = (long)a_.B * a_.Hh, nb = (long)b_.B * b_.Hh;
+  const int wave = threadIdx.x / 64, r = threadIdx.x % 64, R = a_.R;
+  const long i = (long)blockIdx.x * 4 + wave;
+  const bool live = i < na + nb && r < R;
+  if (live) {
+    double sum = 0.0;
+    for (int p = 0; p < parts; ++p) sum += sums[((size_t)i * parts + p) * R + r];
+    s_h2[wave][r] = gelu_f64(sum);
   }
-  return hipGetLastError();
+  __syncthreads();
+  if (!live) return;
+  if (i < na) featmap_store<T>(a_, (int)(i % a_.Hh), i, r, s_h2[wave]);
+  else featmap_store<T>(b_, (int)((i - na) % b_.Hh), i - na, r, s_h2[wave]);
+}
+
+template <typename T, int D>
+static void featmap_launch(const FeatmapArgs &a, const FeatmapArgs &b, bool both, int parts, double *sums, hipStream_t st)
+{
+  auto blocks = [&](const FeatmapArgs &x) { return (unsigned)(x.Hh * parts * (((long)x.B * x.rpu + 15) / 16)); };
+  const unsigned na = blocks(a), grid = na + (both ? blocks(b) : 0u);
+  if (a.R <= 16) featmap_generic_kernel<T, D, 1><<<grid, 64 * kFmWaves, 0, st>>>(a, b, na, parts, sums);
+  else featmap_generic_kernel<T, D, LESSDEC_MAX_RANK / 16><<<grid, 64 * kFmWaves, 0, st>>>(a, b, na, parts, sums);
+}
+static void featmap_launch(const FeatmapArgs &a, const FeatmapArgs &b, bool both, int dtype, int parts, double *sums,
+                           hipStream_t st)
+{
+  if (dtype == LESSDEC_DTYPE_F16) {
+    if (a.D == 128) featmap_launch<__half, 128>(a, b, both, parts, sums, st);
+    else featmap_launch<__half, 64>(a, b, both, parts, sums, st);
+  } else {
+    if (a.D == 128) featmap_launch<float, 128>(a, b, both, parts, sums, st);
+    else featmap_launch<float, 64>(a, b, both, parts, sums, st);
+  }
 }
 
 hipError_t launch_featmap_generic(const FeatmapArgs &a, int dtype, hipStream_t st)
 {
-  return dtype == LESSDEC_DTYPE_F16 ? launch_featmap_generic_t<__half>(a, st)
-                                    : launch_featmap_generic_t<float>(a, st);
+  featmap_launch(a, a, false, dtype, 1, nullptr, st);
+  return hipGetLastError();
+}
+
+hipError_t launch_featmap_step(const FeatmapArgs &a, const FeatmapArgs &b, int dtype, double *sums, size_t bytes, hipStream_t st)
+{
+  // Parts of 64 hidden units (a tile per wave) as far as their sums fit the scratch and until there are 512 blocks.
+  const size_t rows = (size_t)a.B * (a.Hh + b.Hh), per = rows * a.R * sizeof(double);
+  const long chunks = (long)(a.Hh + b.Hh) * ((a.B + 15) / 16);
+  long parts = (a.Rp + 63) / 64;
+  if (parts > (long)(bytes / per)) parts = (long)(bytes / per);
+  if (parts > (512 + chunks - 1) / chunks) parts = (512 + chunks - 1) / chunks;
+  hipError_t e;
+  if (parts < 2) {                                         // a launch per map
+    if ((e = launch_featmap_generic(a, dtype, st)) != hipSuccess) return e;
+    return launch_featmap_generic(b, dtype, st);
+  }
+  featmap_launch(a, b, true, dtype, (int)parts, sums, st);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  const unsigned grid = (unsigned)((rows + 3) / 4);
+  if (dtype == LESSDEC_DTYPE_F16) featmap_finish_kernel<__half><<<grid, 256, 0, st>>>(a, b, (int)parts, sums);
+  else featmap_finish_kernel<float><<<grid, 256, 0, st>>>(a, b, (int)parts, sums);
+  return hipGetLastError();
 }
 
 // =====================================================================================

@@ -20,6 +20,8 @@ struct FeatmapArgs {
   int D, Rp, R;
 };
 hipError_t launch_featmap_generic(const FeatmapArgs &a, int dtype, hipStream_t st);
+// both maps of a decode step (rpu = 1, the same rank, hidden width and head_dim): two launches; sums: scratch
+hipError_t launch_featmap_step(const FeatmapArgs &a, const FeatmapArgs &b, int dtype, double *sums, size_t bytes, hipStream_t st);
 
 // Matrix-core psi (Eq. 2) for many rows: fp16 storage, D in {64,128}, R' a multiple of 32,
 // R <= 16.  Row convention as above; out is [rows, R] fp32.
