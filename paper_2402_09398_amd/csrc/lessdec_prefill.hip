@@ -718,85 +718,162 @@ __global__ __launch_bounds__(64 * kPrefillWaves) void prefill_colpass_kernel(
 // -------------------------------------------------------------------------------------
 // Cheap column sums, fp16 storage only: the same sweep as the column pass on
 // v_mfma_f32_16x16x32_f16 with fp32 accumulation and the fast fp32 exponential.  Their only
-// use is to tell which tokens can possibly matter for the selection (prefill_band_kernel);
+// use is to tell which tokens can possibly matter for the selection (prefill_select_kernel);
 // every value that decides or is stored comes from the exact pass over those tokens.
 // Lane (g, c) supplies elements 32 ks + 8 g .. + 7 of key row c (A) and of query row c (B);
 // result register w holds S^T[key 4 g + w][query c].
+// On the way: the largest squared norms of a unit's query and key rows (qmax, kmax, as bits of
+// floats >= 0, zeroed before), whose product bounds every score and with it the rounding error of these
+// sums; a wave takes the query rows at its keys' positions.
+// The four waves of a workgroup take 16 KT consecutive keys each (in registers) and sweep the same queries, 64
+// at a time through the LDS (two buffers, the next chunk requested before the barrier), so that a query row
+// crosses the L2 once per workgroup: with a row per wave straight from the L2 the sweep waited for it,
+// 950 us for 2048 units x 1024 tokens and 2330 us for 128 x 8192; 713 and 1318 now, the next query
+// tile's products beside this one's exponentials (890 and 1860 without that).
 // -------------------------------------------------------------------------------------
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
-constexpr int kApproxTiles = 4;    // key tiles (of 16) per wave: a query tile is loaded once for all of them
-template <int D>
-__global__ __launch_bounds__(64 * kPrefillWaves) void prefill_colapprox_kernel(
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+constexpr int kApproxQueries = 64; // queries per chunk
+template <int D, int KT>
+__global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void prefill_colapprox_kernel(
     const __half *__restrict__ Q, const __half *__restrict__ K, unsigned U, int P,
-    const double *__restrict__ lse, int G, float *__restrict__ approx)
+    const double *__restrict__ lse, int G, float *__restrict__ approx, unsigned *__restrict__ qmax,
+    unsigned *__restrict__ kmax)
 {
-  constexpr int KS = D / 32, KT = kApproxTiles;
-  const int nblk = (P + 15) / 16;
-  const int nkb = (nblk + KT - 1) / KT;                   // groups of KT key tiles
+  constexpr int KS = D / 32, QC = kApproxQueries, PIECES = D / 8;       // 16-byte pieces per row
+  constexpr int PER = QC * PIECES / (64 * kPrefillWaves);               // pieces per thread and chunk: 4 or 2
+  constexpr double kLog2e = 1.44269504088896340736;
+  // a query tile's piece e of row r, turned so that a wave reads one run and writes spread over the banks
+  __shared__ __attribute__((aligned(16))) unsigned char s_q[2][QC / 16][PIECES][16][16];
+  __shared__ float s_l[2][QC];
+  const int nch = (P + QC - 1) / QC, nkb = (P + 16 * KT - 1) / (16 * KT);
   const int ngrp = (nkb + kPrefillWaves - 1) / kPrefillWaves;
   const PrefillBlock pb = prefill_block(blockIdx.x, ngrp);
+  if (pb.u >= U) return;                                  // uniform over the workgroup
   const size_t u = pb.u;
-  const int l = threadIdx.x % 64, g = l / 16, c = l % 16;
-  const int kb = pb.grp * kPrefillWaves + (int)(threadIdx.x / 64);
-  if (kb >= nkb || pb.u >= U) return;                     // wave-uniform; the waves share nothing
-  const int jt0 = kb * KT, j0 = jt0 * 16;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64, g = l / 16, c = l % 16;
+  const int jt0 = (pb.grp * kPrefillWaves + wave) * KT, j0 = jt0 * 16;  // the wave's keys; past the prompt: none
   const __half *Ku = K + u * (size_t)P * D;
-  const float scale = (float)(1.0 / sqrt((double)D));
-  auto load_row = [&](const __half *row, v8h (&dst)[KS]) {
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) dst[ks] = *reinterpret_cast<const v8h *>(row + 32 * ks + 8 * g);
-  };
-  v8h ka[KT][KS], qa[KS];
+  const float scale = (float)(kLog2e / sqrt((double)D));                // base-2 units: the exponential is one instruction
+  v8h ka[KT][KS];
 #pragma unroll
   for (int t = 0; t < KT; ++t) {
     const int kr = j0 + 16 * t + c;
-    load_row(Ku + (size_t)(kr < P ? kr : P - 1) * D, ka[t]);
-  }
-  float cs[KT][4];
 #pragma unroll
-  for (int t = 0; t < KT; ++t)
+    for (int ks = 0; ks < KS; ++ks)
+      ka[t][ks] = *reinterpret_cast<const v8h *>(Ku + (size_t)(kr < P ? kr : P - 1) * D + 32 * ks + 8 * g);
+  }
+  // the chunk of step i: head i / per, chunk c0 + i % per
+  const int c0 = pb.grp * kPrefillWaves * KT * 16 / QC, per = nch - c0, steps = G * per;
+  v4u raw[PER];
+  float lraw = 0.f;
+  auto fetch = [&](int i) __attribute__((always_inline)) {
+    const int h = i / per, q0 = (c0 + i - h * per) * QC;
+    const __half *Qu = Q + (u * G + h) * (size_t)P * D;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int x = tid + 64 * kPrefillWaves * k, row = q0 + x / PIECES;
+      raw[k] = *reinterpret_cast<const v4u *>(Qu + (size_t)(row < P ? row : P - 1) * D + x % PIECES * 8);
+    }
+    if (tid < QC) lraw = (float)(lse[(u * G + h) * (size_t)P + (q0 + tid < P ? q0 + tid : P - 1)] * kLog2e);
+  };
+  // squared norm of a row that lies over the four lane groups, the largest of the wave's rows into `to`
+  auto norm2 = [&](const v8h (&row)[KS]) {
+    typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+    float ss = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const v2h x = {row[ks][2 * i], row[ks][2 * i + 1]};
+        ss = __builtin_amdgcn_fdot2(x, x, ss, false);
+      }
+    ss += __shfl_xor(ss, 16);
+    return ss + __shfl_xor(ss, 32);
+  };
+  auto leave_max = [&](float mx, unsigned *to) {
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+    if (l == 0) atomicMax(to, __float_as_uint(mx));
+  };
+  fetch(0);
+  float mk = 0.f, mq = 0.f, cs[KT][4];
+#pragma unroll
+  for (int t = 0; t < KT; ++t) {
+    mk = fmaxf(mk, norm2(ka[t]));
 #pragma unroll
     for (int w = 0; w < 4; ++w) cs[t][w] = 0.f;
-  for (int h = 0; h < G; ++h) {                           // the unit's query heads, one sweep each
-  const __half *Qu = Q + (u * G + h) * (size_t)P * D;
-  const double *lse_u = lse + (u * G + h) * (size_t)P;
-  float lq;
-  {
-    const int qr = j0 + c < P ? j0 + c : P - 1;
-    load_row(Qu + (size_t)qr * D, qa);
-    lq = (float)lse_u[qr];
   }
-  // one query tile: request the tile after it into `nxt`, then multiply `cur` (two buffers
-  // that swap roles, so that no register copy has to wait for the request just made)
-  auto tile = [&](int it, const v8h (&cur)[KS], float lcur, v8h (&nxt)[KS], float &lnxt) {
-    const int qi = it * 16 + c;
-    {
-      const int qx = (it + 1 < nblk ? qi + 16 : qi);
-      const int qr = qx < P ? qx : P - 1;
-      load_row(Qu + (size_t)qr * D, nxt);
-      lnxt = (float)lse_u[qr];
+  for (int i = 0; i < steps; ++i) {
+    const int b = i & 1, qc = c0 + i % per;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int x = tid + 64 * kPrefillWaves * k, row = x / PIECES, e = x % PIECES;
+      *reinterpret_cast<v4u *>(s_q[b][row / 16][e][(row ^ e) % 16]) = raw[k];
     }
+    if (tid < QC) s_l[b][tid] = lraw;
+    fetch(i + 1 < steps ? i + 1 : i);
+    // the chunk is complete, and nobody still reads the buffer that the next one will go into
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    if (j0 >= P || qc * QC + QC - 1 < j0) continue;       // wave-uniform: every query before the wave's keys
+    auto query_tile = [&](int qt, v8h (&qa)[KS], float &lq) __attribute__((always_inline)) {
 #pragma unroll
-    for (int t = 0; t < KT; ++t) {
-      if (jt0 + t > it) continue;                         // key tile wholly after these queries (uniform)
-      v4f acc = {0.f, 0.f, 0.f, 0.f};
+      for (int ks = 0; ks < KS; ++ks) qa[ks] = *reinterpret_cast<const v8h *>(s_q[b][qt][4 * ks + g][(c ^ (4 * ks + g)) % 16]);
+      lq = s_l[b][16 * qt + c];
+    };
+    auto products = [&](const v8h (&qa)[KS], v4f (&acc)[KT]) __attribute__((always_inline)) {
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(ka[t][ks], cur[ks], acc, 0, 0, 0);
+      for (int t = 0; t < KT; ++t) acc[t] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const int kj = j0 + 16 * t + 4 * g + w;
-        const float a = __expf(fmaf(acc[w], scale, -lcur));
-        cs[t][w] += (qi < P && kj <= qi) ? a : 0.f;
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int t = 0; t < KT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ka[t][ks], qa[ks], acc[t], 0, 0, 0);
+    };
+    if (qc * QC >= j0 + 16 * KT && qc * QC + QC <= P) {   // wave-uniform: every query after every key
+      // the products of a query tile stand beside the exponentials of the one before
+      v8h qa[2][KS];
+      v4f acc[2][KT];
+      float lq[2];
+      query_tile(0, qa[0], lq[0]);
+      products(qa[0], acc[0]);
+#pragma unroll
+      for (int qt = 0; qt < QC / 16; ++qt) {
+        if (qt + 1 < QC / 16) {
+          query_tile(qt + 1, qa[(qt + 1) & 1], lq[(qt + 1) & 1]);
+          products(qa[(qt + 1) & 1], acc[(qt + 1) & 1]);
+        }
+#pragma unroll
+        for (int t = 0; t < KT; ++t)
+#pragma unroll
+          for (int w = 0; w < 4; ++w) cs[t][w] += __builtin_amdgcn_exp2f(fmaf(acc[qt & 1][t][w], scale, -lq[qt & 1]));
       }
+      continue;
     }
-  };
-  v8h qb[KS];
-  float lb;
-  for (int it = jt0; it < nblk; it += 2) {
-    tile(it, qa, lq, qb, lb);
-    if (it + 1 < nblk) tile(it + 1, qb, lb, qa, lq);
+#pragma unroll 1
+    for (int qt = 0; qt < QC / 16; ++qt) {
+      const int it = qc * (QC / 16) + qt, qi = it * 16 + c;
+      if (it < jt0 || it * 16 >= P) continue;             // wave-uniform
+      v8h qa[KS];
+      v4f acc[KT];
+      float lq;
+      query_tile(qt, qa, lq);
+      if (it < jt0 + KT) mq = fmaxf(mq, norm2(qa));       // the query rows at the wave's own positions
+      products(qa, acc);
+#pragma unroll
+      for (int t = 0; t < KT; ++t)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          const int kj = j0 + 16 * t + 4 * g + w;
+          const float a = __builtin_amdgcn_exp2f(fmaf(acc[t][w], scale, -lq));
+          cs[t][w] += (qi < P && kj <= qi) ? a : 0.f;
+        }
+    }
   }
-  }
+  if (j0 >= P) return;
+  leave_max(mk, kmax + u);
+  leave_max(mq, qmax + u);
 #pragma unroll
   for (int t = 0; t < KT; ++t)
 #pragma unroll
@@ -809,126 +886,160 @@ __global__ __launch_bounds__(64 * kPrefillWaves) void prefill_colapprox_kernel(
 }
 
 // -------------------------------------------------------------------------------------
-// The largest score magnitude a unit's prompt can produce: max_i |q_i| max_j |k_j| / sqrt(D)
-// over its tokens and query heads (>= |q_i . k_j| / sqrt(D) for every pair).  It bounds the rounding
-// error of the cheap column sums (below).  One block per unit, a row per D / 8 lanes.
-// -------------------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(256) void prefill_scorebound_kernel(const __half *__restrict__ Q,
-                                                                 const __half *__restrict__ K, int P, int G,
-                                                                 float *__restrict__ bound)
-{
-  constexpr int LPR = D / 8, RPB = 256 / LPR;
-  __shared__ float s_max[2][256 / kWave];
-  const size_t u = blockIdx.x;
-  const int tid = threadIdx.x, lr = tid % LPR, rb = tid / LPR;
-  float mx[2] = {0.f, 0.f};                               // largest squared norm: queries, keys
-  for (int which = 0; which < 2; ++which) {
-    const __half *base = which ? K + u * (size_t)P * D : Q + u * (size_t)G * P * D;
-    const long rows = which ? P : (long)G * P;
-    for (long r = rb; r < rows; r += RPB) {
-      const uint4 raw = *reinterpret_cast<const uint4 *>(base + r * D + lr * 8);
-      const __half2 *h2 = reinterpret_cast<const __half2 *>(&raw);
-      float ss = 0.f;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float2 f = __half22float2(h2[i]);
-        ss = fmaf(f.x, f.x, fmaf(f.y, f.y, ss));
-      }
-#pragma unroll
-      for (int o = LPR / 2; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
-      mx[which] = fmaxf(mx[which], ss);
-    }
-  }
-#pragma unroll
-  for (int which = 0; which < 2; ++which) {
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) mx[which] = fmaxf(mx[which], __shfl_xor(mx[which], o));
-    if (tid % kWave == 0) s_max[which][tid / kWave] = mx[which];
-  }
-  __syncthreads();
-  if (tid == 0) {
-    float mq = 0.f, mk = 0.f;
-    for (int w = 0; w < 256 / kWave; ++w) {
-      mq = fmaxf(mq, s_max[0][w]);
-      mk = fmaxf(mk, s_max[1][w]);
-    }
-    // rounded up a little: the squared norms above carry fp32 rounding themselves
-    bound[u] = sqrtf(mq) * sqrtf(mk) * (float)(1.0 / sqrt((double)D)) * 1.001f;
-  }
-}
-
-// -------------------------------------------------------------------------------------
 // Which tokens can matter, from the cheap column sums.  A cheap sum a~ and the exact one a
 // satisfy |a~ - a| <= eps a + tau with
 //   eps = 2^-24 ((D + 6) M + 3 ln P + G P / 16 + 6),   M = the unit's score bound (above):
 // D M for the fp32 accumulation of the D exact fp16 products of a score, 5 M + 3 ln P for the
-// rounded 1 / sqrt(D), the row's log-sum rounded to fp32 (|lse| <= M + ln P), the fused
-// multiply-add and the scaling inside the fast exponential (|s - lse| <= 2 M + ln P each), 2
+// rounded log2(e) / sqrt(D), the row's log-sum rounded to fp32 (|lse| <= M + ln P) and the fused
+// multiply-add (|s - lse| <= 2 M + ln P), twice over, 2
 // for the exponential itself, G P / 16 + 4 for a lane's running sum and the four lane exchanges;
 // tau = 2^-100 covers terms flushed to zero.  The band used is twice that, and at least kBand
 // (at the benchmark shapes eps is a tenth of kBand; the band only grows for prompts with far
 // larger queries and keys).  With every cheap value within the band of the exact one, a token
 // is surely a heavy hitter if fewer than Nh others could possibly be larger, surely discarded
 // if at least Nh others are surely larger, and in doubt otherwise.
-// flag[j] = 1 kept for sure (heavy or recent), 0 discarded for sure, 2 in doubt.
-// One thread per token.   grid = U * ceil(P / 256), block = 256.
+// Both counts are compared with the rank of j among the candidates, and hi(a) = a (1 + band) + tau,
+// lo(a) = a (1 - band) - tau grow with a, so two order statistics decide: "fewer than Nh others could be larger"
+// is hi(the (Nh + 1)-th largest) < lo(a_j), "at least Nh others surely are" is lo(the Nh-th largest) > hi(a_j).
+// The Nh-th largest comes from a radix selection over the bits of the values (three passes of 11, 11 and 10
+// bits; a sum that is not a number ranks last and is itself kept), the next one from one more pass.
+// flag[j] = 1 kept for sure (heavy or recent), 0 discarded for sure, 2 in doubt.  list, count: the tokens
+// whose exact column sum is wanted (flag != 0), ascending.  With Lambda-masking (lambda) the first Nh and
+// the last Nr tokens are kept, nothing is in doubt and approx is not looked at.
+// One block per unit.  Counting every pair of candidates took 350 us for 2048 units x 1024 tokens and 1450 us
+// for 128 x 8192; 26 and 56 now, the list included.   grid = U, block = 256.  qmax: see the cheap pass; kmax shares
+// the place of count.
 // -------------------------------------------------------------------------------------
 constexpr float kBand = 1.0f / 256.0f;
 __host__ __device__ inline float colapprox_error_bound(float M, int D, int P, int G)
 {
   return 5.9604645e-08f * ((float)(D + 6) * M + 3.f * logf((float)P) + (float)G * (float)P / 16.f + 6.f);
 }
-__global__ __launch_bounds__(256) void prefill_band_kernel(const float *__restrict__ approx,
-                                                           const float *__restrict__ bound, int D, int G, int P,
-                                                           int Nh, int Nr, int32_t *__restrict__ flag)
+// exclusive sum over the 256 threads of a block; total: the sum of all.  s_wave: 4 ints
+__device__ inline int block_scan(int x, int *s_wave, int &total)
 {
-  const int nb = (P + 255) / 256;
-  const size_t u = blockIdx.x / nb;
-  const int j = (int)(blockIdx.x % nb) * 256 + (int)threadIdx.x;
-  if (j >= P) return;
-  const float *a = approx + u * (size_t)P;
-  const float band = fmaxf(kBand, 2.f * colapprox_error_bound(bound[u], D, P, G));
-  const float tau = 7.8886091e-31f;                      // 2^-100
-  const int ncand = P - Nr;
-  int f = 1;                                    // recent
-  if (j < ncand) {
-    const float lo = a[j] * (1.f - band) - tau, hi = a[j] * (1.f + band) + tau;
-    int maybe_larger = 0, surely_larger = 0;
-    for (int i = 0; i < ncand; ++i) {
-      const float b = a[i];
-      maybe_larger += (b * (1.f + band) + tau >= lo) ? 1 : 0;   // counts j itself
-      surely_larger += (b * (1.f - band) - tau > hi) ? 1 : 0;
-    }
-    f = (maybe_larger - 1 < Nh) ? 1 : (surely_larger >= Nh ? 0 : 2);
+  const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+  int v = x;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(v, o);
+    if (lane >= o) v += y;
   }
-  flag[u * (size_t)P + j] = f;
-}
-
-// -------------------------------------------------------------------------------------
-// List of the tokens whose exact column sum is wanted (flag != 0), ascending, per unit.
-// grid = U, block = 256.
-// -------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void prefill_compact_kernel(const int32_t *__restrict__ flag, int P,
-                                                              int32_t *__restrict__ list,
-                                                              int32_t *__restrict__ count)
-{
-  __shared__ int s_cnt[256];
-  const size_t u = blockIdx.x;
-  const int tid = threadIdx.x;
-  const int32_t *f = flag + u * (size_t)P;
-  int32_t *out = list + u * (size_t)P;
-  const int chunk = (P + 255) / 256;
-  const int lo = tid * chunk < P ? tid * chunk : P, hi = (lo + chunk < P) ? lo + chunk : P;
-  int cnt = 0;
-  for (int j = lo; j < hi; ++j) cnt += f[j] != 0 ? 1 : 0;
-  s_cnt[tid] = cnt;
+  __syncthreads();                                        // the scan before is done with s_wave
+  if (lane == 63) s_wave[wave] = v;
   __syncthreads();
-  int base = 0;
-  for (int t = 0; t < tid; ++t) base += s_cnt[t];
-  for (int j = lo; j < hi; ++j)
-    if (f[j] != 0) out[base++] = j;
-  if (tid == 255) count[u] = base;
+  int before = 0;
+  total = 0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    before += w < wave ? s_wave[w] : 0;
+    total += s_wave[w];
+  }
+  return before + v - x;
+}
+__global__ __launch_bounds__(256) void prefill_select_kernel(const float *__restrict__ approx,
+                                                             const unsigned *__restrict__ qmax, int D, int G, int P,
+                                                             int Nh, int Nr, int lambda, int32_t *__restrict__ flag,
+                                                             int32_t *__restrict__ list, int32_t *__restrict__ count)
+{
+  constexpr int kBins = 2048, kPer = kBins / 256;
+  __shared__ int s_hist[kBins];
+  __shared__ int s_wave[4], s_bin, s_rank, s_more;
+  __shared__ unsigned s_next;
+  const size_t u = blockIdx.x;
+  const int tid = threadIdx.x, ncand = P - Nr;
+  const float *a = approx + u * (size_t)P;
+  float t1 = -1.f, t2 = -1.f, band = 0.f;                 // the Nh-th and (Nh + 1)-th largest; -1: there is none
+  const float tau = 7.8886091e-31f;                       // 2^-100
+  if (!lambda) {
+    // the largest score magnitude: max_i |q_i| max_j |k_j| / sqrt(D), rounded up a little: the squared
+    // norms carry fp32 rounding themselves
+    const float M = sqrtf(__uint_as_float(qmax[u])) * sqrtf(__uint_as_float((unsigned)count[u])) *
+                    (float)(1.0 / sqrt((double)D)) * 1.001f;
+    band = fmaxf(kBand, 2.f * colapprox_error_bound(M, D, P, G));
+    unsigned prefix = 0, mask = 0;                        // bits of the Nh-th largest known so far
+    int rank = Nh;                                        // its rank among the values with those bits, from 1
+    bool found = Nh > 0;
+    for (int pass = 0; pass < 3 && found; ++pass) {
+      const int shift = pass == 0 ? 21 : pass == 1 ? 10 : 0, bins = pass == 2 ? 1024 : kBins;
+      for (int i = tid; i < kBins; i += 256) s_hist[i] = 0;
+      if (tid == 0) s_bin = -1;
+      __syncthreads();
+      for (int j = tid; j < ncand; j += 256) {
+        const unsigned x = __float_as_uint(a[j]);
+        if (x <= 0x7f800000u && (x & mask) == prefix) atomicAdd(&s_hist[(x >> shift) & (bins - 1)], 1);
+      }
+      __syncthreads();
+      // thread t takes the bins from the top down: kPer of them, above them the threads before
+      int mine = 0, total;
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) mine += s_hist[kBins - 1 - (tid * kPer + i)];
+      int above = block_scan(mine, s_wave, total);
+      if (above < rank && above + mine >= rank) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+          const int bin = kBins - 1 - (tid * kPer + i), n = s_hist[bin];
+          if (above < rank && above + n >= rank) {
+            s_bin = bin;
+            s_rank = rank - above;
+          }
+          above += n;
+        }
+      }
+      __syncthreads();
+      found = s_bin >= 0;                                 // not: fewer than Nh values that are numbers
+      if (found) {
+        prefix |= (unsigned)s_bin << shift;
+        mask |= (unsigned)(bins - 1) << shift;
+        rank = s_rank;
+      }
+      __syncthreads();
+    }
+    // the next one: the same value if it is there once more, else the largest below it
+    if (tid == 0) {
+      s_more = 0;
+      s_next = 0;
+    }
+    __syncthreads();
+    if (found || Nh == 0) {
+      int same = 0;
+      unsigned next = 0;
+      for (int j = tid; j < ncand; j += 256) {
+        const unsigned x = __float_as_uint(a[j]);
+        if (x > 0x7f800000u) continue;
+        if (found && x == prefix) ++same;
+        else if ((Nh == 0 || x < prefix) && x + 1u > next) next = x + 1u;   // + 1: 0 stands for none
+      }
+      if (same) atomicAdd(&s_more, same);
+      if (next) atomicMax(&s_next, next);
+      __syncthreads();
+      if (found) t1 = __uint_as_float(prefix);
+      if (found && s_more > rank) t2 = t1;
+      else if (s_next) t2 = __uint_as_float(s_next - 1u);
+    }
+    __syncthreads();
+  }
+  const float keep_above = t2 * (1.f + band) + tau, drop_below = t1 * (1.f - band) - tau;
+  int32_t *f = flag + u * (size_t)P, *out = list + u * (size_t)P;
+  auto flag_of = [&](int j) {
+    if (j >= ncand) return 1;                             // recent
+    if (lambda) return j < Nh ? 1 : 0;
+    const float x = a[j], lo = x * (1.f - band) - tau, hi = x * (1.f + band) + tau;
+    if (!(x == x) || keep_above < lo) return 1;
+    return Nh == 0 || drop_below > hi ? 0 : 2;
+  };
+  const int chunk = (P + 255) / 256;
+  const int j0 = tid * chunk < P ? tid * chunk : P, j1 = j0 + chunk < P ? j0 + chunk : P;
+  int cnt = 0;
+  for (int j = j0; j < j1; ++j) {
+    const int x = flag_of(j);
+    f[j] = x;
+    cnt += x != 0 ? 1 : 0;
+  }
+  int total, base = block_scan(cnt, s_wave, total);
+  for (int j = j0; j < j1; ++j)
+    if (flag_of(j) != 0) out[base++] = j;
+  if (tid == 0) count[u] = total;
 }
 
 // -------------------------------------------------------------------------------------
@@ -1319,7 +1430,7 @@ static hipError_t launch_prefill_t(const PrefillArgs &a, hipStream_t st)
         d->n_heavy, d->n_recent, (d->flags & LESSDEC_FLAG_SPARSE_DENOM) ? 1 : 0, a.lse, (T *)a.out);
   } else {
     if constexpr (sizeof(T) == 2) {
-      if ((e = launch_rows_f16(a.Q, a.K, a.V, U * G, G, P, D, a.lse, a.out, st)) != hipSuccess) return e;
+      if ((e = launch_rows_f16(a.Q, a.K, a.V, U * G, G, P, D, a.lse, a.out, (unsigned *)a.bound, (unsigned *)a.count, st)) != hipSuccess) return e;
     } else {
       prefill_rowpass_kernel<T, D><<<(U * G + kXcds - 1) / kXcds * kXcds * tiles, 64 * kPrefillWaves, 0, st>>>(
           (const T *)a.Q, (const T *)a.K, (const T *)a.V, U * G, G, P, a.lse, (T *)a.out);
@@ -1334,23 +1445,21 @@ static hipError_t launch_prefill_t(const PrefillArgs &a, hipStream_t st)
   const unsigned rank_grid = U * (unsigned)((P + 255) / 256);
   int32_t *keep = a.slot_of;
   if (P > C && (lambda || sizeof(T) == 2)) {
-    if (lambda) {
-      prefill_rank_kernel<<<rank_grid, 256, 0, st>>>(a.colsum, P, d->n_heavy, d->n_recent, 1, a.slot_of);
-    } else {
-      if constexpr (sizeof(T) == 2) {
-        const unsigned agrid = (U + kXcds - 1) / kXcds * kXcds *
-                               (unsigned)((((P + 15) / 16 + kApproxTiles - 1) / kApproxTiles + kPrefillWaves - 1) /
-                                          kPrefillWaves);
-        prefill_colapprox_kernel<D><<<agrid, 64 * kPrefillWaves, 0, st>>>((const __half *)a.Q, (const __half *)a.K, U,
-                                                                         P, a.lse, G, a.approx);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        prefill_scorebound_kernel<D><<<U, 256, 0, st>>>((const __half *)a.Q, (const __half *)a.K, P, G, a.bound);
+    if constexpr (sizeof(T) == 2) {
+      if (!lambda) {
+        // 256 keys per workgroup; 128 where that leaves compute units idle
+        const unsigned wide = prefill_grid(U, (unsigned)((P + 255) / 256)), narrow = prefill_grid(U, (unsigned)((P + 127) / 128));
+        if (wide >= 512)
+          prefill_colapprox_kernel<D, 4><<<wide, 64 * kPrefillWaves, 0, st>>>(
+              (const __half *)a.Q, (const __half *)a.K, U, P, a.lse, G, a.approx, (unsigned *)a.bound, (unsigned *)a.count);
+        else
+          prefill_colapprox_kernel<D, 2><<<narrow, 64 * kPrefillWaves, 0, st>>>(
+              (const __half *)a.Q, (const __half *)a.K, U, P, a.lse, G, a.approx, (unsigned *)a.bound, (unsigned *)a.count);
         if ((e = hipGetLastError()) != hipSuccess) return e;
       }
-      prefill_band_kernel<<<rank_grid, 256, 0, st>>>(a.approx, a.bound, D, G, P, d->n_heavy, d->n_recent, a.slot_of);
     }
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    prefill_compact_kernel<<<U, 256, 0, st>>>(a.slot_of, P, a.list, a.count);
+    prefill_select_kernel<<<U, 256, 0, st>>>(a.approx, (const unsigned *)a.bound, D, G, P, d->n_heavy, d->n_recent,
+                                             lambda ? 1 : 0, a.slot_of, a.list, a.count);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if constexpr (sizeof(T) == 2) {
       e = launch_columns_f16(a.Q, a.K, U, G, P, D, a.lse, a.list, a.count, C, a.colsum, st);

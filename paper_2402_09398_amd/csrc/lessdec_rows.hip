@@ -56,7 +56,7 @@ struct RowTile {
 template <int D, int W, bool OUT>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) void rows_f16_kernel(
     const __half *__restrict__ Q, const __half *__restrict__ K, const __half *__restrict__ V, unsigned U, int G, int P,
-    double *__restrict__ lse, __half *__restrict__ out)
+    double *__restrict__ lse, __half *__restrict__ out, unsigned *__restrict__ zero0, unsigned *__restrict__ zero1)
 {
   // U counts query rows here: unit u's G query heads are rows u G .. u G + G - 1 of Q, out and
   // lse, and attend over unit u's keys and values
@@ -245,6 +245,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     }
   };
   if (tid < 2) s_bad[tid] = -1;
+  if (tid == 0 && pb.grp == 0 && u == ukv * (size_t)G) zero0[ukv] = zero1[ukv] = 0u;
   if constexpr (OUT)                                      // the values of the tile before the first: weighed 0
     for (int i = tid; i < Tile::kValBytes / 4; i += 64 * W) reinterpret_cast<unsigned *>(s_val[2])[i] = 0u;
   fetch(0);
@@ -344,28 +345,28 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 
 template <int D, int W>
 static hipError_t launch_rows_t(const void *Q, const void *K, const void *V, unsigned UG, int G, int P, double *lse,
-                                void *out, hipStream_t st)
+                                void *out, unsigned *zero0, unsigned *zero1, hipStream_t st)
 {
   const unsigned ngrp = (unsigned)((P + 16 * W - 1) / (16 * W));
   if (out != nullptr)
     rows_f16_kernel<D, W, true><<<prefill_grid(UG, ngrp), 64 * W, 0, st>>>((const __half *)Q, (const __half *)K,
-                                                                           (const __half *)V, UG, G, P, lse, (__half *)out);
+                                                                           (const __half *)V, UG, G, P, lse, (__half *)out, zero0, zero1);
   else
     rows_f16_kernel<D, W, false><<<prefill_grid(UG, ngrp), 64 * W, 0, st>>>((const __half *)Q, (const __half *)K,
-                                                                            (const __half *)V, UG, G, P, lse, nullptr);
+                                                                            (const __half *)V, UG, G, P, lse, nullptr, zero0, zero1);
   return hipGetLastError();
 }
 
 hipError_t launch_rows_f16(const void *Q, const void *K, const void *V, unsigned UG, int G, int P, int D, double *lse,
-                           void *out, hipStream_t st)
+                           void *out, unsigned *zero0, unsigned *zero1, hipStream_t st)
 {
   // 128 queries per workgroup halve the splitting of keys into digits (18.9 against 19.5 ms for 128 units x
   // 8192 tokens, the whole call); on shorter prompts the waves of the wider group wait too
   // long for the ones whose diagonal comes last (7.9 against 7.2 ms for 2048 units x 1024 tokens)
   const bool wide = P >= 4096;
   if (D == 128)
-    return wide ? launch_rows_t<128, 8>(Q, K, V, UG, G, P, lse, out, st) : launch_rows_t<128, 4>(Q, K, V, UG, G, P, lse, out, st);
-  return wide ? launch_rows_t<64, 8>(Q, K, V, UG, G, P, lse, out, st) : launch_rows_t<64, 4>(Q, K, V, UG, G, P, lse, out, st);
+    return wide ? launch_rows_t<128, 8>(Q, K, V, UG, G, P, lse, out, zero0, zero1, st) : launch_rows_t<128, 4>(Q, K, V, UG, G, P, lse, out, zero0, zero1, st);
+  return wide ? launch_rows_t<64, 8>(Q, K, V, UG, G, P, lse, out, zero0, zero1, st) : launch_rows_t<64, 4>(Q, K, V, UG, G, P, lse, out, zero0, zero1, st);
 }
 
 // -------------------------------------------------------------------------------------
