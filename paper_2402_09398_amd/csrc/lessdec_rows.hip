@@ -185,14 +185,13 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
       const double d = none ? 0.0 : lim == -__builtin_inf() ? ceil(top) : fmax(0.0, ceil(top));
       const int k = d <= 0.0 ? 0 : d < 2000.0 ? -(int)d : -2000;   // the rescaling is a power of two
       const float af = __builtin_ldexpf(1.f, k);
-      const _Float16 ah = (_Float16)af;
       L = __builtin_ldexp(L, k);
 #pragma unroll
       for (int b = 0; b < DB; ++b) O[b] *= af;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {                       // those not added to O yet
-        ph[i] *= ah;
-        pl[i] *= ah;
+      for (int i = 0; i < 4; ++i) {                       // those not added to O yet (af itself may lie below the halves)
+        ph[i] = v2h{(_Float16)((float)ph[i].x * af), (_Float16)((float)ph[i].y * af)};
+        pl[i] = v2h{(_Float16)((float)pl[i].x * af), (_Float16)((float)pl[i].y * af)};
       }
 #pragma unroll
       for (int w = 0; w < 4; ++w) y[w] -= d;

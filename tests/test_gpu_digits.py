@@ -74,3 +74,19 @@ def test_rows_before_a_value_that_is_not_finite(value):
     dirty["V"][:, 70, 7] = value
     a, b = (hz.gpu_run(w, x)["prefill_out"] for x in (clean, dirty))
     assert np.array_equal(a[:, :64].view(np.uint16), b[:, :64].view(np.uint16))
+
+
+@pytest.mark.parametrize("before,after", [(20, 40), (36, 50), (20, 50), (3, 20)])
+@pytest.mark.parametrize("low,high", [(10.0, 17.5), (10.0, 25.0), (9.0, 11.0)])
+def test_maximum_that_jumps(before, after, low, high):
+    """A weight just below the limit for moving the maximum, not yet multiplied with its value when a far larger
+    score moves it: it keeps its share (e^(low - high), with a value that makes it visible)."""
+    w = shape(70, head_dim=64)
+    inp = wl.all_inputs(w)
+    inp["Q"][...] = 0
+    inp["Q"][..., 0] = 8.0                               # score = first element of the key
+    inp["K"][..., 0] = 0.0
+    inp["K"][:, before, 0] = low
+    inp["K"][:, after, 0] = high
+    inp["V"][:, before, :] = 300.0
+    run(w, inp)
