@@ -308,8 +308,11 @@ __global__ __launch_bounds__(256) void prefill_psimax_kernel(const float *__rest
 // P / 64: what the low-rank part of Eq. 3 needs for a query whose discarded pairs reach at least
 // to 64 kb.  fp32 sums (they only enter attention outputs and their normalisation, never a
 // score; the state itself is built in fp64 by the finalize kernel).
-// One workgroup per unit walks the keys in order, 64 at a time through the LDS; thread (d, rg)
-// owns column d of rows rg, rg + 256 / D, ... of H, RC of them.   grid = U, block = 256.
+// First every block of 64 keys by itself (a workgroup each, psi through the LDS; thread (d, rg)
+// owns column d of rows rg, rg + 256 / D, ... of H, RC of them), its sum left where the prefix
+// after it belongs; then a running sum over the blocks, a thread per entry.  One workgroup per unit walking all keys
+// took 1010 us for 320 units x 2048 tokens at rank 16; 88 + 36 now.
+// grid = U * (P / 64), block = 256;  scan: grid = U * ceil((R D + R) / 256), block = 256.
 // -------------------------------------------------------------------------------------
 constexpr int kPrefixKeys = 64;
 template <typename T, int D, int RC>
@@ -320,42 +323,52 @@ __global__ __launch_bounds__(256) void prefill_prefix_kernel(const T *__restrict
 {
   constexpr int NG = 256 / D;                               // row groups
   __shared__ float s_psi[kPrefixKeys][LESSDEC_MAX_RANK + 1];
-  const size_t u = blockIdx.x;
+  const int nblk = P / kPrefixKeys, kb = (int)(blockIdx.x % nblk), j0 = kb * kPrefixKeys;   // whole blocks only
+  const size_t u = blockIdx.x / nblk;
   const int tid = threadIdx.x, d = tid % D, rg = tid / D;
-  const int nkb = P / kPrefixKeys + 1;
-  const T *Vu = V + u * (size_t)P * D;
-  const float *pa = psi_all + u * (size_t)P * R;
-  float *hu = hpre + u * (size_t)nkb * R * D;
-  float *zu = zpre + u * (size_t)nkb * R;
+  const T *Vu = V + (u * (size_t)P + j0) * D;
+  const float *pa = psi_all + (u * (size_t)P + j0) * R;
+  for (int i = tid; i < kPrefixKeys * R; i += 256) {
+    const int jj = i / R, r = i % R;
+    s_psi[jj][r] = j0 + jj >= Nh ? pa[i] : 0.f;             // the first Nh pairs are never discarded
+  }
+  __syncthreads();
   float acc[RC];
 #pragma unroll
   for (int i = 0; i < RC; ++i) acc[i] = 0.f;
-  float zacc = 0.f;                                         // thread r < R: z's entry r
-  for (int kb = 0; kb < nkb; ++kb) {
-    // the state before this block of keys
-#pragma unroll
-    for (int i = 0; i < RC; ++i) {
-      const int r = rg + NG * i;
-      if (r < R) hu[((size_t)kb * R + r) * D + d] = acc[i];
-    }
-    if (tid < R) zu[(size_t)kb * R + tid] = zacc;
-    const int j0 = kb * kPrefixKeys;
-    if (j0 >= P) break;                                     // uniform
-    const int nj = P - j0 < kPrefixKeys ? P - j0 : kPrefixKeys;
-    __syncthreads();                                        // the previous block's readers are done
-    for (int i = tid; i < nj * R; i += 256) {
-      const int jj = i / R, r = i % R;
-      s_psi[jj][r] = j0 + jj >= Nh ? pa[(size_t)j0 * R + i] : 0.f;   // the first Nh pairs are never discarded
-    }
-    __syncthreads();
 #pragma unroll 8
-    for (int jj = 0; jj < nj; ++jj) {
-      const float v = Store<T>::to_float(Vu[(size_t)(j0 + jj) * D + d]);
+  for (int jj = 0; jj < kPrefixKeys; ++jj) {
+    const float v = Store<T>::to_float(Vu[(size_t)jj * D + d]);
 #pragma unroll
-      for (int i = 0; i < RC; ++i) acc[i] = fmaf(s_psi[jj][(rg + NG * i) % (LESSDEC_MAX_RANK + 1)], v, acc[i]);
-    }
-    if (tid < R)
-      for (int jj = 0; jj < nj; ++jj) zacc += s_psi[jj][tid];
+    for (int i = 0; i < RC; ++i) acc[i] = fmaf(s_psi[jj][(rg + NG * i) % (LESSDEC_MAX_RANK + 1)], v, acc[i]);
+  }
+  float *hu = hpre + (u * (nblk + 1) + kb + 1) * R * D;
+#pragma unroll
+  for (int i = 0; i < RC; ++i) {
+    const int r = rg + NG * i;
+    if (r < R) hu[(size_t)r * D + d] = acc[i];
+  }
+  if (tid < R) {
+    float zacc = 0.f;
+    for (int jj = 0; jj < kPrefixKeys; ++jj) zacc += s_psi[jj][tid];
+    zpre[(u * (nblk + 1) + kb + 1) * R + tid] = zacc;
+  }
+}
+__global__ __launch_bounds__(256) void prefill_prefix_scan_kernel(int nblk, int RD, int R, float *__restrict__ hpre,
+                                                                  float *__restrict__ zpre)
+{
+  const int per = (RD + R + 255) / 256;
+  const size_t u = blockIdx.x / per;
+  const int e = (int)(blockIdx.x % per) * 256 + (int)threadIdx.x;
+  if (e >= RD + R) return;
+  const int stride = e < RD ? RD : R;
+  float *p = e < RD ? hpre + u * (nblk + 1) * (size_t)RD + e : zpre + u * (nblk + 1) * (size_t)R + (e - RD);
+  float run = 0.f;
+  p[0] = 0.f;
+#pragma unroll 8
+  for (int kb = 1; kb <= nblk; ++kb) {
+    run += p[(size_t)kb * stride];
+    p[(size_t)kb * stride] = run;
   }
 }
 
@@ -915,7 +928,8 @@ __host__ __device__ inline float colapprox_error_bound(float M, int D, int P, in
 {
   return 5.9604645e-08f * ((float)(D + 6) * M + 3.f * logf((float)P) + (float)G * (float)P / 16.f + 6.f);
 }
-// exclusive sum over the 256 threads of a block; total: the sum of all.  s_wave: 4 ints
+// exclusive sum over the threads of a block of W waves; total: the sum of all.  s_wave: W ints
+template <int W>
 __device__ inline int block_scan(int x, int *s_wave, int &total)
 {
   const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
@@ -931,7 +945,7 @@ __device__ inline int block_scan(int x, int *s_wave, int &total)
   int before = 0;
   total = 0;
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
+  for (int w = 0; w < W; ++w) {
     before += w < wave ? s_wave[w] : 0;
     total += s_wave[w];
   }
@@ -974,7 +988,7 @@ __global__ __launch_bounds__(256) void prefill_select_kernel(const float *__rest
       int mine = 0, total;
 #pragma unroll
       for (int i = 0; i < kPer; ++i) mine += s_hist[kBins - 1 - (tid * kPer + i)];
-      int above = block_scan(mine, s_wave, total);
+      int above = block_scan<4>(mine, s_wave, total);
       if (above < rank && above + mine >= rank) {
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
@@ -1036,7 +1050,7 @@ __global__ __launch_bounds__(256) void prefill_select_kernel(const float *__rest
     f[j] = x;
     cnt += x != 0 ? 1 : 0;
   }
-  int total, base = block_scan(cnt, s_wave, total);
+  int total, base = block_scan<4>(cnt, s_wave, total);
   for (int j = j0; j < j1; ++j)
     if (flag_of(j) != 0) out[base++] = j;
   if (tid == 0) count[u] = total;
@@ -1223,34 +1237,51 @@ __global__ __launch_bounds__(256) void prefill_rank_kernel(const double *__restr
 // have left them in); their
 // rows are gathered into the cache (acc = column sum, pos, psi), unused slots cleared; the
 // discarded pairs build H = sum psi(k)^T v, z = sum psi(k) (Eq. 6) in fp64.
-// For the state, wave w owns D / 4 columns of H, two per lane, and its lanes split the
-// tokens between them (interleaved parts, combined by lane exchange at the end), R in
-// chunks of RC rows.  slot_of: in 1 / 0 (kept / discarded), out slot index / -1.
-// grid = U, block = 256, dynamic LDS = C ints.
+// For the state a wave takes 512 / D tokens at a time, D / 8 lanes per token with eight columns each, in
+// chunks of eight rows of H: a value of psi is widened once for eight columns and a value of V once for
+// eight rows, and z is one lane's work.  Tokens are dealt to the eight waves; the lane groups meet by a
+// reduce-scatter over the rows of H, the waves in the LDS.  Four waves with two columns a lane, z in every lane, took
+// 496 us for 2048 units x 1024 tokens and 1070 us for 128 x 8192 (one workgroup per unit either way); 291 and 222
+// now.  slot_of: in 1 / 0 (kept / discarded), out slot index / -1.
+// grid = U, block = 512, dynamic LDS = C ints.
 // -------------------------------------------------------------------------------------
-__device__ inline void load_pair(const __half *p, float &a, float &b)
+constexpr int kFinalWaves = 8;
+
+// eight stored elements (16-byte aligned), all zero unless mask is ~0, as doubles
+__device__ inline void load_eight(const __half *p, unsigned mask, double (&v)[8])
 {
-  const __half2 h = *reinterpret_cast<const __half2 *>(p);
-  a = __low2float(h);
-  b = __high2float(h);
+  const uint4 x = *reinterpret_cast<const uint4 *>(p);
+  const unsigned w[4] = {x.x & mask, x.y & mask, x.z & mask, x.w & mask};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const __half2 h = __builtin_bit_cast(__half2, w[i]);
+    v[2 * i] = (double)__low2float(h);
+    v[2 * i + 1] = (double)__high2float(h);
+  }
 }
-__device__ inline void load_pair(const float *p, float &a, float &b)
+__device__ inline void load_eight(const float *p, unsigned mask, double (&v)[8])
 {
-  const float2 f = *reinterpret_cast<const float2 *>(p);
-  a = f.x;
-  b = f.y;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const uint4 x = reinterpret_cast<const uint4 *>(p)[k];
+    const unsigned w[4] = {x.x & mask, x.y & mask, x.z & mask, x.w & mask};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[4 * k + i] = (double)__uint_as_float(w[i]);
+  }
 }
 
-template <typename T, int D, int RC>
-__global__ __launch_bounds__(256) void prefill_finalize_kernel(
+template <typename T, int D>
+__global__ __launch_bounds__(64 * kFinalWaves) void prefill_finalize_kernel(
     const T *__restrict__ K, const T *__restrict__ V, int P, const double *__restrict__ colsum,
     int32_t *__restrict__ slot_of, const float *__restrict__ psi_all, int C, int R,
     T *__restrict__ k_cache, T *__restrict__ v_cache, double *__restrict__ acc,
     int32_t *__restrict__ pos, float *__restrict__ psi, float *__restrict__ H,
     double *__restrict__ z, int32_t *__restrict__ n_seen, int32_t *__restrict__ pend_slot, int ring_nh)
 {
+  constexpr int THREADS = 64 * kFinalWaves, RC = 8;
   extern __shared__ int s_tok[];                           // [C] token held by each slot
-  __shared__ int s_cnt[256];
+  __shared__ int s_wave[kFinalWaves];
+  __shared__ double s_part[kFinalWaves / 2][RC][D], s_z[kFinalWaves][RC];
   const size_t u = blockIdx.x;
   const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
   const T *Ku = K + u * (size_t)P * D, *Vu = V + u * (size_t)P * D;
@@ -1258,16 +1289,13 @@ __global__ __launch_bounds__(256) void prefill_finalize_kernel(
   const float *pa = psi_all + u * (size_t)P * R;
   const int kept = P < C ? P : C;
 
-  // 1) slot = number of kept tokens before j: per-thread contiguous chunk + the 256 counts
+  // 1) slot = number of kept tokens before j: per-thread contiguous chunk + the threads before
   {
-    const int chunk = (P + 255) / 256;
+    const int chunk = (P + THREADS - 1) / THREADS;
     const int lo = tid * chunk < P ? tid * chunk : P, hi = (lo + chunk < P) ? lo + chunk : P;
-    int cnt = 0;
+    int cnt = 0, total;
     for (int j = lo; j < hi; ++j) cnt += so[j];
-    s_cnt[tid] = cnt;
-    __syncthreads();
-    int base = 0;
-    for (int t = 0; t < tid; ++t) base += s_cnt[t];
+    int base = block_scan<kFinalWaves>(cnt, s_wave, total);
     for (int j = lo; j < hi; ++j) {
       const int keep = so[j];
       // ring_nh >= 0: the slots as in-place replacement leaves them when the first ring_nh tokens
@@ -1283,7 +1311,7 @@ __global__ __launch_bounds__(256) void prefill_finalize_kernel(
   // 2) gather: rows moved as 16-byte vectors, 64 / kVecs slots per wave at a time
   constexpr int kVecs = D * (int)sizeof(T) / 16;           // per row: 8, 16 or 32
   constexpr int kSlotsPerWave = 64 / kVecs;
-  for (int s = wave * kSlotsPerWave + lane / kVecs; s < C; s += 4 * kSlotsPerWave) {
+  for (int s = wave * kSlotsPerWave + lane / kVecs; s < C; s += kFinalWaves * kSlotsPerWave) {
     const size_t slot = u * C + s;
     const int i = lane % kVecs;
     if (s < kept) {
@@ -1304,65 +1332,93 @@ __global__ __launch_bounds__(256) void prefill_finalize_kernel(
     }
   }
 
-  // 3) state of the discarded pairs.  Kept tokens go through the same arithmetic with a zero
-  // weight, so that nothing in the loop depends on a load and iterations overlap.
-  constexpr int LW = D / 8, PARTS = 64 / LW;               // lanes per token (2 columns each), parts
-  const int col = wave * (D / 4) + 2 * (lane % LW), part = lane / LW;
+  // 3) state of the discarded pairs.  Kept tokens go through the same arithmetic with values and psi of
+  // z zeroed, so that no load stands under a condition.
+  constexpr int LPT = D / 8, TPW = 64 / LPT;               // lanes per token, tokens per wave at a time
+  const int dl = lane % LPT, tp = lane / LPT;
   const bool vec4 = R % 4 == 0;                            // psi rows readable as 16-byte vectors
-  constexpr int kUnroll = RC >= 16 ? 2 : 4;                // tokens in flight per lane (register budget)
   for (int r0 = 0; r0 < R; r0 += RC) {
     const int rn = R - r0 < RC ? R - r0 : RC;
-    double h0[RC], h1[RC], zs[RC];
+    const int rz = r0 + (dl < rn ? dl : 0);                // the lane's row of z (lanes dl < rn)
+    double h[RC][8], zs = 0.0;
 #pragma unroll
-    for (int r = 0; r < RC; ++r) h0[r] = h1[r] = zs[r] = 0.0;
-    auto token = [&](int j, const float (&gj)[RC]) {
-      const double w = so[j] < 0 ? 1.0 : 0.0;
-      float vf0, vf1;
-      load_pair(Vu + (size_t)j * D + col, vf0, vf1);
-      const double v0 = w * (double)vf0, v1 = w * (double)vf1;
+    for (int r = 0; r < RC; ++r)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) h[r][i] = 0.0;
+#pragma unroll 2
+    for (int j0 = wave * TPW; j0 < P; j0 += kFinalWaves * TPW) {
+      const int j = j0 + tp < P ? j0 + tp : P - 1;
+      const unsigned mask = (so[j] < 0 && j0 + tp < P) ? ~0u : 0u;       // ~0: discarded
+      const float *pj = pa + (size_t)j * R + r0;
+      float gj[RC];
+      // rows past R repeat earlier ones; their sums are never stored
+      if (vec4) {
+#pragma unroll
+        for (int r4 = 0; r4 < RC / 4; ++r4) {
+          const float4 x = *reinterpret_cast<const float4 *>(pj + (4 * r4 < rn ? 4 * r4 : 0));
+          gj[4 * r4] = x.x; gj[4 * r4 + 1] = x.y; gj[4 * r4 + 2] = x.z; gj[4 * r4 + 3] = x.w;
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < RC; ++r) gj[r] = pj[r < rn ? r : 0];
+      }
+      const unsigned gz = __float_as_uint(pa[(size_t)j * R + rz]) & mask;
+      double v[8];
+      load_eight(Vu + (size_t)j * D + 8 * dl, mask, v);
+      zs += (double)__uint_as_float(gz);
 #pragma unroll
       for (int r = 0; r < RC; ++r) {
         const double g = (double)gj[r];
-        h0[r] = fma(g, v0, h0[r]);
-        h1[r] = fma(g, v1, h1[r]);
-        zs[r] = fma(g, w, zs[r]);
-      }
-    };
-    // rows past R repeat row 0 (unconditional loads); their sums are never stored
-    if (vec4) {
-#pragma unroll kUnroll
-      for (int j = part; j < P; j += PARTS) {
-        const float *pj = pa + (size_t)j * R + r0;
-        float gj[RC];
 #pragma unroll
-        for (int r4 = 0; r4 < RC / 4; ++r4)
-          *reinterpret_cast<float4 *>(gj + 4 * r4) = *reinterpret_cast<const float4 *>(pj + (4 * r4 < rn ? 4 * r4 : 0));
-        token(j, gj);
-      }
-    } else {
-#pragma unroll kUnroll
-      for (int j = part; j < P; j += PARTS) {
-        const float *pj = pa + (size_t)j * R + r0;
-        float gj[RC];
-#pragma unroll
-        for (int r = 0; r < RC; ++r) gj[r] = pj[r < rn ? r : 0];
-        token(j, gj);
+        for (int i = 0; i < 8; ++i) h[r][i] = fma(g, v[i], h[r][i]);
       }
     }
+    // the wave's token groups: a lane keeps half of its rows at each distance; row of h[k] is then row0 + k
+    int row0 = 0;
 #pragma unroll
-    for (int r = 0; r < RC; ++r) {
+    for (int o = 32, n = RC / 2; o >= LPT; o >>= 1, n >>= 1) {
+      const bool up = lane & o;
 #pragma unroll
-      for (int o = LW; o < 64; o <<= 1) {
-        h0[r] += __shfl_xor(h0[r], o);
-        h1[r] += __shfl_xor(h1[r], o);
-        zs[r] += __shfl_xor(zs[r], o);
-      }
-      if (r < rn && part == 0) {
-        H[(u * R + r0 + r) * D + col] = (float)h0[r];
-        H[(u * R + r0 + r) * D + col + 1] = (float)h1[r];
-      }
-      if (r < rn && tid == 0) z[u * R + r0 + r] = zs[r];
+      for (int k = 0; k < n; ++k)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const double send = up ? h[k][i] : h[k + n][i], keep = up ? h[k + n][i] : h[k][i];
+          h[k][i] = keep + __shfl_xor(send, o);
+        }
+      row0 += up ? n : 0;
+      zs += __shfl_xor(zs, o);
     }
+    constexpr int KEEP = RC / TPW;                         // rows a lane ends with: 2 or 1
+    // the waves: the upper half through the LDS to the lower, the lower four through the LDS to everyone
+    if (wave >= kFinalWaves / 2) {
+#pragma unroll
+      for (int k = 0; k < KEEP; ++k)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s_part[wave - kFinalWaves / 2][row0 + k][8 * dl + i] = h[k][i];
+    }
+    if (tp == 0 && dl < RC) s_z[wave][dl] = zs;
+    __syncthreads();
+    if (wave < kFinalWaves / 2) {
+#pragma unroll
+      for (int k = 0; k < KEEP; ++k)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s_part[wave][row0 + k][8 * dl + i] += h[k][i];
+    }
+    __syncthreads();
+    for (int x = tid; x < rn * D; x += THREADS) {
+      const int r = x / D, d = x % D;
+      double sum = 0.0;
+#pragma unroll
+      for (int w = 0; w < kFinalWaves / 2; ++w) sum += s_part[w][r][d];
+      H[(u * R + r0 + r) * D + d] = (float)sum;
+    }
+    if (tid < rn) {
+      double sum = 0.0;
+#pragma unroll
+      for (int w = 0; w < kFinalWaves; ++w) sum += s_z[w][tid];
+      z[u * R + r0 + tid] = sum;
+    }
+    if (r0 + RC < R) __syncthreads();                      // s_part, s_z are written again
   }
   if (tid == 0) {
     n_seen[u] = P;
@@ -1418,10 +1474,15 @@ static hipError_t launch_prefill_t(const PrefillArgs &a, hipStream_t st)
     if ((e = hipGetLastError()) != hipSuccess) return e;
     {
       const int rc = (d->rank + 256 / D - 1) / (256 / D);   // rows of H per thread
-#define LESSDEC_PREFIX(RC) prefill_prefix_kernel<T, D, RC><<<U, 256, 0, st>>>((const T *)a.V, a.psi_all, P, d->rank, \
-                                                                              d->n_heavy, a.hpre, a.zpre)
-      if (rc <= 4) LESSDEC_PREFIX(4); else if (rc <= 8) LESSDEC_PREFIX(8);
+      const int nblk = P / kPrefixKeys;
+#define LESSDEC_PREFIX(RC) prefill_prefix_kernel<T, D, RC><<<U * nblk, 256, 0, st>>>((const T *)a.V, a.psi_all, P, d->rank, \
+                                                                                     d->n_heavy, a.hpre, a.zpre)
+      if (nblk == 0) {}
+      else if (rc <= 4) LESSDEC_PREFIX(4); else if (rc <= 8) LESSDEC_PREFIX(8);
       else if (rc <= 16) LESSDEC_PREFIX(16); else LESSDEC_PREFIX(32);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+      prefill_prefix_scan_kernel<<<U * (unsigned)((d->rank * D + d->rank + 255) / 256), 256, 0, st>>>(
+          nblk, d->rank * D, d->rank, a.hpre, a.zpre);
 #undef LESSDEC_PREFIX
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -1489,16 +1550,7 @@ static hipError_t launch_prefill_t(const PrefillArgs &a, hipStream_t st)
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (!masked && (e = key_features()) != hipSuccess) return e;
   const size_t lds = (size_t)C * sizeof(int);
-  if (d->rank <= 4)
-    prefill_finalize_kernel<T, D, 4><<<U, 256, lds, st>>>(
-      (const T *)a.K, (const T *)a.V, P, a.colsum, keep, a.psi_all, C, d->rank, (T *)d->k_cache,
-      (T *)d->v_cache, d->acc, d->pos, d->psi, d->H, d->z, d->n_seen, d->pend_slot, ring_nh);
-  else if (d->rank <= 8)
-    prefill_finalize_kernel<T, D, 8><<<U, 256, lds, st>>>(
-      (const T *)a.K, (const T *)a.V, P, a.colsum, keep, a.psi_all, C, d->rank, (T *)d->k_cache,
-      (T *)d->v_cache, d->acc, d->pos, d->psi, d->H, d->z, d->n_seen, d->pend_slot, ring_nh);
-  else
-    prefill_finalize_kernel<T, D, 16><<<U, 256, lds, st>>>(
+  prefill_finalize_kernel<T, D><<<U, 64 * kFinalWaves, lds, st>>>(
       (const T *)a.K, (const T *)a.V, P, a.colsum, keep, a.psi_all, C, d->rank, (T *)d->k_cache,
       (T *)d->v_cache, d->acc, d->pos, d->psi, d->H, d->z, d->n_seen, d->pend_slot, ring_nh);
   return hipGetLastError();
