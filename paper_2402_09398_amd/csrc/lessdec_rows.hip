@@ -1,5 +1,7 @@
 // Prompt phase, fp16 storage: causal rows (log-sums and attention outputs) and exact column sums,
 // with the scores as exact integer products of digit planes (lessdec_digits.h).
+#include <type_traits>
+
 #include "lessdec_digits.h"
 #include "lessdec_internal.h"
 #include "lessdec_prefill.h"
@@ -9,7 +11,6 @@ namespace lessdec {
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef unsigned v2u __attribute__((ext_vector_type(2)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
-typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 
 // -------------------------------------------------------------------------------------
@@ -25,9 +26,9 @@ typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 //
 // Per 16 x 16 tile the matrix units need 32 x 16 cycles for the digit products and 8 x 16 for p V, the
 // vector units some 160 instructions of 4 to 5 cycles.  The two run side by side (fp64 matrix instructions
-// overlap with nothing), but a wave issues in order, so the loop is pipelined by one half: the
-// products of a half stand in one basic block with the weights of the half before it, p V of
-// the tile before and the staging of the tile after.  One barrier per tile: keys in two buffers, values in
+// overlap with nothing), but a wave issues in order, so the loop is pipelined by one tile: the
+// products of a tile stand in one basic block with the weights and p V of the tile before and the staging
+// of the tile after.  One barrier per tile: keys in two buffers, values in
 // three (p V of tile kt - 1 runs after the barrier of tile kt).
 // -------------------------------------------------------------------------------------
 constexpr int kRowKeys = 32;
@@ -156,16 +157,15 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   v4f O[DB];
 #pragma unroll
   for (int b = 0; b < DB; ++b) O[b] = v4f{0.f, 0.f, 0.f, 0.f};
-  v2h ph[4], pl[4];                                       // weights of a tile's 8 keys per lane, hi + lo
+  // the tile whose weights are still to come: base-2 scores less m of its two halves
+  double y[2][4];
+  auto no_weight = [&](double (&yy)[4]) __attribute__((always_inline)) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) ph[i] = pl[i] = v2h{(_Float16)0.f, (_Float16)0.f};
-  // the half whose weights are still to come: base-2 scores less m
-  double y[4];
-  auto no_weight = [&]() __attribute__((always_inline)) {
-#pragma unroll
-    for (int w = 0; w < 4; ++w) y[w] = kNoWeight;
+    for (int w = 0; w < 4; ++w) yy[w] = kNoWeight;
   };
-  no_weight();
+  no_weight(y[0]);
+  no_weight(y[1]);
+
   auto products = [&](int kt, int half, v4i (&s)[7]) __attribute__((always_inline)) {
     const unsigned char *buf = s_key[kt & 1];
 #pragma unroll
@@ -176,8 +176,8 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
       for (int pa = 0; pa < 4; ++pa)
         dot_planes(*reinterpret_cast<const v4i *>(buf + Tile::key_at(half, pa, kc, g, c)), qd.d[kc], pa, s);
   };
-  auto raise_max = [&]() __attribute__((always_inline)) {
-    double top = fmax(fmax(y[0], y[1]), fmax(y[2], y[3]));
+  auto raise_max = [&](double (&y)[2][4]) __attribute__((always_inline)) {
+    double top = fmax(fmax(fmax(y[0][0], y[0][1]), fmax(y[0][2], y[0][3])), fmax(fmax(y[1][0], y[1][1]), fmax(y[1][2], y[1][3])));
     if (__any(top > lim)) {
       top = fmax(top, __shfl_xor(top, 16));
       top = fmax(top, __shfl_xor(top, 32));
@@ -189,25 +189,24 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 #pragma unroll
       for (int b = 0; b < DB; ++b) O[b] *= af;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {                       // those not added to O yet (af itself may lie below the halves)
-        ph[i] = v2h{(_Float16)((float)ph[i].x * af), (_Float16)((float)ph[i].y * af)};
-        pl[i] = v2h{(_Float16)((float)pl[i].x * af), (_Float16)((float)pl[i].y * af)};
+      for (int w = 0; w < 4; ++w) {
+        y[0][w] -= d;
+        y[1][w] -= d;
       }
-#pragma unroll
-      for (int w = 0; w < 4; ++w) y[w] -= d;
       m += d;
       lim = none ? lim : kSlack;
     }
   };
-  auto scores = [&](const v4i (&s)[7]) __attribute__((always_inline)) {
+  auto scores = [&](const v4i (&s)[7], double (&yy)[4]) __attribute__((always_inline)) {
     const DotParts p = dot_join(s);
 #pragma unroll
-    for (int w = 0; w < 4; ++w) y[w] = dot_affine(p, w, cs, -m);
+    for (int w = 0; w < 4; ++w) yy[w] = dot_affine(p, w, cs, -m);
   };
-  // the weights of half `half` out of y, into ph, pl and L
-  auto weigh = [&](int half) __attribute__((always_inline)) {
+  // the weights of half `half` out of its scores, into hi + lo pairs and L
+  v8h ph, pl;
+  auto weigh = [&](const double (&yy)[4], int half) __attribute__((always_inline)) {
     double e[4];
-    exp2_f64(y, e);
+    exp2_f64(yy, e);
     float ef[4];
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
@@ -218,29 +217,22 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     }
     L += (e[0] + e[1]) + (e[2] + e[3]);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const v2h hi = {(_Float16)ef[2 * i], (_Float16)ef[2 * i + 1]};
-      const v2h lo = {(_Float16)(ef[2 * i] - (float)hi.x), (_Float16)(ef[2 * i + 1] - (float)hi.y)};
-      ph[2 * half + i] = hi;
-      pl[2 * half + i] = lo;
+    for (int w = 0; w < 4; ++w) {
+      const _Float16 hi = (_Float16)ef[w];
+      ph[4 * half + w] = hi;
+      pl[4 * half + w] = (_Float16)(ef[w] - (float)hi);
     }
   };
   // O += V^T p; only0: the tile's second half lies after all of the wave's queries
   auto add_values = [&](const unsigned char *val, bool only0) __attribute__((always_inline)) {
     if constexpr (!OUT) return;
-    v8h h, lo;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      h[2 * i] = ph[i].x; h[2 * i + 1] = ph[i].y;
-      lo[2 * i] = pl[i].x; lo[2 * i + 1] = pl[i].y;
-    }
 #pragma unroll
     for (int b = 0; b < DB; ++b) {
       uint4 raw = *reinterpret_cast<const uint4 *>(val + Tile::val_at(b, c, g));
       if (only0) raw.z = raw.w = 0;                       // whatever is there, infinities too, has no part in it
       const v8h a = __builtin_bit_cast(v8h, raw);
-      O[b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, h, O[b], 0, 0, 0);
-      O[b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, lo, O[b], 0, 0, 0);
+      O[b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, ph, O[b], 0, 0, 0);
+      O[b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, pl, O[b], 0, 0, 0);
     }
   };
   if (tid < 2) s_bad[tid] = -1;
@@ -261,30 +253,39 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     v4i s[7];
     const bool slow = qbad || __builtin_amdgcn_readfirstlane(s_bad[kt & 1]) == kt;
     if (kt < kt_wave && !slow) {                          // wave-uniform: every key before every query
+      double yn[2][4];
+      // one matrix instruction, then the vector instructions it runs beside
+      auto interleave = [](auto count) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < count.value; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);  // (4: 7 % slower)
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      };
       products(kt, 0, s);
-      weigh(1);                                           // the tile before's second half
-      scores(s);
-      raise_max();
+      weigh(y[0], 0);                                     // the tile before
+      weigh(y[1], 1);
+      interleave(std::integral_constant<int, 16 * KC>{});
+      scores(s, yn[0]);
       products(kt, 1, s);
       add_values(v_prev, false);
-      weigh(0);
       stage(kt + 1, v_next);
       fetch(kt + 2 <= kt_last ? kt + 2 : kt_last);
-      // one matrix instruction, then the vector instructions it runs beside (3: the same; 5: 3 % slower)
+      interleave(std::integral_constant<int, (OUT ? 2 * DB : 0) + 16 * KC>{});
+      scores(s, yn[1]);
+      raise_max(yn);
 #pragma unroll
-      for (int i = 0; i < (OUT ? 2 * DB : 0) + 16 * KC; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+      for (int w = 0; w < 4; ++w) {
+        y[0][w] = yn[0][w];
+        y[1][w] = yn[1][w];
       }
-      scores(s);
-      raise_max();
     } else {
       if (kt <= kt_wave) {
         const bool only0 = j0 + 16 > q0 + 15;             // the second half lies after all of the wave's queries
-        weigh(1);
+        weigh(y[0], 0);
+        weigh(y[1], 1);
         add_values(v_prev, false);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) ph[i] = pl[i] = v2h{(_Float16)0.f, (_Float16)0.f};
 #pragma unroll 1
         for (int half = 0; half < (only0 ? 1 : 2); ++half) {
           const int jh = j0 + 16 * half;
@@ -292,28 +293,35 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
             const v4d d = dot_tile_f64<D>([&](int i) { return Ku + (size_t)(jh + i < P ? jh + i : P - 1) * D; },
                                           Qu + (size_t)qrow * D, g, c);
 #pragma unroll
-            for (int w = 0; w < 4; ++w) y[w] = fma(d[w], cs, -m);
+            for (int w = 0; w < 4; ++w) y[0][w] = fma(d[w], cs, -m);
           } else {
             products(kt, half, s);
-            scores(s);
+            scores(s, y[0]);
           }
 #pragma unroll
-          for (int w = 0; w < 4; ++w) y[w] = (jh + 4 * g + w <= qi) ? y[w] : -__builtin_inf();
-          raise_max();
+          for (int w = 0; w < 4; ++w) {
+            y[0][w] = (jh + 4 * g + w <= qi) ? y[0][w] : -__builtin_inf();
+            y[1][w] = -__builtin_inf();
+          }
+          raise_max(y);
           // no weight for keys after the query, scores of -inf and what is not a number
 #pragma unroll
-          for (int w = 0; w < 4; ++w) y[w] = y[w] > kNoWeight ? y[w] : kNoWeight;
-          weigh(0);
-          if (half == 1) {                                // each half with the other half's places empty
-            ph[2] = ph[0]; ph[3] = ph[1]; pl[2] = pl[0]; pl[3] = pl[1];
-            ph[0] = ph[1] = pl[0] = pl[1] = v2h{(_Float16)0.f, (_Float16)0.f};
+          for (int w = 0; w < 4; ++w) y[0][w] = y[0][w] > kNoWeight ? y[0][w] : kNoWeight;
+          weigh(y[0], 0);
+          // each half with the other half's places empty
+          const v8h none = {};
+          const v8h h0 = ph, l0 = pl;
+#pragma unroll
+          for (int w = 0; w < 4; ++w) {
+            ph[w] = half == 0 ? h0[w] : none[w];
+            ph[4 + w] = half == 0 ? none[w] : h0[w];
+            pl[w] = half == 0 ? l0[w] : none[w];
+            pl[4 + w] = half == 0 ? none[w] : l0[w];
           }
           add_values(v_cur, only0);
         }
-        // nothing is left pending
-#pragma unroll
-        for (int i = 0; i < 4; ++i) ph[i] = pl[i] = v2h{(_Float16)0.f, (_Float16)0.f};
-        no_weight();
+        no_weight(y[0]);                                  // nothing is left pending
+        no_weight(y[1]);
       }
       if (kt < kt_last) {
         stage(kt + 1, v_next);
