@@ -96,7 +96,9 @@ __device__ inline float gelu_fast_f32(float x)
   a *= u;
   const float e = __builtin_amdgcn_exp2f(t * t * -0.72134752044448170368f);   // exp(-t^2/2)
   const float tq = t * (a * e);
-  return x >= 0.f ? x - tq : -tq;
+  // max(x, 0) on the bits: one instruction, where fmaxf quiets its input in another (a NaN stays one through tq)
+  const int xi = __builtin_bit_cast(int, x);
+  return __builtin_bit_cast(float, xi > 0 ? xi : 0) - tq;
 }
 
 // The same approximation evaluated in fp64 (absolute error 1e-9): for the handful of

@@ -57,6 +57,43 @@ __device__ inline MlpTiles<D> mlp_load_tiles(const __half *__restrict__ W1, cons
   return t;
 }
 
+// gelu of a lane's 4 + 4 hidden units, split for layer 2.  The vector instructions here bound the maps of
+// many rows, so the split is spelled out: two conversions per hi pair and one mixed-precision
+// fma per lo (x - hi is exact in fp32, so the one rounding is the conversion's, as in
+// (_Float16)(x - (float)hi), which takes three instructions).
+__device__ inline void mlp_activate(const v4f &h0, const v4f &h1, v8h &bhi, v8h &blo)
+{
+  typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+  typedef unsigned v4u __attribute__((ext_vector_type(4)));
+  v4u hi, lo;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const v4f &h = w < 2 ? h0 : h1;
+    float x0 = gelu_fast_f32(h[2 * (w % 2)]), x1 = gelu_fast_f32(h[2 * (w % 2) + 1]);
+    asm("" : "+v"(x0), "+v"(x1));                          // one fp32 value for both halves of the split
+    const unsigned p = __builtin_bit_cast(unsigned, v2h{(_Float16)x0, (_Float16)x1});
+    unsigned q;
+    asm("v_fma_mixlo_f16 %0, -%1, 1.0, %2 op_sel_hi:[1,0,0]" : "=v"(q) : "v"(p), "v"(x0));
+    asm("v_fma_mixhi_f16 %0, -%1, 1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(q) : "v"(p), "v"(x1));
+    hi[w] = p;
+    lo[w] = q;
+  }
+  bhi = __builtin_bit_cast(v8h, hi);
+  blo = __builtin_bit_cast(v8h, lo);
+}
+
+// Layer 1 of one group of 32 hidden units for 16 rows of x: h0[w], h1[w] are hidden units hid + 4 g + w and
+// hid + 16 + 4 g + w of row c.
+template <int D>
+__device__ inline void mlp_hidden(const MlpTiles<D> &t, const v8h (&bx)[D / 32], v4f &h0, v4f &h1)
+{
+#pragma unroll
+  for (int ks = 0; ks < D / 32; ++ks) {
+    h0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(t.a0[ks], bx[ks], h0, 0, 0, 0);
+    h1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(t.a1[ks], bx[ks], h1, 0, 0, 0);
+  }
+}
+
 // One wave, one group of 32 hidden units, 16 rows of x held in bx (lane (g, c): row c,
 // elements 32 ks + 8 g ..): adds W2[:, group] gelu(W1[group] x^T) to c2, whose register w
 // is output r = 4 g + w of row c.
@@ -64,22 +101,9 @@ template <int D>
 __device__ inline void mlp_apply_tiles(const MlpTiles<D> &t, const v8h (&bx)[D / 32], v4f &c2)
 {
   v4f h0 = {0.f, 0.f, 0.f, 0.f}, h1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int ks = 0; ks < D / 32; ++ks) {
-    h0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(t.a0[ks], bx[ks], h0, 0, 0, 0);
-    h1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(t.a1[ks], bx[ks], h1, 0, 0, 0);
-  }
-  // h0[w], h1[w]: hidden units hid + 4 g + w and hid + 16 + 4 g + w of row c
+  mlp_hidden<D>(t, bx, h0, h1);
   v8h bhi, blo;
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    const float x0 = gelu_fast_f32(h0[w]), x1 = gelu_fast_f32(h1[w]);
-    const _Float16 s0 = (_Float16)x0, s1 = (_Float16)x1;
-    bhi[w] = s0;
-    bhi[4 + w] = s1;
-    blo[w] = (_Float16)(x0 - (float)s0);
-    blo[4 + w] = (_Float16)(x1 - (float)s1);
-  }
+  mlp_activate(h0, h1, bhi, blo);
   c2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(t.a2, bhi, c2, 0, 0, 0);
   c2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(t.a2, blo, c2, 0, 0, 0);
 }

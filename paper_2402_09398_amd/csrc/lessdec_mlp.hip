@@ -84,18 +84,21 @@ __global__ __launch_bounds__(256) void mlp_pair_kernel(const MlpArgs a, const Ml
 
 // Many rows per head (the prompt phase): a workgroup keeps its head's weights in registers and
 // streams rows through them.  Wave w holds the groups of 32 hidden units w, w + 4, ... (NGW of
-// them: R' = 128 NGW) for the whole kernel; per chunk of 16 kRowTiles rows it loads the rows,
-// applies its groups, and the block adds the four layer-2 sums through the LDS and finishes the
+// them: R' = 128 NGW) for the whole kernel; per chunk of 16 rows it loads the rows and applies its
+// groups; after two chunks the block adds the four layer-2 sums through the LDS and finishes the
 // outputs as above (same arithmetic in the same order as mlp_psi_block: identical results).  The
 // next chunk's rows are requested before the current chunk's arithmetic.
+// Bound by vector instructions (17 per activation, two of them transcendental).  With one max, one
+// mixed-precision fma per low half, one barrier per 32 rows in place of three per 16, and layer 1 of the
+// next group issued between the activations of this one: 920 -> 787 us for 2048 units x 1024
+// tokens, 460 -> 395 for 128 x 8192 (R' = 512, R = 8).
 // grid = Hh * parts (head fastest), every block a contiguous share of the head's chunks.
-constexpr int kRowTiles = 1;
 template <int D, int NGW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void mlp_rows_kernel(const MlpArgs a,
                                                                                                   int parts)
 {
-  __shared__ float s_red[4][16][16 * kRowTiles + 1];       // [wave][r][row]
-  __shared__ double s_h2[16 * kRowTiles][17];              // [row][r]
+  __shared__ float s_red[2][4][16][32 + 1];                // [pair of chunks, in turn][wave][r][row]
+  __shared__ double s_h2[32][17];                          // [row][r], each row written and read by one wave
   const int tid = threadIdx.x, wave = tid / 64, l = tid % 64, g = l / 16, c = l % 16;
   const int Hh = a.Hh, Rp = a.Rp, R = a.R;
   const int h = (int)blockIdx.x % Hh, part = (int)blockIdx.x / Hh;
@@ -104,7 +107,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // 32-bit row arithmetic (the launcher checks that a head's rows fit): a 64-bit division per row
   // would be a long instruction sequence
   const unsigned rows_head = (unsigned)a.B * (unsigned)a.rpu, rpu = (unsigned)a.rpu;
-  const unsigned nchunk = (rows_head + 16 * kRowTiles - 1) / (16 * kRowTiles);
+  const unsigned nchunk = (rows_head + 15) / 16;
   const unsigned ch0 = (unsigned)((unsigned long)nchunk * part / parts);
   const unsigned ch1 = (unsigned)((unsigned long)nchunk * (part + 1) / parts);
   auto global_row = [&](unsigned i) -> size_t {
@@ -114,49 +117,67 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   MlpTiles<D> w[NGW];
 #pragma unroll
   for (int k = 0; k < NGW; ++k) w[k] = mlp_load_tiles<D>(W1, W2, Rp, R, 32 * (wave + 4 * k), g, c);
-  const int r = tid % 16;
   __shared__ double s_w3[16][17];                          // W3 of the head, widened once; W3 == nullptr: phi (Eq. 1)
   {
-    const int j = tid / 16;
+    const int r = tid % 16, j = tid / 16;
     s_w3[r][j] = (a.W3 != nullptr && r < R && j < R) ? (double)__half2float(a.W3[((size_t)h * R + r) * R + j]) : 0.0;
   }
+  // the lanes that finish a row: 8 where the outputs fit (all lanes have work for 32 rows), else 16
+  const int nr = R <= 8 ? 8 : 16, r = tid % nr, row_first = tid / nr, row_step = 256 / nr;
 
-  auto load_chunk = [&](unsigned ch, v8h (&bx)[kRowTiles][D / 32]) {
-#pragma unroll
-    for (int t = 0; t < kRowTiles; ++t) {
-      const unsigned i = (ch * kRowTiles + t) * 16 + c;
-      mlp_load_row<D>(a.x + (i < rows_head ? global_row(i) : 0) * D, g, bx[t]);   // padding: any row
-    }
+  auto load_chunk = [&](unsigned ch, v8h (&bx)[D / 32]) {
+    const unsigned i = ch * 16 + c;
+    mlp_load_row<D>(a.x + (i < rows_head ? global_row(i) : 0) * D, g, bx);   // padding: any row
   };
-  v8h bx_next[kRowTiles][D / 32];
+  v8h bx_next[D / 32];
   if (ch0 < ch1) load_chunk(ch0, bx_next);
   for (unsigned ch = ch0; ch < ch1; ++ch) {
-    v8h bx[kRowTiles][D / 32];
+    v8h bx[D / 32];
 #pragma unroll
-    for (int t = 0; t < kRowTiles; ++t)
-#pragma unroll
-      for (int ks = 0; ks < D / 32; ++ks) bx[t][ks] = bx_next[t][ks];
+    for (int ks = 0; ks < D / 32; ++ks) bx[ks] = bx_next[ks];
     load_chunk(ch + 1 < ch1 ? ch + 1 : ch, bx_next);
-    v4f c2[kRowTiles];
+    v4f c2 = {0.f, 0.f, 0.f, 0.f};
+    // layer 1 of the next group beside the activations of this one
+    v4f h0 = {0.f, 0.f, 0.f, 0.f}, h1 = {0.f, 0.f, 0.f, 0.f};
+    mlp_hidden<D>(w[0], bx, h0, h1);
 #pragma unroll
-    for (int t = 0; t < kRowTiles; ++t) c2[t] = v4f{0.f, 0.f, 0.f, 0.f};
+    for (int k = 0; k < NGW; ++k) {
+      v4f n0 = {0.f, 0.f, 0.f, 0.f}, n1 = {0.f, 0.f, 0.f, 0.f};
+      if (k + 1 < NGW) mlp_hidden<D>(w[k + 1], bx, n0, n1);
+      v8h bhi, blo;
+      mlp_activate(h0, h1, bhi, blo);
+      c2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[k].a2, bhi, c2, 0, 0, 0);
+      c2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[k].a2, blo, c2, 0, 0, 0);
+      if (k + 1 < NGW) {
 #pragma unroll
-    for (int k = 0; k < NGW; ++k)
+        for (int i = 0; i < 2 * (D / 32); ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x002, 12, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      h0 = n0;
+      h1 = n1;
+    }
+    const unsigned n = ch - ch0, half = n & 1;
+    float(*red)[16][32 + 1] = s_red[(n / 2) & 1];
 #pragma unroll
-      for (int t = 0; t < kRowTiles; ++t) mlp_apply_tiles<D>(w[k], bx[t], c2[t]);
-    __syncthreads();                                       // the previous chunk's readers are done
-#pragma unroll
-    for (int t = 0; t < kRowTiles; ++t)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) s_red[wave][4 * g + q][16 * t + c] = c2[t][q];
+    for (int q = 0; q < 4; ++q) red[wave][4 * g + q][16 * half + c] = c2[q];
+    if (!half && ch + 1 < ch1) continue;
+    // one barrier per pair: a wave that reaches the next pair's barrier has read this pair's sums, and the pair
+    // after that is the first to write over them
     __syncthreads();
-    for (int row = tid / 16; row < 16 * kRowTiles; row += 16) {
-      const float sum = ((s_red[0][r][row] + s_red[1][r][row]) + s_red[2][r][row]) + s_red[3][r][row];
+    const unsigned rows_first = (ch - half) * 16;
+    const int rows = half ? 32 : 16;
+    for (int row = row_first; row < rows; row += row_step) {
+      const float sum = ((red[0][r][row] + red[1][r][row]) + red[2][r][row]) + red[3][r][row];
       s_h2[row][r] = (r < R) ? gelu_poly_f64((double)sum) : 0.0;
     }
-    __syncthreads();
-    for (int row = tid / 16; row < 16 * kRowTiles; row += 16) {
-      const unsigned i = ch * (16 * kRowTiles) + row;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (int row = row_first; row < rows; row += row_step) {
+      const unsigned i = rows_first + row;
       if (r < R && i < rows_head) {
         double acc3 = 0.0;
         if (a.W3 != nullptr) {
@@ -207,7 +228,7 @@ hipError_t launch_mlp(const MlpArgs &a, hipStream_t st)
   const long rows_head = (long)a.B * a.rpu;
   // many rows per head and R' = 128, 256, 384 or 512: weights stay in registers, rows stream through
   const int ngw = a.Rp % 128 == 0 ? a.Rp / 128 : 0;
-  const long nchunk = (rows_head + 16 * kRowTiles - 1) / (16 * kRowTiles);
+  const long nchunk = (rows_head + 15) / 16;
   if (ngw >= 1 && ngw <= 4 && nchunk >= 64 && rows_head < (1L << 31) - 64) {
     long parts = 1024 / a.Hh;                              // about four workgroups per compute unit
     if (parts < 1) parts = 1;
