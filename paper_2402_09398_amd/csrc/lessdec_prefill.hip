@@ -1239,13 +1239,12 @@ __global__ __launch_bounds__(256) void prefill_rank_kernel(const double *__restr
 // discarded pairs build H = sum psi(k)^T v, z = sum psi(k) (Eq. 6) in fp64.
 // For the state a wave takes 512 / D tokens at a time, D / 8 lanes per token with eight columns each, in
 // chunks of eight rows of H: a value of psi is widened once for eight columns and a value of V once for
-// eight rows, and z is one lane's work.  Tokens are dealt to the eight waves; the lane groups meet by a
+// eight rows, and z is one lane's work.  Tokens are dealt to the W waves; the lane groups meet by a
 // reduce-scatter over the rows of H, the waves in the LDS.  Four waves with two columns a lane, z in every lane, took
 // 496 us for 2048 units x 1024 tokens and 1070 us for 128 x 8192 (one workgroup per unit either way); 291 and 222
 // now.  slot_of: in 1 / 0 (kept / discarded), out slot index / -1.
-// grid = U, block = 512, dynamic LDS = C ints.
+// grid = U, block = 64 W, dynamic LDS = C ints.
 // -------------------------------------------------------------------------------------
-constexpr int kFinalWaves = 8;
 
 // eight stored elements (16-byte aligned), all zero unless mask is ~0, as doubles
 __device__ inline void load_eight(const __half *p, unsigned mask, double (&v)[8])
@@ -1270,18 +1269,18 @@ __device__ inline void load_eight(const float *p, unsigned mask, double (&v)[8])
   }
 }
 
-template <typename T, int D>
-__global__ __launch_bounds__(64 * kFinalWaves) void prefill_finalize_kernel(
+template <typename T, int D, int W>
+__global__ __launch_bounds__(64 * W) void prefill_finalize_kernel(
     const T *__restrict__ K, const T *__restrict__ V, int P, const double *__restrict__ colsum,
     int32_t *__restrict__ slot_of, const float *__restrict__ psi_all, int C, int R,
     T *__restrict__ k_cache, T *__restrict__ v_cache, double *__restrict__ acc,
     int32_t *__restrict__ pos, float *__restrict__ psi, float *__restrict__ H,
     double *__restrict__ z, int32_t *__restrict__ n_seen, int32_t *__restrict__ pend_slot, int ring_nh)
 {
-  constexpr int THREADS = 64 * kFinalWaves, RC = 8;
+  constexpr int THREADS = 64 * W, RC = 8;
   extern __shared__ int s_tok[];                           // [C] token held by each slot
-  __shared__ int s_wave[kFinalWaves];
-  __shared__ double s_part[kFinalWaves / 2][RC][D], s_z[kFinalWaves][RC];
+  __shared__ int s_wave[W];
+  __shared__ double s_part[W / 2][RC][D], s_z[W][RC];
   const size_t u = blockIdx.x;
   const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
   const T *Ku = K + u * (size_t)P * D, *Vu = V + u * (size_t)P * D;
@@ -1295,7 +1294,7 @@ __global__ __launch_bounds__(64 * kFinalWaves) void prefill_finalize_kernel(
     const int lo = tid * chunk < P ? tid * chunk : P, hi = (lo + chunk < P) ? lo + chunk : P;
     int cnt = 0, total;
     for (int j = lo; j < hi; ++j) cnt += so[j];
-    int base = block_scan<kFinalWaves>(cnt, s_wave, total);
+    int base = block_scan<W>(cnt, s_wave, total);
     for (int j = lo; j < hi; ++j) {
       const int keep = so[j];
       // ring_nh >= 0: the slots as in-place replacement leaves them when the first ring_nh tokens
@@ -1311,7 +1310,7 @@ __global__ __launch_bounds__(64 * kFinalWaves) void prefill_finalize_kernel(
   // 2) gather: rows moved as 16-byte vectors, 64 / kVecs slots per wave at a time
   constexpr int kVecs = D * (int)sizeof(T) / 16;           // per row: 8, 16 or 32
   constexpr int kSlotsPerWave = 64 / kVecs;
-  for (int s = wave * kSlotsPerWave + lane / kVecs; s < C; s += kFinalWaves * kSlotsPerWave) {
+  for (int s = wave * kSlotsPerWave + lane / kVecs; s < C; s += W * kSlotsPerWave) {
     const size_t slot = u * C + s;
     const int i = lane % kVecs;
     if (s < kept) {
@@ -1346,7 +1345,7 @@ __global__ __launch_bounds__(64 * kFinalWaves) void prefill_finalize_kernel(
 #pragma unroll
       for (int i = 0; i < 8; ++i) h[r][i] = 0.0;
 #pragma unroll 2
-    for (int j0 = wave * TPW; j0 < P; j0 += kFinalWaves * TPW) {
+    for (int j0 = wave * TPW; j0 < P; j0 += W * TPW) {
       const int j = j0 + tp < P ? j0 + tp : P - 1;
       const unsigned mask = (so[j] < 0 && j0 + tp < P) ? ~0u : 0u;       // ~0: discarded
       const float *pj = pa + (size_t)j * R + r0;
@@ -1390,15 +1389,15 @@ __global__ __launch_bounds__(64 * kFinalWaves) void prefill_finalize_kernel(
     }
     constexpr int KEEP = RC / TPW;                         // rows a lane ends with: 2 or 1
     // the waves: the upper half through the LDS to the lower, the lower four through the LDS to everyone
-    if (wave >= kFinalWaves / 2) {
+    if (wave >= W / 2) {
 #pragma unroll
       for (int k = 0; k < KEEP; ++k)
 #pragma unroll
-        for (int i = 0; i < 8; ++i) s_part[wave - kFinalWaves / 2][row0 + k][8 * dl + i] = h[k][i];
+        for (int i = 0; i < 8; ++i) s_part[wave - W / 2][row0 + k][8 * dl + i] = h[k][i];
     }
     if (tp == 0 && dl < RC) s_z[wave][dl] = zs;
     __syncthreads();
-    if (wave < kFinalWaves / 2) {
+    if (wave < W / 2) {
 #pragma unroll
       for (int k = 0; k < KEEP; ++k)
 #pragma unroll
@@ -1409,13 +1408,13 @@ __global__ __launch_bounds__(64 * kFinalWaves) void prefill_finalize_kernel(
       const int r = x / D, d = x % D;
       double sum = 0.0;
 #pragma unroll
-      for (int w = 0; w < kFinalWaves / 2; ++w) sum += s_part[w][r][d];
+      for (int w = 0; w < W / 2; ++w) sum += s_part[w][r][d];
       H[(u * R + r0 + r) * D + d] = (float)sum;
     }
     if (tid < rn) {
       double sum = 0.0;
 #pragma unroll
-      for (int w = 0; w < kFinalWaves; ++w) sum += s_z[w][tid];
+      for (int w = 0; w < W; ++w) sum += s_z[w][tid];
       z[u * R + r0 + tid] = sum;
     }
     if (r0 + RC < R) __syncthreads();                      // s_part, s_z are written again
@@ -1508,9 +1507,10 @@ static hipError_t launch_prefill_t(const PrefillArgs &a, hipStream_t st)
   if (P > C && (lambda || sizeof(T) == 2)) {
     if constexpr (sizeof(T) == 2) {
       if (!lambda) {
-        // 256 keys per workgroup; 128 where that leaves compute units idle
+        // 256 keys per workgroup; 128 where that leaves compute units idle, or most of a workgroup's waves
+        // without keys (640 units x 70 tokens: 13 against 18 us; 512 units x 150, D = 64: 17 against 13)
         const unsigned wide = prefill_grid(U, (unsigned)((P + 255) / 256)), narrow = prefill_grid(U, (unsigned)((P + 127) / 128));
-        if (wide >= 512)
+        if (wide >= 512 && P > 128)
           prefill_colapprox_kernel<D, 4><<<wide, 64 * kPrefillWaves, 0, st>>>(
               (const __half *)a.Q, (const __half *)a.K, U, P, a.lse, G, a.approx, (unsigned *)a.bound, (unsigned *)a.count);
         else
@@ -1550,9 +1550,15 @@ static hipError_t launch_prefill_t(const PrefillArgs &a, hipStream_t st)
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (!masked && (e = key_features()) != hipSuccess) return e;
   const size_t lds = (size_t)C * sizeof(int);
-  prefill_finalize_kernel<T, D><<<U, 64 * kFinalWaves, lds, st>>>(
-      (const T *)a.K, (const T *)a.V, P, a.colsum, keep, a.psi_all, C, d->rank, (T *)d->k_cache,
-      (T *)d->v_cache, d->acc, d->pos, d->psi, d->H, d->z, d->n_seen, d->pend_slot, ring_nh);
+#define LESSDEC_FINALIZE(W)                                                                                   \
+  prefill_finalize_kernel<T, D, W><<<U, 64 * W, lds, st>>>(                                                   \
+      (const T *)a.K, (const T *)a.V, P, a.colsum, keep, a.psi_all, C, d->rank, (T *)d->k_cache,              \
+      (T *)d->v_cache, d->acc, d->pos, d->psi, d->H, d->z, d->n_seen, d->pend_slot, ring_nh)
+  // Four waves a unit on short prompts: a wave has few tokens to sum there, and fewer partial states to add up and twice the
+  // units at once count for more (17 against 24 us for 640 units x 70 tokens, 20 against 30 for 372 x 118, 29 against 35
+  // for 640 x 250)
+  if (P <= 256) LESSDEC_FINALIZE(4); else LESSDEC_FINALIZE(8);
+#undef LESSDEC_FINALIZE
   return hipGetLastError();
 }
 

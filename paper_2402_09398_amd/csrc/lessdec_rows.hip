@@ -9,12 +9,11 @@
 namespace lessdec {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
-typedef unsigned v2u __attribute__((ext_vector_type(2)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 
 // -------------------------------------------------------------------------------------
-// Row pass.  A workgroup of W waves owns 16 W consecutive queries, a wave 16 of them; the workgroup
+// Row pass.  A workgroup of four waves owns 64 consecutive queries, a wave 16 of them; the workgroup
 // sweeps the key tiles of 32 up to its last diagonal.  Per tile all threads
 // fetch the keys, split them into digit planes and put those into the LDS in operand order, and the
 // values transposed, as the A operand of p V.  A wave multiplies each 16-key half with its queries
@@ -30,6 +29,9 @@ typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 // products of a tile stand in one basic block with the weights and p V of the tile before and the staging
 // of the tile after.  One barrier per tile: keys in two buffers, values in
 // three (p V of tile kt - 1 runs after the barrier of tile kt).
+// 7390 us for 2048 units x 1024 tokens and 23540 for 128 x 8192 with fp64 matrix products; 3550 and 10870 now.
+// Eight waves to a workgroup split each key half as often, but wait longer for the waves whose diagonal
+// comes last: 4560 and 11330.
 // -------------------------------------------------------------------------------------
 constexpr int kRowKeys = 32;
 constexpr double kSlack = 15.0;                           // weights up to 2^15: they fit a half
@@ -54,16 +56,16 @@ struct RowTile {
 };
 
 // OUT: attention outputs are wanted too
-template <int D, int W, bool OUT>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) void rows_f16_kernel(
+template <int D, bool OUT>
+__global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void rows_f16_kernel(
     const __half *__restrict__ Q, const __half *__restrict__ K, const __half *__restrict__ V, unsigned U, int G, int P,
     double *__restrict__ lse, __half *__restrict__ out, unsigned *__restrict__ zero0, unsigned *__restrict__ zero1)
 {
   // U counts query rows here: unit u's G query heads are rows u G .. u G + G - 1 of Q, out and
   // lse, and attend over unit u's keys and values
   using Tile = RowTile<D>;
-  constexpr int KC = D / 64, DB = D / 16, BQ = 16 * W;
-  constexpr int EPT = kRowKeys * D / (64 * W);            // consecutive key elements a thread splits: 4, 8 or 16
+  constexpr int W = kPrefillWaves, KC = D / 64, DB = D / 16, BQ = 16 * W;
+  constexpr int EPT = kRowKeys * D / (64 * W);            // consecutive key elements a thread splits: 8 or 16
   constexpr int VK = EPT / 2;                             // value rows a thread takes two columns of
   __shared__ __attribute__((aligned(16))) unsigned char s_key[2][Tile::kKeyBytes], s_val[3][Tile::kValBytes];
   __shared__ int s_bad[3];                                // last tile of this key buffer that lacks digits; [2]: any other
@@ -93,15 +95,10 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     const int r0 = kt * kRowKeys, bytes = (P - r0 < kRowKeys ? P - r0 : kRowKeys) * D * 2;
     const __amdgpu_buffer_rsrc_t rk =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<__half *>(Ku + (size_t)r0 * D), 0, bytes, 0x00020000);
-    if constexpr (EPT == 4) {
-      const v2u x = __builtin_amdgcn_raw_buffer_load_b64(rk, k_src, 0, 0);
-      kraw[0] = x.x; kraw[1] = x.y;
-    } else {
 #pragma unroll
-      for (int i = 0; i < EPT / 8; ++i) {
-        const v4u x = __builtin_amdgcn_raw_buffer_load_b128(rk, k_src, 16 * i, 0);
-        kraw[4 * i] = x.x; kraw[4 * i + 1] = x.y; kraw[4 * i + 2] = x.z; kraw[4 * i + 3] = x.w;
-      }
+    for (int i = 0; i < EPT / 8; ++i) {
+      const v4u x = __builtin_amdgcn_raw_buffer_load_b128(rk, k_src, 16 * i, 0);
+      kraw[4 * i] = x.x; kraw[4 * i + 1] = x.y; kraw[4 * i + 2] = x.z; kraw[4 * i + 3] = x.w;
     }
     if constexpr (OUT) {
       const __amdgpu_buffer_rsrc_t rv =
@@ -125,8 +122,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     for (int q = 0; q < 4; ++q) {
       unsigned char *dst = buf + k_dst + q * Tile::kPlaneBytes;
       if constexpr (EPT == 16) *reinterpret_cast<uint4 *>(dst) = uint4{plane[q][0], plane[q][1], plane[q][2], plane[q][3]};
-      else if constexpr (EPT == 8) *reinterpret_cast<uint2 *>(dst) = uint2{plane[q][0], plane[q][1]};
-      else *reinterpret_cast<unsigned *>(dst) = plane[q][0];
+      else *reinterpret_cast<uint2 *>(dst) = uint2{plane[q][0], plane[q][1]};
     }
     s_bad[without_digits(kraw) ? kt & 1 : 2] = kt;        // (a branch here would end the block the products stand in)
     if constexpr (OUT) {
@@ -139,12 +135,9 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
       if constexpr (VK == 8) {
         *reinterpret_cast<uint4 *>(val + v_dst0) = uint4{lo[0], lo[1], lo[2], lo[3]};
         *reinterpret_cast<uint4 *>(val + v_dst1) = uint4{hi[0], hi[1], hi[2], hi[3]};
-      } else if constexpr (VK == 4) {
+      } else {
         *reinterpret_cast<uint2 *>(val + v_dst0) = uint2{lo[0], lo[1]};
         *reinterpret_cast<uint2 *>(val + v_dst1) = uint2{hi[0], hi[1]};
-      } else {
-        *reinterpret_cast<unsigned *>(val + v_dst0) = lo[0];
-        *reinterpret_cast<unsigned *>(val + v_dst1) = hi[0];
       }
     }
   };
@@ -350,30 +343,25 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   }
 }
 
-template <int D, int W>
+template <int D>
 static hipError_t launch_rows_t(const void *Q, const void *K, const void *V, unsigned UG, int G, int P, double *lse,
                                 void *out, unsigned *zero0, unsigned *zero1, hipStream_t st)
 {
-  const unsigned ngrp = (unsigned)((P + 16 * W - 1) / (16 * W));
+  const unsigned ngrp = (unsigned)((P + 16 * kPrefillWaves - 1) / (16 * kPrefillWaves));
   if (out != nullptr)
-    rows_f16_kernel<D, W, true><<<prefill_grid(UG, ngrp), 64 * W, 0, st>>>((const __half *)Q, (const __half *)K,
-                                                                           (const __half *)V, UG, G, P, lse, (__half *)out, zero0, zero1);
+    rows_f16_kernel<D, true><<<prefill_grid(UG, ngrp), 64 * kPrefillWaves, 0, st>>>(
+        (const __half *)Q, (const __half *)K, (const __half *)V, UG, G, P, lse, (__half *)out, zero0, zero1);
   else
-    rows_f16_kernel<D, W, false><<<prefill_grid(UG, ngrp), 64 * W, 0, st>>>((const __half *)Q, (const __half *)K,
-                                                                            (const __half *)V, UG, G, P, lse, nullptr, zero0, zero1);
+    rows_f16_kernel<D, false><<<prefill_grid(UG, ngrp), 64 * kPrefillWaves, 0, st>>>(
+        (const __half *)Q, (const __half *)K, (const __half *)V, UG, G, P, lse, nullptr, zero0, zero1);
   return hipGetLastError();
 }
 
 hipError_t launch_rows_f16(const void *Q, const void *K, const void *V, unsigned UG, int G, int P, int D, double *lse,
                            void *out, unsigned *zero0, unsigned *zero1, hipStream_t st)
 {
-  // 128 queries per workgroup halve the splitting of keys into digits (18.9 against 19.5 ms for 128 units x
-  // 8192 tokens, the whole call); on shorter prompts the waves of the wider group wait too
-  // long for the ones whose diagonal comes last (7.9 against 7.2 ms for 2048 units x 1024 tokens)
-  const bool wide = P >= 4096;
-  if (D == 128)
-    return wide ? launch_rows_t<128, 8>(Q, K, V, UG, G, P, lse, out, zero0, zero1, st) : launch_rows_t<128, 4>(Q, K, V, UG, G, P, lse, out, zero0, zero1, st);
-  return wide ? launch_rows_t<64, 8>(Q, K, V, UG, G, P, lse, out, zero0, zero1, st) : launch_rows_t<64, 4>(Q, K, V, UG, G, P, lse, out, zero0, zero1, st);
+  return D == 128 ? launch_rows_t<128>(Q, K, V, UG, G, P, lse, out, zero0, zero1, st)
+                  : launch_rows_t<64>(Q, K, V, UG, G, P, lse, out, zero0, zero1, st);
 }
 
 // -------------------------------------------------------------------------------------
@@ -514,8 +502,9 @@ hipError_t launch_columns_f16(const void *Q, const void *K, unsigned U, int G, i
                               const int32_t *list, const int32_t *count, int C, double *colsum, hipStream_t st)
 {
   const int keys = list && C + 16 < P ? C + 16 : P;       // a handful of tokens in doubt behind the budget
-  // 128 keys share a split query tile; 32 where that leaves compute units idle
-  const bool wide = (size_t)U * ((keys + 127) / 128) >= 256;
+  // 128 keys share a split query tile; 32 where that leaves compute units idle, or where 32 hold the whole list
+  // (640 units x 70 tokens, 10 kept: 18 against 32 us; 640 x 200, 90 kept: 89 against 56 with three narrow ones)
+  const bool wide = keys > 32 && (size_t)U * ((keys + 127) / 128) >= 256;
 #define LESSDEC_COLUMNS(DD, NT) launch_columns_t<DD, NT>(Q, K, U, G, P, lse, list, count, keys, colsum, st)
   if (D == 128) return wide ? LESSDEC_COLUMNS(128, 8) : LESSDEC_COLUMNS(128, 2);
   return wide ? LESSDEC_COLUMNS(64, 8) : LESSDEC_COLUMNS(64, 2);

@@ -37,8 +37,8 @@ def test_tile_edges(prompt, head_dim):
     run(w, wl.all_inputs(w))
 
 
-def test_wide_workgroup():
-    """Prompts of 4096 tokens and more take 128 queries per workgroup."""
+def test_long_prompt():
+    """A prompt of many key tiles that ends inside one."""
     w = shape(4096 + 37, heads=1)
     run(w, wl.all_inputs(w))
 

@@ -20,6 +20,7 @@ def shape(**kw):
     dict(rank=1, hidden=32), dict(rank=7), dict(rank=8), dict(rank=9), dict(rank=16), dict(rank=64, hidden=48),
     dict(prompt=12), dict(prompt=33, head_dim=64), dict(prompt=700, head_dim=64, rank=12), dict(dtype="f32", rank=5),
     dict(dtype="f32", head_dim=64, rank=10, prompt=70), dict(prompt=8, n_heavy=8, n_recent=8), dict(prompt=1500, n_heavy=600, n_recent=300),
+    dict(prompt=256), dict(prompt=257), dict(prompt=300, dtype="f32", rank=9),
 ], ids=lambda kw: "-".join(f"{k}{v}" for k, v in kw.items()))
 def test_state(kw):
     w = shape(**kw)
