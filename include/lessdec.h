@@ -26,7 +26,8 @@
  *    are only compared, never used as addresses.
  *
  * Arithmetic: everything that decides an eviction (scores, exponentials, the
- * denominator, accumulated probabilities, z, prompt column sums) is computed in fp64;
+ * denominator, accumulated probabilities, z, prompt column sums) is computed in fp64 (products of
+ * fp16 rows partly as exact integer sums that are joined in fp64);
  * value-side sums (numerator, H, outputs) in fp32; the feature-map MLPs in fp32 with
  * fp16 matrix-core products when dtype is fp16.
  */

@@ -5,7 +5,7 @@ computes exact fp64 sums only for tokens whose cheap sum lies within a relative 
 selection boundary.  That is sound if every cheap sum is within the band of the exact one.  Here
 the cheap path is emulated in numpy fp32 arithmetic on the workloads whose column sums lie close
 together and on heavy-tailed keys, and compared with the oracle's fp64 column sums: the error
-must stay inside the bound the kernel derives (lessdec_prefill.hip, prefill_band_kernel), and the
+must stay inside the bound the kernel derives (lessdec_prefill.hip, prefill_select_kernel), and the
 bound inside half the band the kernel then uses."""
 import numpy as np
 import pytest
@@ -18,7 +18,7 @@ U32 = 2.0 ** -24
 
 
 def error_bound(M, D, P, G):
-    """eps of prefill_band_kernel's comment: relative error bound of a cheap column sum."""
+    """eps of prefill_select_kernel's comment: relative error bound of a cheap column sum."""
     return U32 * ((D + 6) * M + 3 * np.log(P) + G * P / 16 + 6)
 
 
