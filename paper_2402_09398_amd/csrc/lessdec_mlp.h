@@ -58,25 +58,29 @@ __device__ inline MlpTiles<D> mlp_load_tiles(const __half *__restrict__ W1, cons
 }
 
 // gelu of a lane's 4 + 4 hidden units, split for layer 2.  The vector instructions here bound the maps of
-// many rows, so the split is spelled out: two conversions per hi pair and one mixed-precision
-// fma per lo (x - hi is exact in fp32, so the one rounding is the conversion's, as in
-// (_Float16)(x - (float)hi), which takes three instructions).
+// many rows, so the split is written for them: two conversions per hi pair and one mixed-precision fma
+// per lo (x - hi is exact in fp32, so the one rounding is the conversion's, as in
+// (_Float16)(x - (float)hi), which takes three instructions).  The compiler has to make that
+// fma itself: a matrix instruction may read a vector result only two wait states later, which it counts
+// for its own instructions and not for an asm block's.
 __device__ inline void mlp_activate(const v4f &h0, const v4f &h1, v8h &bhi, v8h &blo)
 {
   typedef _Float16 v2h __attribute__((ext_vector_type(2)));
   typedef unsigned v4u __attribute__((ext_vector_type(4)));
+  float one = 1.f;
+  asm("" : "+s"(one));                                     // unknown to the compiler, which else makes a subtraction of the fma
   v4u hi, lo;
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
     const v4f &h = w < 2 ? h0 : h1;
     float x0 = gelu_fast_f32(h[2 * (w % 2)]), x1 = gelu_fast_f32(h[2 * (w % 2) + 1]);
     asm("" : "+v"(x0), "+v"(x1));                          // one fp32 value for both halves of the split
-    const unsigned p = __builtin_bit_cast(unsigned, v2h{(_Float16)x0, (_Float16)x1});
-    unsigned q;
-    asm("v_fma_mixlo_f16 %0, -%1, 1.0, %2 op_sel_hi:[1,0,0]" : "=v"(q) : "v"(p), "v"(x0));
-    asm("v_fma_mixhi_f16 %0, -%1, 1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(q) : "v"(p), "v"(x1));
+    unsigned p = __builtin_bit_cast(unsigned, v2h{(_Float16)x0, (_Float16)x1});
+    asm("" : "+v"(p));                                     // converted once, as a pair
+    const v2h x = __builtin_bit_cast(v2h, p);
     hi[w] = p;
-    lo[w] = q;
+    lo[w] = __builtin_bit_cast(unsigned, v2h{(_Float16)__builtin_fmaf(-(float)x.x, one, x0),
+                                             (_Float16)__builtin_fmaf(-(float)x.y, one, x1)});
   }
   bhi = __builtin_bit_cast(v8h, hi);
   blo = __builtin_bit_cast(v8h, lo);
