@@ -90,7 +90,8 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
   const int v_dst0 = Tile::val_at(vd % DB, vd / DB, vs / 8) + vs % 8 * 2, v_dst1 = Tile::val_at((vd + 1) % DB, (vd + 1) / DB, vs / 8) + vs % 8 * 2;
   const int k_src = (kr * D + ke) * 2, v_src = ((16 * (vs / 4 % 2) + 4 * (vs / 8) + vs % 4) * D + vd) * 2;
   unsigned kraw[EPT / 2], vraw[VK];
-  // rows past the prompt read as zeros
+  // Rows past the prompt read as zeros: a buffer load is in range where its vector offset lies below num_records less
+  // the scalar offset, so the latter never passes num_records (the row steps of a short last tile would).
   auto fetch = [&](int kt) __attribute__((always_inline)) {
     const int r0 = kt * kRowKeys, bytes = (P - r0 < kRowKeys ? P - r0 : kRowKeys) * D * 2;
     const __amdgpu_buffer_rsrc_t rk =
@@ -105,7 +106,7 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
           __builtin_amdgcn_make_buffer_rsrc(const_cast<__half *>(Vu + (size_t)r0 * D), 0, bytes, 0x00020000);
 #pragma unroll
       for (int i = 0; i < VK; ++i)                        // slots vs + 4 ..: the tile's second half
-        vraw[i] = __builtin_amdgcn_raw_buffer_load_b32(rv, v_src, (i / 4 * 16 + i % 4) * D * 2, 0);
+        vraw[i] = __builtin_amdgcn_raw_buffer_load_b32(rv, v_src, min((i / 4 * 16 + i % 4) * D * 2, bytes), 0);
     }
   };
   auto stage = [&](int kt, unsigned char *val) __attribute__((always_inline)) {

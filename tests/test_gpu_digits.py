@@ -90,3 +90,17 @@ def test_maximum_that_jumps(before, after, low, high):
     inp["K"][:, after, 0] = high
     inp["V"][:, before, :] = 300.0
     run(w, inp)
+
+
+@pytest.mark.parametrize("prompt", [65, 79, 81, 95])
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+def test_last_tile_reads_nothing_of_the_next_unit(prompt, value):
+    """A prompt that ends inside a tile of 32 keys: rows past it, which are the next unit's first, have no part in
+    the last queries' outputs, whatever they hold (a weight of zero would still make NaN of them)."""
+    w = shape(prompt, steps=0)
+    clean = wl.all_inputs(w)
+    dirty = {k: v.copy() for k, v in clean.items()}
+    for name in "KV":
+        dirty[name][1:, :20] = value
+    a, b = (hz.gpu_run(w, x)["prefill_out"] for x in (clean, dirty))
+    assert np.array_equal(a[0].view(np.uint16), b[0].view(np.uint16))

@@ -3,6 +3,8 @@ compiler makes of this repository's own files (CPU: hipcc cross-compiles for gfx
 
 * A matrix instruction may read a vector instruction's result only two wait states after it.  The compiler
   counts them for the instructions that it makes itself, not for those inside an asm block.
+* A buffer load is in range where its vector offset lies below num_records less its scalar offset: a load
+  that relies on reading zeros past the end keeps the scalar offset within num_records.
 """
 import re
 import subprocess
@@ -71,3 +73,19 @@ def test_the_reader_of_wait_states():
                                   if "mfma" in (hip_build.CSRC / s).read_text() or "lessdec_mlp.h" in (hip_build.CSRC / s).read_text()])
 def test_matrix_instructions_wait_for_vector_results(assembly, name):
     assert early_matrix_reads(assembly(name)) == []
+
+
+def test_prompt_rows_past_the_end_are_in_the_range_check(assembly):
+    """The row pass reads a tile through a buffer of the rows that the prompt still has, one at least: constant
+    scalar offsets stay below a row of 64 halves, the others are clamped to the buffer's size."""
+    written, loads = {}, 0
+    for line in assembly("lessdec_rows.hip"):
+        op, _, rest = line.split(";")[0].strip().partition(" ")
+        operands = [x.strip() for x in rest.split(",")]
+        if op.startswith("buffer_load"):
+            soffset = operands[2].split(" ")[0] if "[" not in operands[2] else operands[3].split(" ")[0]
+            loads += 1
+            assert soffset.isdigit() and int(soffset) <= 64 or written.get(soffset, "").startswith("s_min_"), line
+        elif op.startswith("s_") and operands[0].startswith("s"):
+            written[operands[0]] = op
+    assert loads
