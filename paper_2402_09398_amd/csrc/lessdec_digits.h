@@ -29,7 +29,7 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 typedef double v4d __attribute__((ext_vector_type(4)));
 
 // Values of this magnitude and above (infinities and NaN among them) have no digits: the tile that
-// holds one is multiplied in fp64 (dot_tile_f64).  127.0 as a half.
+// holds one is multiplied in fp64 (dot_tiles_f64).  127.0 as a half.
 constexpr unsigned kDigitMax = 0x57F0;
 
 // Joined sums of one lane's four elements of a tile.
@@ -118,18 +118,54 @@ __device__ inline double dot_affine(const DotParts &p, int w, double c, double s
                  fma((double)p.p32[w], c * (kDotUnit * 0x1p16), fma((double)p.p10[w], c * kDotUnit, shift))));
 }
 
-// The same tile in fp64, for operands that have no digits: element w of lane (g, c) is
-// key[4 g + w] . query[c].  krow(i): row of the tile's key i (any readable row), qrow: the lane's query.
+// half e of a 16-byte piece
+__device__ inline double half_of(const uint4 &x, int e)
+{
+  const unsigned w = e < 2 ? x.x : e < 4 ? x.y : e < 6 ? x.z : x.w;
+  const __half2 h = __builtin_bit_cast(__half2, w);
+  return (double)(e % 2 ? __high2float(h) : __low2float(h));
+}
+
+// The same in fp64, for operands that have no digits: N tiles of 16 keys against 16 queries, element w of lane (g, c)
+// of tile t is key[16 t + 4 g + w] . query[c].  krow(i): row of key i (any readable row), qrow: the lane's query.
+// Lane group g supplies the D / 4 elements from g D / 4 on of its row, read as 16-byte pieces, all ahead of the products;
+// a query element is widened once for the N tiles.
+template <int D, int N, typename KRow>
+__device__ inline void dot_tiles_f64(KRow krow, const __half *qrow, int g, int c, v4d (&acc)[N])
+{
+  constexpr int NV = D / 32;                              // pieces of 8 halves
+  uint4 k[N][NV], q[NV];
+  // result register v of v_mfma_f64_16x16x4 holds row g + 4 v, so matrix row i stands for key 4 (i % 4) + i / 4
+#pragma unroll
+  for (int t = 0; t < N; ++t) {
+    const uint4 *kr = reinterpret_cast<const uint4 *>(krow(16 * t + 4 * (c % 4) + c / 4) + g * (D / 4));
+#pragma unroll
+    for (int i = 0; i < NV; ++i) k[t][i] = kr[i];
+    acc[t] = v4d{0.0, 0.0, 0.0, 0.0};
+  }
+#pragma unroll
+  for (int i = 0; i < NV; ++i) q[i] = reinterpret_cast<const uint4 *>(qrow + g * (D / 4))[i];
+#pragma unroll
+  for (int i = 0; i < NV; ++i)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const double qe = half_of(q[i], e);
+#pragma unroll
+      for (int t = 0; t < N; ++t) acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(half_of(k[t][i], e), qe, acc[t], 0, 0, 0);
+    }
+}
+// One tile, a piece of 8 halves at a time: for kernels without the registers to hold all pieces.
 template <int D, typename KRow>
 __device__ inline v4d dot_tile_f64(KRow krow, const __half *qrow, int g, int c)
 {
-  // result register v of v_mfma_f64_16x16x4 holds row g + 4 v, so matrix row i stands for key 4 (i % 4) + i / 4
-  const __half *kr = krow(4 * (c % 4) + c / 4);
+  const __half *kr = krow(4 * (c % 4) + c / 4) + g * (D / 4), *qr = qrow + g * (D / 4);
   v4d acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 1
-  for (int s = 0; s < D / 4; ++s)
-    acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)__half2float(kr[4 * s + g]),
-                                               (double)__half2float(qrow[4 * s + g]), acc, 0, 0, 0);
+  for (int i = 0; i < D / 32; ++i) {
+    const uint4 k = reinterpret_cast<const uint4 *>(kr)[i], q = reinterpret_cast<const uint4 *>(qr)[i];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(half_of(k, e), half_of(q, e), acc, 0, 0, 0);
+  }
   return acc;
 }
 

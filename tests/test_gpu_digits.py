@@ -104,3 +104,34 @@ def test_last_tile_reads_nothing_of_the_next_unit(prompt, value):
         dirty[name][1:, :20] = value
     a, b = (hz.gpu_run(w, x)["prefill_out"] for x in (clean, dirty))
     assert np.array_equal(a[0].view(np.uint16), b[0].view(np.uint16))
+
+
+@pytest.mark.parametrize("which", ["K", "Q"])
+def test_values_without_digits_keep_the_speed_of_fp64_products(which):
+    """One channel of 200 in every row sends every tile to the fp64 matrix unit.  A 16 x 16 tile is D / 4 products of 66
+    cycles there against D / 4 of 16 with digits, and the rest of a tile (weights, values, staging) is the same: at
+    most 66 / 16 times the clean prompt's time even if nothing else counted, two times measured.  Bound: 3."""
+    import torch
+    w = shape(1024, batch=16, heads=16, steps=0, n_heavy=51, n_recent=51, rank=8, hidden=512)
+    gpu = hz.make_gpu(w)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = {n: torch.randn(w.units, w.prompt, w.head_dim, generator=g, device="cuda").half() for n in "QKV"}
+    out = torch.empty_like(x["Q"])
+
+    def ms():
+        times = []
+        for _ in range(7):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            gpu.prefill(x["Q"], x["K"], x["V"], out=out)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        return sorted(times)[2]
+
+    clean = ms()
+    x[which][..., 3] = 200.0
+    x["KQ".replace(which, "")][..., 3] *= 1 / 64
+    large = ms()
+    print(f"\nclean {clean:.3f} ms, with a channel of 200 in {which} {large:.3f} ms", flush=True)
+    assert large < 3 * clean
