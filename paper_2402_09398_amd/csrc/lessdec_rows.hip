@@ -18,8 +18,9 @@ typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 // fetch the keys, split them into digit planes and put those into the LDS in operand order, and the
 // values transposed, as the A operand of p V.  A wave multiplies each 16-key half with its queries
 // (digits in registers): scores S^T[key][query], lane (g, c) holding keys 4 g + w of query c.
-// The running maximum m is an integer in base-2 units, set by the first half and moved when a score passes
-// it by kSlack, which is rare and exact.  The weights are fp64; their sum gives lse, and p V takes
+// The running maximum m is an integer in base-2 units, the one below the largest score of the first tile (so that
+// the largest weight is above 1 and the fp16 pairs' floor of 2^-24 as far below it as with weights up to 1), moved when a
+// score passes it by kSlack, which is rare and exact.  The weights are fp64; their sum gives lse, and p V takes
 // them as an fp16 pair hi + lo (22 bits) with fp32 accumulation.  Leaves lse_i = ln sum_j e^{s_ij}.
 // A tile with a value that has no digits (|x| >= 127), and every tile of a wave whose queries hold one, is multiplied
 // in fp64 instead, from rows read as 16-byte pieces: 512 units x 1024 tokens with such a key channel in every token take
@@ -148,7 +149,7 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
 
   RowDigits<D> qd;
   const bool qbad = __any(!qd.load(Qu + (size_t)qrow * D, g));
-  // m: the query's maximum when it was last moved, an integer; lim: by how much a score may pass it, -inf
+  // m: an integer below the query's maximum when it was last moved; lim: by how much a score may pass it, -inf
   // before the first one
   double m = 0.0, lim = -__builtin_inf(), L = 0.0;
   v4f O[DB];
@@ -179,7 +180,7 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
       top = fmax(top, __shfl_xor(top, 16));
       top = fmax(top, __shfl_xor(top, 32));
       const bool none = top == -__builtin_inf();          // nothing to see yet
-      const double d = none ? 0.0 : lim == -__builtin_inf() ? ceil(top) : fmax(0.0, ceil(top));
+      const double d = none ? 0.0 : lim == -__builtin_inf() ? ceil(top) - 1.0 : fmax(0.0, ceil(top) - 1.0);
       const int k = d <= 0.0 ? 0 : d < 2000.0 ? -(int)d : -2000;   // the rescaling is a power of two
       const float af = __builtin_ldexpf(1.f, k);
       L = __builtin_ldexp(L, k);

@@ -135,3 +135,29 @@ def test_values_without_digits_keep_the_speed_of_fp64_products(which):
     large = ms()
     print(f"\nclean {clean:.3f} ms, with a channel of 200 in {which} {large:.3f} ms", flush=True)
     assert large < 3 * clean
+
+
+def test_small_weights_keep_their_bits():
+    """Weights near the floor of the fp16 pairs that p V takes: relative to the row's largest weight none is off by more
+    than 2^-25 (half a step of the halves below 2^-14, for a largest weight of 1).  Keys of two scores: one of the
+    largest, a little above an integer in base-2 units, with value 0, and many 24 octaves below it with value 60000."""
+    w = shape(64, head_dim=64, heads=1, steps=0)
+    top = np.arange(8, 16, 2.0 ** -7)
+    top = top[(top / np.log(2) % 1 > 0.002) & (top / np.log(2) % 1 < 0.02)]
+    low = np.arange(-8, -4, 2.0 ** -8)
+    gap = (top[:, None] - low[None, :]) / np.log(2) - 24 - top[:, None] / np.log(2) % 1
+    i, j = np.argwhere((gap > 0.002) & (gap < 0.02))[0]
+    inp = wl.all_inputs(w)
+    inp["Q"][...] = 0
+    inp["Q"][..., 0] = 8.0                               # score = first element of the key
+    inp["K"][...] = 0
+    inp["K"][..., 0] = low[j]
+    inp["K"][:, 0, 0] = top[i]
+    inp["V"][...] = 60000.0
+    inp["V"][:, 0] = 0
+    assert inp["K"][0, 0, 0] == top[i] and inp["K"][0, 1, 0] == low[j]
+    got = hz.gpu_run(w, inp)["prefill_out"].astype(np.float64)[0]
+    n = np.arange(w.prompt)[:, None]                     # query n sees n of the small ones
+    r = np.exp(low[j] - top[i])
+    exact = n * r * 60000 / (1 + n * r)
+    assert (np.abs(got - exact) <= n * 2.0 ** -25 * 60000 + exact * 2.0 ** -10).all(), np.abs(got - exact).max() / exact.max()
