@@ -453,35 +453,37 @@ __global__ __launch_bounds__(256) void gqa_finish_kernel(const StepArgs a, int n
 // rows belongs to wave T mod 8, which keeps its scores in registers (NTW tiles).  Scores are exact
 // integer products of digit planes (lessdec_digits.h; fp64 matrix products where a value has no
 // digits), lane (g, c) holding rows 4 g + w of head c; softmax in fp64, maximum and sum through the LDS; a
-// pair's share of the accumulated scores is its row's sum over the lanes c; p V takes the fp32
-// weights to v_mfma_f32_16x16x4_f32, a row's values straight from memory (element d = D / 16 i + b
-// is operand row i of block b, so a lane reads one run per row), and the waves' partial outputs meet
-// in the LDS in wave order.  The vector form above (other shapes) scores a row for four heads at a time on the fp64
-// vector units: 52 us for 64 units x 71 heads x 204 slots, against 19 here (a step: 64 us before, 36 now).
+// pair's share of the accumulated scores is its row's sum over the lanes c; p V in fp64 on
+// v_mfma_f64_16x16x4_f64, as the vector form accumulates it, a row's values straight from memory (element
+// d = D / 16 i + b is operand row i of block b, so a lane reads one run per row), and the waves' partial
+// outputs meet in the LDS in wave order.  The vector form above (other shapes) scores a row for four heads at a time
+// on the fp64 vector units: 64 us a step for 64 units x 71 heads x 204 slots (D = 64), against 35 here.
+// Bound by latency: the two launches beside it, then a chain of key rows, two exchanges of the softmax, p V and the
+// exchange of the outputs.  (p V on fp32 tiles: the same time at D = 64, 7 % less at D = 128 with 400 slots.)
 // Dynamic LDS: gqm_lds.
 // -------------------------------------------------------------------------------------
 constexpr int kGqmWaves = 8, kGqmHeads = 16, kGqmMaxRows = 1024;
-typedef float v4f __attribute__((ext_vector_type(4)));
 
 template <int D, int NTW>
 __global__ __launch_bounds__(64 * kGqmWaves, D == 64 && NTW <= 2 ? 4 : 2) void gqm_step_kernel(const StepArgs a, int G, int nhb, int finish)
 {
   using T = __half;
-  constexpr int KC = D / 64, DB = D / 16, NV = DB / 2, THREADS = 64 * kGqmWaves;
+  constexpr int KC = D / 64, DB = D / 16, NV = DB / 2, THREADS = 64 * kGqmWaves, OS = D + 2;   // (two doubles behind a head's outputs, against bank conflicts)
   extern __shared__ __attribute__((aligned(16))) double dyn[];
   __shared__ double s_mx[kGqmWaves][kGqmHeads], s_sum[kGqmWaves][kGqmHeads], s_hd[kGqmHeads][2];
   const int C = a.C, R = a.R, rows_cap = C + 2;
-  double *s_inc = dyn;                               // [C+1] this step's probabilities per pair, summed over the heads
-  double *s_e = s_inc + rows_cap;                    // [C+1] scratch of the finish
-  double *s_z = s_e + rows_cap;                      // [R] z
-  double *s_f = s_z + LESSDEC_MAX_RANK;              // [16][R] phi(q) of the group
-  float *s_o = reinterpret_cast<float *>(s_f + kGqmHeads * LESSDEC_MAX_RANK);   // [8][16][D] partial outputs
-  Cand *s_cand = reinterpret_cast<Cand *>(s_o);      // after the last group
-  static_assert(sizeof(Cand) * THREADS <= sizeof(float) * kGqmWaves * kGqmHeads * D, "candidates overlay the partial outputs");
+  double *s_inc = dyn;                               // [C+2, even] this step's probabilities per pair, summed over the heads
+  double *s_z = s_inc + (rows_cap + 1) / 2 * 2;      // [R, even] z
+  double *s_f = s_z + (R + 1) / 2 * 2;               // [16][R] phi(q) of the group
+  double *s_o = s_f + kGqmHeads * R;                 // [8][16][OS] partial outputs
+  double *s_e = s_o;                                 // [C+1] scratch of the finish, after the last group
+  Cand *s_cand = reinterpret_cast<Cand *>(s_o + kGqmMaxRows);
+  static_assert(sizeof(Cand) * THREADS + sizeof(double) * kGqmMaxRows <= sizeof(double) * kGqmWaves * kGqmHeads * OS,
+                "scores and candidates overlay the partial outputs");
   const int u = (int)blockIdx.x / nhb, hb = (int)blockIdx.x % nhb;
   const int ngrp = (G + kGqmHeads - 1) / kGqmHeads;
   const int grp0 = ngrp * hb / nhb, grp1 = ngrp * (hb + 1) / nhb;
-  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64, g = l / 16, c = l % 16;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64);
   const int n = sane_n_seen(a.n_seen[u]);
   const int m = n < C ? n : C;             // live slots are 0..m-1 (slots fill in order)
   const int rows = m + 1;                  // + the appended pair (K', V' of Eq. 3)
@@ -496,6 +498,10 @@ __global__ __launch_bounds__(64 * kGqmWaves, D == 64 && NTW <= 2 ? 4 : 2) void g
   for (int r = tid; r < rows; r += THREADS) s_inc[r] = 0.0;
   if (tid < R) s_z[tid] = a.z[(size_t)u * R + tid];
   for (int grp = grp0; grp < grp1; ++grp) {
+    // the lane's place is unknown to the compiler anew for every group, or it computes all addresses ahead of the
+    // loop and spills them
+    int g = tid % 64 / 16, c = tid % 16;
+    asm volatile("" : "+v"(g), "+v"(c));
     const int h0 = grp * kGqmHeads;
     const int hc = h0 + c < G ? h0 + c : G - 1;      // heads past the last repeat it: computed, never kept
     const bool head = h0 + c < G;
@@ -599,9 +605,9 @@ __global__ __launch_bounds__(64 * kGqmWaves, D == 64 && NTW <= 2 ? 4 : 2) void g
       s_hd[c][1] = 1.0 / den;
     }
     const double ascale = head ? 1.0 / (sparse_den ? sum : den) : 0.0;
-    v4f O[DB];
+    v4d O[DB];
 #pragma unroll
-    for (int b = 0; b < DB; ++b) O[b] = v4f{0.f, 0.f, 0.f, 0.f};
+    for (int b = 0; b < DB; ++b) O[b] = v4d{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int t = 0; t < NTW; ++t) {
       const int r0 = 16 * (t * kGqmWaves + wave);
@@ -612,20 +618,18 @@ __global__ __launch_bounds__(64 * kGqmWaves, D == 64 && NTW <= 2 ? 4 : 2) void g
         const double inc = row16_allreduce(e[t][w] * ascale, OpAdd{});
         const int r = r0 + 4 * g + w;
         if (c == 0 && r < rows) s_inc[r] += inc;     // the row is this wave's alone
-        const float pw = (float)e[t][w];
 #pragma unroll
         for (int b = 0; b < DB; ++b) {
           const __half2 h = __builtin_bit_cast(__half2, vraw[kAhead ? t : 0][w][b / 2]);
-          O[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(b % 2 ? __high2float(h) : __low2float(h), pw, O[b], 0, 0, 0);
+          O[b] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)(b % 2 ? __high2float(h) : __low2float(h)), e[t][w], O[b], 0, 0, 0);
         }
       }
     }
 #pragma unroll
     for (int w = 0; w < 4; ++w)
 #pragma unroll
-      for (int b = 0; b < DB; b += 4)
-        *reinterpret_cast<float4 *>(s_o + (wave * kGqmHeads + c) * D + DB * (4 * g + w) + b) =
-            float4{O[b][w], O[b + 1][w], O[b + 2][w], O[b + 3][w]};
+      for (int b = 0; b < DB; b += 2)
+        *reinterpret_cast<double2 *>(s_o + (wave * kGqmHeads + c) * OS + DB * (g + 4 * w) + b) = double2{O[b][w], O[b + 1][w]};
     __syncthreads();
     // outputs, two adjacent columns of a head per thread: (phi(q) H 2^{-m*} + sum_j 2^{s_j - m*} V_j) / den
     for (int i = tid; i < kGqmHeads * D / 2; i += THREADS) {
@@ -644,9 +648,9 @@ __global__ __launch_bounds__(64 * kGqmWaves, D == 64 && NTW <= 2 ? 4 : 2) void g
       }
 #pragma unroll
       for (int w = 0; w < kGqmWaves; ++w) {
-        const float2 o = *reinterpret_cast<const float2 *>(s_o + (w * kGqmHeads + h) * D + d);
-        n0 += (double)o.x;
-        n1 += (double)o.y;
+        const double2 o = *reinterpret_cast<const double2 *>(s_o + (w * kGqmHeads + h) * OS + d);
+        n0 += o.x;
+        n1 += o.y;
       }
       float f0 = (float)(n0 * s_hd[h][1]), f1 = (float)(n1 * s_hd[h][1]);
       asm volatile("" : "+v"(f0), "+v"(f1));         // fp64 -> fp16 in one step would be a software sequence
@@ -664,10 +668,9 @@ __global__ __launch_bounds__(64 * kGqmWaves, D == 64 && NTW <= 2 ? 4 : 2) void g
 }
 
 // Dynamic LDS of gqm_step_kernel, in bytes.
-static size_t gqm_lds(int C, int D)
+static size_t gqm_lds(int C, int R, int D)
 {
-  return (size_t)(2 * (C + 2) + (1 + kGqmHeads) * LESSDEC_MAX_RANK) * sizeof(double) +
-         (size_t)kGqmWaves * kGqmHeads * D * sizeof(float);
+  return ((size_t)(C + 3) / 2 * 2 + (R + 1) / 2 * 2 + kGqmHeads * R + (size_t)kGqmWaves * kGqmHeads * (D + 2)) * sizeof(double);
 }
 
 // Sixteen heads to a matrix tile pay from nine heads on (up to eight the streaming kernel takes them).
@@ -708,7 +711,7 @@ static hipError_t launch_step_gqm_t(const StepArgs &a, int G, hipStream_t st)
   int nhb = gqa_head_blocks(a.U, G);
   const bool split = nhb > 1;                               // few units: the finish is spread thinner as a launch of its own
   if (nhb > ngrp) nhb = ngrp;
-  const size_t lds = gqm_lds(a.C, D);
+  const size_t lds = gqm_lds(a.C, a.R, D);
   if (lds > block_lds_limit()) return hipErrorInvalidValue;
 #define LESSDEC_GQM(NTW) gqm_step_kernel<D, NTW><<<a.U * nhb, 64 * kGqmWaves, lds, st>>>(a, G, nhb, split ? 0 : 1)
   if (ntw <= 1) LESSDEC_GQM(1); else if (ntw <= 2) LESSDEC_GQM(2); else if (ntw <= 4) LESSDEC_GQM(4); else LESSDEC_GQM(8);

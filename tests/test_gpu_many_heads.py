@@ -60,3 +60,22 @@ def test_values_without_digits():
     rep = hz.check_against_oracle(w, inp, units, res)
     rep.failures.extend(hz.check_every_unit(w, res))
     assert rep.ok(), rep.failures[:10]
+
+
+def test_values_that_cancel():
+    """Two keys of nearly the same score with opposite large values: what is left is the difference of their weights,
+    1e-6 of each, so weights or sums of 24 bits would leave an error of some percent."""
+    w = shape("cancel", prompt=20, steps=1)                 # a full cache, nothing discarded: regular attention
+    inp = wl.all_inputs(w)
+    for name in "QKVkv":
+        inp[name][...] = 0
+    inp["K"][:, 3, 0], inp["K"][:, 7, 0] = 1 + 2.0 ** -10, 1
+    inp["V"][:, 3], inp["V"][:, 7] = 60000, -60000
+    q0 = 2.0 ** -7 * (1 + np.arange(17) / 32)
+    inp["q"][...] = 0
+    inp["q"][..., 0] = q0
+    assert (inp["q"][0, 0, :, 0] == q0).all()
+    got = hz.gpu_run(w, inp)["outs"][0].astype(np.float64)  # [U,G,D]
+    low = q0 / 8
+    exact = 60000 * np.exp(low) * np.expm1(low * 2.0 ** -10) / (np.exp(low) * (2 + np.expm1(low * 2.0 ** -10)) + 19)
+    assert (np.abs(got / exact[None, :, None] - 1) < 2.0 ** -10).all(), np.abs(got / exact[None, :, None] - 1).max()
