@@ -576,7 +576,8 @@ __global__ __launch_bounds__(64 * kGqmWaves, D == 64 && NTW <= 2 ? 4 : 2) void g
     // 2^{-m*} + sum_j 2^{s_j - m*}
     double fz = 0.0;
     for (int r = 0; r < R; ++r) fz = fma(s_f[c * R + r], s_z[r], fz);
-    const double mstar = fz > 0.0 ? fmax(mx, (double)__builtin_amdgcn_frexp_exp(fz)) : mx;
+    // (an infinite phi(q) z^T leaves no number, as ln of it would)
+    const double mstar = fz > 0.0 ? fmax(mx, fz < __builtin_inf() ? (double)__builtin_amdgcn_frexp_exp(fz) : fz) : mx;
     double down[1] = {-mstar}, hs[1];
     exp2_f64(down, hs);
     if (!(fz > 0.0)) hs[0] = 0.0;

@@ -4,6 +4,7 @@ edges of the row tiles (16 rows, 8 waves, up to 1024 rows) and beyond them, a ca
 options, one block per unit and several.  Tolerances: tests/harness.py."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2402_09398_amd import workloads as wl
 from tests import harness as hz
@@ -79,3 +80,18 @@ def test_values_that_cancel():
     low = q0 / 8
     exact = 60000 * np.exp(low) * np.expm1(low * 2.0 ** -10) / (np.exp(low) * (2 + np.expm1(low * 2.0 ** -10)) + 19)
     assert (np.abs(got / exact[None, :, None] - 1) < 2.0 ** -10).all(), np.abs(got / exact[None, :, None] - 1).max()
+
+
+def test_state_that_is_not_finite():
+    """An infinite phi(q) z^T: no number comes out, for that unit alone."""
+    w = shape("infinite-state", steps=1)
+    inp = wl.all_inputs(w)
+    gpu = hz.make_gpu(w)
+    Q, K, V = (torch.from_numpy(inp[n]).cuda() for n in "QKV")
+    gpu.prefill(Q, K, V)
+    gpu.z[1] = float("inf")
+    q, k, v = (torch.from_numpy(inp[n][0]).cuda() for n in "qkv")
+    out = torch.empty_like(q)
+    gpu.step(q, k, v, out)
+    out = out.cpu().numpy()
+    assert np.isnan(out[1]).all() and np.isfinite(out[0]).all()
