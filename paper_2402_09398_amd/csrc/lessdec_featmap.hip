@@ -99,7 +99,8 @@ __global__ __launch_bounds__(64 * kFmWaves) void featmap_generic_kernel(const Fe
       for (int t = 0; t < RT; ++t) {
         const int r = 16 * t + c;
         const double w2 = (double)Store<T>::to_float(W2[(size_t)(r < R ? r : R - 1) * Rp + (j < Rp ? j : Rp - 1)]);
-        c2[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(w2, act, c2[t], 0, 0, 0);
+        // (past the last unit a zero on both sides: the weight read in its place may be an infinity)
+        c2[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(j < Rp ? w2 : 0.0, act, c2[t], 0, 0, 0);
       }
     }
   }
