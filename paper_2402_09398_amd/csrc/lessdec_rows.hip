@@ -437,7 +437,8 @@ __global__ __launch_bounds__(64 * kColWaves) __attribute__((amdgpu_waves_per_eu(
       RowDigits<D> qd;
       const bool qbad = __any(!qd.load(qp, g));
       // rows past the prompt, and rows without a log-sum, have no part in any column
-      const double shift = (qi < P && fabs(lq) < 1e300) ? -lq * kLog2E : -1e300;
+      const bool has_sum = qi < P && fabs(lq) < 1e300;
+      const double shift = has_sum ? -lq * kLog2E : -1e300;
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
         if (t >= nt || s_pos[16 * t] > it * 16 + 15) break;             // wave-uniform
@@ -459,8 +460,9 @@ __global__ __launch_bounds__(64 * kColWaves) __attribute__((amdgpu_waves_per_eu(
           dot_tiles_f64<D, 1>([&](int i) { return Ku + (size_t)s_pos[16 * t + i < nk ? 16 * t + i : 0] * D; }, qp, g, c, s);
 #pragma unroll
           for (int w = 0; w < 4; ++w) {
+            // (a row without a log-sum may hold infinite scores)
             y[w] = fma(s[0][w], cs, shift);
-            y[w] = y[w] > kNoWeight ? y[w] : kNoWeight;
+            y[w] = has_sum && y[w] > kNoWeight ? y[w] : kNoWeight;
           }
         }
         exp2_f64(y, e);

@@ -161,3 +161,19 @@ def test_small_weights_keep_their_bits():
     r = np.exp(low[j] - top[i])
     exact = n * r * 60000 / (1 + n * r)
     assert (np.abs(got - exact) <= n * 2.0 ** -25 * 60000 + exact * 2.0 ** -10).all(), np.abs(got - exact).max() / exact.max()
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf])
+def test_row_without_a_log_sum_has_no_part_in_column_sums(value):
+    """An infinite query element: its row's scores are infinite and the row has no log-sum.  The column sums are
+    those of the other rows (its own weights are not numbers), and whatever they decide stays decidable."""
+    w = shape(100, steps=0)
+    inp = wl.all_inputs(w)
+    inp["Q"][0, 40, 5] = value
+    acc, pos = (hz.gpu_run(w, inp)["after_prefill"][n][0] for n in ("acc", "pos"))
+    s = inp["Q"][0].astype(np.float64) @ inp["K"][0].astype(np.float64).T / np.sqrt(w.head_dim)
+    s[40] = 0
+    a = np.exp(np.where(np.tril(np.ones_like(s, dtype=bool)), s, -np.inf))
+    a /= a.sum(1, keepdims=True)
+    a[40] = 0
+    assert np.isfinite(acc).all() and np.allclose(acc, a.sum(0)[pos], rtol=1e-6, atol=0)
