@@ -1331,8 +1331,8 @@ __global__ __launch_bounds__(64 * W) void prefill_finalize_kernel(
     }
   }
 
-  // 3) state of the discarded pairs.  Kept tokens go through the same arithmetic with values and psi of
-  // z zeroed, so that no load stands under a condition.
+  // 3) state of the discarded pairs.  Kept tokens go through the same arithmetic with values and psi
+  // zeroed (both: an infinity or NaN in one of them has no part in the state), so that no load stands under a condition.
   constexpr int LPT = D / 8, TPW = 64 / LPT;               // lanes per token, tokens per wave at a time
   const int dl = lane % LPT, tp = lane / LPT;
   const bool vec4 = R % 4 == 0;                            // psi rows readable as 16-byte vectors
@@ -1361,6 +1361,8 @@ __global__ __launch_bounds__(64 * W) void prefill_finalize_kernel(
 #pragma unroll
         for (int r = 0; r < RC; ++r) gj[r] = pj[r < rn ? r : 0];
       }
+#pragma unroll
+      for (int r = 0; r < RC; ++r) gj[r] = __uint_as_float(__float_as_uint(gj[r]) & mask);
       const unsigned gz = __float_as_uint(pa[(size_t)j * R + rz]) & mask;
       double v[8];
       load_eight(Vu + (size_t)j * D + 8 * dl, mask, v);

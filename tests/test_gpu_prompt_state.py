@@ -1,6 +1,7 @@
 """The state a prompt leaves (GPU, against the oracle): slots, gathered rows, H and z of the discarded pairs, at ranks
 around the chunk of eight rows, ragged prompts, both storage types; and the prefix states of Lambda-masking through the
 prompt at prompts around the block of 64 keys.  Tolerances: tests/harness.py."""
+import numpy as np
 import pytest
 
 from paper_2402_09398_amd import workloads as wl
@@ -37,3 +38,18 @@ def test_prefix_states(kw):
     w = shape(**kw)
     rep = hz.run_workload(w, range(w.units), flags=2 | 4)
     assert rep.ok(), rep.failures[:10]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+def test_kept_tokens_that_are_not_finite(dtype):
+    """Kept tokens have no part in H and z, whatever their psi and values are (Lambda-masking: the kept set does not
+    depend on them)."""
+    w = shape(dtype=dtype, steps=0)
+    clean = wl.all_inputs(w)
+    dirty = {k: v.copy() for k, v in clean.items()}
+    dirty["K"][:, -1, 5] = np.nan
+    dirty["V"][:, -2, 7] = np.inf
+    a, b = (hz.gpu_run(w, x, flags=2)["after_prefill"] for x in (clean, dirty))
+    assert np.isnan(b["psi"]).any()
+    for name in ("H", "z"):
+        assert np.array_equal(a[name], b[name]), name
