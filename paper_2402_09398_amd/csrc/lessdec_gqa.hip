@@ -614,6 +614,12 @@ __global__ __launch_bounds__(64 * kGqmWaves, D == 64 && NTW <= 2 ? 4 : 2) void g
       const int r0 = 16 * (t * kGqmWaves + wave);
       if (r0 >= rows) continue;                      // wave-uniform
       if constexpr (!kAhead) load_values(t, vraw[0]);
+      if (r0 + 16 > rows) {                          // wave-uniform: rows past the last have no value either
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+#pragma unroll
+          for (int i = 0; i < NV; ++i) vraw[kAhead ? t : 0][w][i] = r0 + 4 * g + w < rows ? vraw[kAhead ? t : 0][w][i] : 0u;
+      }
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
         const double inc = row16_allreduce(e[t][w] * ascale, OpAdd{});

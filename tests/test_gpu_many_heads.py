@@ -95,3 +95,14 @@ def test_state_that_is_not_finite():
     gpu.step(q, k, v, out)
     out = out.cpu().numpy()
     assert np.isnan(out[1]).all() and np.isfinite(out[0]).all()
+
+
+def test_rows_past_the_last_have_no_value():
+    """An infinite element of the step's own value row, which stands in for the rows past the last of a tile: the
+    outputs are infinite there, as its weight is not zero, and finite elsewhere."""
+    w = shape("infinite-value", steps=1)
+    assert (w.capacity + 1) % 16
+    inp = wl.all_inputs(w)
+    inp["v"][0, :, 7] = np.inf
+    out = hz.gpu_run(w, inp)["outs"][0]
+    assert np.isposinf(out[..., 7]).all() and np.isfinite(np.delete(out, 7, axis=-1)).all()
