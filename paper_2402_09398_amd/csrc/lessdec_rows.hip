@@ -370,22 +370,21 @@ hipError_t launch_rows_f16(const void *Q, const void *K, const void *V, unsigned
 // Exact column sums sum_i e^{s_ij - lse_i} of listed keys (list == nullptr: of every key): the accumulated
 // attention probability of each prompt token (H2O's score, Sec. 2.1).  A workgroup takes 16 NT
 // listed keys, ascending, splits their rows into digit planes once, into the LDS, and deals the query
-// tiles of 16, from the one of its earliest key on and over all the unit's query heads, to its eight
+// tiles of 16, from the one of its earliest key on and over all the unit's query heads, to its W
 // waves.  A wave splits a query tile in registers and multiplies it with every key tile that
 // begins before the tile ends (a prefix of them).  No atomics: every wave sums its query tiles in order, and
 // the waves' sums are added in order.  The length of the list is only known on the device: a unit gets
 // enough workgroups for a list a little longer than the budget, and they loop should it be longer.
 // grid = ceil(U / 8) * 8 * groups.
 // -------------------------------------------------------------------------------------
-constexpr int kColWaves = 8;
-template <int D, int NT>
-__global__ __launch_bounds__(64 * kColWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void columns_f16_kernel(
+template <int D, int NT, int W>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) void columns_f16_kernel(
     const __half *__restrict__ Q, const __half *__restrict__ K, unsigned U, int G, int P, const double *__restrict__ lse,
     const int32_t *__restrict__ list, const int32_t *__restrict__ count, int groups, double *__restrict__ colsum)
 {
   constexpr int KC = D / 64, KEYS = 16 * NT, kTile = 4 * KC * 1024;
   __shared__ __attribute__((aligned(16))) unsigned char s_key[NT * kTile];
-  __shared__ double s_sum[kColWaves][KEYS];
+  __shared__ double s_sum[W][KEYS];
   __shared__ int s_pos[KEYS], s_bad[NT];
   const PrefillBlock pb = prefill_block(blockIdx.x, groups);
   if (pb.u >= U) return;
@@ -404,7 +403,7 @@ __global__ __launch_bounds__(64 * kColWaves) __attribute__((amdgpu_waves_per_eu(
     if (tid < KEYS) s_pos[tid] = tid < nk ? (li ? li[grp * KEYS + tid] : grp * KEYS + tid) : INT_MAX;
     if (tid < NT) s_bad[tid] = 0;
     __syncthreads();
-    for (int i = tid; i < nt * 16 * (D / 16); i += 64 * kColWaves) {    // a piece of 16 elements of a listed key
+    for (int i = tid; i < nt * 16 * (D / 16); i += 64 * W) {    // a piece of 16 elements of a listed key
       const int key = i / (D / 16), e = i % (D / 16) * 16;
       const uint4 *src = reinterpret_cast<const uint4 *>(Ku + (size_t)s_pos[key < nk ? key : 0] * D + e);
       const uint4 x = src[0], y = src[1];
@@ -430,7 +429,7 @@ __global__ __launch_bounds__(64 * kColWaves) __attribute__((amdgpu_waves_per_eu(
     for (int t = 0; t < NT; ++t)
 #pragma unroll
       for (int w = 0; w < 4; ++w) sum[t][w] = 0.0;
-    for (int idx = wave; idx < G * per; idx += kColWaves) {
+    for (int idx = wave; idx < G * per; idx += W) {
       const int h = idx / per, it = it0 + idx - h * per, qi = it * 16 + c, qrow = qi < P ? qi : P - 1;
       const __half *qp = Q + ((u * G + h) * (size_t)P + qrow) * D;
       const double lq = lse[(u * G + h) * (size_t)P + qrow];
@@ -486,19 +485,19 @@ __global__ __launch_bounds__(64 * kColWaves) __attribute__((amdgpu_waves_per_eu(
     if (tid < nk) {
       double total = 0.0;
 #pragma unroll
-      for (int w = 0; w < kColWaves; ++w) total += s_sum[w][tid];
+      for (int w = 0; w < W; ++w) total += s_sum[w][tid];
       colsum[u * (size_t)P + s_pos[tid]] = total;
     }
     __syncthreads();                                      // before the next list's positions
   }
 }
 
-template <int D, int NT>
+template <int D, int NT, int W>
 static hipError_t launch_columns_t(const void *Q, const void *K, unsigned U, int G, int P, const double *lse,
                                    const int32_t *list, const int32_t *count, int keys, double *colsum, hipStream_t st)
 {
   const int groups = (keys + 16 * NT - 1) / (16 * NT);
-  columns_f16_kernel<D, NT><<<prefill_grid(U, (unsigned)groups), 64 * kColWaves, 0, st>>>(
+  columns_f16_kernel<D, NT, W><<<prefill_grid(U, (unsigned)groups), 64 * W, 0, st>>>(
       (const __half *)Q, (const __half *)K, U, G, P, lse, list, count, groups, colsum);
   return hipGetLastError();
 }
@@ -507,12 +506,26 @@ hipError_t launch_columns_f16(const void *Q, const void *K, unsigned U, int G, i
                               const int32_t *list, const int32_t *count, int C, double *colsum, hipStream_t st)
 {
   const int keys = list && C + 16 < P ? C + 16 : P;       // a handful of tokens in doubt behind the budget
-  // 128 keys share a split query tile; 32 where that leaves compute units idle, or where 32 hold the whole list
-  // (640 units x 70 tokens, 10 kept: 18 against 32 us; 640 x 200, 90 kept: 89 against 56 with three narrow ones)
-  const bool wide = keys > 32 && (size_t)U * ((keys + 127) / 128) >= 256;
-#define LESSDEC_COLUMNS(DD, NT) launch_columns_t<DD, NT>(Q, K, U, G, P, lse, list, count, keys, colsum, st)
-  if (D == 128) return wide ? LESSDEC_COLUMNS(128, 8) : LESSDEC_COLUMNS(128, 2);
-  return wide ? LESSDEC_COLUMNS(64, 8) : LESSDEC_COLUMNS(64, 2);
+  const int tiles = (keys + 15) / 16;
+#define LESSDEC_COLUMNS(NT, W)                                                                       \
+  return D == 128 ? launch_columns_t<128, NT, W>(Q, K, U, G, P, lse, list, count, keys, colsum, st)  \
+                  : launch_columns_t<64, NT, W>(Q, K, U, G, P, lse, list, count, keys, colsum, st)
+  // (NT key tiles to a workgroup, W waves; microseconds of a prompt phase.)  Few units: many waves divide a sweep, and a
+  // unit's keys, whose sweeps differ in length, are spread thin (<2, 8>: 8 units x 2048 tokens 188, <8, 8> 239; 128 x
+  // 4 heads x 2048, 204 kept: 3480 against 3590), unless there are so many keys that splitting the queries anew for every
+  // 32 costs more (64 x 500, all kept: <8, 8> 144, <2, 8> 153).  Else long sweeps: many keys to a split query tile
+  // (256 x 2 heads x 1000: <8, 8> 766, <8, 4> 786, <2, 8> 834; 1024 x 500: <8, 4> 610, <8, 8> 631, <4, 2> 662).  Short
+  // ones, where a workgroup has few query tiles to deal out: two waves, and four key tiles where they come out
+  // filled (2048 x 64, all kept: <4, 2> 108, <8, 8> 162; 2048 x 200: <2, 2> 439, <4, 2> 482, <8, 8> 566; 2048 x 300:
+  // <4, 2> 653, <2, 2> 694, <8, 4> 685; 512 x 400: <4, 2> 274, <2, 2> 277, <8, 4> 314).
+  const size_t wide = (size_t)U * ((tiles + 7) / 8);      // workgroups of eight key tiles
+  if (U < 256 && (tiles < 24 || wide < 256)) LESSDEC_COLUMNS(2, 8);
+  if ((long)G * P > 448) {
+    if (wide < 768) LESSDEC_COLUMNS(8, 8);
+    LESSDEC_COLUMNS(8, 4);
+  }
+  if (tiles % 4 == 0 || tiles % 4 == 3) LESSDEC_COLUMNS(4, 2);
+  LESSDEC_COLUMNS(2, 2);
 #undef LESSDEC_COLUMNS
 }
 

@@ -38,3 +38,15 @@ def test_nearly_equal_sums(spread):
     rep = hz.check_against_oracle(w, inp, list(range(w.units)), res)
     rep.failures.extend(hz.check_every_unit(w, res))
     assert rep.ok(), rep.failures[:10]
+
+
+@pytest.mark.parametrize("prompt,heavy,recent,kw", [
+    (64, 32, 32, {}), (64, 6, 6, {}), (40, 14, 14, {}), (130, 65, 65, dict(head_dim=128)), (257, 30, 30, {}),
+    (120, 10, 20, dict(q_per_kv=4, head_dim=128)), (460, 20, 20, {}), (460, 240, 240, dict(head_dim=128)),
+    (450, 60, 60, dict(heads=24)), (500, 40, 30, dict(heads=24, batch=33)),
+], ids=lambda x: str(x))
+def test_kept_set_of_many_units(prompt, heavy, recent, kw):
+    """256 units and more: the forms of the exact column sums for short and for long sweeps, by the number of key tiles."""
+    w = shape(prompt, heavy, recent, **{**dict(batch=32, heads=8), **kw})
+    rep = hz.run_workload(w, [0, 1, 100, w.units // 2 + 5, w.units - 1])
+    assert rep.ok(), rep.failures[:10]
