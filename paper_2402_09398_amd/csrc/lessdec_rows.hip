@@ -280,9 +280,12 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
       }
     } else {
       if (kt <= kt_wave) {
-        weigh(y[0], 0);                                   // the tile before
-        weigh(y[1], 1);
-        add_values(v_prev, false);
+        if (kt > 0) {                                     // the tile before
+          weigh(y[0], 0);
+          weigh(y[1], 1);
+          add_values(v_prev, false);
+        }
+        const bool only0 = j0 + 16 > q0 + 15;             // the second half lies after all of the wave's queries
         if (slow) {
           v4d d[2];
           dot_tiles_f64<D, 2>([&](int i) { return Ku + (size_t)(j0 + i < P ? j0 + i : P - 1) * D; }, Qu + (size_t)qrow * D, g, c, d);
@@ -292,10 +295,11 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
             y[1][w] = fma(d[1][w], cs, -m);
           }
         } else {
-#pragma unroll
-          for (int half = 0; half < 2; ++half) {
-            products(kt, half, s);
-            scores(s, y[half]);
+          products(kt, 0, s);
+          scores(s, y[0]);
+          if (!only0) {                                   // (else masked below)
+            products(kt, 1, s);
+            scores(s, y[1]);
           }
         }
         if (kt == kt_wave) {
@@ -315,7 +319,7 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
         if (kt == kt_wave) {                              // the wave's last tile
           weigh(y[0], 0);
           weigh(y[1], 1);
-          add_values(v_cur, j0 + 16 > q0 + 15);
+          add_values(v_cur, only0);
         }
       }
       if (kt < kt_last) {
