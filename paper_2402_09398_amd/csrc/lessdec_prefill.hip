@@ -915,7 +915,8 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
 // lo(a) = a (1 - band) - tau grow with a, so two order statistics decide: "fewer than Nh others could be larger"
 // is hi(the (Nh + 1)-th largest) < lo(a_j), "at least Nh others surely are" is lo(the Nh-th largest) > hi(a_j).
 // The Nh-th largest comes from a radix selection over the bits of the values (three passes of 11, 11 and 10
-// bits; a sum that is not a number ranks last and is itself kept), the next one from one more pass.
+// bits; a sum that is not a number ranks last and is itself kept), the next one from one more pass; up to 256
+// candidates, both by counting.
 // flag[j] = 1 kept for sure (heavy or recent), 0 discarded for sure, 2 in doubt.  list, count: the tokens
 // whose exact column sum is wanted (flag != 0), ascending.  With Lambda-masking (lambda) the first Nh and
 // the last Nr tokens are kept, nothing is in doubt and approx is not looked at.
@@ -971,67 +972,83 @@ __global__ __launch_bounds__(256) void prefill_select_kernel(const float *__rest
     const float M = sqrtf(__uint_as_float(qmax[u])) * sqrtf(__uint_as_float((unsigned)count[u])) *
                     (float)(1.0 / sqrt((double)D)) * 1.001f;
     band = fmaxf(kBand, 2.f * colapprox_error_bound(M, D, P, G));
-    unsigned prefix = 0, mask = 0;                        // bits of the Nh-th largest known so far
-    int rank = Nh;                                        // its rank among the values with those bits, from 1
-    bool found = Nh > 0;
-    for (int pass = 0; pass < 3 && found; ++pass) {
-      const int shift = pass == 0 ? 21 : pass == 1 ? 10 : 0, bins = pass == 2 ? 1024 : kBins;
-      for (int i = tid; i < kBins; i += 256) s_hist[i] = 0;
-      if (tid == 0) s_bin = -1;
+    if (ncand <= 256) {
+      // a value per thread: its rank by counting (equal ones by position)
+      float *s_val = reinterpret_cast<float *>(s_hist), *s_t = s_val + 256;
+      const float x = tid < ncand ? a[tid] : -1.f;
+      s_val[tid] = x;
+      if (tid < 2) s_t[tid] = -1.f;
       __syncthreads();
-      for (int j = tid; j < ncand; j += 256) {
-        const unsigned x = __float_as_uint(a[j]);
-        if (x <= 0x7f800000u && (x & mask) == prefix) atomicAdd(&s_hist[(x >> shift) & (bins - 1)], 1);
-      }
+      int above = 0;
+      for (int j = 0; j < ncand; ++j) above += (s_val[j] > x || (s_val[j] == x && j < tid)) ? 1 : 0;
+      if (x >= 0.f && above == Nh - 1) s_t[0] = x;
+      if (x >= 0.f && above == Nh) s_t[1] = x;
       __syncthreads();
-      // thread t takes the bins from the top down: kPer of them, above them the threads before
-      int mine = 0, total;
-#pragma unroll
-      for (int i = 0; i < kPer; ++i) mine += s_hist[kBins - 1 - (tid * kPer + i)];
-      int above = block_scan<4>(mine, s_wave, total);
-      if (above < rank && above + mine >= rank) {
-#pragma unroll
-        for (int i = 0; i < kPer; ++i) {
-          const int bin = kBins - 1 - (tid * kPer + i), n = s_hist[bin];
-          if (above < rank && above + n >= rank) {
-            s_bin = bin;
-            s_rank = rank - above;
-          }
-          above += n;
+      t1 = s_t[0];
+      t2 = s_t[1];
+    } else {
+      unsigned prefix = 0, mask = 0;                        // bits of the Nh-th largest known so far
+      int rank = Nh;                                        // its rank among the values with those bits, from 1
+      bool found = Nh > 0;
+      for (int pass = 0; pass < 3 && found; ++pass) {
+        const int shift = pass == 0 ? 21 : pass == 1 ? 10 : 0, bins = pass == 2 ? 1024 : kBins;
+        for (int i = tid; i < kBins; i += 256) s_hist[i] = 0;
+        if (tid == 0) s_bin = -1;
+        __syncthreads();
+        for (int j = tid; j < ncand; j += 256) {
+          const unsigned x = __float_as_uint(a[j]);
+          if (x <= 0x7f800000u && (x & mask) == prefix) atomicAdd(&s_hist[(x >> shift) & (bins - 1)], 1);
         }
+        __syncthreads();
+        // thread t takes the bins from the top down: kPer of them, above them the threads before
+        int mine = 0, total;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) mine += s_hist[kBins - 1 - (tid * kPer + i)];
+        int above = block_scan<4>(mine, s_wave, total);
+        if (above < rank && above + mine >= rank) {
+#pragma unroll
+          for (int i = 0; i < kPer; ++i) {
+            const int bin = kBins - 1 - (tid * kPer + i), n = s_hist[bin];
+            if (above < rank && above + n >= rank) {
+              s_bin = bin;
+              s_rank = rank - above;
+            }
+            above += n;
+          }
+        }
+        __syncthreads();
+        found = s_bin >= 0;                                 // not: fewer than Nh values that are numbers
+        if (found) {
+          prefix |= (unsigned)s_bin << shift;
+          mask |= (unsigned)(bins - 1) << shift;
+          rank = s_rank;
+        }
+        __syncthreads();
+      }
+      // the next one: the same value if it is there once more, else the largest below it
+      if (tid == 0) {
+        s_more = 0;
+        s_next = 0;
       }
       __syncthreads();
-      found = s_bin >= 0;                                 // not: fewer than Nh values that are numbers
-      if (found) {
-        prefix |= (unsigned)s_bin << shift;
-        mask |= (unsigned)(bins - 1) << shift;
-        rank = s_rank;
+      if (found || Nh == 0) {
+        int same = 0;
+        unsigned next = 0;
+        for (int j = tid; j < ncand; j += 256) {
+          const unsigned x = __float_as_uint(a[j]);
+          if (x > 0x7f800000u) continue;
+          if (found && x == prefix) ++same;
+          else if ((Nh == 0 || x < prefix) && x + 1u > next) next = x + 1u;   // + 1: 0 stands for none
+        }
+        if (same) atomicAdd(&s_more, same);
+        if (next) atomicMax(&s_next, next);
+        __syncthreads();
+        if (found) t1 = __uint_as_float(prefix);
+        if (found && s_more > rank) t2 = t1;
+        else if (s_next) t2 = __uint_as_float(s_next - 1u);
       }
       __syncthreads();
     }
-    // the next one: the same value if it is there once more, else the largest below it
-    if (tid == 0) {
-      s_more = 0;
-      s_next = 0;
-    }
-    __syncthreads();
-    if (found || Nh == 0) {
-      int same = 0;
-      unsigned next = 0;
-      for (int j = tid; j < ncand; j += 256) {
-        const unsigned x = __float_as_uint(a[j]);
-        if (x > 0x7f800000u) continue;
-        if (found && x == prefix) ++same;
-        else if ((Nh == 0 || x < prefix) && x + 1u > next) next = x + 1u;   // + 1: 0 stands for none
-      }
-      if (same) atomicAdd(&s_more, same);
-      if (next) atomicMax(&s_next, next);
-      __syncthreads();
-      if (found) t1 = __uint_as_float(prefix);
-      if (found && s_more > rank) t2 = t1;
-      else if (s_next) t2 = __uint_as_float(s_next - 1u);
-    }
-    __syncthreads();
   }
   const float keep_above = t2 * (1.f + band) + tau, drop_below = t1 * (1.f - band) - tau;
   int32_t *f = flag + u * (size_t)P, *out = list + u * (size_t)P;
@@ -1512,12 +1529,13 @@ static hipError_t launch_prefill_t(const PrefillArgs &a, hipStream_t st)
         // 256 keys per workgroup; 128 where that leaves compute units idle, or most of a workgroup's waves
         // without keys (640 units x 70 tokens: 13 against 18 us; 512 units x 150, D = 64: 17 against 13)
         const unsigned wide = prefill_grid(U, (unsigned)((P + 255) / 256)), narrow = prefill_grid(U, (unsigned)((P + 127) / 128));
-        if (wide >= 512 && P > 128)
-          prefill_colapprox_kernel<D, 4><<<wide, 64 * kPrefillWaves, 0, st>>>(
-              (const __half *)a.Q, (const __half *)a.K, U, P, a.lse, G, a.approx, (unsigned *)a.bound, (unsigned *)a.count);
-        else
-          prefill_colapprox_kernel<D, 2><<<narrow, 64 * kPrefillWaves, 0, st>>>(
-              (const __half *)a.Q, (const __half *)a.K, U, P, a.lse, G, a.approx, (unsigned *)a.bound, (unsigned *)a.count);
+#define LESSDEC_APPROX(KT, GRID)                                                                                        \
+  prefill_colapprox_kernel<D, KT><<<GRID, 64 * kPrefillWaves, 0, st>>>((const __half *)a.Q, (const __half *)a.K, U, P, a.lse, G, \
+                                                                       a.approx, (unsigned *)a.bound, (unsigned *)a.count)
+        if (P <= 64) LESSDEC_APPROX(1, prefill_grid(U, 1));
+        else if (wide >= 512 && P > 128) LESSDEC_APPROX(4, wide);
+        else LESSDEC_APPROX(2, narrow);
+#undef LESSDEC_APPROX
         if ((e = hipGetLastError()) != hipSuccess) return e;
       }
     }
