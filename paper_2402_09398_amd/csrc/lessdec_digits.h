@@ -170,15 +170,15 @@ __device__ inline v4d dot_tile_f64(KRow krow, const __half *qrow, int g, int c)
 }
 
 // 2^y of N values in fp64, y <= a few: y = n + f with |f| <= 1/2, polynomial of degree 9 in f
-// (interpolated at Chebyshev points, 1.9e-14 relative), scaled by 2^n; 0 where that underflows.
+// (interpolated at Chebyshev points, fit_exp2_poly.py, 1.9e-14 relative), scaled by 2^n; 0 where that underflows.
 // Scores come in base-2 units, so no reduction by ln 2 is needed.  The N chains run side by
 // side: one alone would wait for every multiply-add.
 template <int N>
 __device__ inline void exp2_f64(const double (&y)[N], double (&e)[N])
 {
-  constexpr double kPoly[9] = {1.3259645242976312e-06, 1.5252672925061028e-05, 0.00015403433751260721,
-                               0.0013333558200794317,  0.009618129193934294,   0.05550410866465167,
-                               0.2402265069564034,     0.6931471805599462,     1.0000000000000135};
+  constexpr double kPoly[9] = {1.325964524488711e-06, 1.5252672924850737e-05, 0.0001540343375125101,
+                               0.0013333558200794592, 0.009618129193934313,   0.05550410866465167,
+                               0.2402265069564034,    0.6931471805599462,     1.0000000000000135};
   double f[N], p[N];
   int n[N];
 #pragma unroll
@@ -186,7 +186,7 @@ __device__ inline void exp2_f64(const double (&y)[N], double (&e)[N])
     const double r = __builtin_rint(y[i]);
     f[i] = y[i] - r;
     n[i] = (int)r;
-    p[i] = 1.0205905366707709e-07;
+    p[i] = 1.0205905413765595e-07;
   }
 #pragma unroll
   for (int k = 0; k < 9; ++k)

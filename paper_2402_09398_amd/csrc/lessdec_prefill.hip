@@ -34,17 +34,8 @@ struct Chunk {
   __device__ inline double get(int s) const { return (double)Store<T>::get(v[s / EPV], s % EPV); }
 };
 
-// S^T tile: acc[v] = sum_d K[key g+4v][d] * Q[query c][d]; `a` holds the lane's key chunk,
-// `b` the lane's query chunk (one of them already widened to fp64 by the caller).
-template <typename T, int D>
-__device__ inline v4d tile_kq(const Chunk<T, D> &kraw, const double (&qd)[D / 4])
-{
-  v4d acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int s = 0; s < D / 4; ++s)
-    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(kraw.get(s), qd[s], acc, 0, 0, 0);
-  return acc;
-}
+// S^T tile: acc[v] = sum_d K[key g+4v][d] * Q[query c][d] of the lane's key chunk, already widened to fp64 by the
+// caller, and its query chunk.
 template <typename T, int D>
 __device__ inline v4d tile_kq(const double (&kd)[D / 4], const Chunk<T, D> &qraw)
 {
@@ -214,10 +205,8 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
     if constexpr (EPT * sizeof(T) == 32) {
       reinterpret_cast<uint4 *>(raw)[0] = reinterpret_cast<const uint4 *>(src)[0];
       reinterpret_cast<uint4 *>(raw)[1] = reinterpret_cast<const uint4 *>(src)[1];
-    } else if constexpr (EPT * sizeof(T) == 16) {
-      reinterpret_cast<uint4 *>(raw)[0] = reinterpret_cast<const uint4 *>(src)[0];
     } else {
-      reinterpret_cast<uint2 *>(raw)[0] = reinterpret_cast<const uint2 *>(src)[0];
+      reinterpret_cast<uint4 *>(raw)[0] = reinterpret_cast<const uint4 *>(src)[0];
     }
   };
   fetch(0);
@@ -1218,13 +1207,12 @@ __global__ __launch_bounds__(256) void prefill_refine_kernel(const double *__res
 // -------------------------------------------------------------------------------------
 // Selection: the last Nr tokens are recent; among the others the Nh largest (column sum,
 // position) pairs are heavy hitters; everything else is discarded.  Exact rank counting,
-// no sort: token j is heavy iff fewer than Nh candidates are larger.  Under Lambda-masking
-// (Sec. 4, "Setup") the first Nh tokens take the place of the heavy hitters.
+// no sort: token j is heavy iff fewer than Nh candidates are larger.  (Lambda-masking past the budget:
+// prefill_select_kernel.)
 // One thread per token: keep[j] = 1 / 0.   grid = U * ceil(P / 256), block = 256.
 // -------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void prefill_rank_kernel(const double *__restrict__ colsum, int P,
-                                                           int Nh, int Nr, int lambda,
-                                                           int32_t *__restrict__ keep_of)
+                                                           int Nh, int Nr, int32_t *__restrict__ keep_of)
 {
   const int nb = (P + 255) / 256;
   const size_t u = blockIdx.x / nb;
@@ -1234,9 +1222,7 @@ __global__ __launch_bounds__(256) void prefill_rank_kernel(const double *__restr
   const int C = Nh + Nr;
   const int ncand = P - Nr;                     // positions < P - Nr compete for the heavy slots
   int keep = 1;
-  if (P > C && lambda) {
-    keep = (j < Nh || j >= ncand) ? 1 : 0;
-  } else if (P > C && j < ncand) {
+  if (P > C && j < ncand) {
     const double a = cs[j];
     int larger = 0;
     for (int i = 0; i < ncand; ++i) {
@@ -1564,8 +1550,7 @@ static hipError_t launch_prefill_t(const PrefillArgs &a, hipStream_t st)
       e = hipGetLastError();
     }
     if (e != hipSuccess) return e;
-    prefill_rank_kernel<<<rank_grid, 256, 0, st>>>(a.colsum, P, d->n_heavy, d->n_recent, lambda ? 1 : 0,
-                                                   a.slot_of);
+    prefill_rank_kernel<<<rank_grid, 256, 0, st>>>(a.colsum, P, d->n_heavy, d->n_recent, a.slot_of);
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (!masked && (e = key_features()) != hipSuccess) return e;

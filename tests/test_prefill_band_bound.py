@@ -1,12 +1,15 @@
 """The selection band of the prompt phase (H2O scores of the prompt, Sec. 2.1: column sums of the
 causal attention matrix).  With fp16 storage the library first sums every column cheaply (fp16
-matrix products with fp32 accumulation, fp32 log-sums, fp32 exponential, fp32 running sums) and
+matrix products with fp32 accumulation; in base-2 units, with the factor log2(e) / sqrt(D) and the log-sums
+times log2(e) rounded to fp32; the base-2 exponential; fp32 running sums) and
 computes exact fp64 sums only for tokens whose cheap sum lies within a relative band of the
 selection boundary.  That is sound if every cheap sum is within the band of the exact one.  Here
 the cheap path is emulated in numpy fp32 arithmetic on the workloads whose column sums lie close
 together and on heavy-tailed keys, and compared with the oracle's fp64 column sums: the error
 must stay inside the bound the kernel derives (lessdec_prefill.hip, prefill_select_kernel), and the
-bound inside half the band the kernel then uses."""
+bound inside half the band the kernel then uses.  The bound takes the largest norms of a unit's query and key
+rows, which the kernel finds as fp32 sums of pairs of fp16 products: with the kernel's margin of 1.001 they must not
+fall below the true ones."""
 import numpy as np
 import pytest
 
@@ -25,18 +28,34 @@ def error_bound(M, D, P, G):
 def cheap_column_sums(Q, K, lse):
     """fp32 emulation of the cheap pass for one unit: Q [G,P,D], K [P,D] fp16, lse [G,P] fp64."""
     G, P, D = Q.shape
-    scale = np.float32(1.0 / np.sqrt(D))
+    scale = np.float32(np.log2(np.e) / np.sqrt(D))
     cs = np.zeros(P, dtype=np.float32)
     K32 = K.astype(np.float32)
     causal = np.tril(np.ones((P, P), dtype=bool))
     for g in range(G):
         acc = (Q[g].astype(np.float32) @ K32.T).astype(np.float32)           # fp32 accumulation of exact products
-        x = (acc * scale).astype(np.float32) - lse[g].astype(np.float32)[:, None]
+        lq = (lse[g] * np.log2(np.e)).astype(np.float32)
+        x = (acc.astype(np.float64) * np.float64(scale) - lq[:, None]).astype(np.float32)   # fused multiply-add
         with np.errstate(over="ignore"):                                    # entries above the diagonal are masked out
-            a = np.where(causal, np.exp(x.astype(np.float32)), np.float32(0)).astype(np.float32)
+            a = np.where(causal, np.exp2(x), np.float32(0)).astype(np.float32)
         # a lane's running sum over its share of the rows, then the lanes: sequential fp32 sums
         cs = (cs + np.cumsum(a, axis=0, dtype=np.float32)[-1]).astype(np.float32)
     return cs
+
+
+def score_bound(Q, K):
+    """M as the kernel finds it: fp32 squared norms of a lane group's 8 elements in pairs, then the groups."""
+    D = Q.shape[-1]
+
+    def largest(rows):
+        x = rows.reshape(-1, D // 32, 4, 4, 2).astype(np.float64)               # [row][step][group][pair][2]
+        ss = np.zeros((x.shape[0], 4), dtype=np.float32)                        # a lane group's sum, pairs in order
+        for ks in range(D // 32):
+            for i in range(4):
+                ss = (ss + (x[:, ks, :, i] ** 2).sum(-1)).astype(np.float32)
+        return ((ss[:, 0] + ss[:, 1]) + (ss[:, 2] + ss[:, 3])).max()
+
+    return np.sqrt(largest(Q)) * np.sqrt(largest(K)) * np.float32(1 / np.sqrt(D)) * np.float32(1.001)
 
 
 CASES = [
@@ -73,6 +92,7 @@ def test_cheap_column_sums_stay_inside_the_band(w):
         cheap = cheap_column_sums(Qu, Ku, lse).astype(np.float64)
         err = np.abs(cheap - exact) / exact
         M = np.linalg.norm(Qu.astype(np.float64), axis=-1).max() * np.linalg.norm(Ku.astype(np.float64), axis=-1).max() / np.sqrt(D)
+        assert M <= score_bound(Qu, Ku) <= 1.002 * M
         eps = error_bound(M, D, P, G)
         worst, worst_bound = max(worst, err.max()), max(worst_bound, eps)
         assert err.max() <= eps, (u, err.max(), eps)
