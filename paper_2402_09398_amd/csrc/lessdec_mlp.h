@@ -70,17 +70,20 @@ __device__ inline void mlp_activate(const v4f &h0, const v4f &h1, v8h &bhi, v8h 
   float one = 1.f;
   asm("" : "+s"(one));                                     // unknown to the compiler, which else makes a subtraction of the fma
   v4u hi, lo;
+  float x[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    x[i] = gelu_fast_f32(i < 4 ? h0[i] : h1[i - 4]);
+    asm("" : "+v"(x[i]));                                  // one fp32 value for both halves of the split
+  }
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
-    const v4f &h = w < 2 ? h0 : h1;
-    float x0 = gelu_fast_f32(h[2 * (w % 2)]), x1 = gelu_fast_f32(h[2 * (w % 2) + 1]);
-    asm("" : "+v"(x0), "+v"(x1));                          // one fp32 value for both halves of the split
-    unsigned p = __builtin_bit_cast(unsigned, v2h{(_Float16)x0, (_Float16)x1});
+    unsigned p = __builtin_bit_cast(unsigned, v2h{(_Float16)x[2 * w], (_Float16)x[2 * w + 1]});
     asm("" : "+v"(p));                                     // converted once, as a pair
-    const v2h x = __builtin_bit_cast(v2h, p);
+    const v2h y = __builtin_bit_cast(v2h, p);
     hi[w] = p;
-    lo[w] = __builtin_bit_cast(unsigned, v2h{(_Float16)__builtin_fmaf(-(float)x.x, one, x0),
-                                             (_Float16)__builtin_fmaf(-(float)x.y, one, x1)});
+    lo[w] = __builtin_bit_cast(unsigned, v2h{(_Float16)__builtin_fmaf(-(float)y.x, one, x[2 * w]),
+                                             (_Float16)__builtin_fmaf(-(float)y.y, one, x[2 * w + 1])});
   }
   bhi = __builtin_bit_cast(v8h, hi);
   blo = __builtin_bit_cast(v8h, lo);
