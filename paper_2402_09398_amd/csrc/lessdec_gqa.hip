@@ -680,7 +680,11 @@ static size_t gqm_lds(int C, int R, int D)
   return ((size_t)(C + 3) / 2 * 2 + (R + 1) / 2 * 2 + kGqmHeads * R + (size_t)kGqmWaves * kGqmHeads * (D + 2)) * sizeof(double);
 }
 
-// Sixteen heads to a matrix tile pay from nine heads on (up to eight the streaming kernel takes them).
+// Sixteen heads to a matrix tile pay from nine heads on (up to eight the streaming kernel takes them), also where a unit's
+// one group of heads leaves it one block and the vector form would have had up to eight: a step against the
+// vector form, us, 204 slots, D = 64: 9 heads x 8 units 23.0 and 25.8, x 64 23.5 and 26.2, x 512 29.8 and 56.3; 16 x 128 24.3
+// and 32.1; 17 x 32 25.5 and 26.6; 800 slots: 9 x 8 36.6 and 50.5; D = 128, 800 slots: 16 x 256 58.8 and 181.  The two are
+// level (within 2 %) with 16 slots and up to 64 units.
 static bool gqm_supported(int dtype, int C, int G)
 {
   return dtype == LESSDEC_DTYPE_F16 && G > 8 && C + 1 <= kGqmMaxRows;
@@ -716,7 +720,9 @@ static hipError_t launch_step_gqm_t(const StepArgs &a, int G, hipStream_t st)
 {
   const int ngrp = (G + kGqmHeads - 1) / kGqmHeads, tiles = (a.C + 1 + 15) / 16, ntw = (tiles + kGqmWaves - 1) / kGqmWaves;
   int nhb = gqa_head_blocks(a.U, G);
-  const bool split = nhb > 1;                               // few units: the finish is spread thinner as a launch of its own
+  // Few units: the finish is a launch of its own, also where the heads are one group and the block could finish its
+  // unit itself (2 us a step less: 21.1 against 23.0 for 8 units x 16 heads), as lessdec_step_launches answers for the shape.
+  const bool split = nhb > 1;
   if (nhb > ngrp) nhb = ngrp;
   const size_t lds = gqm_lds(a.C, a.R, D);
   if (lds > block_lds_limit()) return hipErrorInvalidValue;
