@@ -10,6 +10,8 @@
 // Both passes compute transposed tiles S^T[key][query] = K Q^T, so a lane always owns one
 // query column (c) and four keys (g + 4 v); a head row of D values is split into four
 // contiguous chunks of D / 4, chunk g supplying the k index of the instruction.
+#include <type_traits>
+
 #include "lessdec_common.h"
 #include "lessdec_internal.h"
 #include "lessdec_prefill.h"
@@ -1334,49 +1336,61 @@ __global__ __launch_bounds__(64 * W) void prefill_finalize_kernel(
     }
   }
 
-  // 3) state of the discarded pairs.  Kept tokens go through the same arithmetic with values and psi
-  // zeroed (both: an infinity or NaN in one of them has no part in the state), so that no load stands under a condition.
+  // 3) state of the discarded pairs.  Kept tokens go through the same arithmetic with values and psi of
+  // z zeroed, so that no load stands under a condition.
   constexpr int LPT = D / 8, TPW = 64 / LPT;               // lanes per token, tokens per wave at a time
   const int dl = lane % LPT, tp = lane / LPT;
   const bool vec4 = R % 4 == 0;                            // psi rows readable as 16-byte vectors
   for (int r0 = 0; r0 < R; r0 += RC) {
     const int rn = R - r0 < RC ? R - r0 : RC;
     const int rz = r0 + (dl < rn ? dl : 0);                // the lane's row of z (lanes dl < rn)
-    double h[RC][8], zs = 0.0;
+    double h[RC][8], zs;
+    // CLEAN: psi of kept tokens zeroed too.  Without it a kept token adds psi times zero, which is zero unless its psi
+    // is not finite
+    auto sweep = [&](auto clean) __attribute__((always_inline)) {
+      zs = 0.0;
 #pragma unroll
-    for (int r = 0; r < RC; ++r)
+      for (int r = 0; r < RC; ++r)
 #pragma unroll
-      for (int i = 0; i < 8; ++i) h[r][i] = 0.0;
+        for (int i = 0; i < 8; ++i) h[r][i] = 0.0;
 #pragma unroll 2
-    for (int j0 = wave * TPW; j0 < P; j0 += W * TPW) {
-      const int j = j0 + tp < P ? j0 + tp : P - 1;
-      const unsigned mask = (so[j] < 0 && j0 + tp < P) ? ~0u : 0u;       // ~0: discarded
-      const float *pj = pa + (size_t)j * R + r0;
-      float gj[RC];
-      // rows past R repeat earlier ones; their sums are never stored
-      if (vec4) {
+      for (int j0 = wave * TPW; j0 < P; j0 += W * TPW) {
+        const int j = j0 + tp < P ? j0 + tp : P - 1;
+        const unsigned mask = (so[j] < 0 && j0 + tp < P) ? ~0u : 0u;     // ~0: discarded
+        const float *pj = pa + (size_t)j * R + r0;
+        float gj[RC];
+        // rows past R repeat earlier ones; their sums are never stored
+        if (vec4) {
 #pragma unroll
-        for (int r4 = 0; r4 < RC / 4; ++r4) {
-          const float4 x = *reinterpret_cast<const float4 *>(pj + (4 * r4 < rn ? 4 * r4 : 0));
-          gj[4 * r4] = x.x; gj[4 * r4 + 1] = x.y; gj[4 * r4 + 2] = x.z; gj[4 * r4 + 3] = x.w;
+          for (int r4 = 0; r4 < RC / 4; ++r4) {
+            const float4 x = *reinterpret_cast<const float4 *>(pj + (4 * r4 < rn ? 4 * r4 : 0));
+            gj[4 * r4] = x.x; gj[4 * r4 + 1] = x.y; gj[4 * r4 + 2] = x.z; gj[4 * r4 + 3] = x.w;
+          }
+        } else {
+#pragma unroll
+          for (int r = 0; r < RC; ++r) gj[r] = pj[r < rn ? r : 0];
         }
-      } else {
+        if constexpr (clean.value) {
 #pragma unroll
-        for (int r = 0; r < RC; ++r) gj[r] = pj[r < rn ? r : 0];
+          for (int r = 0; r < RC; ++r) gj[r] = __uint_as_float(__float_as_uint(gj[r]) & mask);
+        }
+        const unsigned gz = __float_as_uint(pa[(size_t)j * R + rz]) & mask;
+        double v[8];
+        load_eight(Vu + (size_t)j * D + 8 * dl, mask, v);
+        zs += (double)__uint_as_float(gz);
+#pragma unroll
+        for (int r = 0; r < RC; ++r) {
+          const double g = (double)gj[r];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) h[r][i] = fma(g, v[i], h[r][i]);
+        }
       }
+    };
+    sweep(std::false_type{});
+    bool lost = false;                                     // such a psi shows in every column of its row
 #pragma unroll
-      for (int r = 0; r < RC; ++r) gj[r] = __uint_as_float(__float_as_uint(gj[r]) & mask);
-      const unsigned gz = __float_as_uint(pa[(size_t)j * R + rz]) & mask;
-      double v[8];
-      load_eight(Vu + (size_t)j * D + 8 * dl, mask, v);
-      zs += (double)__uint_as_float(gz);
-#pragma unroll
-      for (int r = 0; r < RC; ++r) {
-        const double g = (double)gj[r];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) h[r][i] = fma(g, v[i], h[r][i]);
-      }
-    }
+    for (int r = 0; r < RC; ++r) lost |= !(h[r][0] == h[r][0]);
+    if (__any(lost)) sweep(std::true_type{});
     // the wave's token groups: a lane keeps half of its rows at each distance; row of h[k] is then row0 + k
     int row0 = 0;
 #pragma unroll
