@@ -90,8 +90,8 @@ __global__ __launch_bounds__(256) void mlp_pair_kernel(const MlpArgs a, const Ml
 // next chunk's rows are requested before the current chunk's arithmetic.
 // Bound by vector instructions (17 per activation, two of them transcendental).  With one max, one
 // mixed-precision fma per low half, one barrier per 32 rows in place of three per 16, and layer 1 of the
-// next group issued between the activations of this one: 920 -> 787 us for 2048 units x 1024
-// tokens, 460 -> 395 for 128 x 8192 (R' = 512, R = 8).
+// next group issued between the activations of this one: 920 -> 756 us for 2048 units x 1024
+// tokens, 460 -> 391 for 128 x 8192 (R' = 512, R = 8).
 // grid = Hh * parts (head fastest), every block a contiguous share of the head's chunks.
 template <int D, int NGW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void mlp_rows_kernel(const MlpArgs a,

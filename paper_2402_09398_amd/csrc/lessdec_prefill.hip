@@ -1246,7 +1246,7 @@ __global__ __launch_bounds__(256) void prefill_rank_kernel(const double *__restr
 // chunks of eight rows of H: a value of psi is widened once for eight columns and a value of V once for
 // eight rows, and z is one lane's work.  Tokens are dealt to the W waves; the lane groups meet by a
 // reduce-scatter over the rows of H, the waves in the LDS.  Four waves with two columns a lane, z in every lane, took
-// 496 us for 2048 units x 1024 tokens and 1070 us for 128 x 8192 (one workgroup per unit either way); 291 and 222
+// 496 us for 2048 units x 1024 tokens and 1070 us for 128 x 8192 (one workgroup per unit either way); 281 and 210
 // now.  slot_of: in 1 / 0 (kept / discarded), out slot index / -1.
 // grid = U, block = 64 W, dynamic LDS = C ints.
 // -------------------------------------------------------------------------------------

@@ -28,12 +28,14 @@ typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 // singly, each product waiting for its own).
 //
 // Per 16 x 16 tile the matrix units need 32 x 16 cycles for the digit products and 8 x 16 for p V, the
-// vector units some 160 instructions of 4 to 5 cycles.  The two run side by side (fp64 matrix instructions
+// vector units 222 instructions (8192 tokens; 246 at 1024) of 4 to 5 cycles; a tile takes 1570 cycles of a SIMD (1950), issue
+// two thirds of them: the rest are dependent fp64 chains, LDS reads and the barrier, which two waves a SIMD do not cover,
+// and with short sweeps the wait for a workgroup's longest wave.  The two kinds run side by side (fp64 matrix instructions
 // overlap with nothing), but a wave issues in order, so the loop is pipelined by one tile: the
 // products of a tile stand in one basic block with the weights and p V of the tile before and the staging
 // of the tile after.  One barrier per tile: keys in two buffers, values in
 // three (p V of tile kt - 1 runs after the barrier of tile kt).
-// 7390 us for 2048 units x 1024 tokens and 23540 for 128 x 8192 with fp64 matrix products; 3550 and 10870 now.
+// 7390 us for 2048 units x 1024 tokens and 23540 for 128 x 8192 with fp64 matrix products; 3530 and 10900 to 11200 now.
 // Eight waves to a workgroup split each key half as often, but wait longer for the waves whose diagonal
 // comes last: 4560 and 11330.
 // -------------------------------------------------------------------------------------
