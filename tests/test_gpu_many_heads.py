@@ -32,6 +32,7 @@ CASES = [
     (shape("rows-257-d128", n_heavy=128, n_recent=128, head_dim=128, prompt=300), 0),
     (shape("rows-513", n_heavy=256, n_recent=256, prompt=540, batch=1, steps=4), 0),
     (shape("rows-1024-d128", n_heavy=500, n_recent=523, head_dim=128, prompt=1030, batch=1, steps=4), 0),
+    (shape("rows-1024-rank-64-d128", n_heavy=500, n_recent=523, head_dim=128, prompt=1030, batch=1, steps=2, rank=64, hidden=48), 0),
     (shape("rows-1025", n_heavy=512, n_recent=512, prompt=1030, batch=1, steps=4), 0),
     (shape("filling", prompt=0, steps=30), 0),
     (shape("sparse-denominator"), 1),
