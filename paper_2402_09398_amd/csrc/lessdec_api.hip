@@ -23,6 +23,7 @@ inline bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_
 
 struct Shape {
   size_t U, C, D, R, Rp, G;
+  bool f16;
 };
 
 bool shape_ok(const lessdec_desc *d, Shape *s)
@@ -45,16 +46,17 @@ bool shape_ok(const lessdec_desc *d, Shape *s)
   s->D = (size_t)d->head_dim;
   s->R = (size_t)d->rank;
   s->Rp = (size_t)d->hidden;
+  s->f16 = d->dtype == LESSDEC_DTYPE_F16;
   s->G = d->q_per_kv > 1 ? (size_t)d->q_per_kv : 1;
   return true;
 }
 
 // Workspace: [ f_phi U*R f64 | f_psi U*R f32 | mlp_parts 2*ceil(R'/64)*U*16 f32 |
-//              prefill: 4 staged rows U*D (4 bytes each) | lse U*G*P f64, colsum U*P f64 | approx U*P f32, list U*P i32, count U i32, bound U f32 | slot_of U*P i32 | psi_all U*P*R f32 | phi_all U*G*P*R f32, psimax U*R f32, hpre U*(P/64+1)*R*D f32, zpre U*(P/64+1)*R f32 (masked prompt only) ],
+//              prefill: 4 staged rows U*D (4 bytes each) | lse U*G*P f64, colsum U*P f64 | approx U*P f32, list U*P i32, count U i32, bound U f32 | slot_of U*P i32 | psi_all U*P*R f32 | digits (fp16, digit_bytes) | phi_all U*G*P*R f32, psimax U*R f32, hpre U*(P/64+1)*R*D f32, zpre U*(P/64+1)*R f32 (masked prompt only) ],
 // every part 256-byte aligned.
 struct Workspace {
   size_t off_fphi, off_fpsi, off_parts, off_gqa, off_stage, off_lse, off_colsum, off_approx, off_list, off_count, off_bound, off_slot,
-      off_psiall, off_phiall, off_psimax, off_hpre, off_zpre, total;
+      off_psiall, off_digits, off_phiall, off_psimax, off_hpre, off_zpre, total;
 };
 
 Workspace carve(const Shape &s, size_t P, unsigned flags)
@@ -74,6 +76,7 @@ Workspace carve(const Shape &s, size_t P, unsigned flags)
   w.off_bound = o; o = align_up(o + (P ? s.U * sizeof(float) : 0), 256);
   w.off_slot = o; o = align_up(o + s.U * P * sizeof(int32_t), 256);
   w.off_psiall = o; o = align_up(o + s.U * P * s.R * sizeof(float), 256);
+  w.off_digits = o; o = align_up(o + (s.f16 ? digit_bytes(s.U, P, s.D) : 0), 256);
   // phi of every prompt query: only for Lambda-masking taken through the prompt token by token
   const bool masked = (flags & LESSDEC_FLAG_LAMBDA) && (flags & LESSDEC_FLAG_PROMPT_STEPWISE);
   w.off_phiall = o; o = align_up(o + (masked ? s.U * s.G * P * s.R * sizeof(float) : 0), 256);
@@ -148,13 +151,18 @@ MlpPartsArgs parts_args(const lessdec_desc *desc, const void *q, const void *k, 
   return fm;
 }
 
-// The per-step exchange array of the streaming path starts out empty (see wpu_step_kernel).
+// The per-step exchange array of the streaming path, which starts out empty (see wpu_step_kernel); no entries on other paths.
+struct Exchange { float *entries; size_t count; };
+Exchange exchange(const lessdec_desc *desc, const Shape &s)
+{
+  if (!use_wpu(desc, s) && !gq_parts(desc, s)) return {nullptr, 0};
+  return {reinterpret_cast<float *>(static_cast<char *>(desc->workspace) + carve(s, 0, desc->flags).off_parts),
+          (s.G > 1 ? s.G + 1 : 2) * (size_t)mlp_nparts((int)s.Rp) * s.U * 16};
+}
 hipError_t empty_exchange(const lessdec_desc *desc, const Shape &s, hipStream_t st)
 {
-  if (!use_wpu(desc, s) && !gq_parts(desc, s)) return hipSuccess;
-  const Workspace w = carve(s, 0, desc->flags);
-  return launch_fill_empty(reinterpret_cast<float *>(static_cast<char *>(desc->workspace) + w.off_parts),
-                           (s.G > 1 ? s.G + 1 : 2) * (size_t)mlp_nparts((int)s.Rp) * s.U * 16, st);
+  const Exchange x = exchange(desc, s);
+  return launch_fill_empty(x.entries, x.count, st);
 }
 
 // Device address of `scratch` on the current device, looked up once per device.
@@ -454,12 +462,14 @@ int lessdec_prefill(const lessdec_desc *desc, const void *Q, const void *K, cons
   a.count = reinterpret_cast<int32_t *>(ws + w.off_count);
   a.bound = reinterpret_cast<float *>(ws + w.off_bound);
   a.psi_all = reinterpret_cast<float *>(ws + w.off_psiall);
+  a.digits = ws + w.off_digits;
   a.phi_all = reinterpret_cast<float *>(ws + w.off_phiall);
   a.psimax = reinterpret_cast<float *>(ws + w.off_psimax);
   a.hpre = reinterpret_cast<float *>(ws + w.off_hpre);
   a.zpre = reinterpret_cast<float *>(ws + w.off_zpre);
   a.masked = masked ? 1 : 0;
-  if (empty_exchange(desc, s, (hipStream_t)hip_stream) != hipSuccess) return LESSDEC_EHIP;
+  const Exchange x = exchange(desc, s);
+  a.empty = x.entries; a.empty_count = x.count;
   return launch_prefill(a, (hipStream_t)hip_stream) == hipSuccess ? LESSDEC_OK : LESSDEC_EHIP;
 }
 

@@ -40,10 +40,10 @@ struct DotParts {
 constexpr double kDotUnit = 0x1p-48;
 
 // Digits of 4 halves (two dwords): plane p's dword holds digit p of the four.
-__device__ inline void digits_of4(unsigned h01, unsigned h23, unsigned (&plane)[4])
+__device__ inline void digits_of4(unsigned h01, unsigned h23, unsigned (&plane)[4], float unit = 0x1p24f)
 {
-  auto digit_word = [](unsigned short h) {
-    const float f = fmaf((float)__builtin_bit_cast(_Float16, h), 0x1p24f, 0.f);   // exact
+  auto digit_word = [unit](unsigned short h) {
+    const float f = fmaf((float)__builtin_bit_cast(_Float16, h), unit, 0.f);   // exact
     // adding 128 to every digit makes the digits the bytes of the sum; the sign bits flip back below
     return (unsigned)(int)f + 0x80808080u;
   };
@@ -92,6 +92,69 @@ struct RowDigits {
       }
     }
     return !bad;
+  }
+};
+
+// Digits of rows scaled by a power of two, so that the largest value uses the top digit in full.  A half has 11 significant
+// bits, so the lowest of four digits is then zero but for values 2^-12 of the largest and below: few blocks of 16 rows x 64
+// elements hold one (about a third with normal values), and without it a dot product takes nine products
+// of planes instead of sixteen.  A lane's 16 elements of a 64-wide block are 64 kc + 8 g .. + 7 and 32 further:
+// the order within a dot product is free as long as both sides keep to it.
+template <int D>
+struct ScaledDigits {
+  static constexpr int KC = D / 64;
+  v4i d[KC][4];
+  int scale;                                              // the digits are those of the values times 2^scale, 0 .. 20
+  // row: the lane's; every lane of the wave must call.  ALL: one scale for all 16 rows, else one per row.  Returns
+  // whether the lane's elements all have digits.
+  template <bool ALL>
+  __device__ inline bool load(const __half *row, int g)
+  {
+    unsigned w[KC][8], top = 0;
+#pragma unroll
+    for (int kc = 0; kc < KC; ++kc)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const uint4 x = *reinterpret_cast<const uint4 *>(row + 64 * kc + 8 * g + 32 * i);
+        w[kc][4 * i] = x.x; w[kc][4 * i + 1] = x.y; w[kc][4 * i + 2] = x.z; w[kc][4 * i + 3] = x.w;
+      }
+    typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+    us2 m = {0, 0};
+#pragma unroll
+    for (int kc = 0; kc < KC; ++kc)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) m = __builtin_elementwise_max(m, __builtin_bit_cast(us2, w[kc][i] & 0x7fff7fffu));
+    top = m.x > m.y ? m.x : m.y;
+    const bool ok = top < kDigitMax;
+    unsigned all = ok ? top : 0;
+#pragma unroll
+    for (int o = ALL ? 1 : 16; o < 64; o *= 2) {
+      const unsigned t = (unsigned)__shfl_xor((int)all, o);
+      all = t > all ? t : all;
+    }
+    // 2^e (1 + f) 2^(6 - e) < 128; below 127 unless f >= 63 / 64
+    const int e = (all >> 10 ? (int)(all >> 10) : 1) - 15;
+    scale = 6 - e - ((all & 0x3ffu) >= 0x3f0u ? 1 : 0);
+    scale = scale > 0 ? scale : 0;
+    const float unit = __builtin_ldexpf(1.f, 24 + scale);
+#pragma unroll
+    for (int kc = 0; kc < KC; ++kc)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        unsigned p[4];
+        digits_of4(w[kc][2 * i], w[kc][2 * i + 1], p, unit);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) d[kc][q][i] = (int)p[q];
+      }
+    return ok;
+  }
+  // bit kc: some lane has a lowest digit in that block
+  __device__ inline unsigned lowest() const
+  {
+    unsigned r = 0;
+#pragma unroll
+    for (int kc = 0; kc < KC; ++kc) r |= __any((d[kc][0][0] | d[kc][0][1] | d[kc][0][2] | d[kc][0][3]) != 0) ? 1u << kc : 0u;
+    return r;
   }
 };
 

@@ -54,6 +54,11 @@ hipError_t launch_mlp_parts(const MlpPartsArgs &a, hipStream_t st);
 // for psi, (G + 1) * B * Hh * nparts * mlp_entry_stride(R) floats
 hipError_t launch_mlp_parts_gq(const MlpPartsArgs &a, int G, hipStream_t st);
 
+// An entry of the per-step exchange between the feature-map jobs and the attention waves that no
+// job has written yet: a NaN that no sum of finite products can be (all bits set; a caller clears
+// a workspace with a byte fill of 0xFF).
+constexpr unsigned kMlpEmpty = 0xffffffffu;
+
 // pend_slot: -1 nothing; else slot index (C = the step's own pair) | kPendNoFold
 constexpr int kPendNoFold = 1 << 30;
 
@@ -115,6 +120,19 @@ hipError_t launch_fill_empty(float *parts, size_t count, hipStream_t st);
 
 hipError_t launch_reset(const lessdec_desc *d, hipStream_t st);
 
+// Digit planes of prompt keys: four bytes an element, a word per tile of 32 keys.  They live between the kernel that writes them
+// and the row pass, so units take turns in a part of the workspace of limited size: 640 MiB hold a million tokens of
+// D = 128 (a share of the work that fills the chip many times over), and a unit longer than that gets its own size.
+constexpr size_t kDigitBytes = (size_t)640 << 20;
+inline size_t digit_bytes_unit(size_t P, size_t D) { return (P + 31) / 32 * (32 * D * 4 + 4); }
+inline size_t digit_units(size_t U, size_t P, size_t D)
+{
+  size_t n = kDigitBytes / digit_bytes_unit(P, D);
+  if (n >= 8) n = n / 8 * 8;                               // whole rounds over the dies
+  return n < 1 ? 1 : n < U ? n : U;
+}
+inline size_t digit_bytes(size_t U, size_t P, size_t D) { return P ? digit_units(U, P, D) * digit_bytes_unit(P, D) : 0; }
+
 struct PrefillArgs {
   const lessdec_desc *d;
   const void *Q, *K, *V;
@@ -129,6 +147,9 @@ struct PrefillArgs {
   int32_t *count;           // [U] length of each unit's list
   float *bound;             // [U] largest score magnitude the unit's prompt can produce (selection band)
   float *psi_all;           // [U,P,R]
+  void *digits = nullptr;   // digit planes of the keys of digit_units(U, P, D) units (fp16)
+  float *empty = nullptr;   // entries of the decode step's exchange array, to be emptied
+  size_t empty_count = 0;
   float *phi_all = nullptr; // [U*G,P,R], only for the masked form
   float *psimax = nullptr;  // [U,R] feature-wise maximum of psi over the prompt, only for the masked form
   float *hpre = nullptr;    // [U, P/64+1, R, D] prefix sums of psi^T v, only for the masked form

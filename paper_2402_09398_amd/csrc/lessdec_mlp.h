@@ -20,11 +20,6 @@
 
 namespace lessdec {
 
-// An entry of the per-step exchange between the feature-map jobs and the attention waves that no
-// job has written yet: a NaN that no sum of finite products can be (all bits set; a caller clears
-// a workspace with a byte fill of 0xFF).
-constexpr unsigned kMlpEmpty = 0xffffffffu;
-
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef _Float16 v4h __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));

@@ -21,9 +21,18 @@ __device__ inline PrefillBlock prefill_block(unsigned b, int ngrp)
 inline unsigned prefill_grid(unsigned U, unsigned ngrp) { return (U + kXcds - 1) / kXcds * kXcds * ngrp; }
 
 // fp16 storage, scores from digit products (lessdec_rows.hip)
-// zero0, zero1: a word per unit that a later kernel takes a maximum into
-hipError_t launch_rows_f16(const void *Q, const void *K, const void *V, unsigned UG, int G, int P, int D, double *lse,
-                           void *out, unsigned *zero0, unsigned *zero1, hipStream_t st);
+struct RowArgs {
+  const void *Q, *K, *V;
+  unsigned U;
+  int G, P;
+  void *digits;              // digit_bytes(U, P, D)
+  double *lse;
+  void *out;                 // or NULL
+  unsigned *zero0, *zero1;   // a word per unit that a later kernel takes a maximum into
+  unsigned *fill;            // words to be set to kMlpEmpty
+  size_t fill_count;
+};
+hipError_t launch_rows_f16(const RowArgs &a, int D, hipStream_t st);
 // list == nullptr: every column
 hipError_t launch_columns_f16(const void *Q, const void *K, unsigned U, int G, int P, int D, const double *lse,
                               const int32_t *list, const int32_t *count, int C, double *colsum, hipStream_t st);

@@ -1472,6 +1472,8 @@ static hipError_t launch_prefill_t(const PrefillArgs &a, hipStream_t st)
     fa.B = d->batch; fa.Hh = d->heads; fa.rpu = P; fa.D = d->head_dim; fa.Rp = d->hidden; fa.R = d->rank;
     return launch_featmap_generic(fa, d->dtype, st);
   };
+  // the key digits' kernel empties the exchange array on its way
+  if ((masked || sizeof(T) != 2) && (e = launch_fill_empty(a.empty, a.empty_count, st)) != hipSuccess) return e;
   if (masked) {
     // psi of every prompt key, phi of every prompt query (Eq. 1, Eq. 2), then the masked rows
     if ((e = key_features()) != hipSuccess) return e;
@@ -1509,7 +1511,9 @@ static hipError_t launch_prefill_t(const PrefillArgs &a, hipStream_t st)
         d->n_heavy, d->n_recent, (d->flags & LESSDEC_FLAG_SPARSE_DENOM) ? 1 : 0, a.lse, (T *)a.out);
   } else {
     if constexpr (sizeof(T) == 2) {
-      if ((e = launch_rows_f16(a.Q, a.K, a.V, U * G, G, P, D, a.lse, a.out, (unsigned *)a.bound, (unsigned *)a.count, st)) != hipSuccess) return e;
+      const RowArgs r = {a.Q, a.K, a.V, U, G, P, a.digits, a.lse, a.out, (unsigned *)a.bound, (unsigned *)a.count,
+                         (unsigned *)a.empty, a.empty_count};
+      if ((e = launch_rows_f16(r, D, st)) != hipSuccess) return e;
     } else {
       prefill_rowpass_kernel<T, D><<<(U * G + kXcds - 1) / kXcds * kXcds * tiles, 64 * kPrefillWaves, 0, st>>>(
           (const T *)a.Q, (const T *)a.K, (const T *)a.V, U * G, G, P, a.lse, (T *)a.out);

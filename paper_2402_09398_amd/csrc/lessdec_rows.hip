@@ -11,70 +11,124 @@ namespace lessdec {
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 
 // -------------------------------------------------------------------------------------
-// Row pass.  A workgroup of four waves owns 64 consecutive queries, a wave 16 of them; the workgroup
-// sweeps the key tiles of 32 up to its last diagonal.  Per tile all threads
-// fetch the keys, split them into digit planes and put those into the LDS in operand order, and the
-// values transposed, as the A operand of p V.  A wave multiplies each 16-key half with its queries
-// (digits in registers): scores S^T[key][query], lane (g, c) holding keys 4 g + w of query c.
+// Row pass.  key_digits_kernel splits every key into digit planes once; then a workgroup of four waves owns 64 consecutive
+// queries, a wave 16 of them, and sweeps the key tiles of 32 up to its last diagonal.  The tiles go from memory into the
+// LDS without passing through registers: digits in operand order, value rows as they are, transposed by the reads of
+// p V.  A wave multiplies each 16-key half with its queries (digits in registers): scores S^T[key][query], lane (g, c)
+// holding keys 4 g + w of query c.
 // The running maximum m is an integer in base-2 units, the one below the largest score of the first tile (so that
 // the largest weight is above 1 and the fp16 pairs' floor of 2^-24 as far below it as with weights up to 1), moved when a
 // score passes it by kSlack, which is rare and exact.  The weights are fp64; their sum gives lse, and p V takes
 // them as an fp16 pair hi + lo (22 bits) with fp32 accumulation.  Leaves lse_i = ln sum_j e^{s_ij}.
 // A tile with a value that has no digits (|x| >= 127), and every tile of a wave whose queries hold one, is multiplied
-// in fp64 instead, from rows read as 16-byte pieces: 512 units x 1024 tokens with such a key channel in every token take
+// in fp64 instead, from rows read as 16-byte pieces: 512 units x 1024 tokens with such a key channel in every token took
 // 2907 us in all against 1486 with digits throughout and 3010 with fp64 products throughout (10560 with halves read
 // singly, each product waiting for its own).
 //
-// Per 16 x 16 tile the matrix units need 32 x 16 cycles for the digit products and 8 x 16 for p V, the
-// vector units 222 instructions (8192 tokens; 246 at 1024) of 4 to 5 cycles; a tile takes 1570 cycles of a SIMD (1950), issue
-// two thirds of them: the rest are dependent fp64 chains, LDS reads and the barrier, which two waves a SIMD do not cover,
-// and with short sweeps the wait for a workgroup's longest wave.  The two kinds run side by side (fp64 matrix instructions
-// overlap with nothing), but a wave issues in order, so the loop is pipelined by one tile: the
-// products of a tile stand in one basic block with the weights and p V of the tile before and the staging
-// of the tile after.  One barrier per tile: keys in two buffers, values in
-// three (p V of tile kt - 1 runs after the barrier of tile kt).
-// 7390 us for 2048 units x 1024 tokens and 23540 for 128 x 8192 with fp64 matrix products; 3530 and 10900 to 11200 now.
-// Eight waves to a workgroup split each key half as often, but wait longer for the waves whose diagonal
-// comes last: 4560 and 11330.
+// What bounds it: issue (an instruction in 98 % of the SIMD cycles at 8192 tokens) and power.  With the matrix units busy
+// half of the time the card lowers its clock, from 2.35 GHz to 2.0 here, more so the more the operands' bits change: a
+// schedule without gaps gained cycles and no time, fewer products and fewer vector instructions do.  Hence
+//   - keys are split once, not by every workgroup that meets them (62 of 222 vector instructions per 16 x 16 tile);
+//   - rows are scaled by powers of two, so that most blocks have an empty lowest plane and are nine products of
+//     planes, not sixteen (ScaledDigits; 30 matrix instructions per 16 x 16 tile, p V's 8 among them, where there were 40);
+//   - one path for all tiles: with a second one for those before the diagonal the compiler moved the scores and the
+//     accumulators between registers in every tile (30 instructions);
+//   - three waves a SIMD in place of two and a software pipeline: no slower with long sweeps, and with short ones the
+//     start and the end of a workgroup, in which its waves wait, are covered (2810 against 3040 us at 1024 tokens).
+// 2048 units x 1024 tokens: 3600 us before, 2545 now and 270 for the digits (1.6 GB at 5.9 TB/s); 128 x 8192:
+// 11000, 8340 and 125; 32 x 777: 65, 51 and 6.
 // -------------------------------------------------------------------------------------
 constexpr int kRowKeys = 32;
 constexpr double kSlack = 15.0;                           // weights up to 2^15: they fit a half
 constexpr double kNoWeight = -5000.0;                     // the weight of this score is 0
 
-// One key tile in the LDS.  Both operands lie as 1 KiB blocks [lane group g][16 rows] of 16 bytes, in
-// which a wave's read is one contiguous run; the row's place is turned by the block, so that writes of
-// one row to several blocks fall into different banks.
+// One tile of keys and values in the LDS.  Key digits lie as in memory (key_digits_kernel): a wave's read of a plane is one
+// contiguous KiB.  Value rows are whole, their 16-byte chunks permuted by val_swizzle.
 template <int D>
 struct RowTile {
-  static constexpr int KC = D / 64, DB = D / 16;
+  static constexpr int KC = D / 64;
   static constexpr int kHalfBytes = 4 * KC * 1024;        // planes of 16 keys
-  static constexpr int kPlaneBytes = KC * 1024;
-  static constexpr int kKeyBytes = 2 * kHalfBytes, kValBytes = DB * 1024;
-  // 16 digits of plane `plane` of key `row` of a half: elements 64 kc + 16 g ..
-  static __device__ inline int key_at(int half, int plane, int kc, int g, int row)
-  {
-    return half * kHalfBytes + plane * kPlaneBytes + (kc * 4 + g) * 256 + (row ^ (2 * (kc * 4 + g))) * 16;
-  }
-  // value column d = DB i + b as A operand row i of block b; key slot 8 g + 4 half + w stands for key 16 half + 4 g + w
-  static __device__ inline int val_at(int b, int i, int g) { return b * 1024 + g * 256 + (i ^ (2 * b % 16)) * 16; }
+  static constexpr int kKeyBytes = 2 * kHalfBytes, kValBytes = kRowKeys * D * 2;
+  // 16 lanes of a transposing read touch 8 bytes in each of four chunks of four consecutive rows
+  static __device__ inline int val_swizzle(int row) { return D == 128 ? row & 3 : (row >> 1) & 1; }
 };
+typedef short v4s __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) v4s lds_v4s;
+typedef __attribute__((address_space(3))) unsigned char lds_bytes;
+__device__ inline unsigned lds_offset(const unsigned char *p) { return (unsigned)(unsigned long long)(lds_bytes *)p; }
+// 1 KiB from memory into the LDS, 16 bytes a lane: lane l's from base + offset (of the lane), to `to` + 16 l.  base and to are
+// the same for the whole wave.  Written as asm because the compiler, which cannot tell the tile buffers apart,
+// would wait for the whole transfer before the next LDS read; nothing is returned in registers, and the
+// readers stand behind a wait for the counter and a barrier of their own.
+__device__ inline void lds_load_kib(const void *base, unsigned bytes, int offset, unsigned char *to)
+{
+  const unsigned long long b = reinterpret_cast<unsigned long long>(base);
+  const v4u rsrc = {(unsigned)b, (unsigned)(b >> 32) & 0xffffu, bytes, 0x00020000u};
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+               :
+               : "s"(lds_offset(to)), "v"(offset), "s"(rsrc)
+               : "memory");
+}
+// The 16-lane groups' transposing read: lane i of a group points at 4 halves, element i % 4 .. of row i / 4 of the group's
+// four rows by pieces of 4 columns, and gets column i of the four rows.
+__device__ inline v4s lds_read_transposed(unsigned offset)
+{
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s *)(unsigned long long)offset);
+}
+// What the row pass has to know of a tile of 32 keys besides its digits, one word: bit 0: a value has no digits; bits 2 + 2
+// half + kc: that block has lowest digits; bits 8 + 8 half ..: scale of the half.
+struct TileWord {
+  unsigned w;
+  __device__ inline bool bad() const { return w & 1; }
+  __device__ inline unsigned lowest(int half) const { return w >> (2 + 2 * half) & 3; }
+  __device__ inline int scale(int half) const { return w >> (8 + 8 * half) & 0xff; }
+};
+
+// Digit planes of every key, laid out as the row pass wants them in the LDS: per unit, per 16 keys (past the prompt the last
+// one again, up to a whole tile of 32) a block [plane][kc][lane = 16 g + row] of 16 digits.  One scale per 16 keys.
+// Lowest planes that are empty are not written (nothing reads them).  Bound by memory.
+// fill: words of the decode step's exchange array to be emptied on the way, which saves a launch.
+template <int D>
+__global__ __launch_bounds__(128) void key_digits_kernel(const __half *__restrict__ K, unsigned tiles, int P,
+                                                         unsigned char *__restrict__ digits, unsigned *__restrict__ words,
+                                                         unsigned *__restrict__ fill, size_t fill_count)
+{
+  constexpr int KC = D / 64;
+  __shared__ unsigned s_word[2];
+  for (size_t i = (size_t)blockIdx.x * 128 + threadIdx.x; i < fill_count; i += (size_t)gridDim.x * 128) fill[i] = kMlpEmpty;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), l = threadIdx.x % 64, g = l / 16, c = l % 16;
+  const unsigned u = blockIdx.x / tiles, t = blockIdx.x % tiles;
+  const int row = (int)t * kRowKeys + 16 * wave + c;
+  ScaledDigits<D> kd;
+  const bool bad = __any(!kd.template load<true>(K + ((size_t)u * P + (row < P ? row : P - 1)) * D, g));
+  const unsigned lowest = kd.lowest();
+  unsigned char *dst = digits + ((size_t)blockIdx.x * 2 + wave) * RowTile<D>::kHalfBytes + l * 16;
+#pragma unroll
+  for (int p = 0; p < 4; ++p)
+#pragma unroll
+    for (int kc = 0; kc < KC; ++kc)
+      if (p > 0 || (lowest >> kc & 1)) *reinterpret_cast<v4i *>(dst + (p * KC + kc) * 1024) = kd.d[kc][p];
+  if (l == 0) s_word[wave] = (bad ? 1u : 0u) | lowest << (2 + 2 * wave) | (unsigned)kd.scale << (8 + 8 * wave);
+  __syncthreads();
+  if (threadIdx.x == 0) words[blockIdx.x] = s_word[0] | s_word[1];
+}
 
 // OUT: attention outputs are wanted too
 template <int D, bool OUT>
-__global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void rows_f16_kernel(
+__global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per_eu(3, 3))) void rows_f16_kernel(
     const __half *__restrict__ Q, const __half *__restrict__ K, const __half *__restrict__ V, unsigned U, int G, int P,
+    const unsigned char *__restrict__ digits, const unsigned *__restrict__ words,
     double *__restrict__ lse, __half *__restrict__ out, unsigned *__restrict__ zero0, unsigned *__restrict__ zero1)
 {
   // U counts query rows here: unit u's G query heads are rows u G .. u G + G - 1 of Q, out and
   // lse, and attend over unit u's keys and values
   using Tile = RowTile<D>;
   constexpr int W = kPrefillWaves, KC = D / 64, DB = D / 16, BQ = 16 * W;
-  constexpr int EPT = kRowKeys * D / (64 * W);            // consecutive key elements a thread splits: 8 or 16
-  constexpr int VK = EPT / 2;                             // value rows a thread takes two columns of
-  __shared__ __attribute__((aligned(16))) unsigned char s_key[2][Tile::kKeyBytes], s_val[3][Tile::kValBytes];
-  __shared__ int s_bad[3];                                // last tile of this key buffer that lacks digits; [2]: any other
+  __shared__ __attribute__((aligned(16))) unsigned char s_key[2][Tile::kKeyBytes], s_val[2][Tile::kValBytes];
+  __shared__ __attribute__((aligned(64))) unsigned char s_zero[64];
   const int ngrp = (P + BQ - 1) / BQ;
   const PrefillBlock pb = prefill_block(blockIdx.x, ngrp);
   if (pb.u >= U) return;                                  // uniform over the workgroup
@@ -82,131 +136,127 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
   const size_t u = pb.u, ukv = u / (unsigned)G;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64, g = l / 16, c = l % 16;
   const __half *Qu = Q + u * (size_t)P * D, *Ku = K + ukv * (size_t)P * D, *Vu = V + ukv * (size_t)P * D;
+  const int tiles = (P + kRowKeys - 1) / kRowKeys;
+  const unsigned char *Du = digits + ukv * (size_t)tiles * Tile::kKeyBytes;
+  const unsigned *wu = words + ukv * (size_t)tiles;
   const int q0 = grp * BQ + wave * 16;                    // the wave's first query
   const int qi = q0 + c, qrow = qi < P ? qi : P - 1;
   const int kt_last = ((grp * BQ + BQ < P ? grp * BQ + BQ : P) - 1) / kRowKeys;   // the workgroup's last tile
   const int kt_wave = q0 < P ? q0 / kRowKeys : -1;        // the wave's last tile; none
   const double cs = kLog2E / sqrt((double)D);             // q . k to base-2 units
 
-  // this thread's share of a tile: EPT consecutive elements of key row kr, and columns vd, vd + 1 of VK
-  // value rows, which lie in one lane group's slots
-  const int kr = tid / (D / EPT), ke = tid % (D / EPT) * EPT;
-  const int k_dst = Tile::key_at(kr / 16, 0, ke / 64, ke % 64 / 16, kr % 16) + ke % 16;
-  const int vd = 2 * (tid % (D / 2)), vs = VK * (tid / (D / 2));               // first of the VK slots
-  const int v_dst0 = Tile::val_at(vd % DB, vd / DB, vs / 8) + vs % 8 * 2, v_dst1 = Tile::val_at((vd + 1) % DB, (vd + 1) / DB, vs / 8) + vs % 8 * 2;
-  const int k_src = (kr * D + ke) * 2, v_src = ((16 * (vs / 4 % 2) + 4 * (vs / 8) + vs % 4) * D + vd) * 2;
-  unsigned kraw[EPT / 2], vraw[VK];
-  // Rows past the prompt read as zeros: a buffer load is in range where its vector offset lies below num_records less
-  // the scalar offset, so the latter never passes num_records (the row steps of a short last tile would).
-  auto fetch = [&](int kt) __attribute__((always_inline)) {
-    const int r0 = kt * kRowKeys, bytes = (P - r0 < kRowKeys ? P - r0 : kRowKeys) * D * 2;
-    const __amdgpu_buffer_rsrc_t rk =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<__half *>(Ku + (size_t)r0 * D), 0, bytes, 0x00020000);
+  // Tile kt into the LDS: the workgroup's waves bring 1 KiB pieces, key digits as they lie, value rows with their 16-byte
+  // chunks permuted within a row (val_swizzle) so that the transposing reads meet no bank twice.  Rows past the
+  // prompt repeat the last one: they come after every query.
+  constexpr int RB = 2 * D, kRowsPer = 1024 / RB, CH = RB / 16;       // bytes, rows and chunks of a value piece
+  auto load_tile = [&](int kt, unsigned char *key, unsigned char *val) __attribute__((always_inline)) {
+    int lane = l;
+    asm("" : "+v"(lane));                                 // (as in add_values)
+    const int vr = lane / CH, vch = lane % CH;            // row and chunk within the piece
 #pragma unroll
-    for (int i = 0; i < EPT / 8; ++i) {
-      const v4u x = __builtin_amdgcn_raw_buffer_load_b128(rk, k_src, 16 * i, 0);
-      kraw[4 * i] = x.x; kraw[4 * i + 1] = x.y; kraw[4 * i + 2] = x.z; kraw[4 * i + 3] = x.w;
+    for (int i = 0; i < Tile::kKeyBytes / 1024 / W; ++i) {
+      const int piece = (wave * (Tile::kKeyBytes / 1024 / W) + i) * 1024;
+      lds_load_kib(Du + (size_t)kt * Tile::kKeyBytes + piece, 1024, lane * 16, key + piece);
     }
     if constexpr (OUT) {
-      const __amdgpu_buffer_rsrc_t rv =
-          __builtin_amdgcn_make_buffer_rsrc(const_cast<__half *>(Vu + (size_t)r0 * D), 0, bytes, 0x00020000);
+      const int r0 = kt * kRowKeys, last = P - 1 - r0;    // last row of the tile that exists
 #pragma unroll
-      for (int i = 0; i < VK; ++i)                        // slots vs + 4 ..: the tile's second half
-        vraw[i] = __builtin_amdgcn_raw_buffer_load_b32(rv, v_src, min((i / 4 * 16 + i % 4) * D * 2, bytes), 0);
-    }
-  };
-  auto stage = [&](int kt, unsigned char *val) __attribute__((always_inline)) {
-    unsigned char *buf = s_key[kt & 1];
-    unsigned plane[4][EPT / 4];
-#pragma unroll
-    for (int i = 0; i < EPT / 4; ++i) {
-      unsigned p[4];
-      digits_of4(kraw[2 * i], kraw[2 * i + 1], p);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) plane[q][i] = p[q];
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      unsigned char *dst = buf + k_dst + q * Tile::kPlaneBytes;
-      if constexpr (EPT == 16) *reinterpret_cast<uint4 *>(dst) = uint4{plane[q][0], plane[q][1], plane[q][2], plane[q][3]};
-      else *reinterpret_cast<uint2 *>(dst) = uint2{plane[q][0], plane[q][1]};
-    }
-    s_bad[without_digits(kraw) ? kt & 1 : 2] = kt;        // (a branch here would end the block the products stand in)
-    if constexpr (OUT) {
-      unsigned lo[VK / 2], hi[VK / 2];                    // columns vd and vd + 1 of the thread's keys
-#pragma unroll
-      for (int i = 0; i < VK / 2; ++i) {
-        lo[i] = __builtin_amdgcn_perm(vraw[2 * i + 1], vraw[2 * i], 0x05040100u);
-        hi[i] = __builtin_amdgcn_perm(vraw[2 * i + 1], vraw[2 * i], 0x07060302u);
-      }
-      if constexpr (VK == 8) {
-        *reinterpret_cast<uint4 *>(val + v_dst0) = uint4{lo[0], lo[1], lo[2], lo[3]};
-        *reinterpret_cast<uint4 *>(val + v_dst1) = uint4{hi[0], hi[1], hi[2], hi[3]};
-      } else {
-        *reinterpret_cast<uint2 *>(val + v_dst0) = uint2{lo[0], lo[1]};
-        *reinterpret_cast<uint2 *>(val + v_dst1) = uint2{hi[0], hi[1]};
+      for (int i = 0; i < Tile::kValBytes / 1024 / W; ++i) {
+        const int piece = wave * (Tile::kValBytes / 1024 / W) + i, row = piece * kRowsPer + vr;
+        const int from = (row < last ? row : last) * RB + (vch ^ Tile::val_swizzle(row)) * 16;
+        lds_load_kib(Vu + (size_t)r0 * D, Tile::kValBytes, from, val + piece * 1024);
       }
     }
   };
 
-  RowDigits<D> qd;
-  const bool qbad = __any(!qd.load(Qu + (size_t)qrow * D, g));
-  // m: an integer below the query's maximum when it was last moved; lim: by how much a score may pass it, -inf
-  // before the first one
-  double m = 0.0, lim = -__builtin_inf(), L = 0.0;
+  unsigned char *v_cur = s_val[0], *v_next = s_val[1];
+  unsigned char *k_cur = s_key[0], *k_next = s_key[1];
+  load_tile(0, k_cur, v_cur);
+  TileWord word = {wu[0]};
+  ScaledDigits<D> qd;
+  const bool qbad = __any(!qd.template load<false>(Qu + (size_t)qrow * D, g));
+  const unsigned qlow = qd.lowest();
+  const double cq = __builtin_ldexp(cs * kDotUnit, -qd.scale);         // a product of digit planes to base-2 units, but for the keys' scale
+  // m: an integer below the query's maximum when it was last moved, which a score may pass by kSlack
+  double m = 0.0, L = 0.0;
   v4f O[DB];
 #pragma unroll
   for (int b = 0; b < DB; ++b) O[b] = v4f{0.f, 0.f, 0.f, 0.f};
-  // the tile whose weights are still to come: base-2 scores less m of its two halves
-  double y[2][4];
-  auto no_weight = [&](double (&yy)[4]) __attribute__((always_inline)) {
+  // base-2 scores less m of the keys of a half: nine products of the three upper planes, and those with the lowest
+  // planes where there are any
+  auto scores = [&](const unsigned char *key, const TileWord word, int half, double *yy) __attribute__((always_inline)) {
+    const unsigned char *at = key + half * Tile::kHalfBytes + l * 16;
+    auto plane = [&](int kc, int p) __attribute__((always_inline)) { return *reinterpret_cast<const v4i *>(at + (p * KC + kc) * 1024); };
+    v4i s[7];
 #pragma unroll
-    for (int w = 0; w < 4; ++w) yy[w] = kNoWeight;
+    for (int i = 2; i < 7; ++i) s[i] = v4i{0, 0, 0, 0};
+#pragma unroll
+    for (int kc = 0; kc < KC; ++kc) {
+      v4i k[4];
+#pragma unroll
+      for (int pa = 1; pa < 4; ++pa) k[pa] = plane(kc, pa);
+#pragma unroll
+      for (int pb = 1; pb < 4; ++pb)
+#pragma unroll
+        for (int pa = 1; pa < 4; ++pa) s[pa + pb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(k[pa], qd.d[kc][pb], s[pa + pb], 0, 0, 0);
+    }
+    const unsigned klow = word.lowest(half);
+    const int e = -word.scale(half);
+    const double c40 = __builtin_ldexp(cq, e + 40), c32 = __builtin_ldexp(cq, e + 32), c16 = __builtin_ldexp(cq, e + 16);
+#pragma unroll
+    for (int w = 0; w < 4; ++w) yy[w] = -m;
+    if (klow | qlow) {                                    // wave-uniform
+      s[0] = s[1] = v4i{0, 0, 0, 0};
+#pragma unroll
+      for (int kc = 0; kc < KC; ++kc) {
+        if (klow >> kc & 1) {
+          const v4i k0 = plane(kc, 0);
+#pragma unroll
+          for (int pb = 0; pb < 4; ++pb) s[pb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(k0, qd.d[kc][pb], s[pb], 0, 0, 0);
+        }
+        if (qlow >> kc & 1) {
+#pragma unroll
+          for (int pa = 1; pa < 4; ++pa) s[pa] = __builtin_amdgcn_mfma_i32_16x16x64_i8(plane(kc, pa), qd.d[kc][0], s[pa], 0, 0, 0);
+        }
+      }
+      const double c0 = __builtin_ldexp(cq, e);
+      const v4i p10 = (s[1] << 8) + s[0];
+#pragma unroll
+      for (int w = 0; w < 4; ++w) yy[w] = fma((double)p10[w], c0, -m);
+    }
+    const v4i p65 = (s[6] << 8) + s[5], p32 = (s[3] << 8) + s[2];
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+      yy[w] = fma((double)p65[w], c40, fma((double)s[4][w], c32, fma((double)p32[w], c16, yy[w])));
   };
-  no_weight(y[0]);
-  no_weight(y[1]);
-
-  auto products = [&](int kt, int half, v4i (&s)[7]) __attribute__((always_inline)) {
-    const unsigned char *buf = s_key[kt & 1];
-#pragma unroll
-    for (int i = 0; i < 7; ++i) s[i] = v4i{0, 0, 0, 0};
-#pragma unroll
-    for (int kc = 0; kc < KC; ++kc)
-#pragma unroll
-      for (int pa = 0; pa < 4; ++pa)
-        dot_planes(*reinterpret_cast<const v4i *>(buf + Tile::key_at(half, pa, kc, g, c)), qd.d[kc], pa, s);
-  };
-  auto raise_max = [&](double (&y)[2][4]) __attribute__((always_inline)) {
-    double top = fmax(fmax(fmax(y[0][0], y[0][1]), fmax(y[0][2], y[0][3])), fmax(fmax(y[1][0], y[1][1]), fmax(y[1][2], y[1][3])));
-    if (__any(top > lim)) {
+  // High word of the limit, least before the first maximum: as signed integers the high words order what matters, everything
+  // below zero lies below kSlack.
+  int lim_hi = INT_MIN;
+  auto raise_max = [&](double (&y)[8]) __attribute__((always_inline)) {
+    double top = fmax(fmax(fmax(y[0], y[1]), fmax(y[2], y[3])), fmax(fmax(y[4], y[5]), fmax(y[6], y[7])));
+    if (__any(lim_hi == INT_MIN || top > kSlack)) {
       top = fmax(top, __shfl_xor(top, 16));
       top = fmax(top, __shfl_xor(top, 32));
       const bool none = top == -__builtin_inf();          // nothing to see yet
-      const double d = none ? 0.0 : lim == -__builtin_inf() ? ceil(top) - 1.0 : fmax(0.0, ceil(top) - 1.0);
+      const double d = none ? 0.0 : lim_hi == INT_MIN ? ceil(top) - 1.0 : fmax(0.0, ceil(top) - 1.0);
       const int k = d <= 0.0 ? 0 : d < 2000.0 ? -(int)d : -2000;   // the rescaling is a power of two
       const float af = __builtin_ldexpf(1.f, k);
       L = __builtin_ldexp(L, k);
 #pragma unroll
       for (int b = 0; b < DB; ++b) O[b] *= af;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        y[0][w] -= d;
-        y[1][w] -= d;
-      }
+      for (int w = 0; w < 8; ++w) y[w] -= d;
       m += d;
-      lim = none ? lim : kSlack;
+      lim_hi = none ? lim_hi : __double2hiint(kSlack);
     }
-  };
-  auto scores = [&](const v4i (&s)[7], double (&yy)[4]) __attribute__((always_inline)) {
-    const DotParts p = dot_join(s);
-#pragma unroll
-    for (int w = 0; w < 4; ++w) yy[w] = dot_affine(p, w, cs, -m);
   };
   // the weights of half `half` out of its scores, into hi + lo pairs and L
   v8h ph, pl;
-  auto weigh = [&](const double (&yy)[4], int half) __attribute__((always_inline)) {
+  float one = 1.f;
+  asm("" : "+s"(one));                                    // unknown to the compiler, which else makes a subtraction of the fma
+  auto weigh = [&](const double *yy, int half) __attribute__((always_inline)) {
     double e[4];
-    exp2_f64(yy, e);
+    exp2_f64<4>({yy[0], yy[1], yy[2], yy[3]}, e);
     float ef[4];
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
@@ -217,133 +267,97 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
     }
     L += (e[0] + e[1]) + (e[2] + e[3]);
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const _Float16 hi = (_Float16)ef[w];
-      ph[4 * half + w] = hi;
-      pl[4 * half + w] = (_Float16)(ef[w] - (float)hi);
+    for (int w = 0; w < 4; w += 2) {
+      unsigned p = __builtin_bit_cast(unsigned, v2h{(_Float16)ef[w], (_Float16)ef[w + 1]});
+      asm("" : "+v"(p));                                  // converted once, as a pair
+      const v2h hi = __builtin_bit_cast(v2h, p);
+      // x - hi is exact in fp32; as fused multiply-adds that take the halves as they are
+      const v2h lo = {(_Float16)__builtin_fmaf(-(float)hi.x, one, ef[w]), (_Float16)__builtin_fmaf(-(float)hi.y, one, ef[w + 1])};
+      ph[4 * half + w] = hi.x;
+      ph[4 * half + w + 1] = hi.y;
+      pl[4 * half + w] = lo.x;
+      pl[4 * half + w + 1] = lo.y;
     }
   };
-  // O += V^T p; only0: the tile's second half lies after all of the wave's queries
+  // O += V^T p; only0: the tile's second half lies after all of the wave's queries.  A lane's four rows of a 16-lane group
+  // and the piece of four columns it points at: the transposing read hands lane i column i of the group's four rows.
+  // A-operand row i of block b is value column 4 DB (i / 4) + 4 b + i % 4, so that a lane's outputs are one run.
+  const int v_at = (4 * g + c / 4) * RB + (((DB / 2) * (c % 4)) ^ Tile::val_swizzle(4 * g + c / 4)) * 16;
   auto add_values = [&](const unsigned char *val, bool only0) __attribute__((always_inline)) {
     if constexpr (!OUT) return;
+    unsigned at0 = lds_offset(val) + v_at, at1 = only0 ? lds_offset(s_zero) : at0 + 16 * RB;   // (values without a weight may be infinite)
+    asm("" : "+v"(at0), "+v"(at1));                       // else the addresses of all blocks stay in registers between the tiles
 #pragma unroll
     for (int b = 0; b < DB; ++b) {
-      uint4 raw = *reinterpret_cast<const uint4 *>(val + Tile::val_at(b, c, g));
-      if (only0) raw.z = raw.w = 0;                       // whatever is there, infinities too, has no part in it
-      const v8h a = __builtin_bit_cast(v8h, raw);
+      const v4s h0 = lds_read_transposed((at0 ^ (b / 2 * 16)) + b % 2 * 8), h1 = lds_read_transposed((at1 ^ (b / 2 * 16)) + b % 2 * 8);
+      const v8h a = __builtin_bit_cast(v8h, __builtin_shufflevector(h0, h1, 0, 1, 2, 3, 4, 5, 6, 7));
       O[b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, ph, O[b], 0, 0, 0);
       O[b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, pl, O[b], 0, 0, 0);
     }
   };
-  if (tid < 2) s_bad[tid] = -1;
+  if (tid < 16) reinterpret_cast<unsigned *>(s_zero)[tid] = 0u;        // (the first tile's barrier stands before its readers)
   if (tid == 0 && pb.grp == 0 && u == ukv * (size_t)G) zero0[ukv] = zero1[ukv] = 0u;
-  if constexpr (OUT)                                      // the values of the tile before the first: weighed 0
-    for (int i = tid; i < Tile::kValBytes / 4; i += 64 * W) reinterpret_cast<unsigned *>(s_val[2])[i] = 0u;
-  fetch(0);
-  __syncthreads();
-  unsigned char *v_prev = s_val[2], *v_cur = s_val[0], *v_next = s_val[1];
-  stage(0, v_cur);
-  fetch(kt_last > 0 ? 1 : 0);
   for (int kt = 0; kt <= kt_last; ++kt) {
-    // tile kt is complete; nobody still reads the buffers that tile kt + 1 will go into
+    // tile kt has arrived for all waves; nobody still reads the buffers that tile kt + 1 will go into
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
     const int j0 = kt * kRowKeys;
-    v4i s[7];
-    const bool slow = qbad || __builtin_amdgcn_readfirstlane(s_bad[kt & 1]) == kt;
-    if (kt < kt_wave && !slow) {                          // wave-uniform: every key before every query
-      double yn[2][4];
-      // one matrix instruction, then the vector instructions it runs beside
-      auto interleave = [](auto count) __attribute__((always_inline)) {
+    const TileWord here = word;
+    const bool slow = qbad || here.bad();
+    if (kt < kt_last) {
+      load_tile(kt + 1, k_next, v_next);
+      word.w = wu[kt + 1];
+    }
+    if (kt <= kt_wave) {                                  // wave-uniform, like all that follows
+      const bool diag = kt == kt_wave;                    // some keys come after some queries,
+      const bool only0 = j0 + 16 > q0 + 15;               // the second half after all of them
+      double y[8];
+      if (!slow) {
+        scores(k_cur, here, 0, &y[0]);
+        if (!only0) scores(k_cur, here, 1, &y[4]);        // (else masked below)
+      } else {
+        v4d d[2];
+        dot_tiles_f64<D, 2>([&](int i) { return Ku + (size_t)(j0 + i < P ? j0 + i : P - 1) * D; }, Qu + (size_t)qrow * D, g, c, d);
 #pragma unroll
-        for (int i = 0; i < count.value; ++i) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);  // (4: 7 % slower)
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      };
-      products(kt, 0, s);
-      weigh(y[0], 0);                                     // the tile before
-      weigh(y[1], 1);
-      interleave(std::integral_constant<int, 16 * KC>{});
-      scores(s, yn[0]);
-      products(kt, 1, s);
-      add_values(v_prev, false);
-      stage(kt + 1, v_next);
-      fetch(kt + 2 <= kt_last ? kt + 2 : kt_last);
-      interleave(std::integral_constant<int, (OUT ? 2 * DB : 0) + 16 * KC>{});
-      scores(s, yn[1]);
-      raise_max(yn);
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        y[0][w] = yn[0][w];
-        y[1][w] = yn[1][w];
+        for (int w = 0; w < 8; ++w) y[w] = fma(d[w / 4][w % 4], cs, -m);
       }
-    } else {
-      if (kt <= kt_wave) {
-        if (kt > 0) {                                     // the tile before
-          weigh(y[0], 0);
-          weigh(y[1], 1);
-          add_values(v_prev, false);
-        }
-        const bool only0 = j0 + 16 > q0 + 15;             // the second half lies after all of the wave's queries
-        if (slow) {
-          v4d d[2];
-          dot_tiles_f64<D, 2>([&](int i) { return Ku + (size_t)(j0 + i < P ? j0 + i : P - 1) * D; }, Qu + (size_t)qrow * D, g, c, d);
+      if (diag) {
 #pragma unroll
-          for (int w = 0; w < 4; ++w) {
-            y[0][w] = fma(d[0][w], cs, -m);
-            y[1][w] = fma(d[1][w], cs, -m);
-          }
-        } else {
-          products(kt, 0, s);
-          scores(s, y[0]);
-          if (!only0) {                                   // (else masked below)
-            products(kt, 1, s);
-            scores(s, y[1]);
-          }
-        }
-        if (kt == kt_wave) {
+        for (int w = 0; w < 8; ++w) y[w] = j0 + 16 * (w / 4) + 4 * g + w % 4 <= qi ? y[w] : -__builtin_inf();
+      }
+      int top = INT_MIN;
 #pragma unroll
-          for (int w = 0; w < 4; ++w) {
-            y[0][w] = (j0 + 4 * g + w <= qi) ? y[0][w] : -__builtin_inf();
-            y[1][w] = (j0 + 16 + 4 * g + w <= qi) ? y[1][w] : -__builtin_inf();
-          }
-        }
+      for (int w = 0; w < 8; ++w) top = max(top, __double2hiint(y[w]));
+      if (diag || slow || __any(top >= lim_hi)) {
         raise_max(y);
         // no weight for keys after the query, scores of -inf and what is not a number
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          y[0][w] = y[0][w] > kNoWeight ? y[0][w] : kNoWeight;
-          y[1][w] = y[1][w] > kNoWeight ? y[1][w] : kNoWeight;
-        }
-        if (kt == kt_wave) {                              // the wave's last tile
-          weigh(y[0], 0);
-          weigh(y[1], 1);
-          add_values(v_cur, only0);
-        }
+        for (int w = 0; w < 8; ++w) y[w] = y[w] > kNoWeight ? y[w] : kNoWeight;
       }
-      if (kt < kt_last) {
-        stage(kt + 1, v_next);
-        fetch(kt + 2 <= kt_last ? kt + 2 : kt_last);
-      }
+      weigh(&y[0], 0);
+      __builtin_amdgcn_sched_barrier(0);
+      weigh(&y[4], 1);
+      __builtin_amdgcn_sched_barrier(0);
+      add_values(v_cur, only0);
     }
-    unsigned char *t = v_prev;
-    v_prev = v_cur; v_cur = v_next; v_next = t;
+    unsigned char *t = v_cur;
+    v_cur = v_next; v_next = t;
+    t = k_cur; k_cur = k_next; k_next = t;
   }
   L += __shfl_xor(L, 16);
   L += __shfl_xor(L, 32);
   if (qi < P) {
     if (g == 0) lse[u * (size_t)P + qi] = fma(m, kLn2, log(L));
     if constexpr (OUT) {
-      // O[b][w] is output element DB (4 g + w) + b: the lane's elements are one run of 4 DB halves
+      // O[b][w] is output element 4 (DB g + b) + w: the lane's elements are one run of 4 DB halves
       const float inv = (float)(1.0 / L);
       __half run[4 * DB];
 #pragma unroll
       for (int w = 0; w < 4; ++w)
 #pragma unroll
-        for (int b = 0; b < DB; ++b) run[DB * w + b] = __float2half_rn(O[b][w] * inv);
+        for (int b = 0; b < DB; ++b) run[4 * b + w] = __float2half_rn(O[b][w] * inv);
       __half *orow = out + (u * (size_t)P + qi) * D + 4 * DB * g;
 #pragma unroll
       for (int i = 0; i < 4 * DB / 8; ++i) reinterpret_cast<uint4 *>(orow)[i] = reinterpret_cast<const uint4 *>(run)[i];
@@ -352,24 +366,36 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
 }
 
 template <int D>
-static hipError_t launch_rows_t(const void *Q, const void *K, const void *V, unsigned UG, int G, int P, double *lse,
-                                void *out, unsigned *zero0, unsigned *zero1, hipStream_t st)
+static hipError_t launch_rows_t(const RowArgs &a, hipStream_t st)
 {
-  const unsigned ngrp = (unsigned)((P + 16 * kPrefillWaves - 1) / (16 * kPrefillWaves));
-  if (out != nullptr)
-    rows_f16_kernel<D, true><<<prefill_grid(UG, ngrp), 64 * kPrefillWaves, 0, st>>>(
-        (const __half *)Q, (const __half *)K, (const __half *)V, UG, G, P, lse, (__half *)out, zero0, zero1);
-  else
-    rows_f16_kernel<D, false><<<prefill_grid(UG, ngrp), 64 * kPrefillWaves, 0, st>>>(
-        (const __half *)Q, (const __half *)K, (const __half *)V, UG, G, P, lse, nullptr, zero0, zero1);
-  return hipGetLastError();
+  const unsigned tiles = (unsigned)((a.P + kRowKeys - 1) / kRowKeys);
+  const unsigned ngrp = (unsigned)((a.P + 16 * kPrefillWaves - 1) / (16 * kPrefillWaves));
+  // as many units at a time as the digits' part of the workspace holds, in shares of about the same size
+  const size_t U = a.U, most = digit_units(U, a.P, D), shares = (U + most - 1) / most;
+  size_t n = (U + shares - 1) / shares;
+  if (most >= kXcds) n = (n + kXcds - 1) / kXcds * kXcds;
+  unsigned char *digits = (unsigned char *)a.digits;
+  unsigned *words = (unsigned *)(digits + most * tiles * RowTile<D>::kKeyBytes);
+  for (size_t u = 0; u < U; u += n) {
+    const unsigned nu = (unsigned)(U - u < n ? U - u : n);
+    const size_t kv = u * a.P * D, q = kv * a.G, rows = u * a.G * a.P;
+    const __half *K = (const __half *)a.K + kv;
+    key_digits_kernel<D><<<nu * tiles, 128, 0, st>>>(K, tiles, a.P, digits, words, a.fill, u == 0 ? a.fill_count : 0);
+    const unsigned grid = prefill_grid(nu * a.G, ngrp);
+#define LESSDEC_ROWS(OUT, O) rows_f16_kernel<D, OUT><<<grid, 64 * kPrefillWaves, 0, st>>>(                              \
+      (const __half *)a.Q + q, K, (const __half *)a.V + kv, nu * a.G, a.G, a.P, digits, words, a.lse + rows, O, a.zero0 + u, a.zero1 + u)
+    if (a.out != nullptr) LESSDEC_ROWS(true, (__half *)a.out + q);
+    else LESSDEC_ROWS(false, nullptr);
+#undef LESSDEC_ROWS
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
-hipError_t launch_rows_f16(const void *Q, const void *K, const void *V, unsigned UG, int G, int P, int D, double *lse,
-                           void *out, unsigned *zero0, unsigned *zero1, hipStream_t st)
+hipError_t launch_rows_f16(const RowArgs &a, int D, hipStream_t st)
 {
-  return D == 128 ? launch_rows_t<128>(Q, K, V, UG, G, P, lse, out, zero0, zero1, st)
-                  : launch_rows_t<64>(Q, K, V, UG, G, P, lse, out, zero0, zero1, st);
+  return D == 128 ? launch_rows_t<128>(a, st) : launch_rows_t<64>(a, st);
 }
 
 // -------------------------------------------------------------------------------------
