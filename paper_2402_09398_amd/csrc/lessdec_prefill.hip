@@ -14,6 +14,7 @@
 
 #include "lessdec_common.h"
 #include "lessdec_internal.h"
+#include "lessdec_lds.h"
 #include "lessdec_prefill.h"
 
 namespace lessdec {
@@ -730,26 +731,29 @@ __global__ __launch_bounds__(64 * kPrefillWaves) void prefill_colpass_kernel(
 // floats >= 0, zeroed before), whose product bounds every score and with it the rounding error of these
 // sums; a wave takes the query rows at its keys' positions.
 // The four waves of a workgroup take 16 KT consecutive keys each (in registers) and sweep the same queries, 64
-// at a time through the LDS (two buffers, the next chunk requested before the barrier), so that a query row
-// crosses the L2 once per workgroup: with a row per wave straight from the L2 the sweep waited for it,
-// 950 us for 2048 units x 1024 tokens and 2330 us for 128 x 8192; 713 and 1318 now, the next query
-// tile's products beside this one's exponentials (890 and 1860 without that).
+// at a time through the LDS, so that a query row crosses the L2 once per workgroup; the next query tile's
+// products stand beside this one's exponentials.  The chunks go straight into the LDS, two ahead of their use: with one ahead,
+// through registers, the sweep waited for memory wherever a chunk's work was shorter than a round trip, and the
+// registers held it to two waves a SIMD (three now).  717 -> 582 us for 2048 units x 1024 tokens, 1334 -> 1270 for 128 x
+// 8192, 601 -> 511 for 128 x 4 heads x 2048.  Bound by issue (an instruction in 83 % of the cycles: exponentials take
+// two slots, a matrix instruction blocks about two) and by the clock that the card lowers meanwhile (2.1 GHz).
 // -------------------------------------------------------------------------------------
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 constexpr int kApproxQueries = 64; // queries per chunk
 template <int D, int KT>
-__global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void prefill_colapprox_kernel(
+__global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per_eu(3, 3))) void prefill_colapprox_kernel(
     const __half *__restrict__ Q, const __half *__restrict__ K, unsigned U, int P,
     const double *__restrict__ lse, int G, float *__restrict__ approx, unsigned *__restrict__ qmax,
     unsigned *__restrict__ kmax)
 {
-  constexpr int KS = D / 32, QC = kApproxQueries, PIECES = D / 8;       // 16-byte pieces per row
-  constexpr int PER = QC * PIECES / (64 * kPrefillWaves);               // pieces per thread and chunk: 4 or 2
+  constexpr int KS = D / 32, QC = kApproxQueries, RB = 2 * D, CH = D / 8;    // bytes and 16-byte chunks of a row
+  constexpr int LOADS = QC * RB / 1024 / kPrefillWaves + 1;             // a wave's loads per chunk of queries
   constexpr double kLog2e = 1.44269504088896340736;
-  // a query tile's piece e of row r, turned so that a wave reads one run and writes spread over the banks
-  __shared__ __attribute__((aligned(16))) unsigned char s_q[2][QC / 16][PIECES][16][16];
-  __shared__ float s_l[2][QC];
+  // rows as they are, their 16-byte chunks turned by the row: 16 rows' reads of the same piece meet every bank once
+  __shared__ __attribute__((aligned(16))) unsigned char s_q[3][QC * RB];
+  __shared__ __attribute__((aligned(16))) double s_l[3][QC];
+  auto turned = [](unsigned row, unsigned chunk) { return chunk ^ (D == 128 ? row % 16 : row / 2 % 8); };
   const int nch = (P + QC - 1) / QC, nkb = (P + 16 * KT - 1) / (16 * KT);
   const int ngrp = (nkb + kPrefillWaves - 1) / kPrefillWaves;
   const PrefillBlock pb = prefill_block(blockIdx.x, ngrp);
@@ -767,19 +771,27 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
     for (int ks = 0; ks < KS; ++ks)
       ka[t][ks] = *reinterpret_cast<const v8h *>(Ku + (size_t)(kr < P ? kr : P - 1) * D + 32 * ks + 8 * g);
   }
-  // the chunk of step i: head i / per, chunk c0 + i % per
+  // step by step the chunks from that of the workgroup's first key on, head after head
   const int c0 = pb.grp * kPrefillWaves * KT * 16 / QC, per = nch - c0, steps = G * per;
-  v4u raw[PER];
-  float lraw = 0.f;
-  auto fetch = [&](int i) __attribute__((always_inline)) {
-    const int h = i / per, q0 = (c0 + i - h * per) * QC;
-    const __half *Qu = Q + (u * G + h) * (size_t)P * D;
+  int h = 0, q0 = c0 * QC;                                // the chunk to load next
+  auto load = [&](int buf) __attribute__((always_inline)) {
+    const int last = P - 1 - q0;                          // rows past the prompt: the last one
+    const size_t first = (u * G + h) * (size_t)P + q0;
+    unsigned l = tid % 64;
+    asm("" : "+v"(l));                                    // else the addresses stay in registers between the chunks
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int x = tid + 64 * kPrefillWaves * k, row = q0 + x / PIECES;
-      raw[k] = *reinterpret_cast<const v4u *>(Qu + (size_t)(row < P ? row : P - 1) * D + x % PIECES * 8);
+    for (int k = 0; k < LOADS - 1; ++k) {
+      const int piece = wave * (LOADS - 1) + k, row = piece * (1024 / RB) + (int)(l / CH);
+      const int from = (row < last ? row : last) * RB + (int)turned(row, l % CH) * 16;
+      lds_load<16>(Q + first * D, QC * RB, from, s_q[buf] + piece * 1024);
     }
-    if (tid < QC) lraw = (float)(lse[(u * G + h) * (size_t)P + (q0 + tid < P ? q0 + tid : P - 1)] * kLog2e);
+    const int row = wave * (QC / kPrefillWaves) + (int)(l / 2), from = (row < last ? row : last) * 8 + (int)(l % 2) * 4;
+    if (l < 2 * (QC / kPrefillWaves))
+      lds_load<4>(lse + first, QC * 8, from, reinterpret_cast<unsigned char *>(s_l[buf] + wave * (QC / kPrefillWaves)));
+    if ((q0 += QC) >= P) {                                // the next head's first chunk
+      q0 = c0 * QC;
+      ++h;
+    }
   };
   // squared norm of a row that lies over the four lane groups, the largest of the wave's rows into `to`
   auto norm2 = [&](const v8h (&row)[KS]) {
@@ -800,7 +812,8 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
     for (int o = 8; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
     if (l == 0) atomicMax(to, __float_as_uint(mx));
   };
-  fetch(0);
+  load(0);
+  if (steps > 1) load(1);
   float mk = 0.f, mq = 0.f, cs[KT][4];
 #pragma unroll
   for (int t = 0; t < KT; ++t) {
@@ -808,24 +821,18 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
 #pragma unroll
     for (int w = 0; w < 4; ++w) cs[t][w] = 0.f;
   }
-  for (int i = 0; i < steps; ++i) {
-    const int b = i & 1, qc = c0 + i % per;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int x = tid + 64 * kPrefillWaves * k, row = x / PIECES, e = x % PIECES;
-      *reinterpret_cast<v4u *>(s_q[b][row / 16][e][(row ^ e) % 16]) = raw[k];
-    }
-    if (tid < QC) s_l[b][tid] = lraw;
-    fetch(i + 1 < steps ? i + 1 : i);
-    // the chunk is complete, and nobody still reads the buffer that the next one will go into
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+  for (int i = 0, b = 0, qc = c0; i < steps; ++i, b = b < 2 ? b + 1 : 0, qc = qc + 1 < nch ? qc + 1 : c0) {
+    if (i + 1 < steps) lds_arrived<LOADS>(); else lds_arrived<0>();
+    lds_barrier();                                        // the chunk is complete, and nobody still reads the one before it
+    if (i + 2 < steps) load(b ? b - 1 : 2);
     if (j0 >= P || qc * QC + QC - 1 < j0) continue;       // wave-uniform: every query before the wave's keys
     auto query_tile = [&](int qt, v8h (&qa)[KS], float &lq) __attribute__((always_inline)) {
+      int c = l % 16;
+      asm("" : "+v"(c));                                  // (as above)
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) qa[ks] = *reinterpret_cast<const v8h *>(s_q[b][qt][4 * ks + g][(c ^ (4 * ks + g)) % 16]);
-      lq = s_l[b][16 * qt + c];
+      for (int ks = 0; ks < KS; ++ks)
+        qa[ks] = *reinterpret_cast<const v8h *>(s_q[b] + (16 * qt + c) * RB + turned(c, 4 * ks + g) * 16);
+      lq = (float)(s_l[b][16 * qt + c] * kLog2e);
     };
     auto products = [&](const v8h (&qa)[KS], v4f (&acc)[KT]) __attribute__((always_inline)) {
 #pragma unroll

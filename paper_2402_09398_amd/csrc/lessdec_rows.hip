@@ -4,6 +4,7 @@
 
 #include "lessdec_digits.h"
 #include "lessdec_internal.h"
+#include "lessdec_lds.h"
 #include "lessdec_prefill.h"
 
 namespace lessdec {
@@ -57,21 +58,6 @@ struct RowTile {
 };
 typedef short v4s __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4s lds_v4s;
-typedef __attribute__((address_space(3))) unsigned char lds_bytes;
-__device__ inline unsigned lds_offset(const unsigned char *p) { return (unsigned)(unsigned long long)(lds_bytes *)p; }
-// 1 KiB from memory into the LDS, 16 bytes a lane: lane l's from base + offset (of the lane), to `to` + 16 l.  base and to are
-// the same for the whole wave.  Written as asm because the compiler, which cannot tell the tile buffers apart,
-// would wait for the whole transfer before the next LDS read; nothing is returned in registers, and the
-// readers stand behind a wait for the counter and a barrier of their own.
-__device__ inline void lds_load_kib(const void *base, unsigned bytes, int offset, unsigned char *to)
-{
-  const unsigned long long b = reinterpret_cast<unsigned long long>(base);
-  const v4u rsrc = {(unsigned)b, (unsigned)(b >> 32) & 0xffffu, bytes, 0x00020000u};
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-               :
-               : "s"(lds_offset(to)), "v"(offset), "s"(rsrc)
-               : "memory");
-}
 // The 16-lane groups' transposing read: lane i of a group points at 4 halves, element i % 4 .. of row i / 4 of the group's
 // four rows by pieces of 4 columns, and gets column i of the four rows.
 __device__ inline v4s lds_read_transposed(unsigned offset)
@@ -156,7 +142,7 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
 #pragma unroll
     for (int i = 0; i < Tile::kKeyBytes / 1024 / W; ++i) {
       const int piece = (wave * (Tile::kKeyBytes / 1024 / W) + i) * 1024;
-      lds_load_kib(Du + (size_t)kt * Tile::kKeyBytes + piece, 1024, lane * 16, key + piece);
+      lds_load<16>(Du + (size_t)kt * Tile::kKeyBytes + piece, 1024, lane * 16, key + piece);
     }
     if constexpr (OUT) {
       const int r0 = kt * kRowKeys, last = P - 1 - r0;    // last row of the tile that exists
@@ -164,7 +150,7 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
       for (int i = 0; i < Tile::kValBytes / 1024 / W; ++i) {
         const int piece = wave * (Tile::kValBytes / 1024 / W) + i, row = piece * kRowsPer + vr;
         const int from = (row < last ? row : last) * RB + (vch ^ Tile::val_swizzle(row)) * 16;
-        lds_load_kib(Vu + (size_t)r0 * D, Tile::kValBytes, from, val + piece * 1024);
+        lds_load<16>(Vu + (size_t)r0 * D, Tile::kValBytes, from, val + piece * 1024);
       }
     }
   };
@@ -299,10 +285,8 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
   if (tid == 0 && pb.grp == 0 && u == ukv * (size_t)G) zero0[ukv] = zero1[ukv] = 0u;
   for (int kt = 0; kt <= kt_last; ++kt) {
     // tile kt has arrived for all waves; nobody still reads the buffers that tile kt + 1 will go into
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    lds_arrived<0>();
+    lds_barrier();
     const int j0 = kt * kRowKeys;
     const TileWord here = word;
     const bool slow = qbad || here.bad();
