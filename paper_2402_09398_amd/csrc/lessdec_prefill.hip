@@ -3,7 +3,7 @@
 // low-rank state of everything cut away (Eq. 6).
 //
 // The scores decide which tokens are kept, so Q K^T is needed to fp64 precision: with fp16 storage
-// as integer products of digit planes (lessdec_rows.hip), with fp32 storage and in the masked row pass
+// as integer products of digit planes (lessdec_rows.hip), with fp32 storage
 // in fp64 on the matrix cores (v_mfma_f64_16x16x4_f64).  Operand layout of that instruction, wave64, lane = 16 * g + c:
 //   A[i][k] is taken from lane i + 16 k, B[k][j] from lane j + 16 k,
 //   result register v of lane (g, c) holds D[g + 4 v][c].
@@ -73,78 +73,6 @@ __device__ inline void store_out(float *orow, int g, const v4f (&O)[D / 16], flo
   for (int b = 0; b < D / 16; ++b)
 #pragma unroll
     for (int w = 0; w < 4; ++w) orow[b * 16 + 4 * g + w] = O[b][w] * inv;
-}
-
-// The same for fp16 storage on v_mfma_f32_16x16x16_f16: all 16 keys in one instruction.
-// Lane (g, c) supplies k index 4 g + w, which stands for key g + 4 w (the keys whose
-// probabilities the lane holds), and row i = c of the V^T operand stands for output element
-// d = (D / 16) c + b in block b, so that a lane's operand values for all blocks are one
-// contiguous run of each key row.  The probabilities go in as an fp16 pair hi + lo (22
-// bits), accumulation is fp32.  O[b][w] is output element d = (D / 16)(4 g + w) + b.
-template <int D>
-struct VTile {
-  static constexpr int NB = D / 16;                      // blocks = halves per lane per key row
-  unsigned d[4][NB / 2];                                 // key row w: NB halves in NB / 2 dwords
-  __device__ inline void load(const __half *Vu, int P, int j0, int g, int c)
-  {
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const int kj = j0 + g + 4 * w;
-      const __half *src = Vu + (size_t)(kj < P ? kj : P - 1) * D + NB * c;
-      if constexpr (NB == 8) {
-        const uint4 t = *reinterpret_cast<const uint4 *>(src);
-        d[w][0] = t.x; d[w][1] = t.y; d[w][2] = t.z; d[w][3] = t.w;
-      } else {
-        const uint2 t = *reinterpret_cast<const uint2 *>(src);
-        d[w][0] = t.x; d[w][1] = t.y;
-      }
-    }
-  }
-  // the operand of block b: element b of the four key rows, picked out of the dwords with byte
-  // permutes (an array indexed per element would make a round trip through scratch memory)
-  __device__ inline v4h operand(int b) const
-  {
-    typedef unsigned u2v __attribute__((ext_vector_type(2)));
-    const unsigned sel = (b & 1) ? 0x07060302u : 0x05040100u;
-    const u2v r = {__builtin_amdgcn_perm(d[1][b / 2], d[0][b / 2], sel),
-                   __builtin_amdgcn_perm(d[3][b / 2], d[2][b / 2], sel)};
-    return __builtin_bit_cast(v4h, r);
-  }
-};
-template <int D>
-__device__ inline void tile_pv(const VTile<D> &vt, const double (&e)[4], v4f (&O)[D / 16])
-{
-  v4h ph, pl;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    float ef = (float)e[v];
-    // keep the fp32 value: folded into one fp64 -> fp16 conversion this becomes a long software
-    // sequence (there is no such instruction)
-    asm volatile("" : "+v"(ef));
-    const _Float16 hi = (_Float16)ef;
-    ph[v] = hi;
-    pl[v] = (_Float16)(ef - (float)hi);
-  }
-#pragma unroll
-  for (int b = 0; b < D / 16; ++b) {
-    const v4h a = vt.operand(b);
-    O[b] = __builtin_amdgcn_mfma_f32_16x16x16f16(a, ph, O[b], 0, 0, 0);
-    O[b] = __builtin_amdgcn_mfma_f32_16x16x16f16(a, pl, O[b], 0, 0, 0);
-  }
-}
-template <int D>
-__device__ inline void store_out(__half *orow, int g, const v4f (&O)[D / 16], float inv)
-{
-  constexpr int NB = D / 16;
-  // the lane owns elements NB (4 g + w) + b: one contiguous run of 4 NB halves
-  __half run[4 * NB];
-#pragma unroll
-  for (int w = 0; w < 4; ++w)
-#pragma unroll
-    for (int b = 0; b < NB; ++b) run[NB * w + b] = __float2half_rn(O[b][w] * inv);
-#pragma unroll
-  for (int i = 0; i < 4 * NB / 8; ++i)
-    *reinterpret_cast<uint4 *>(orow + 4 * NB * g + 8 * i) = *reinterpret_cast<const uint4 *>(run + 8 * i);
 }
 
 // -------------------------------------------------------------------------------------
@@ -277,19 +205,24 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
 // -------------------------------------------------------------------------------------
 // Feature-wise maximum of psi over a unit's prompt keys: psimax[u][r] = max_j psi_all[u][j][r].
 // The values are >= 0 (Eq. 2 ends in an absolute value), so they order like their bit patterns
-// and an integer LDS maximum does.   grid = U, block = 256.
+// and an integer LDS maximum does.  A thread keeps to one feature and 256 / R keys apart, eight of them in flight: bound
+// by memory (an LDS maximum per value took 49 us for 320 units x 2048 tokens at rank 16).   grid = U, block = 256.
 // -------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void prefill_psimax_kernel(const float *__restrict__ psi_all, int P, int R,
                                                              float *__restrict__ psimax)
 {
   __shared__ int s_max[LESSDEC_MAX_RANK];
   const size_t u = blockIdx.x;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, rows = 256 / R, r = tid % R, first = tid / R;
   if (tid < R) s_max[tid] = 0;
   __syncthreads();
-  const float *pa = psi_all + u * (size_t)P * R;
-  const int n = P * R;
-  for (int i = tid; i < n; i += 256) atomicMax(&s_max[i % R], __float_as_int(pa[i]));
+  if (first < rows) {
+    const float *pa = psi_all + u * (size_t)P * R + r;
+    int top = 0;
+#pragma unroll 8
+    for (int j = first; j < P; j += rows) top = max(top, __float_as_int(pa[(size_t)j * R]));
+    atomicMax(&s_max[r], top);
+  }
   __syncthreads();
   if (tid < R) psimax[u * R + tid] = __int_as_float(s_max[tid]);
 }
@@ -306,7 +239,6 @@ __global__ __launch_bounds__(256) void prefill_psimax_kernel(const float *__rest
 // took 1010 us for 320 units x 2048 tokens at rank 16; 88 + 36 now.
 // grid = U * (P / 64), block = 256;  scan: grid = U * ceil((R D + R) / 256), block = 256.
 // -------------------------------------------------------------------------------------
-constexpr int kPrefixKeys = 64;
 template <typename T, int D, int RC>
 __global__ __launch_bounds__(256) void prefill_prefix_kernel(const T *__restrict__ V,
                                                              const float *__restrict__ psi_all, int P, int R,
@@ -365,7 +297,7 @@ __global__ __launch_bounds__(256) void prefill_prefix_scan_kernel(int nblk, int 
 }
 
 // -------------------------------------------------------------------------------------
-// Masked row pass: Lambda-masking taken through the prompt token by token (Sec. 4, "Setup";
+// Masked row pass, fp32 storage (fp16: lessdec_rows.hip): Lambda-masking taken through the prompt token by token (Sec. 4, "Setup";
 // Sec. 3.2 builds the same matrix for training), all rows at once.  Under that policy the cache
 // that token t meets is known beforehand: the first Nh tokens and the Nr tokens before it, the
 // pairs discarded by then are Nh .. t - Nr - 1.  Row t of the attention matrix therefore has
@@ -382,15 +314,15 @@ __global__ __launch_bounds__(256) void prefill_prefix_scan_kernel(int nblk, int 
 // Leaves lse_t = m_t + ln(sum of the entries that H2O's scores are normalised by): all of them,
 // or with the sparse-denominator flag the exponentials only.
 // -------------------------------------------------------------------------------------
-template <typename T, int D>
+template <int D>
 __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void prefill_maskedrows_kernel(
-    const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V, unsigned U, int G, int P,
-    const float *__restrict__ phi, const float *__restrict__ psi, const float *__restrict__ psimax,
-    const float *__restrict__ hpre, const float *__restrict__ zpre, int R, int Nh, int Nr, int sparse_den,
-    double *__restrict__ lse, T *__restrict__ out)
+    const float *__restrict__ Q, const float *__restrict__ K, const float *__restrict__ V, unsigned U, int G, int P,
+    const MaskedArgs mk, double *__restrict__ lse, float *__restrict__ out)
 {
+  using T = float;
+  const float *phi = mk.phi, *psi = mk.psi, *psimax = mk.psimax, *hpre = mk.hpre, *zpre = mk.zpre;
+  const int R = mk.R, Nh = mk.Nh, Nr = mk.Nr, sparse_den = mk.sparse_den;
   constexpr int CH = D / 4, DB = D / 16;
-  constexpr bool kHalf = sizeof(T) == 2;
   constexpr int EPT = 16 * D / (64 * kPrefillWaves);
   static_assert(EPT % 2 == 0 && CH % EPT == 0, "a thread's elements stay within one lane group");
   __shared__ double2 s_k[2][16 * D / 2];
@@ -441,14 +373,8 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
   auto fetch = [&](int jt) {
     const int kr = jt * 16 + wc;
     const T *src = Ku + (size_t)(kr < P ? kr : P - 1) * D + we;
-    if constexpr (EPT * sizeof(T) == 32) {
-      reinterpret_cast<uint4 *>(raw)[0] = reinterpret_cast<const uint4 *>(src)[0];
-      reinterpret_cast<uint4 *>(raw)[1] = reinterpret_cast<const uint4 *>(src)[1];
-    } else if constexpr (EPT * sizeof(T) == 16) {
-      reinterpret_cast<uint4 *>(raw)[0] = reinterpret_cast<const uint4 *>(src)[0];
-    } else {
-      reinterpret_cast<uint2 *>(raw)[0] = reinterpret_cast<const uint2 *>(src)[0];
-    }
+    reinterpret_cast<uint4 *>(raw)[0] = reinterpret_cast<const uint4 *>(src)[0];
+    if constexpr (EPT == 8) reinterpret_cast<uint4 *>(raw)[1] = reinterpret_cast<const uint4 *>(src)[1];
   };
   // 1) the cached pairs: the row pass over the tiles that can hold any, other entries masked out
   if (ndense > 0) fetch(tile_of(0));
@@ -460,10 +386,6 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
       buf[((wi + p) * 4 + wg) * 16 + wc] =
           double2{(double)Store<T>::to_float(raw[2 * p]), (double)Store<T>::to_float(raw[2 * p + 1])};
     fetch(tile_of(idx + 1 < ndense ? idx + 1 : idx));
-    VTile<D> vt;
-    if constexpr (kHalf) {
-      if (out != nullptr) vt.load(reinterpret_cast<const __half *>(Vu), P, j0, g, c);
-    }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
@@ -504,16 +426,13 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
       esum += e[v];
     }
     L += esum;
-    if (out != nullptr) {
-      if constexpr (kHalf) tile_pv<D>(vt, e, O);
-      else tile_pv<D>(reinterpret_cast<const float *>(Vu), P, j0, g, c, e, O);
-    }
+    if (out != nullptr) tile_pv<D>(Vu, P, j0, g, c, e, O);
   }
 
   // 2) the discarded pairs, every wave on its own: key tiles from Nh's tile to the last one that
   // holds a pair older than the window of the wave's last query.  The tile psi(K) phi(Q)^T is
   // R / 4 matrix instructions; entries of pairs that are cached for the lane's query are masked
-  // out.  The next tile's value rows and psi operands are requested before this tile's arithmetic.
+  // out.  The next tile's psi operands are requested before this tile's arithmetic.
   double Lw = 0.0;                                         // sum of the low-rank entries, times e^{-m_run}
   int jt_lo = Nh / 16;
   const int jt_hi = (it * 16 + 14 - Nr) >= 0 ? (it * 16 + 14 - Nr) / 16 : -1;
@@ -572,7 +491,7 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
           const float bf = (float)(f * em_run);
 #pragma unroll
           for (int b = 0; b < DB; ++b) {
-            const float a = hk[(size_t)rc * D + (kHalf ? DB * c + b : 16 * b + c)];
+            const float a = hk[(size_t)rc * D + 16 * b + c];
             O[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bf, O[b], 0, 0, 0);
           }
         }
@@ -597,18 +516,14 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
         a[s] = r < R ? x : 0.f;
       }
     };
-    VTile<D> vt_next;
     float pa_next[4];
-    if constexpr (kHalf) vt_next.load(reinterpret_cast<const __half *>(Vu), P, jt_lo * 16, g, c);
     psi_operands(jt_lo * 16, pa_next);
     for (int jt = jt_lo; jt <= jt_hi; ++jt) {
       const int j0 = jt * 16;
-      const VTile<D> vt = vt_next;
       float pa[4];
 #pragma unroll
       for (int s = 0; s < 4; ++s) pa[s] = pa_next[s];
       const int jn = jt < jt_hi ? j0 + 16 : j0;
-      if constexpr (kHalf) vt_next.load(reinterpret_cast<const __half *>(Vu), P, jn, g, c);
       psi_operands(jn, pa_next);
       v4d wt = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -628,10 +543,7 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
         wsum += e[v];
       }
       Lw += wsum;
-      if (out != nullptr) {
-        if constexpr (kHalf) tile_pv<D>(vt, e, O);
-        else tile_pv<D>(reinterpret_cast<const float *>(Vu), P, j0, g, c, e, O);
-      }
+      if (out != nullptr) tile_pv<D>(Vu, P, j0, g, c, e, O);
     }
   }
   double Ls = L;                                           // exponentials only
@@ -1480,7 +1392,7 @@ static hipError_t launch_prefill_t(const PrefillArgs &a, hipStream_t st)
     return launch_featmap_generic(fa, d->dtype, st);
   };
   // the key digits' kernel empties the exchange array on its way
-  if ((masked || sizeof(T) != 2) && (e = launch_fill_empty(a.empty, a.empty_count, st)) != hipSuccess) return e;
+  if (sizeof(T) != 2 && (e = launch_fill_empty(a.empty, a.empty_count, st)) != hipSuccess) return e;
   if (masked) {
     // psi of every prompt key, phi of every prompt query (Eq. 1, Eq. 2), then the masked rows
     if ((e = key_features()) != hipSuccess) return e;
@@ -1513,21 +1425,23 @@ static hipError_t launch_prefill_t(const PrefillArgs &a, hipStream_t st)
 #undef LESSDEC_PREFIX
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    prefill_maskedrows_kernel<T, D><<<(U * G + kXcds - 1) / kXcds * kXcds * tiles, 64 * kPrefillWaves, 0, st>>>(
-        (const T *)a.Q, (const T *)a.K, (const T *)a.V, U * G, G, P, a.phi_all, a.psi_all, a.psimax, a.hpre, a.zpre, d->rank,
-        d->n_heavy, d->n_recent, (d->flags & LESSDEC_FLAG_SPARSE_DENOM) ? 1 : 0, a.lse, (T *)a.out);
-  } else {
-    if constexpr (sizeof(T) == 2) {
-      const RowArgs r = {a.Q, a.K, a.V, U, G, P, a.digits, a.lse, a.out, (unsigned *)a.bound, (unsigned *)a.count,
-                         (unsigned *)a.empty, a.empty_count};
-      if ((e = launch_rows_f16(r, D, st)) != hipSuccess) return e;
-    } else {
-      prefill_rowpass_kernel<T, D><<<(U * G + kXcds - 1) / kXcds * kXcds * tiles, 64 * kPrefillWaves, 0, st>>>(
-          (const T *)a.Q, (const T *)a.K, (const T *)a.V, U * G, G, P, a.lse, (T *)a.out);
-    }
   }
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  const MaskedArgs mk = {a.phi_all, a.psi_all, a.psimax, a.hpre, a.zpre, d->rank, d->n_heavy, d->n_recent,
+                         (d->flags & LESSDEC_FLAG_SPARSE_DENOM) ? 1 : 0};
+  if constexpr (sizeof(T) == 2) {
+    const RowArgs r = {a.Q, a.K, a.V, U, G, P, a.digits, a.lse, a.out, (unsigned *)a.bound, (unsigned *)a.count,
+                       (unsigned *)a.empty, a.empty_count, masked ? &mk : nullptr};
+    if ((e = launch_rows_f16(r, D, st)) != hipSuccess) return e;
+  } else {
+    const unsigned rows = prefill_grid(U * G, tiles);
+    if (masked)
+      prefill_maskedrows_kernel<D><<<rows, 64 * kPrefillWaves, 0, st>>>((const float *)a.Q, (const float *)a.K, (const float *)a.V,
+                                                                       U * G, G, P, mk, a.lse, (float *)a.out);
+    else
+      prefill_rowpass_kernel<T, D><<<rows, 64 * kPrefillWaves, 0, st>>>((const T *)a.Q, (const T *)a.K, (const T *)a.V, U * G, G, P,
+                                                                       a.lse, (T *)a.out);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
   // Column sums and selection.  Exact sums are needed of the kept tokens (they become the
   // accumulated scores) and of those whose rank is in doubt; with fp16 storage the cheap pass
   // tells which those are, with Lambda-masking the kept set is known beforehand.  Otherwise

@@ -39,6 +39,19 @@ typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 //     accumulators between registers in every tile (30 instructions);
 //   - three waves a SIMD in place of two and a software pipeline: no slower with long sweeps, and with short ones the
 //     start and the end of a workgroup, in which its waves wait, are covered (2810 against 3040 us at 1024 tokens).
+//
+// MASKED: Lambda-masking taken through the prompt token by token (Sec. 4, "Setup"; Sec. 3.2 builds the same matrix for
+// training), all rows at once.  Under that policy the cache that token t meets is known beforehand: the first Nh tokens and
+// the Nr tokens before it; the pairs discarded by then are Nh .. t - Nr - 1.  Row t of the attention matrix therefore
+// has e^{q_t k_j / sqrt(D)} where pair j is cached (or is t itself) and phi(q_t) psi(k_j)^T where it was discarded, and
+// out_t = (row t) V / (row t) 1 is Eq. 3 with H, z of Eq. 6.  The workgroup sweeps the tiles that can hold cached pairs
+// of any of its queries, other entries masked out; then the discarded pairs: those before the last prefix state (every 64
+// keys) older than a wave's windows come with that state, on fp32 matrix tiles, the few tiles after it entry by entry
+// (psi(K) phi(Q)^T on fp64 matrix tiles, R / 4 instructions; values through the LDS as before).  m rises once to the integer
+// below log2 of an upper bound of the low-rank weights, phi(q) . max_j psi(k_j).  Leaves lse_t = m_t ln 2 + ln(sum of the
+// entries that H2O's scores are normalised by): all, or with the sparse-denominator flag the exponentials.
+// 320 units x 2048 tokens, window 158, rank 16: 568 us and 70 for the digits, 1158 with scores on fp64 matrix tiles.
+//
 // 2048 units x 1024 tokens: 3600 us before, 2545 now and 270 for the digits (1.6 GB at 5.9 TB/s); 128 x 8192:
 // 11000, 8340 and 125; 32 x 777: 65, 51 and 6.
 // -------------------------------------------------------------------------------------
@@ -102,12 +115,12 @@ __global__ __launch_bounds__(128) void key_digits_kernel(const __half *__restric
   if (threadIdx.x == 0) words[blockIdx.x] = s_word[0] | s_word[1];
 }
 
-// OUT: attention outputs are wanted too
-template <int D, bool OUT>
+// OUT: attention outputs are wanted too.  MASKED: the rows of Lambda-masking taken through the prompt (below).
+template <int D, bool OUT, bool MASKED>
 __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per_eu(3, 3))) void rows_f16_kernel(
     const __half *__restrict__ Q, const __half *__restrict__ K, const __half *__restrict__ V, unsigned U, int G, int P,
     const unsigned char *__restrict__ digits, const unsigned *__restrict__ words,
-    double *__restrict__ lse, __half *__restrict__ out, unsigned *__restrict__ zero0, unsigned *__restrict__ zero1)
+    double *__restrict__ lse, __half *__restrict__ out, unsigned *__restrict__ zero0, unsigned *__restrict__ zero1, const MaskedArgs mk)
 {
   // U counts query rows here: unit u's G query heads are rows u G .. u G + G - 1 of Q, out and
   // lse, and attend over unit u's keys and values
@@ -135,10 +148,11 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
   // chunks permuted within a row (val_swizzle) so that the transposing reads meet no bank twice.  Rows past the
   // prompt repeat the last one: they come after every query.
   constexpr int RB = 2 * D, kRowsPer = 1024 / RB, CH = RB / 16;       // bytes, rows and chunks of a value piece
-  auto load_tile = [&](int kt, unsigned char *key, unsigned char *val) __attribute__((always_inline)) {
+  auto load_tile = [&](int kt, unsigned char *key, unsigned char *val, bool keys) __attribute__((always_inline)) {
     int lane = l;
     asm("" : "+v"(lane));                                 // (as in add_values)
     const int vr = lane / CH, vch = lane % CH;            // row and chunk within the piece
+    if (keys)
 #pragma unroll
     for (int i = 0; i < Tile::kKeyBytes / 1024 / W; ++i) {
       const int piece = (wave * (Tile::kKeyBytes / 1024 / W) + i) * 1024;
@@ -155,10 +169,24 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
     }
   };
 
+  // The tiles to sweep: all up to the last diagonal; MASKED: those that can hold a cached pair of the workgroup's queries
+  const int q0b = grp * BQ, q_end = (q0b + BQ < P ? q0b + BQ : P) - 1;
+  int nfirst = 0, band0 = 0, tiles_here = kt_last + 1;
+  if constexpr (MASKED) {
+    nfirst = min((mk.Nh + kRowKeys - 1) / kRowKeys, kt_last + 1);
+    band0 = max(nfirst, q0b > mk.Nr ? (q0b - mk.Nr) / kRowKeys : 0);
+    tiles_here = nfirst + kt_last + 1 - band0;
+  }
+  auto tile_of = [&](int i) { return !MASKED || i < nfirst ? i : band0 + i - nfirst; };
   unsigned char *v_cur = s_val[0], *v_next = s_val[1];
   unsigned char *k_cur = s_key[0], *k_next = s_key[1];
-  load_tile(0, k_cur, v_cur);
-  TileWord word = {wu[0]};
+  auto swap_buffers = [&] {
+    unsigned char *t = v_cur;
+    v_cur = v_next; v_next = t;
+    t = k_cur; k_cur = k_next; k_next = t;
+  };
+  load_tile(tile_of(0), k_cur, v_cur, true);
+  TileWord word = {wu[tile_of(0)]};
   ScaledDigits<D> qd;
   const bool qbad = __any(!qd.template load<false>(Qu + (size_t)qrow * D, g));
   const unsigned qlow = qd.lowest();
@@ -218,31 +246,11 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
   // High word of the limit, least before the first maximum: as signed integers the high words order what matters, everything
   // below zero lies below kSlack.
   int lim_hi = INT_MIN;
-  auto raise_max = [&](double (&y)[8]) __attribute__((always_inline)) {
-    double top = fmax(fmax(fmax(y[0], y[1]), fmax(y[2], y[3])), fmax(fmax(y[4], y[5]), fmax(y[6], y[7])));
-    if (__any(lim_hi == INT_MIN || top > kSlack)) {
-      top = fmax(top, __shfl_xor(top, 16));
-      top = fmax(top, __shfl_xor(top, 32));
-      const bool none = top == -__builtin_inf();          // nothing to see yet
-      const double d = none ? 0.0 : lim_hi == INT_MIN ? ceil(top) - 1.0 : fmax(0.0, ceil(top) - 1.0);
-      const int k = d <= 0.0 ? 0 : d < 2000.0 ? -(int)d : -2000;   // the rescaling is a power of two
-      const float af = __builtin_ldexpf(1.f, k);
-      L = __builtin_ldexp(L, k);
-#pragma unroll
-      for (int b = 0; b < DB; ++b) O[b] *= af;
-#pragma unroll
-      for (int w = 0; w < 8; ++w) y[w] -= d;
-      m += d;
-      lim_hi = none ? lim_hi : __double2hiint(kSlack);
-    }
-  };
-  // the weights of half `half` out of its scores, into hi + lo pairs and L
+  // weights of half `half` as hi + lo pairs
   v8h ph, pl;
   float one = 1.f;
   asm("" : "+s"(one));                                    // unknown to the compiler, which else makes a subtraction of the fma
-  auto weigh = [&](const double *yy, int half) __attribute__((always_inline)) {
-    double e[4];
-    exp2_f64<4>({yy[0], yy[1], yy[2], yy[3]}, e);
+  auto split = [&](const double (&e)[4], int half) __attribute__((always_inline)) {
     float ef[4];
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
@@ -251,7 +259,6 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
       // sequence (there is no such instruction)
       asm("" : "+v"(ef[w]));
     }
-    L += (e[0] + e[1]) + (e[2] + e[3]);
 #pragma unroll
     for (int w = 0; w < 4; w += 2) {
       unsigned p = __builtin_bit_cast(unsigned, v2h{(_Float16)ef[w], (_Float16)ef[w + 1]});
@@ -263,6 +270,35 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
       ph[4 * half + w + 1] = hi.y;
       pl[4 * half + w] = lo.x;
       pl[4 * half + w + 1] = lo.y;
+    }
+  };
+  // the same out of its scores, and their sum into L
+  auto weigh = [&](const double *yy, int half) __attribute__((always_inline)) {
+    double e[4];
+    exp2_f64<4>({yy[0], yy[1], yy[2], yy[3]}, e);
+    L += (e[0] + e[1]) + (e[2] + e[3]);
+    split(e, half);
+  };
+  // everything so far times 2^-d, d an integer >= 0 (per query)
+  auto rescale = [&](double d) __attribute__((always_inline)) {
+    const int k = d <= 0.0 ? 0 : d < 2000.0 ? -(int)d : -2000;
+    const float af = __builtin_ldexpf(1.f, k);
+    L = __builtin_ldexp(L, k);
+#pragma unroll
+    for (int b = 0; b < DB; ++b) O[b] *= af;
+    m += d;
+  };
+  auto raise_max = [&](double (&y)[8]) __attribute__((always_inline)) {
+    double top = fmax(fmax(fmax(y[0], y[1]), fmax(y[2], y[3])), fmax(fmax(y[4], y[5]), fmax(y[6], y[7])));
+    if (__any(lim_hi == INT_MIN || top > kSlack)) {
+      top = fmax(top, __shfl_xor(top, 16));
+      top = fmax(top, __shfl_xor(top, 32));
+      const bool none = top == -__builtin_inf();          // nothing to see yet
+      const double d = none ? 0.0 : lim_hi == INT_MIN ? ceil(top) - 1.0 : fmax(0.0, ceil(top) - 1.0);
+      rescale(d);
+#pragma unroll
+      for (int w = 0; w < 8; ++w) y[w] -= d;
+      lim_hi = none ? lim_hi : __double2hiint(kSlack);
     }
   };
   // O += V^T p; only0: the tile's second half lies after all of the wave's queries.  A lane's four rows of a 16-lane group
@@ -283,40 +319,53 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
   };
   if (tid < 16) reinterpret_cast<unsigned *>(s_zero)[tid] = 0u;        // (the first tile's barrier stands before its readers)
   if (tid == 0 && pb.grp == 0 && u == ukv * (size_t)G) zero0[ukv] = zero1[ukv] = 0u;
-  for (int kt = 0; kt <= kt_last; ++kt) {
-    // tile kt has arrived for all waves; nobody still reads the buffers that tile kt + 1 will go into
+  int lo_wg = 0, nlow = 0;                                // MASKED: the tiles of the second sweep
+  if constexpr (MASKED) {
+    lo_wg = mk.first_low(q0b) / kRowKeys;
+    nlow = max(0, (q_end - 1 - mk.Nr >= 0 ? (q_end - 1 - mk.Nr) / kRowKeys : -1) - lo_wg + 1);
+  }
+  for (int i = 0; i < tiles_here; ++i) {
+    // the tile has arrived for all waves; nobody still reads the buffers that the next one will go into
     lds_arrived<0>();
     lds_barrier();
-    const int j0 = kt * kRowKeys;
+    const int kt = tile_of(i), j0 = kt * kRowKeys;
     const TileWord here = word;
-    const bool slow = qbad || here.bad();
-    if (kt < kt_last) {
-      load_tile(kt + 1, k_next, v_next);
-      word.w = wu[kt + 1];
+    if (i + 1 < tiles_here) {
+      const int next = tile_of(i + 1);
+      load_tile(next, k_next, v_next, true);
+      word.w = wu[next];
+    } else if (MASKED && nlow > 0) {
+      load_tile(lo_wg, k_next, v_next, false);
     }
-    if (kt <= kt_wave) {                                  // wave-uniform, like all that follows
-      const bool diag = kt == kt_wave;                    // some keys come after some queries,
-      const bool only0 = j0 + 16 > q0 + 15;               // the second half after all of them
+    // wave-uniform, like all that follows
+    if (kt <= kt_wave && (!MASKED || j0 < mk.Nh || j0 + kRowKeys - 1 >= q0 - mk.Nr)) {
+      const bool slow = qbad || here.bad();
+      // some keys come after some queries (MASKED: or are not cached for them), the second half after all of them
+      const bool some = MASKED ? j0 + kRowKeys - 1 > q0 || !(j0 + kRowKeys <= mk.Nh || j0 >= q0 + 15 - mk.Nr) : kt == kt_wave;
+      const bool only0 = j0 + 16 > q0 + 15;
       double y[8];
       if (!slow) {
         scores(k_cur, here, 0, &y[0]);
         if (!only0) scores(k_cur, here, 1, &y[4]);        // (else masked below)
       } else {
         v4d d[2];
-        dot_tiles_f64<D, 2>([&](int i) { return Ku + (size_t)(j0 + i < P ? j0 + i : P - 1) * D; }, Qu + (size_t)qrow * D, g, c, d);
+        dot_tiles_f64<D, 2>([&](int r) { return Ku + (size_t)(j0 + r < P ? j0 + r : P - 1) * D; }, Qu + (size_t)qrow * D, g, c, d);
 #pragma unroll
         for (int w = 0; w < 8; ++w) y[w] = fma(d[w / 4][w % 4], cs, -m);
       }
-      if (diag) {
+      if (some) {
 #pragma unroll
-        for (int w = 0; w < 8; ++w) y[w] = j0 + 16 * (w / 4) + 4 * g + w % 4 <= qi ? y[w] : -__builtin_inf();
+        for (int w = 0; w < 8; ++w) {
+          const int kj = j0 + 16 * (w / 4) + 4 * g + w % 4;
+          y[w] = kj <= qi && (!MASKED || kj < mk.Nh || kj >= qi - mk.Nr) ? y[w] : -__builtin_inf();
+        }
       }
       int top = INT_MIN;
 #pragma unroll
       for (int w = 0; w < 8; ++w) top = max(top, __double2hiint(y[w]));
-      if (diag || slow || __any(top >= lim_hi)) {
+      if (some || slow || __any(top >= lim_hi)) {
         raise_max(y);
-        // no weight for keys after the query, scores of -inf and what is not a number
+        // no weight for keys without a part in it, scores of -inf and what is not a number
 #pragma unroll
         for (int w = 0; w < 8; ++w) y[w] = y[w] > kNoWeight ? y[w] : kNoWeight;
       }
@@ -326,14 +375,108 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
       __builtin_amdgcn_sched_barrier(0);
       add_values(v_cur, only0);
     }
-    unsigned char *t = v_cur;
-    v_cur = v_next; v_next = t;
-    t = k_cur; k_cur = k_next; k_next = t;
+    swap_buffers();
   }
+  double Lw = 0.0;                                        // sum of the low-rank entries
+  if constexpr (MASKED) {
+    const int R = mk.R, lo = mk.first_low(q0);            // first key that this wave's second sweep takes
+    const float *psi_u = mk.psi + ukv * (size_t)P * R, *phi_q = mk.phi + (u * (size_t)P + qrow) * R;
+    // phi of the lane's query: feature 4 s + g is the lane's operand of step s
+    double fq[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int r = 4 * s + g;
+      const float x = phi_q[r < R ? r : R - 1];
+      fq[s] = r < R ? (double)x : 0.0;
+    }
+    const bool discarded = q0 < P && mk.Nh < q0 + 15 - mk.Nr;     // before some query of the wave
+    if (discarded) {
+      // No weight of the query can exceed wb = phi(q) . max_j psi(k_j) (all features are >= 0), so m rises to the integer
+      // below log2(wb) once, here, and every weight handed to p V below is at most 2.
+      const float *pm = mk.psimax + ukv * (size_t)R;
+      double wb = 0.0;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int r = 4 * s + g;
+        wb = fma(fq[s], (double)pm[r < R ? r : R - 1], wb);       // fq is 0 past R
+      }
+      for (int r = 16 + g; r < R; r += 4) wb = fma((double)phi_q[r], (double)pm[r], wb);
+      wb += __shfl_xor(wb, 16);
+      wb += __shfl_xor(wb, 32);
+      rescale(wb > 0.0 ? fmax(0.0, (double)(__builtin_amdgcn_frexp_exp(wb) - 1) - m) : 0.0);
+      // Pairs before `lo` were discarded before every query of this wave (the first Nh are left out of the prefix
+      // states): their share of Eq. 3 is phi(q) hpre 2^-m in the numerator, on fp32 matrix tiles in the layout
+      // of p V, and phi(q) zpre 2^-m in the denominator.
+      if (lo > mk.Nh) {
+        const int kb = lo / kPrefixKeys, nkb = P / kPrefixKeys + 1, mi = -(int)m;
+        const float *hk = mk.hpre + (ukv * (size_t)nkb + kb) * R * D + 4 * DB * (c / 4) + c % 4;
+        const float *zk = mk.zpre + (ukv * (size_t)nkb + kb) * R;
+        // one step = features 4 s + g: f the lane's phi entry (0 past R), rc its clamped row
+        auto prefix_step = [&](double f, int rc) __attribute__((always_inline)) {
+          f = __builtin_ldexp(f, mi);
+          Lw = fma(f, (double)zk[rc], Lw);
+          if constexpr (OUT) {
+            const float bf = (float)f;
+#pragma unroll
+            for (int b = 0; b < DB; ++b) O[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(hk[(size_t)rc * D + 4 * b], bf, O[b], 0, 0, 0);
+          }
+        };
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+          if (4 * s < R) prefix_step(fq[s], 4 * s + g < R ? 4 * s + g : R - 1);
+        for (int s = 4; 4 * s < R; ++s) {
+          const int r = 4 * s + g, rc = r < R ? r : R - 1;
+          prefix_step(r < R ? (double)phi_q[rc] : 0.0, rc);
+        }
+      }
+    }
+    for (int i = 0; i < nlow; ++i) {
+      lds_arrived<0>();
+      lds_barrier();
+      const int j0 = (lo_wg + i) * kRowKeys;
+      if (i + 1 < nlow) load_tile(lo_wg + i + 1, k_next, v_next, false);
+      if (discarded && j0 >= lo / kRowKeys * kRowKeys && j0 < q0 + 15 - mk.Nr) {    // wave-uniform
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          // psi(K) phi(Q)^T: result register v of v_mfma_f64_16x16x4 holds row g + 4 v, so matrix row i stands for key
+          // 4 (i % 4) + i / 4
+          const int kr = j0 + 16 * half + 4 * (c % 4) + c / 4;
+          const float *prow = psi_u + (size_t)(kr < P ? kr : P - 1) * R;
+          v4d wt = {0.0, 0.0, 0.0, 0.0};
+          float x[4];
+#pragma unroll
+          for (int s = 0; s < 4; ++s) x[s] = prow[4 * s + g < R ? 4 * s + g : R - 1];
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+            if (4 * s < R) wt = __builtin_amdgcn_mfma_f64_16x16x4f64(4 * s + g < R ? (double)x[s] : 0.0, fq[s], wt, 0, 0, 0);
+          for (int s = 4; 4 * s < R; ++s) {
+            const int r = 4 * s + g;
+            wt = __builtin_amdgcn_mfma_f64_16x16x4f64(r < R ? (double)prow[r] : 0.0, r < R ? (double)phi_q[r] : 0.0, wt, 0, 0, 0);
+          }
+          double e[4];
+#pragma unroll
+          for (int w = 0; w < 4; ++w) {
+            const int kj = j0 + 16 * half + 4 * g + w;
+            e[w] = kj >= mk.Nh && kj < qi - mk.Nr ? __builtin_ldexp(wt[w], -(int)m) : 0.0;
+          }
+          Lw += (e[0] + e[1]) + (e[2] + e[3]);
+          split(e, half);
+        }
+        add_values(v_cur, j0 + 16 > q0 + 15);
+      }
+      swap_buffers();
+    }
+  }
+  double Ls = L;                                          // the exponentials alone
+  L += Lw;
   L += __shfl_xor(L, 16);
   L += __shfl_xor(L, 32);
+  if constexpr (MASKED) {
+    Ls += __shfl_xor(Ls, 16);
+    Ls += __shfl_xor(Ls, 32);
+  }
   if (qi < P) {
-    if (g == 0) lse[u * (size_t)P + qi] = fma(m, kLn2, log(L));
+    if (g == 0) lse[u * (size_t)P + qi] = fma(m, kLn2, log(MASKED && mk.sparse_den ? Ls : L));
     if constexpr (OUT) {
       // O[b][w] is output element 4 (DB g + b) + w: the lane's elements are one run of 4 DB halves
       const float inv = (float)(1.0 / L);
@@ -366,10 +509,15 @@ static hipError_t launch_rows_t(const RowArgs &a, hipStream_t st)
     const __half *K = (const __half *)a.K + kv;
     key_digits_kernel<D><<<nu * tiles, 128, 0, st>>>(K, tiles, a.P, digits, words, a.fill, u == 0 ? a.fill_count : 0);
     const unsigned grid = prefill_grid(nu * a.G, ngrp);
-#define LESSDEC_ROWS(OUT, O) rows_f16_kernel<D, OUT><<<grid, 64 * kPrefillWaves, 0, st>>>(                              \
-      (const __half *)a.Q + q, K, (const __half *)a.V + kv, nu * a.G, a.G, a.P, digits, words, a.lse + rows, O, a.zero0 + u, a.zero1 + u)
-    if (a.out != nullptr) LESSDEC_ROWS(true, (__half *)a.out + q);
-    else LESSDEC_ROWS(false, nullptr);
+    const MaskedArgs mk = a.masked ? a.masked->from_unit(u, a.G, a.P, D) : MaskedArgs{};
+#define LESSDEC_ROWS(OUT, MASKED, O) rows_f16_kernel<D, OUT, MASKED><<<grid, 64 * kPrefillWaves, 0, st>>>(               \
+      (const __half *)a.Q + q, K, (const __half *)a.V + kv, nu * a.G, a.G, a.P, digits, words, a.lse + rows, O, a.zero0 + u, a.zero1 + u, mk)
+    __half *out = a.out != nullptr ? (__half *)a.out + q : nullptr;
+    if (a.masked) {
+      if (out != nullptr) LESSDEC_ROWS(true, true, out); else LESSDEC_ROWS(false, true, out);
+    } else {
+      if (out != nullptr) LESSDEC_ROWS(true, false, out); else LESSDEC_ROWS(false, false, out);
+    }
 #undef LESSDEC_ROWS
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
