@@ -463,6 +463,9 @@ int lessdec_prefill(const lessdec_desc *desc, const void *Q, const void *K, cons
   a.bound = reinterpret_cast<float *>(ws + w.off_bound);
   a.psi_all = reinterpret_cast<float *>(ws + w.off_psiall);
   a.digits = ws + w.off_digits;
+  // fp16: the digits' place; fp32, which has none: that of the rows' log-sums, read for the last time by the column sums
+  a.part = s.f16 ? reinterpret_cast<double *>(ws + w.off_digits) : a.lse;
+  a.part_bytes = s.f16 ? digit_bytes(s.U, (size_t)P, s.D) : s.U * s.G * (size_t)P * sizeof(double);
   a.phi_all = reinterpret_cast<float *>(ws + w.off_phiall);
   a.psimax = reinterpret_cast<float *>(ws + w.off_psimax);
   a.hpre = reinterpret_cast<float *>(ws + w.off_hpre);

@@ -148,6 +148,8 @@ struct PrefillArgs {
   float *bound;             // [U] largest score magnitude the unit's prompt can produce (selection band)
   float *psi_all;           // [U,P,R]
   void *digits = nullptr;   // digit planes of the keys of digit_units(U, P, D) units (fp16)
+  double *part = nullptr;   // sums of shares of units' states: room that the row pass no longer needs then
+  size_t part_bytes = 0;
   float *empty = nullptr;   // entries of the decode step's exchange array, to be emptied
   size_t empty_count = 0;
   float *phi_all = nullptr; // [U*G,P,R], only for the masked form

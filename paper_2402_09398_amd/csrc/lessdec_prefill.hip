@@ -1156,59 +1156,177 @@ __global__ __launch_bounds__(256) void prefill_rank_kernel(const double *__restr
 }
 
 // -------------------------------------------------------------------------------------
-// Finalize, one workgroup per unit: kept tokens get slots in ascending position (or, for the
-// prompt taken token by token under Lambda-masking, the slots that in-place replacement would
-// have left them in); their
-// rows are gathered into the cache (acc = column sum, pos, psi), unused slots cleared; the
-// discarded pairs build H = sum psi(k)^T v, z = sum psi(k) (Eq. 6) in fp64.
-// For the state a wave takes 512 / D tokens at a time, D / 8 lanes per token with eight columns each, in
-// chunks of eight rows of H: a value of psi is widened once for eight columns and a value of V once for
-// eight rows, and z is one lane's work.  Tokens are dealt to the W waves; the lane groups meet by a
-// reduce-scatter over the rows of H, the waves in the LDS.  Four waves with two columns a lane, z in every lane, took
-// 496 us for 2048 units x 1024 tokens and 1070 us for 128 x 8192 (one workgroup per unit either way); 281 and 210
-// now.  slot_of: in 1 / 0 (kept / discarded), out slot index / -1.
-// grid = U, block = 64 W, dynamic LDS = C ints.
+// State of the discarded pairs, H = sum psi(k)^T v and z = sum psi(k) (Eq. 6) in fp64, of a share of a unit's tokens.
+// A wave takes 256 / D tokens at a time, D / 4 lanes per token with four columns each, in chunks of eight rows of H: a
+// value of psi is widened once for four columns and a value of V once for eight rows, and z is one lane's work.  Four
+// columns and not eight: with 64 sums a lane the registers allow two waves a SIMD, too few to cover the loads.
+// A unit's tokens are cut into `shares`, a workgroup each, whose sums the finalize kernel adds in order (part); one
+// share stores H and z itself.  The lane groups meet by a reduce-scatter over the rows of H, the waves in the LDS.
+// keep: 1 / 0 (kept / discarded).   grid = U shares, block = 256.
+// One workgroup of eight waves per unit with eight columns a lane, slots and cache in the same kernel, took 282 us for
+// 2048 units x 1024 tokens, 211 for 128 x 8192, 200 for 320 x 2048 at rank 16, 22 for 32 x 777; this kernel and the next:
+// 192 + 48 (the cache's rows: bound by memory), 104 + 33, 131 + 28, 7 + 9.
 // -------------------------------------------------------------------------------------
 
-// eight stored elements (16-byte aligned), all zero unless mask is ~0, as doubles
-__device__ inline void load_eight(const __half *p, unsigned mask, double (&v)[8])
+// four stored elements, all zero unless mask is ~0, as doubles
+__device__ inline void load_four(const __half *p, unsigned mask, double (&v)[4])
 {
-  const uint4 x = *reinterpret_cast<const uint4 *>(p);
-  const unsigned w[4] = {x.x & mask, x.y & mask, x.z & mask, x.w & mask};
+  const uint2 x = *reinterpret_cast<const uint2 *>(p);
+  const unsigned w[2] = {x.x & mask, x.y & mask};
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < 2; ++i) {
     const __half2 h = __builtin_bit_cast(__half2, w[i]);
     v[2 * i] = (double)__low2float(h);
     v[2 * i + 1] = (double)__high2float(h);
   }
 }
-__device__ inline void load_eight(const float *p, unsigned mask, double (&v)[8])
+__device__ inline void load_four(const float *p, unsigned mask, double (&v)[4])
 {
+  const uint4 x = *reinterpret_cast<const uint4 *>(p);
+  const unsigned w[4] = {x.x & mask, x.y & mask, x.z & mask, x.w & mask};
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const uint4 x = reinterpret_cast<const uint4 *>(p)[k];
-    const unsigned w[4] = {x.x & mask, x.y & mask, x.z & mask, x.w & mask};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v[4 * k + i] = (double)__uint_as_float(w[i]);
-  }
+  for (int i = 0; i < 4; ++i) v[i] = (double)__uint_as_float(w[i]);
 }
 
-template <typename T, int D, int W>
+constexpr int kStateWaves = 4;
+template <typename T, int D>
+__device__ inline void discarded_state(size_t u, int share, int shares, const T *__restrict__ V, int P,
+                                       const int32_t *__restrict__ keep, const float *__restrict__ psi_all, int R,
+                                       float *__restrict__ H, double *__restrict__ z, double *__restrict__ part)
+{
+  constexpr int W = kStateWaves, RC = 8, LPT = D / 4, TPW = 64 / LPT;   // lanes per token, tokens per wave at a time
+  __shared__ double s_part[W][RC][D], s_z[W][RC];
+  const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64, dl = lane % LPT, tp = lane / LPT;
+  const int lo = (int)((long)P * share / shares), hi = (int)((long)P * (share + 1) / shares);
+  const T *Vu = V + u * (size_t)P * D;
+  const int32_t *ku = keep + u * (size_t)P;
+  const float *pa = psi_all + u * (size_t)P * R;
+  const bool vec4 = R % 4 == 0;                            // psi rows readable as 16-byte vectors
+  for (int r0 = 0; r0 < R; r0 += RC) {
+    const int rn = R - r0 < RC ? R - r0 : RC;
+    const int rz = r0 + (dl < rn ? dl : 0);                // the lane's row of z (lanes dl < rn)
+    double h[RC][4], zs;
+    // Kept tokens go through the same arithmetic with values and psi of z zeroed, so that no load stands under a
+    // condition.  CLEAN: psi of kept tokens zeroed too; without it a kept token adds psi times zero, which is zero
+    // unless its psi is not finite
+    auto sweep = [&](auto clean) __attribute__((always_inline)) {
+      zs = 0.0;
+#pragma unroll
+      for (int r = 0; r < RC; ++r)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) h[r][i] = 0.0;
+#pragma unroll 4
+      for (int j0 = lo + wave * TPW; j0 < hi; j0 += W * TPW) {
+        const int j = j0 + tp < hi ? j0 + tp : hi - 1;
+        const unsigned mask = (ku[j] == 0 && j0 + tp < hi) ? ~0u : 0u;   // ~0: discarded
+        const float *pj = pa + (size_t)j * R + r0;
+        float gj[RC];
+        // rows past R repeat earlier ones; their sums are never stored
+        if (vec4) {
+#pragma unroll
+          for (int r4 = 0; r4 < RC / 4; ++r4) {
+            const float4 x = *reinterpret_cast<const float4 *>(pj + (4 * r4 < rn ? 4 * r4 : 0));
+            gj[4 * r4] = x.x; gj[4 * r4 + 1] = x.y; gj[4 * r4 + 2] = x.z; gj[4 * r4 + 3] = x.w;
+          }
+        } else {
+#pragma unroll
+          for (int r = 0; r < RC; ++r) gj[r] = pj[r < rn ? r : 0];
+        }
+        if constexpr (clean.value) {
+#pragma unroll
+          for (int r = 0; r < RC; ++r) gj[r] = __uint_as_float(__float_as_uint(gj[r]) & mask);
+        }
+        const unsigned gz = __float_as_uint(pa[(size_t)j * R + rz]) & mask;
+        double v[4];
+        load_four(Vu + (size_t)j * D + 4 * dl, mask, v);
+        zs += (double)__uint_as_float(gz);
+#pragma unroll
+        for (int r = 0; r < RC; ++r) {
+          const double g = (double)gj[r];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) h[r][i] = fma(g, v[i], h[r][i]);
+        }
+      }
+    };
+    sweep(std::false_type{});
+    bool lost = false;                                     // such a psi shows in every column of its row
+#pragma unroll
+    for (int r = 0; r < RC; ++r) lost |= !(h[r][0] == h[r][0]);
+    if (__any(lost)) sweep(std::true_type{});
+    // the wave's token groups: a lane keeps half of its rows at each distance; row of h[k] is then row0 + k
+    int row0 = 0;
+    auto halve = [&](auto distance, auto rows) __attribute__((always_inline)) {
+      constexpr int o = distance.value, n = rows.value;
+      const bool up = lane & o;
+#pragma unroll
+      for (int k = 0; k < n; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const double send = up ? h[k][i] : h[k + n][i], mine = up ? h[k + n][i] : h[k][i];
+          h[k][i] = mine + __shfl_xor(send, o);
+        }
+      row0 += up ? n : 0;
+      zs += __shfl_xor(zs, o);
+    };
+    halve(std::integral_constant<int, 32>{}, std::integral_constant<int, RC / 2>{});
+    if constexpr (TPW == 4) halve(std::integral_constant<int, 16>{}, std::integral_constant<int, RC / 4>{});
+    constexpr int KEEP = RC / TPW;                         // rows a lane ends with
+#pragma unroll
+    for (int k = 0; k < KEEP; ++k)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s_part[wave][row0 + k][4 * dl + i] = h[k][i];
+    if (tp == 0 && dl < RC) s_z[wave][dl] = zs;
+    __syncthreads();
+    double *pu = part + (u * shares + share) * (size_t)(R * D + R);
+    for (int x = tid; x < rn * D; x += 64 * W) {
+      const int r = x / D, d = x % D;
+      double sum = s_part[0][r][d];
+#pragma unroll
+      for (int w = 1; w < W; ++w) sum += s_part[w][r][d];
+      if (shares > 1) pu[(r0 + r) * D + d] = sum;
+      else H[(u * R + r0 + r) * D + d] = (float)sum;
+    }
+    if (tid < rn) {
+      double sum = s_z[0][tid];
+#pragma unroll
+      for (int w = 1; w < W; ++w) sum += s_z[w][tid];
+      if (shares > 1) pu[R * D + r0 + tid] = sum;
+      else z[u * R + r0 + tid] = sum;
+    }
+    if (r0 + RC < R) __syncthreads();                      // s_part, s_z are written again
+  }
+}
+template <typename T, int D>
+__global__ __launch_bounds__(64 * kStateWaves) void prefill_state_kernel(
+    const T *__restrict__ V, int P, const int32_t *__restrict__ keep, const float *__restrict__ psi_all, int R, int shares,
+    float *__restrict__ H, double *__restrict__ z, double *__restrict__ part)
+{
+  discarded_state<T, D>(blockIdx.x / (unsigned)shares, (int)(blockIdx.x % (unsigned)shares), shares, V, P, keep, psi_all, R, H, z, part);
+}
+
+// -------------------------------------------------------------------------------------
+// Slots and cache: the kept tokens get slots in order (ring_nh >= 0: as in-place replacement leaves them) and their
+// rows are gathered into the cache (acc = column sum, pos, psi), unused slots cleared; the shares of H and z (more than
+// one; none: nothing was discarded, both are zero) are added up.  slot_of: 1 / 0 (kept / discarded).  STATE: the state
+// too, in one share (short prompts of few units, where a launch costs more than it spreads).
+// grid = U, block = 64 W, dynamic LDS = C ints.
+// -------------------------------------------------------------------------------------
+template <typename T, int D, int W, bool STATE>
 __global__ __launch_bounds__(64 * W) void prefill_finalize_kernel(
     const T *__restrict__ K, const T *__restrict__ V, int P, const double *__restrict__ colsum,
-    int32_t *__restrict__ slot_of, const float *__restrict__ psi_all, int C, int R,
+    const int32_t *__restrict__ slot_of, const float *__restrict__ psi_all, int C, int R,
     T *__restrict__ k_cache, T *__restrict__ v_cache, double *__restrict__ acc,
     int32_t *__restrict__ pos, float *__restrict__ psi, float *__restrict__ H,
-    double *__restrict__ z, int32_t *__restrict__ n_seen, int32_t *__restrict__ pend_slot, int ring_nh)
+    double *__restrict__ z, int32_t *__restrict__ n_seen, int32_t *__restrict__ pend_slot, int ring_nh,
+    const double *__restrict__ part, int shares)
 {
-  constexpr int THREADS = 64 * W, RC = 8;
+  constexpr int THREADS = 64 * W;
   extern __shared__ int s_tok[];                           // [C] token held by each slot
   __shared__ int s_wave[W];
-  __shared__ double s_part[W / 2][RC][D], s_z[W][RC];
   const size_t u = blockIdx.x;
   const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
   const T *Ku = K + u * (size_t)P * D, *Vu = V + u * (size_t)P * D;
-  int32_t *so = slot_of + u * (size_t)P;
+  const int32_t *so = slot_of + u * (size_t)P;
   const float *pa = psi_all + u * (size_t)P * R;
   const int kept = P < C ? P : C;
 
@@ -1224,14 +1342,24 @@ __global__ __launch_bounds__(64 * W) void prefill_finalize_kernel(
       // ring_nh >= 0: the slots as in-place replacement leaves them when the first ring_nh tokens
       // stay and the others pass through the remaining slots in turn (Sec. 3.2)
       const int slot = (ring_nh < 0 || j < ring_nh || P <= C || C <= ring_nh) ? base : ring_nh + (j - ring_nh) % (C - ring_nh);
-      so[j] = keep ? slot : -1;
       if (keep && slot < C) s_tok[slot] = j;
       base += keep;
     }
   }
+  // 2) the shares of the state, in order
+  if (!STATE && shares != 1) {
+    const double *pu = part + u * shares * (size_t)(R * D + R);
+    for (int x = tid; x < R * D + R; x += THREADS) {
+      double sum = 0.0;
+#pragma unroll 4
+      for (int i = 0; i < shares; ++i) sum += pu[(size_t)i * (R * D + R) + x];
+      if (x < R * D) H[u * R * D + x] = (float)sum;
+      else z[u * R + x - R * D] = sum;
+    }
+  }
   __syncthreads();
 
-  // 2) gather: rows moved as 16-byte vectors, 64 / kVecs slots per wave at a time
+  // 3) gather: rows moved as 16-byte vectors, 64 / kVecs slots per wave at a time
   constexpr int kVecs = D * (int)sizeof(T) / 16;           // per row: 8, 16 or 32
   constexpr int kSlotsPerWave = 64 / kVecs;
   for (int s = wave * kSlotsPerWave + lane / kVecs; s < C; s += W * kSlotsPerWave) {
@@ -1254,112 +1382,13 @@ __global__ __launch_bounds__(64 * W) void prefill_finalize_kernel(
       for (int r = i; r < R; r += kVecs) psi[slot * R + r] = 0.f;
     }
   }
-
-  // 3) state of the discarded pairs.  Kept tokens go through the same arithmetic with values and psi of
-  // z zeroed, so that no load stands under a condition.
-  constexpr int LPT = D / 8, TPW = 64 / LPT;               // lanes per token, tokens per wave at a time
-  const int dl = lane % LPT, tp = lane / LPT;
-  const bool vec4 = R % 4 == 0;                            // psi rows readable as 16-byte vectors
-  for (int r0 = 0; r0 < R; r0 += RC) {
-    const int rn = R - r0 < RC ? R - r0 : RC;
-    const int rz = r0 + (dl < rn ? dl : 0);                // the lane's row of z (lanes dl < rn)
-    double h[RC][8], zs;
-    // CLEAN: psi of kept tokens zeroed too.  Without it a kept token adds psi times zero, which is zero unless its psi
-    // is not finite
-    auto sweep = [&](auto clean) __attribute__((always_inline)) {
-      zs = 0.0;
-#pragma unroll
-      for (int r = 0; r < RC; ++r)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) h[r][i] = 0.0;
-#pragma unroll 2
-      for (int j0 = wave * TPW; j0 < P; j0 += W * TPW) {
-        const int j = j0 + tp < P ? j0 + tp : P - 1;
-        const unsigned mask = (so[j] < 0 && j0 + tp < P) ? ~0u : 0u;     // ~0: discarded
-        const float *pj = pa + (size_t)j * R + r0;
-        float gj[RC];
-        // rows past R repeat earlier ones; their sums are never stored
-        if (vec4) {
-#pragma unroll
-          for (int r4 = 0; r4 < RC / 4; ++r4) {
-            const float4 x = *reinterpret_cast<const float4 *>(pj + (4 * r4 < rn ? 4 * r4 : 0));
-            gj[4 * r4] = x.x; gj[4 * r4 + 1] = x.y; gj[4 * r4 + 2] = x.z; gj[4 * r4 + 3] = x.w;
-          }
-        } else {
-#pragma unroll
-          for (int r = 0; r < RC; ++r) gj[r] = pj[r < rn ? r : 0];
-        }
-        if constexpr (clean.value) {
-#pragma unroll
-          for (int r = 0; r < RC; ++r) gj[r] = __uint_as_float(__float_as_uint(gj[r]) & mask);
-        }
-        const unsigned gz = __float_as_uint(pa[(size_t)j * R + rz]) & mask;
-        double v[8];
-        load_eight(Vu + (size_t)j * D + 8 * dl, mask, v);
-        zs += (double)__uint_as_float(gz);
-#pragma unroll
-        for (int r = 0; r < RC; ++r) {
-          const double g = (double)gj[r];
-#pragma unroll
-          for (int i = 0; i < 8; ++i) h[r][i] = fma(g, v[i], h[r][i]);
-        }
-      }
-    };
-    sweep(std::false_type{});
-    bool lost = false;                                     // such a psi shows in every column of its row
-#pragma unroll
-    for (int r = 0; r < RC; ++r) lost |= !(h[r][0] == h[r][0]);
-    if (__any(lost)) sweep(std::true_type{});
-    // the wave's token groups: a lane keeps half of its rows at each distance; row of h[k] is then row0 + k
-    int row0 = 0;
-#pragma unroll
-    for (int o = 32, n = RC / 2; o >= LPT; o >>= 1, n >>= 1) {
-      const bool up = lane & o;
-#pragma unroll
-      for (int k = 0; k < n; ++k)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const double send = up ? h[k][i] : h[k + n][i], keep = up ? h[k + n][i] : h[k][i];
-          h[k][i] = keep + __shfl_xor(send, o);
-        }
-      row0 += up ? n : 0;
-      zs += __shfl_xor(zs, o);
-    }
-    constexpr int KEEP = RC / TPW;                         // rows a lane ends with: 2 or 1
-    // the waves: the upper half through the LDS to the lower, the lower four through the LDS to everyone
-    if (wave >= W / 2) {
-#pragma unroll
-      for (int k = 0; k < KEEP; ++k)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) s_part[wave - W / 2][row0 + k][8 * dl + i] = h[k][i];
-    }
-    if (tp == 0 && dl < RC) s_z[wave][dl] = zs;
-    __syncthreads();
-    if (wave < W / 2) {
-#pragma unroll
-      for (int k = 0; k < KEEP; ++k)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) s_part[wave][row0 + k][8 * dl + i] += h[k][i];
-    }
-    __syncthreads();
-    for (int x = tid; x < rn * D; x += THREADS) {
-      const int r = x / D, d = x % D;
-      double sum = 0.0;
-#pragma unroll
-      for (int w = 0; w < W / 2; ++w) sum += s_part[w][r][d];
-      H[(u * R + r0 + r) * D + d] = (float)sum;
-    }
-    if (tid < rn) {
-      double sum = 0.0;
-#pragma unroll
-      for (int w = 0; w < W; ++w) sum += s_z[w][tid];
-      z[u * R + r0 + tid] = sum;
-    }
-    if (r0 + RC < R) __syncthreads();                      // s_part, s_z are written again
-  }
   if (tid == 0) {
     n_seen[u] = P;
     pend_slot[u] = -1;
+  }
+  if constexpr (STATE) {
+    static_assert(W == kStateWaves, "one state block per workgroup");
+    discarded_state<T, D>(u, 0, 1, V, P, slot_of, psi_all, R, H, z, nullptr);
   }
 }
 
@@ -1493,15 +1522,28 @@ static hipError_t launch_prefill_t(const PrefillArgs &a, hipStream_t st)
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (!masked && (e = key_features()) != hipSuccess) return e;
-  const size_t lds = (size_t)C * sizeof(int);
-#define LESSDEC_FINALIZE(W)                                                                                   \
-  prefill_finalize_kernel<T, D, W><<<U, 64 * W, lds, st>>>(                                                   \
-      (const T *)a.K, (const T *)a.V, P, a.colsum, keep, a.psi_all, C, d->rank, (T *)d->k_cache,              \
-      (T *)d->v_cache, d->acc, d->pos, d->psi, d->H, d->z, d->n_seen, d->pend_slot, ring_nh)
-  // Four waves a unit on short prompts: a wave has few tokens to sum there, and fewer partial states to add up and twice the
-  // units at once count for more (17 against 24 us for 640 units x 70 tokens, 20 against 30 for 372 x 118, 29 against 35
-  // for 640 x 250)
-  if (P <= 256) LESSDEC_FINALIZE(4); else LESSDEC_FINALIZE(8);
+  // A unit's tokens in so many shares that about eight workgroups are there for every compute unit, 64 tokens to a share
+  // at least; as many as the scratch holds
+  int shares = P > C ? 1 : 0;
+  if (P > C && U < 2048) {
+    const size_t each = U * (size_t)(d->rank * D + d->rank) * sizeof(double), most = a.part_bytes / each;
+    shares = (int)((2048 + U - 1) / U);
+    if (shares > P / 64) shares = P / 64;
+    if ((size_t)shares > most) shares = (int)most;
+    if (shares < 1) shares = 1;
+  }
+  const bool fused = P > C && P <= 64 && U <= 512;         // (32 units x 12 tokens: 40.7 us in all, 41.6 with two launches)
+  if (shares > 0 && !fused) {
+    prefill_state_kernel<T, D><<<U * shares, 64 * kStateWaves, 0, st>>>((const T *)a.V, P, keep, a.psi_all, d->rank, shares,
+                                                                        d->H, d->z, a.part);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+#define LESSDEC_FINALIZE(W, STATE)                                                                                         \
+  prefill_finalize_kernel<T, D, W, STATE><<<U, 64 * W, (size_t)C * sizeof(int), st>>>(                                    \
+      (const T *)a.K, (const T *)a.V, P, a.colsum, keep, a.psi_all, C, d->rank, (T *)d->k_cache, (T *)d->v_cache, d->acc, \
+      d->pos, d->psi, d->H, d->z, d->n_seen, d->pend_slot, ring_nh, a.part, shares)
+  if (fused) LESSDEC_FINALIZE(kStateWaves, true);
+  else LESSDEC_FINALIZE(8, false);
 #undef LESSDEC_FINALIZE
   return hipGetLastError();
 }
