@@ -22,7 +22,8 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 // (head, 16 rows) pairs, spreads the hidden units over blocks that leave their sums (fp64) in the workspace, and
 // featmap_finish_kernel adds them in part order: the two launches that phi and psi took one each.
 // Bound by the fp64 matrix rate (66 cycles an instruction) and the erfc of the hidden units, about half and half.
-// 8 x 32 units, D = 128, R' = 512, fp32 storage: 16 us for both maps, against 82 with a hidden unit per
+// 8 x 32 units, D = 128, R' = 512, fp32 storage: 10.8 + 4.1 us for both maps (11.5 + 4.8 with the weights of the second layer
+// requested after the first's products, a branch around every activation and divisions ahead of the first request), against 82 with a hidden unit per
 // thread on the vector units and a block per (head, 8 rows).
 // =====================================================================================
 constexpr int kFmWaves = 4;
@@ -37,6 +38,7 @@ __device__ inline void featmap_store(const FeatmapArgs &a, int h, long row, int 
   } else {
     const T *W3 = reinterpret_cast<const T *>(a.W3) + ((size_t)h * a.R + r) * a.R;
     double s = 0.0;
+#pragma unroll 8
     for (int j = 0; j < a.R; ++j) s = fma(h2[j], (double)Store<T>::to_float(W3[j]), s);
     f = fabs(s);
   }
@@ -64,6 +66,7 @@ __global__ __launch_bounds__(64 * kFmWaves) void featmap_generic_kernel(const Fe
   const long rows_head = (long)a.B * rpu, i0 = (long)(bid / (unsigned)parts) * 16;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64, g = l / 16, c = l % 16;
   auto global_row = [&](long i) -> long {                  // i-th row of this head -> row in x / out
+    if (rpu == 1) return i * Hh + h;                       // (a decode step: without the division)
     const long b = i / rpu, p = i % rpu;
     return (b * Hh + h) * rpu + p;
   };
@@ -83,24 +86,35 @@ __global__ __launch_bounds__(64 * kFmWaves) void featmap_generic_kernel(const Fe
   for (int tile = t0 + wave; tile < t1; tile += kFmWaves) {
     const int hid = 16 * tile;
     const T *w1 = W1 + (size_t)(hid + c < Rp ? hid + c : Rp - 1) * D + g * CH;
+    // all of the tile's weights are requested ahead of the products, the second layer's behind the first's
+    typename Store<T>::Vec w[NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) w[k] = load_vec<T>(w1 + k * EPV);
+    T w2[4][RT];
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int t = 0; t < RT; ++t) {
+        const int r = 16 * t + c, j = hid + g + 4 * v;
+        w2[v][t] = W2[(size_t)(r < R ? r : R - 1) * Rp + (j < Rp ? j : Rp - 1)];
+      }
     v4d acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int k = 0; k < NV; ++k) {
-      const typename Store<T>::Vec w = load_vec<T>(w1 + k * EPV);
+    for (int k = 0; k < NV; ++k)
 #pragma unroll
       for (int e = 0; e < EPV; ++e)
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)Store<T>::get(w, e), (double)Store<T>::get(xr[k], e), acc, 0, 0, 0);
-    }
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)Store<T>::get(w[k], e), (double)Store<T>::get(xr[k], e), acc, 0, 0, 0);
+    double act[4];                                         // (four chains side by side: no branch around one)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) act[v] = gelu_f64(acc[v]);
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int j = hid + g + 4 * v;
-      const double act = j < Rp ? gelu_f64(acc[v]) : 0.0;
+      if (j >= Rp) act[v] = 0.0;
 #pragma unroll
       for (int t = 0; t < RT; ++t) {
-        const int r = 16 * t + c;
-        const double w2 = (double)Store<T>::to_float(W2[(size_t)(r < R ? r : R - 1) * Rp + (j < Rp ? j : Rp - 1)]);
         // (past the last unit a zero on both sides: the weight read in its place may be an infinity)
-        c2[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(j < Rp ? w2 : 0.0, act, c2[t], 0, 0, 0);
+        c2[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(j < Rp ? (double)Store<T>::to_float(w2[v][t]) : 0.0, act[v], c2[t], 0, 0, 0);
       }
     }
   }
@@ -145,6 +159,7 @@ __global__ __launch_bounds__(256) void featmap_finish_kernel(const FeatmapArgs a
   const bool live = i < na + nb && r < R;
   if (live) {
     double sum = 0.0;
+#pragma unroll 8
     for (int p = 0; p < parts; ++p) sum += sums[((size_t)i * parts + p) * R + r];
     s_h2[wave][r] = gelu_f64(sum);
   }

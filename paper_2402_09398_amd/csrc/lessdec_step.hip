@@ -6,21 +6,28 @@ namespace lessdec {
 
 // Waves per SIMD the register allocation aims for (the K and V rows held in registers
 // take 4 VGPRs per iteration, the values reusing the keys' registers).
-constexpr int step_waves_per_simd(int nit) { return nit == 0 ? 6 : nit <= 2 ? 6 : nit <= 7 ? 5 : nit <= 11 ? 3 : 2; }
+constexpr int step_waves_per_simd(int nit, int w)
+{
+  const int n = nit == 0 ? 6 : nit <= 2 ? 6 : nit <= 7 ? 5 : nit <= 11 ? 3 : 2;
+  return w == 4 ? n : n < w / 4 ? w / 4 : n / (w / 4) * (w / 4);         // whole blocks
+}
 
 // =====================================================================================
-// General form of the step: one block of four waves per unit, any capacity, rank and storage
+// General form of the step: one block of W (four or eight) waves per unit, any capacity, rank and storage
 // type.  The feature maps phi(q), psi(k) of the step come from the launches before it.
 //
 // A cache row is D * sizeof(T) bytes = LPR lanes of 16 bytes; the block covers RPB =
-// 256 / LPR rows (4096 bytes) per iteration with fully coalesced 16-byte loads.  With
+// 64 W / LPR rows per iteration with fully coalesced 16-byte loads.  With
 // NIT > 0 every key row of the unit is requested at kernel entry (NIT buffer loads per
 // thread sharing one offset register; rows past the capacity read as zero; non-temporal,
 // a row is not touched again before the same layer's next token) and every value row right
 // after the scores, into the same registers.  Loads come back to a wave in issue order, so
 // anything the head of the kernel wants early is requested before the keys, and nothing
 // after the decisions waits on a load whose address depends on them.  NIT = 0 is the
-// looped form for any capacity.
+// looped form for any capacity, eight iterations' rows requested before the first is used.
+// 256 units x 102 slots, D = 128, fp32: 14.6 us with four waves, 21 requests a wave for 13 iterations and the sum of a row's 32
+// lanes by LDS shuffles; 8.8 now.  In the loop, one row at a time, 400 slots took 75 us a step (maps included), 46 now.
+// Bound by the chain of requests, scores, softmax and values of a unit.
 //
 // Roles: wave 0 owns the scores (phase 2); wave 1 owns the low-rank side (phi(q), the
 // pending fold of z, phi(q) z^T); the last D / 64 waves own one output column per thread
@@ -43,10 +50,10 @@ constexpr int step_waves_per_simd(int nit) { return nit == 0 ? 6 : nit <= 2 ? 6 
 // Phase 4  column threads: out = p V + phi(q) H / den (Eq. 3); the new pair goes into the
 //          freed slot (Sec. 3.2); the discarded value row is left pending.
 // =====================================================================================
-template <typename T, int D, int NIT>
-__global__ __launch_bounds__(256, step_waves_per_simd(NIT)) void step_kernel(const StepArgs a)
+template <typename T, int D, int NIT, int W>
+__global__ __launch_bounds__(64 * W, step_waves_per_simd(NIT, W)) void step_kernel(const StepArgs a)
 {
-  constexpr int kThreads = 256;
+  constexpr int kThreads = 64 * W;
   constexpr int EPL = Store<T>::kPerVec;   // elements per lane
   constexpr int LPR = D / EPL;             // lanes per row
   constexpr int RPB = kThreads / LPR;      // rows per block iteration
@@ -139,6 +146,25 @@ __global__ __launch_bounds__(256, step_waves_per_simd(NIT)) void step_kernel(con
     }
   }
 
+  // looped form: kAhead iterations' rows (of keys or values) are requested before the first of them is used; row m is the
+  // appended pair's
+  constexpr int kAhead = 8;
+  auto sweep = [&](const T *rows_at, const Vec appended, auto &&use) __attribute__((always_inline)) {
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(rows_at), 0, C * D * (int)sizeof(T), 0x00020000);
+    for (int r0 = 0; r0 < rows; r0 += kAhead * RPB) {
+      Vec x[kAhead];
+#pragma unroll
+      for (int it = 0; it < kAhead; ++it) x[it] = buffer_load_nt<T>(rs, (r0 + it * RPB) * (kIterBytes / RPB) + tid * 16, 0);
+#pragma unroll
+      for (int it = 0; it < kAhead; ++it) {
+        const int r = r0 + it * RPB + rb;
+        if (r == m) x[it] = appended;
+        use(r, x[it]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
   // ---- phase 1: scores ---------------------------------------------------------------
   {
     double qd[EPL];
@@ -159,12 +185,7 @@ __global__ __launch_bounds__(256, step_waves_per_simd(NIT)) void step_kernel(con
         __builtin_amdgcn_sched_barrier(0);        // one row at a time: keeps the fp64 temporaries few
       }
     } else {
-      for (int r0 = 0; r0 < rows; r0 += RPB) {
-        const int r = r0 + rb;
-        Vec kv = knv;
-        if (r < m) kv = load_vec_nt<T>(kc + (size_t)r * D + lr * EPL);
-        score_row(r, kv);
-      }
+      sweep(kc, knv, score_row);
     }
   }
   if constexpr (NIT > 0) {
@@ -323,12 +344,7 @@ __global__ __launch_bounds__(256, step_waves_per_simd(NIT)) void step_kernel(con
         __builtin_amdgcn_sched_barrier(0);
       }
     } else {
-      for (int r0 = 0; r0 < rows; r0 += RPB) {
-        const int r = r0 + rb;
-        Vec vv = vnv;
-        if (r < m) vv = load_vec_nt<T>(vc + (size_t)r * D + lr * EPL);
-        pv_row(r, vv);
-      }
+      sweep(vc, vnv, pv_row);
     }
     float4 *so4 = reinterpret_cast<float4 *>(s_o + rb * D + lr * EPL);
 #pragma unroll
@@ -341,9 +357,9 @@ __global__ __launch_bounds__(256, step_waves_per_simd(NIT)) void step_kernel(con
     const int eslot = s_eslot;
     const bool evict = eslot >= 0;
     const int ins_slot = full ? ((evict && eslot < m) ? eslot : -1) : m;
-    float pv = 0.f;
+    double pv = 0.0;                                       // (the groups' fp32 sums in fp64: no rounding of its own)
 #pragma unroll
-    for (int gidx = 0; gidx < RPB; ++gidx) pv += s_o[gidx * D + col];
+    for (int gidx = 0; gidx < RPB; ++gidx) pv += (double)s_o[gidx * D + col];
     float fh = 0.f;
     if (R <= 16) {
 #pragma unroll
@@ -353,7 +369,7 @@ __global__ __launch_bounds__(256, step_waves_per_simd(NIT)) void step_kernel(con
       const float *Hu = a.H + (size_t)u * R * D;
       for (int r = 0; r < R; ++r) fh = fmaf(s_f[r], Hu[(size_t)r * D + col], fh);
     }
-    const double o = (double)pv + s_lscale * (double)fh;
+    const double o = pv + s_lscale * (double)fh;
     float of = (float)o;
     asm volatile("" : "+v"(of));                             // fp64 -> fp16 in one step would be a software sequence
     reinterpret_cast<T *>(a.out)[(size_t)u * D + col] = Store<T>::from_float(of);
@@ -394,15 +410,29 @@ __global__ __launch_bounds__(256) void state_sync_kernel(const StepArgs a, int D
 template <typename T, int D>
 static hipError_t launch_step_t(const StepArgs &a, hipStream_t st)
 {
-  constexpr int RPB = 256 / (D / Store<T>::kPerVec);
+  constexpr int LPR = D / Store<T>::kPerVec, RPB = 256 / LPR;
   const size_t lds = (size_t)(a.C + 1) * (sizeof(double) + sizeof(float));
-  const int need = (a.C + 1 + RPB - 1) / RPB;            // row iterations to cover C + 1 rows
   const unsigned grid = (unsigned)a.U;
-  if (need <= 2) step_kernel<T, D, 2><<<grid, 256, lds, st>>>(a);
-  else if (need <= 7) step_kernel<T, D, 7><<<grid, 256, lds, st>>>(a);
-  else if (need <= 11) step_kernel<T, D, 11><<<grid, 256, lds, st>>>(a);
-  else if (need <= 21) step_kernel<T, D, 21><<<grid, 256, lds, st>>>(a);
-  else step_kernel<T, D, 0><<<grid, 256, lds, st>>>(a);
+  const int need = (a.C + 1 + RPB - 1) / RPB;            // row iterations of four waves to cover C + 1 rows
+#define LESSDEC_STEP(NIT, W) step_kernel<T, D, NIT, W><<<grid, 64 * W, lds, st>>>(a)
+  // Eight waves per unit where four would take more than eleven turns and there are few units: a unit's rows are then
+  // requested at once instead of in a loop, by twice the waves.  fp32, us of eight steps: 12 units x 200 slots, D = 128, 161
+  // against 226, 256 x 400 379 / 384, 512 x 200 341 / 398, 1280 x 300 915 / 910; D = 64 256 x 400 218 / 256, 512 x 300
+  // 268 / 249.  (Sixteen waves: 154 at 12 x 200, 613 against 470 at 256 x 640.)
+  if (need > 11 && grid <= (LPR == 32 ? 1024u : 384u)) {
+    const int turns = (need + 1) / 2;
+    if (turns <= 7) LESSDEC_STEP(7, 8);
+    else if (turns <= 11) LESSDEC_STEP(11, 8);
+    else if (turns <= 21) LESSDEC_STEP(21, 8);
+    else LESSDEC_STEP(0, 8);
+  } else if (need <= 2) LESSDEC_STEP(2, 4);
+  else if (need <= 4) LESSDEC_STEP(4, 4);
+  else if (need <= 7) LESSDEC_STEP(7, 4);
+  else if (need <= 11) LESSDEC_STEP(11, 4);
+  else if (need <= 15) LESSDEC_STEP(15, 4);
+  else if (need <= 21) LESSDEC_STEP(21, 4);
+  else LESSDEC_STEP(0, 4);
+#undef LESSDEC_STEP
   return hipGetLastError();
 }
 

@@ -49,15 +49,28 @@ struct OpMax { __device__ double operator()(double a, double b) const { return f
 struct OpMin { __device__ double operator()(double a, double b) const { return fmin(a, b); } };
 struct OpMinI { __device__ int operator()(int a, int b) const { return a < b ? a : b; } };
 
+// x of the lane 16 further in a pair of 16-lane rows, added: after a row's all-reduce every lane of the pair has the pair's sum.
+// (v_permlane16_swap: the odd rows of the first operand and the even rows of the second change places)
+__device__ inline double add_other_row16(double x)
+{
+  typedef unsigned v2u __attribute__((ext_vector_type(2)));
+  const v2u lo = __builtin_bit_cast(v2u, __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(x), (unsigned)__double2loint(x), false, false));
+  const v2u hi = __builtin_bit_cast(v2u, __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(x), false, false));
+  return __hiloint2double((int)hi.x, (int)lo.x) + __hiloint2double((int)hi.y, (int)lo.y);
+}
+// Sum over the LPR lanes that hold a cache row, in every one of them, without a trip through the LDS (a shuffle waits for
+// one at every step; a row's 32 lanes took five).
 template <int LPR>
 __device__ inline double row_sum(double v)
 {
-  if constexpr (LPR == 16) {
-    return row16_allreduce(v, OpAdd{});
+  static_assert(LPR == 8 || LPR == 16 || LPR == 32, "a row spans 8, 16 or 32 lanes");
+  if constexpr (LPR == 8) {
+    v += dpp_mov<0xB1>(v);
+    v += dpp_mov<0x4E>(v);
+    return v + dpp_mov<0x141>(v);                          // row_half_mirror: the other quad of eight lanes
   } else {
-#pragma unroll
-    for (int o = LPR / 2; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
+    v = row16_allreduce(v, OpAdd{});
+    return LPR == 32 ? add_other_row16(v) : v;
   }
 }
 
