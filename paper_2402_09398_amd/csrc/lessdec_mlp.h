@@ -287,4 +287,73 @@ __device__ __forceinline__ void mlp_parts_gq_job(const __half *q, const __half *
                                  part, chunk, slab, job_ < njobs, wave, l);
 }
 
+// One block = 16 kTiles rows that share a head, as kTiles tiles of 16 (head fastest in blockIdx: with
+// Hh a multiple of 8 every block of a head lands on the same XCD and shares its L2 copy of the
+// weights).  The four waves split the groups of 32 hidden units and apply each loaded weight
+// tile to all the row tiles, add their layer-2 sums through the LDS, and 256 threads finish
+// the rows x 16 outputs (activation, W3, absolute value) in fp64.
+constexpr int kPsiTiles = 4;      // prompt phase: 64 rows per block
+constexpr int kPairTiles = 1;     // decode step: 16 rows per block, so that a batch of 64 fills more of the chip
+inline unsigned mlp_psi_blocks(const MlpArgs &a, int tiles)
+{
+  return (unsigned)((((long)a.B * a.rpu + 16 * tiles - 1) / (16 * tiles)) * a.Hh);
+}
+// lds: mlp_psi_lds(kTiles) bytes, 16-byte aligned
+constexpr int mlp_psi_lds(int tiles) { return 16 * tiles * 17 * 8 + 4 * 16 * (16 * tiles + 1) * 4; }
+template <int D, int kTiles>
+__device__ inline void mlp_psi_block(const MlpArgs &a, unsigned bid, unsigned char *lds)
+{
+  double (*s_h2)[17] = reinterpret_cast<double (*)[17]>(lds);                       // [row][r]
+  float (*s_red)[16][16 * kTiles + 1] = reinterpret_cast<float (*)[16][16 * kTiles + 1]>(lds + 16 * kTiles * 17 * sizeof(double));   // [wave][r][row]
+  const int tid = threadIdx.x, wave = tid / 64, l = tid % 64, g = l / 16, c = l % 16;
+  const int Hh = a.Hh, Rp = a.Rp, R = a.R;
+  const int h = bid % Hh, chunk = bid / Hh;
+  const __half *W1 = a.W1 + (size_t)h * Rp * D;
+  const __half *W2 = a.W2 + (size_t)h * R * Rp;
+  const long rows_head = (long)a.B * a.rpu;
+  auto global_row = [&](long i) -> long {
+    const long bb = i / a.rpu, p = i % a.rpu;
+    return (bb * Hh + h) * (long)a.rpu + p;
+  };
+  v8h bx[kTiles][D / 32];
+#pragma unroll
+  for (int t = 0; t < kTiles; ++t) {
+    const long i = ((long)chunk * kTiles + t) * 16 + c;
+    mlp_load_row<D>(a.x + (i < rows_head ? global_row(i) : 0) * D, g, bx[t]);   // padding: any row
+  }
+  v4f c2[kTiles];
+#pragma unroll
+  for (int t = 0; t < kTiles; ++t) c2[t] = v4f{0.f, 0.f, 0.f, 0.f};
+  for (int grp = wave; grp < Rp / 32; grp += 4) {
+    const MlpTiles<D> w = mlp_load_tiles<D>(W1, W2, Rp, R, 32 * grp, g, c);
+#pragma unroll
+    for (int t = 0; t < kTiles; ++t) mlp_apply_tiles<D>(w, bx[t], c2[t]);
+  }
+#pragma unroll
+  for (int t = 0; t < kTiles; ++t)
+#pragma unroll
+    for (int w = 0; w < 4; ++w) s_red[wave][4 * g + w][16 * t + c] = c2[t][w];
+  __syncthreads();
+  const int r = tid % 16;
+  for (int row = tid / 16; row < 16 * kTiles; row += 16) {
+    const float sum = ((s_red[0][r][row] + s_red[1][r][row]) + s_red[2][r][row]) + s_red[3][r][row];
+    s_h2[row][r] = (r < R) ? gelu_poly_f64((double)sum) : 0.0;
+  }
+  __syncthreads();
+  // W3 == nullptr: the map has no third matrix (phi, Eq. 1)
+  const __half *W3 = a.W3 ? a.W3 + ((size_t)h * R + (r < R ? r : 0)) * R : nullptr;
+  for (int row = tid / 16; row < 16 * kTiles; row += 16) {
+    const long i = (long)chunk * (16 * kTiles) + row;
+    if (r < R && i < rows_head) {
+      double acc3 = 0.0;
+      if (W3 != nullptr) {
+        for (int j = 0; j < R; ++j) acc3 = fma(s_h2[row][j], (double)__half2float(W3[j]), acc3);
+      } else {
+        acc3 = s_h2[row][r];
+      }
+      a.out[(size_t)global_row(i) * R + r] = (float)fabs(acc3);
+    }
+  }
+}
+
 }  // namespace lessdec

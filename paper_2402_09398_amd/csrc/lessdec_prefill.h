@@ -2,6 +2,7 @@
 #pragma once
 
 #include "lessdec_common.h"
+#include "lessdec_internal.h"
 
 namespace lessdec {
 
@@ -55,7 +56,9 @@ struct RowArgs {
   unsigned *fill;            // words to be set to kMlpEmpty
   size_t fill_count;
   const MaskedArgs *masked;  // or NULL: all causal pairs
+  const MlpArgs *maps;       // psi of the keys in the same launch (rows_f16_take_maps), or NULL
 };
+bool rows_f16_take_maps(unsigned U, int G, int P);
 hipError_t launch_rows_f16(const RowArgs &a, int D, hipStream_t st);
 // list == nullptr: every column
 hipError_t launch_columns_f16(const void *Q, const void *K, unsigned U, int G, int P, int D, const double *lse,

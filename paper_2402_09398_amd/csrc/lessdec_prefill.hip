@@ -1407,14 +1407,14 @@ static hipError_t launch_prefill_t(const PrefillArgs &a, hipStream_t st)
   const bool masked = a.masked && lambda && P > C;
   const int ring_nh = masked ? d->n_heavy : -1;
   hipError_t e;
+  MlpArgs fm;                                             // psi of every key on the matrix cores
+  fm.B = d->batch; fm.Hh = d->heads; fm.rpu = P; fm.D = d->head_dim; fm.Rp = d->hidden; fm.R = d->rank;
+  fm.x = (const __half *)a.K; fm.W1 = (const __half *)d->Wk1; fm.W2 = (const __half *)d->Wk2;
+  fm.W3 = (const __half *)d->Wk3; fm.out = a.psi_all;
+  const bool matrix_maps = mlp_mfma_supported(d->dtype, d->head_dim, d->hidden, d->rank);
+  const bool maps_ride = matrix_maps && !masked && rows_f16_take_maps(U, G, P);
   auto key_features = [&]() -> hipError_t {
-    if (mlp_mfma_supported(d->dtype, d->head_dim, d->hidden, d->rank)) {
-      MlpArgs fm;
-      fm.B = d->batch; fm.Hh = d->heads; fm.rpu = P; fm.D = d->head_dim; fm.Rp = d->hidden; fm.R = d->rank;
-      fm.x = (const __half *)a.K; fm.W1 = (const __half *)d->Wk1; fm.W2 = (const __half *)d->Wk2;
-      fm.W3 = (const __half *)d->Wk3; fm.out = a.psi_all;
-      return launch_mlp(fm, st);
-    }
+    if (matrix_maps) return launch_mlp(fm, st);
     FeatmapArgs fa;
     fa.x = a.K; fa.W1 = d->Wk1; fa.W2 = d->Wk2; fa.W3 = d->Wk3; fa.out = a.psi_all; fa.out_f64 = 0;
     fa.B = d->batch; fa.Hh = d->heads; fa.rpu = P; fa.D = d->head_dim; fa.Rp = d->hidden; fa.R = d->rank;
@@ -1459,7 +1459,7 @@ static hipError_t launch_prefill_t(const PrefillArgs &a, hipStream_t st)
                          (d->flags & LESSDEC_FLAG_SPARSE_DENOM) ? 1 : 0};
   if constexpr (sizeof(T) == 2) {
     const RowArgs r = {a.Q, a.K, a.V, U, G, P, a.digits, a.lse, a.out, (unsigned *)a.bound, (unsigned *)a.count,
-                       (unsigned *)a.empty, a.empty_count, masked ? &mk : nullptr};
+                       (unsigned *)a.empty, a.empty_count, masked ? &mk : nullptr, maps_ride ? &fm : nullptr};
     if ((e = launch_rows_f16(r, D, st)) != hipSuccess) return e;
   } else {
     const unsigned rows = prefill_grid(U * G, tiles);
@@ -1521,7 +1521,7 @@ static hipError_t launch_prefill_t(const PrefillArgs &a, hipStream_t st)
     prefill_rank_kernel<<<rank_grid, 256, 0, st>>>(a.colsum, P, d->n_heavy, d->n_recent, a.slot_of);
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (!masked && (e = key_features()) != hipSuccess) return e;
+  if (!masked && !maps_ride && (e = key_features()) != hipSuccess) return e;
   // A unit's tokens in so many shares that about eight workgroups are there for every compute unit, 64 tokens to a share
   // at least; as many as the scratch holds
   int shares = P > C ? 1 : 0;

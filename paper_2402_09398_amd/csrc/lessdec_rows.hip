@@ -5,6 +5,7 @@
 #include "lessdec_digits.h"
 #include "lessdec_internal.h"
 #include "lessdec_lds.h"
+#include "lessdec_mlp.h"
 #include "lessdec_prefill.h"
 
 namespace lessdec {
@@ -115,19 +116,28 @@ __global__ __launch_bounds__(128) void key_digits_kernel(const __half *__restric
   if (threadIdx.x == 0) words[blockIdx.x] = s_word[0] | s_word[1];
 }
 
-// OUT: attention outputs are wanted too.  MASKED: the rows of Lambda-masking taken through the prompt (below).
-template <int D, bool OUT, bool MASKED>
+// OUT: attention outputs are wanted too.  MASKED: the rows of Lambda-masking taken through the prompt (above).  MAPS: the
+// workgroups from n_rows on evaluate psi of the prompt's keys, which nothing here needs: few units leave the chip room for them.
+template <int D, bool OUT, bool MASKED, bool MAPS>
 __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per_eu(3, 3))) void rows_f16_kernel(
     const __half *__restrict__ Q, const __half *__restrict__ K, const __half *__restrict__ V, unsigned U, int G, int P,
     const unsigned char *__restrict__ digits, const unsigned *__restrict__ words,
-    double *__restrict__ lse, __half *__restrict__ out, unsigned *__restrict__ zero0, unsigned *__restrict__ zero1, const MaskedArgs mk)
+    double *__restrict__ lse, __half *__restrict__ out, unsigned *__restrict__ zero0, unsigned *__restrict__ zero1, const MaskedArgs mk, const MlpArgs maps, unsigned n_rows)
 {
+  // two buffers of keys and two of values, and 64 bytes of zeros
+  constexpr int kZero = 2 * (RowTile<D>::kKeyBytes + RowTile<D>::kValBytes), kRows = kZero + 64;
+  constexpr int kLds = MAPS && mlp_psi_lds(kPsiTiles) > kRows ? mlp_psi_lds(kPsiTiles) : kRows;   // the maps' sums lie in the tiles' place
+  __shared__ __attribute__((aligned(64))) unsigned char s_lds[kLds];
+  if constexpr (MAPS) {
+    if (blockIdx.x >= n_rows) {
+      mlp_psi_block<D, kPsiTiles>(maps, blockIdx.x - n_rows, s_lds);
+      return;
+    }
+  }
   // U counts query rows here: unit u's G query heads are rows u G .. u G + G - 1 of Q, out and
   // lse, and attend over unit u's keys and values
   using Tile = RowTile<D>;
   constexpr int W = kPrefillWaves, KC = D / 64, DB = D / 16, BQ = 16 * W;
-  __shared__ __attribute__((aligned(16))) unsigned char s_key[2][Tile::kKeyBytes], s_val[2][Tile::kValBytes];
-  __shared__ __attribute__((aligned(64))) unsigned char s_zero[64];
   const int ngrp = (P + BQ - 1) / BQ;
   const PrefillBlock pb = prefill_block(blockIdx.x, ngrp);
   if (pb.u >= U) return;                                  // uniform over the workgroup
@@ -178,8 +188,8 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
     tiles_here = nfirst + kt_last + 1 - band0;
   }
   auto tile_of = [&](int i) { return !MASKED || i < nfirst ? i : band0 + i - nfirst; };
-  unsigned char *v_cur = s_val[0], *v_next = s_val[1];
-  unsigned char *k_cur = s_key[0], *k_next = s_key[1];
+  unsigned char *k_cur = s_lds, *k_next = k_cur + Tile::kKeyBytes, *v_cur = k_next + Tile::kKeyBytes, *v_next = v_cur + Tile::kValBytes;
+  unsigned char *s_zero = s_lds + kZero;
   auto swap_buffers = [&] {
     unsigned char *t = v_cur;
     v_cur = v_next; v_next = t;
@@ -510,19 +520,33 @@ static hipError_t launch_rows_t(const RowArgs &a, hipStream_t st)
     key_digits_kernel<D><<<nu * tiles, 128, 0, st>>>(K, tiles, a.P, digits, words, a.fill, u == 0 ? a.fill_count : 0);
     const unsigned grid = prefill_grid(nu * a.G, ngrp);
     const MaskedArgs mk = a.masked ? a.masked->from_unit(u, a.G, a.P, D) : MaskedArgs{};
-#define LESSDEC_ROWS(OUT, MASKED, O) rows_f16_kernel<D, OUT, MASKED><<<grid, 64 * kPrefillWaves, 0, st>>>(               \
-      (const __half *)a.Q + q, K, (const __half *)a.V + kv, nu * a.G, a.G, a.P, digits, words, a.lse + rows, O, a.zero0 + u, a.zero1 + u, mk)
+#define LESSDEC_ROWS(OUT, MASKED, MAPS) rows_f16_kernel<D, OUT, MASKED, MAPS><<<grid + n_maps, 64 * kPrefillWaves, 0, st>>>(      \
+      (const __half *)a.Q + q, K, (const __half *)a.V + kv, nu * a.G, a.G, a.P, digits, words, a.lse + rows, out, a.zero0 + u,      \
+      a.zero1 + u, mk, n_maps ? *a.maps : MlpArgs{}, grid)
     __half *out = a.out != nullptr ? (__half *)a.out + q : nullptr;
+    const unsigned n_maps = a.maps && u == 0 ? mlp_psi_blocks(*a.maps, kPsiTiles) : 0;      // all units' with the first share
     if (a.masked) {
-      if (out != nullptr) LESSDEC_ROWS(true, true, out); else LESSDEC_ROWS(false, true, out);
+      if (out != nullptr) LESSDEC_ROWS(true, true, false); else LESSDEC_ROWS(false, true, false);
+    } else if (n_maps) {
+      if (out != nullptr) LESSDEC_ROWS(true, false, true); else LESSDEC_ROWS(false, false, true);
     } else {
-      if (out != nullptr) LESSDEC_ROWS(true, false, out); else LESSDEC_ROWS(false, false, out);
+      if (out != nullptr) LESSDEC_ROWS(true, false, false); else LESSDEC_ROWS(false, false, false);
     }
 #undef LESSDEC_ROWS
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+// Whether psi rides along: it needs nothing of the row pass and is bound by other instructions, so it fills what the longest
+// sweeps leave idle, and a launch is saved (us of a whole prompt phase, D = 128, psi in a launch of its own against riding along:
+// 32 units x 64 tokens 47.2 and 40.0, 32 x 777 151.8 and 130.2, 64 x 1000 269 and 234, 128 x 2000 1097 and 1041).  Past 8192
+// workgroups of rows the maps that keep a head's weights in registers win: 2048 x 512 1700 and 1760, 2048 x 1024 4530 and
+// 4610 (128 x 4 heads x 2048: 3160 and 3090).
+bool rows_f16_take_maps(unsigned U, int G, int P)
+{
+  return (size_t)U * G * ((P + 16 * kPrefillWaves - 1) / (16 * kPrefillWaves)) <= 8192;
 }
 
 hipError_t launch_rows_f16(const RowArgs &a, int D, hipStream_t st)
