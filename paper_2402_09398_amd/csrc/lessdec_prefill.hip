@@ -1481,12 +1481,14 @@ static hipError_t launch_prefill_t(const PrefillArgs &a, hipStream_t st)
     if constexpr (sizeof(T) == 2) {
       if (!lambda) {
         // 256 keys per workgroup; 128 where that leaves compute units idle, or most of a workgroup's waves
-        // without keys (640 units x 70 tokens: 13 against 18 us; 512 units x 150, D = 64: 17 against 13)
+        // without keys (640 units x 70 tokens: 13 against 18 us; 512 units x 150, D = 64: 17 against 13); 64 where even that
+        // is one round (a whole prompt phase: 32 units x 500 94.5 against 97.8, 128 x 128 58.4 / 59.7; 64 x 500 114.4 / 113.9)
         const unsigned wide = prefill_grid(U, (unsigned)((P + 255) / 256)), narrow = prefill_grid(U, (unsigned)((P + 127) / 128));
 #define LESSDEC_APPROX(KT, GRID)                                                                                        \
   prefill_colapprox_kernel<D, KT><<<GRID, 64 * kPrefillWaves, 0, st>>>((const __half *)a.Q, (const __half *)a.K, U, P, a.lse, G, \
                                                                        a.approx, (unsigned *)a.bound, (unsigned *)a.count)
-        if (P <= 64) LESSDEC_APPROX(1, prefill_grid(U, 1));
+        const unsigned thin = (unsigned)((P + 63) / 64);
+        if (P <= 64 || (size_t)U * thin <= 448) LESSDEC_APPROX(1, prefill_grid(U, thin));
         else if (wide >= 512 && P > 128) LESSDEC_APPROX(4, wide);
         else LESSDEC_APPROX(2, narrow);
 #undef LESSDEC_APPROX

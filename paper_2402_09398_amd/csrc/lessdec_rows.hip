@@ -707,6 +707,10 @@ hipError_t launch_columns_f16(const void *Q, const void *K, unsigned U, int G, i
   // filled (2048 x 64, all kept: <4, 2> 108, <8, 8> 162; 2048 x 200: <2, 2> 439, <4, 2> 482, <8, 8> 566; 2048 x 300:
   // <4, 2> 653, <2, 2> 694, <8, 4> 685; 512 x 400: <4, 2> 274, <2, 2> 277, <8, 4> 314).
   const size_t wide = (size_t)U * ((tiles + 7) / 8);      // workgroups of eight key tiles
+  // Fewest of all: a tile to a workgroup, as long as that does not make more workgroups than the chip takes at once (a whole prompt
+  // phase, <1, 8> against <2, 8>: 32 units x 500 tokens, 142 kept or in doubt, 93.7 against 97.8; 12 x 777, 210: 114.5 against
+  // 118.7; 64 x 256, 82: 74.6 against 70.1; 32 x 777, 210: 133.7 against 130.5).
+  if ((size_t)U * tiles <= 320) LESSDEC_COLUMNS(1, 8);
   if (U < 256 && (tiles < 24 || wide < 256)) LESSDEC_COLUMNS(2, 8);
   if ((long)G * P > 448) {
     if (wide < 768) LESSDEC_COLUMNS(8, 8);
