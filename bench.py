@@ -251,14 +251,18 @@ def main():
     launches = lessdec_step_launches(layers[0].desc)
     one_launch = launches == 1
     extras = implementation_extra_bytes_per_unit_step(w) if w.q_per_kv == 1 else {}
-    fp64_flops = U * G * (Pn ** 2 * D + 2.0 * min(Cn, Pn) * Pn * D * 0.5)    # row pass + exact columns of the kept/doubtful tokens (about)
-    fp16_flops = prefill_flops - U * G * Pn ** 2 * D                          # everything else: A V, cheap column sums, psi, state
-    masked = args.policy == "lambda" and args.prompt_stepwise                 # its row pass multiplies fp16 rows in fp64 too
+    masked = args.policy == "lambda" and args.prompt_stepwise                 # its rows see only the cached pairs (and psi phi^T)
+    row_flops = U * G * (2.0 * min(Cn, Pn) * Pn * D if masked else Pn ** 2 * D)
+    col_flops = U * G * 2.0 * min(Cn, Pn) * Pn * D * 0.5                       # exact columns of the kept/doubtful tokens (about)
+    fp64_flops = row_flops + col_flops
+    fp16_flops = prefill_flops - row_flops                                    # everything else: A V, cheap column sums, psi, state
     what = "Q K^T of the row pass and the exact column sums (they decide the heavy set)"
-    if w.dtype == "f16" and not masked:
-        # exact integer products: sixteen digit-plane products a term; 16x16x64 i8 in 16 cycles on 1024 units at 2.4 GHz
-        iops = 16.0 * fp64_flops / (prefill_ms * 1e-3) / 1e12
-        score_rate = {"int8_matrix": {"ops": 16.0 * fp64_flops, "achieved": iops, "peak": 5033.0, "unit": "TOP/s", "frac": iops / 5033.0,
+    if w.dtype == "f16":
+        # exact integer products of digit planes: nine a term in the row pass (sixteen in blocks with lowest digits, not
+        # counted), sixteen in the columns; 16x16x64 i8 in 16 cycles on 1024 units at 2.4 GHz
+        ops = 9.0 * row_flops + 16.0 * col_flops
+        iops = ops / (prefill_ms * 1e-3) / 1e12
+        score_rate = {"int8_matrix": {"ops": ops, "achieved": iops, "peak": 5033.0, "unit": "TOP/s", "frac": iops / 5033.0,
                                       "what": what + ", as products of digit planes"}}
     else:
         rate = fp64_flops / (prefill_ms * 1e-3) / 1e12
