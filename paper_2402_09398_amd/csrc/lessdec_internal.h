@@ -123,15 +123,21 @@ hipError_t launch_reset(const lessdec_desc *d, hipStream_t st);
 // Digit planes of prompt keys: four bytes an element, a word per tile of 32 keys.  They live between the kernel that writes them
 // and the row pass, so units take turns in a part of the workspace of limited size: 640 MiB hold a million tokens of
 // D = 128 (a share of the work that fills the chip many times over), and a unit longer than that gets its own size.
+// The part's size is a limit in bytes and not a number of units, so that it never falls with P: a workspace for a prompt
+// holds every shorter one.
 constexpr size_t kDigitBytes = (size_t)640 << 20;
 inline size_t digit_bytes_unit(size_t P, size_t D) { return (P + 31) / 32 * (32 * D * 4 + 4); }
+inline size_t digit_bytes(size_t U, size_t P, size_t D)
+{
+  const size_t unit = digit_bytes_unit(P, D), most = unit > kDigitBytes ? unit : kDigitBytes;
+  return P == 0 ? 0 : U <= most / unit ? U * unit : most;
+}
+// units at a time, one at least
 inline size_t digit_units(size_t U, size_t P, size_t D)
 {
-  size_t n = kDigitBytes / digit_bytes_unit(P, D);
-  if (n >= 8) n = n / 8 * 8;                               // whole rounds over the dies
-  return n < 1 ? 1 : n < U ? n : U;
+  const size_t n = digit_bytes(U, P, D) / digit_bytes_unit(P, D);
+  return n < U && n >= 8 ? n / 8 * 8 : n;                  // whole rounds over the dies
 }
-inline size_t digit_bytes(size_t U, size_t P, size_t D) { return P ? digit_units(U, P, D) * digit_bytes_unit(P, D) : 0; }
 
 struct PrefillArgs {
   const lessdec_desc *d;

@@ -120,6 +120,25 @@ def test_calls_reject_bad_descriptors_on_the_host():
     assert L.lessdec_strerror(12345) is not None
 
 
+@pytest.mark.parametrize("units,max_prompt,more", [
+    ((4, 40), 8192, {}), ((8, 32), 8192, {}), ((4, 32), 16384, {}), ((2, 32), 32768, {}), ((16, 40), 4096, {}),
+    ((64, 32), 4096, {}), ((4, 40), 8192, dict(flags=6)), ((1, 1), 70000, dict(head_dim=64)), ((2, 12), 3000, dict(dtype=0)),
+    ((64, 40), 2048, dict(q_per_kv=4, rank=16))])
+def test_a_workspace_holds_every_shorter_prompt(units, max_prompt, more):
+    """lessdec_workspace_bytes never falls with max_prompt, and lessdec_prefill takes prompts up to it (here it stops at the
+    missing arrays, behind the check of the workspace)."""
+    d = _desc(batch=units[0], heads=units[1], **more)
+    for f in ("k_cache", "v_cache", "acc", "pos", "psi", "H", "z", "n_seen",
+              "pend_slot", "pend_v", "pend_psi", "Wq1", "Wq2", "Wk1", "Wk2", "Wk3", "workspace"):
+        setattr(d, f, 0x10000)
+    d.workspace_bytes = binding.lessdec_workspace_bytes(d, max_prompt)
+    L = binding.lib()
+    refused = [p for p in range(1, max_prompt + 1)
+               if L.lessdec_prefill(C.byref(d), None, None, None, p, None, None) != binding.EINVAL]
+    assert refused == []
+    assert L.lessdec_prefill(C.byref(d), None, None, None, max_prompt + 1000, None, None) == binding.EWORKSPACE
+
+
 def test_product_does_not_import_the_oracle():
     pkg = os.path.join(ROOT, "paper_2402_09398_amd")
     for dirpath, _, files in os.walk(pkg):
