@@ -311,13 +311,14 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
       lim_hi = none ? lim_hi : __double2hiint(kSlack);
     }
   };
-  // O += V^T p; only0: the tile's second half lies after all of the wave's queries.  A lane's four rows of a 16-lane group
+  // O += V^T p; skip0, skip1: no key of that half has a weight for any of the wave's queries.  A lane's four rows of a 16-lane group
   // and the piece of four columns it points at: the transposing read hands lane i column i of the group's four rows.
   // A-operand row i of block b is value column 4 DB (i / 4) + 4 b + i % 4, so that a lane's outputs are one run.
   const int v_at = (4 * g + c / 4) * RB + (((DB / 2) * (c % 4)) ^ Tile::val_swizzle(4 * g + c / 4)) * 16;
-  auto add_values = [&](const unsigned char *val, bool only0) __attribute__((always_inline)) {
+  auto add_values = [&](const unsigned char *val, bool skip0, bool skip1) __attribute__((always_inline)) {
     if constexpr (!OUT) return;
-    unsigned at0 = lds_offset(val) + v_at, at1 = only0 ? lds_offset(s_zero) : at0 + 16 * RB;   // (values without a weight may be infinite)
+    unsigned at0 = lds_offset(val) + v_at, at1 = skip1 ? lds_offset(s_zero) : at0 + 16 * RB;   // (values without a weight may be infinite)
+    if (MASKED && skip0) at0 = lds_offset(s_zero);
     asm("" : "+v"(at0), "+v"(at1));                       // else the addresses of all blocks stay in registers between the tiles
 #pragma unroll
     for (int b = 0; b < DB; ++b) {
@@ -350,13 +351,15 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
     // wave-uniform, like all that follows
     if (kt <= kt_wave && (!MASKED || j0 < mk.Nh || j0 + kRowKeys - 1 >= q0 - mk.Nr)) {
       const bool slow = qbad || here.bad();
-      // some keys come after some queries (MASKED: or are not cached for them), the second half after all of them
+      // some keys come after some queries (MASKED: or are not cached for them)
       const bool some = MASKED ? j0 + kRowKeys - 1 > q0 || !(j0 + kRowKeys <= mk.Nh || j0 >= q0 + 15 - mk.Nr) : kt == kt_wave;
-      const bool only0 = j0 + 16 > q0 + 15;
+      // halves without a key for any of them: after them all, or (MASKED) discarded by them all, which come with the second sweep
+      auto gone = [&](int a) { return MASKED && a >= mk.Nh && a + 15 < q0 - mk.Nr; };
+      const bool skip0 = gone(j0), skip1 = j0 + 16 > q0 + 15 || gone(j0 + 16);
       double y[8];
       if (!slow) {
-        scores(k_cur, here, 0, &y[0]);
-        if (!only0) scores(k_cur, here, 1, &y[4]);        // (else masked below)
+        if (!skip0) scores(k_cur, here, 0, &y[0]);        // (else masked below)
+        if (!skip1) scores(k_cur, here, 1, &y[4]);
       } else {
         v4d d[2];
         dot_tiles_f64<D, 2>([&](int r) { return Ku + (size_t)(j0 + r < P ? j0 + r : P - 1) * D; }, Qu + (size_t)qrow * D, g, c, d);
@@ -383,7 +386,7 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
       __builtin_amdgcn_sched_barrier(0);
       weigh(&y[4], 1);
       __builtin_amdgcn_sched_barrier(0);
-      add_values(v_cur, only0);
+      add_values(v_cur, skip0, skip1);
     }
     swap_buffers();
   }
@@ -472,7 +475,7 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
           Lw += (e[0] + e[1]) + (e[2] + e[3]);
           split(e, half);
         }
-        add_values(v_cur, j0 + 16 > q0 + 15);
+        add_values(v_cur, j0 + 16 <= lo, j0 + 16 > q0 + 14 - mk.Nr);
       }
       swap_buffers();
     }
