@@ -30,3 +30,28 @@ def test_infinite_value(n_heavy, key, value, head_dim):
     assert same[:, :key // 16 * 16].all()                # (rows of the key's own 16 share its block)
     rows = [t for t in range(w.prompt) if (t // 16 * 16 - w.n_recent) // 64 * 64 > key]
     assert len(rows) > 50 and (b[:, rows, 7] == value).all()
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("which", ["K", "Q", "KQ"])
+def test_values_without_digits(which, head_dim):
+    """Elements of 127 and more: their tiles, and all tiles of a wave whose queries hold one, are multiplied in fp64."""
+    w = shape(150, head_dim=head_dim, q_per_kv=2, n_heavy=5, n_recent=20)
+    inp = wl.all_inputs(w)
+    rng = np.random.default_rng(6)
+    for name in which:
+        x = inp[name].reshape(w.units, -1, w.prompt, head_dim)
+        for value in (126.9375, -126.9375, 127.0, -300.0):
+            for u in range(w.units):
+                for head in range(x.shape[1]):
+                    x[u, head, rng.integers(2, w.prompt), rng.integers(head_dim)] = value
+    other = {"K": "Q", "Q": "K"}.get(which)              # what the large channel meets is small, so that the rows stay soft
+    if other:
+        big = np.abs(inp[which].astype(np.float32)).reshape(-1, head_dim).max(axis=0) > 100
+        inp[other][..., big] *= np.float16(1 / 64)
+    units = list(range(w.units))
+    res = hz.gpu_run(w, inp, flags=FLAGS)
+    rep = hz.check_against_oracle(w, inp, units, res, flags=FLAGS)
+    rep.failures.extend(hz.check_every_unit(w, res, flags=FLAGS))
+    print("\n" + rep.summary(), flush=True)
+    assert rep.ok(), rep.failures[:10]
