@@ -52,11 +52,11 @@ bool shape_ok(const lessdec_desc *d, Shape *s)
 }
 
 // Workspace: [ f_phi U*R f64 | f_psi U*R f32 | mlp_parts 2*ceil(R'/64)*U*16 f32 |
-//              prefill: 4 staged rows U*D (4 bytes each) | lse U*G*P f64, colsum U*P f64 | approx U*P f32, list U*P i32, count U i32, bound U f32 | slot_of U*P i32 | psi_all U*P*R f32 | digits (fp16, digit_bytes) | phi_all U*G*P*R f32, psimax U*R f32, hpre U*(P/64+1)*R*D f32, zpre U*(P/64+1)*R f32 (masked prompt only) ],
+//              prefill: 4 staged rows U*D (4 bytes each) | lse U*G*P f64, colsum U*P f64 | approx U*P f32, list U*P i32, count U i32, bound U f32 | slot_of U*P i32 | psi_all U*P*R f32 | digits (fp16, digit_bytes) | part (fp32, state_part_bytes) | phi_all U*G*P*R f32, psimax U*R f32, hpre U*(P/64+1)*R*D f32, zpre U*(P/64+1)*R f32 (masked prompt only) ],
 // every part 256-byte aligned.
 struct Workspace {
   size_t off_fphi, off_fpsi, off_parts, off_gqa, off_stage, off_lse, off_colsum, off_approx, off_list, off_count, off_bound, off_slot,
-      off_psiall, off_digits, off_phiall, off_psimax, off_hpre, off_zpre, total;
+      off_psiall, off_digits, off_part, off_phiall, off_psimax, off_hpre, off_zpre, total;
 };
 
 Workspace carve(const Shape &s, size_t P, unsigned flags)
@@ -77,6 +77,7 @@ Workspace carve(const Shape &s, size_t P, unsigned flags)
   w.off_slot = o; o = align_up(o + s.U * P * sizeof(int32_t), 256);
   w.off_psiall = o; o = align_up(o + s.U * P * s.R * sizeof(float), 256);
   w.off_digits = o; o = align_up(o + (s.f16 ? digit_bytes(s.U, P, s.D) : 0), 256);
+  w.off_part = o; o = align_up(o + (s.f16 ? 0 : state_part_bytes(s.U, P, s.R, s.D)), 256);
   // phi of every prompt query: only for Lambda-masking taken through the prompt token by token
   const bool masked = (flags & LESSDEC_FLAG_LAMBDA) && (flags & LESSDEC_FLAG_PROMPT_STEPWISE);
   w.off_phiall = o; o = align_up(o + (masked ? s.U * s.G * P * s.R * sizeof(float) : 0), 256);
@@ -463,9 +464,8 @@ int lessdec_prefill(const lessdec_desc *desc, const void *Q, const void *K, cons
   a.bound = reinterpret_cast<float *>(ws + w.off_bound);
   a.psi_all = reinterpret_cast<float *>(ws + w.off_psiall);
   a.digits = ws + w.off_digits;
-  // fp16: the digits' place; fp32, which has none: that of the rows' log-sums, read for the last time by the column sums
-  a.part = s.f16 ? reinterpret_cast<double *>(ws + w.off_digits) : a.lse;
-  a.part_bytes = s.f16 ? digit_bytes(s.U, (size_t)P, s.D) : s.U * s.G * (size_t)P * sizeof(double);
+  a.part = reinterpret_cast<double *>(ws + (s.f16 ? w.off_digits : w.off_part));
+  a.part_bytes = s.f16 ? digit_bytes(s.U, (size_t)P, s.D) : state_part_bytes(s.U, (size_t)P, s.R, s.D);
   a.phi_all = reinterpret_cast<float *>(ws + w.off_phiall);
   a.psimax = reinterpret_cast<float *>(ws + w.off_psimax);
   a.hpre = reinterpret_cast<float *>(ws + w.off_hpre);

@@ -139,6 +139,26 @@ inline size_t digit_units(size_t U, size_t P, size_t D)
   return n < U && n >= 8 ? n / 8 * 8 : n;                  // whole rounds over the dies
 }
 
+// State of the discarded prompt pairs: a unit's tokens in so many shares that about eight workgroups are there for every compute
+// unit, 64 tokens to a share at least; every share leaves H and z in fp64.  fp16: in the digits' place, which the row pass no
+// longer needs then, as many as that holds; fp32: in a part of their own, 64 MiB of them at most (rank 64 of few units; at rank 8
+// all of 2048 take 17).
+inline size_t state_share_bytes(size_t U, size_t R, size_t D) { return U * (R * D + R) * sizeof(double); }
+inline size_t state_shares(size_t U, size_t P, size_t R, size_t D, size_t bytes)
+{
+  if (U >= 2048) return 1;
+  size_t n = (2048 + U - 1) / U;
+  const size_t most = bytes / state_share_bytes(U, R, D);
+  if (n > P / 64) n = P / 64;
+  if (n > most) n = most;
+  return n < 1 ? 1 : n;
+}
+inline size_t state_part_bytes(size_t U, size_t P, size_t R, size_t D)
+{
+  const size_t n = state_shares(U, P, R, D, (size_t)64 << 20);
+  return n > 1 ? n * state_share_bytes(U, R, D) : 0;
+}
+
 struct PrefillArgs {
   const lessdec_desc *d;
   const void *Q, *K, *V;
@@ -154,7 +174,7 @@ struct PrefillArgs {
   float *bound;             // [U] largest score magnitude the unit's prompt can produce (selection band)
   float *psi_all;           // [U,P,R]
   void *digits = nullptr;   // digit planes of the keys of digit_units(U, P, D) units (fp16)
-  double *part = nullptr;   // sums of shares of units' states: room that the row pass no longer needs then
+  double *part = nullptr;   // sums of shares of units' states (state_shares)
   size_t part_bytes = 0;
   float *empty = nullptr;   // entries of the decode step's exchange array, to be emptied
   size_t empty_count = 0;

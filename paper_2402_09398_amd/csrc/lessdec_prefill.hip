@@ -1165,7 +1165,8 @@ __global__ __launch_bounds__(256) void prefill_rank_kernel(const double *__restr
 // keep: 1 / 0 (kept / discarded).   grid = U shares, block = 256.
 // One workgroup of eight waves per unit with eight columns a lane, slots and cache in the same kernel, took 282 us for
 // 2048 units x 1024 tokens, 211 for 128 x 8192, 200 for 320 x 2048 at rank 16, 22 for 32 x 777; this kernel and the next:
-// 192 + 48 (the cache's rows: bound by memory), 104 + 33, 131 + 28, 7 + 9.
+// 192 + 48 (the cache's rows: bound by memory), 104 + 33, 131 + 28, 7 + 9.  fp32, a whole prompt phase, one workgroup per unit as
+// above and in shares: 12 units x 2000 tokens at rank 32 1267 and 1168 us, 32 x 777 466 and 436.
 // -------------------------------------------------------------------------------------
 
 // four stored elements, all zero unless mask is ~0, as doubles
@@ -1524,16 +1525,7 @@ static hipError_t launch_prefill_t(const PrefillArgs &a, hipStream_t st)
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (!masked && !maps_ride && (e = key_features()) != hipSuccess) return e;
-  // A unit's tokens in so many shares that about eight workgroups are there for every compute unit, 64 tokens to a share
-  // at least; as many as the scratch holds
-  int shares = P > C ? 1 : 0;
-  if (P > C && U < 2048) {
-    const size_t each = U * (size_t)(d->rank * D + d->rank) * sizeof(double), most = a.part_bytes / each;
-    shares = (int)((2048 + U - 1) / U);
-    if (shares > P / 64) shares = P / 64;
-    if ((size_t)shares > most) shares = (int)most;
-    if (shares < 1) shares = 1;
-  }
+  const int shares = P > C ? (int)state_shares(U, (size_t)P, (size_t)d->rank, D, a.part_bytes) : 0;
   const bool fused = P > C && P <= 64 && U <= 512;         // (32 units x 12 tokens: 40.7 us in all, 41.6 with two launches)
   if (shares > 0 && !fused) {
     prefill_state_kernel<T, D><<<U * shares, 64 * kStateWaves, 0, st>>>((const T *)a.V, P, keep, a.psi_all, d->rank, shares,

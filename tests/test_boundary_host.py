@@ -139,6 +139,18 @@ def test_a_workspace_holds_every_shorter_prompt(units, max_prompt, more):
     assert L.lessdec_prefill(C.byref(d), None, None, None, max_prompt + 1000, None, None) == binding.EWORKSPACE
 
 
+@pytest.mark.parametrize("heads,prompt,rank,head_dim", [(32, 2000, 8, 128), (12, 2000, 32, 128), (3, 129, 16, 128), (3, 300, 20, 64),
+                                                        (3, 1000, 5, 128), (64, 777, 8, 64)])
+def test_fp32_prompts_have_room_for_the_shares_of_the_state(heads, prompt, rank, head_dim):
+    """The state of the discarded pairs is cut into shares of 64 tokens (up to 2048 workgroups in all), each of which leaves
+    rank x (head_dim + 1) doubles a unit; the rest of the workspace is 28 + 4 rank bytes a token."""
+    d = _desc(batch=1, heads=heads, dtype=binding.DTYPE_F32, rank=rank, head_dim=head_dim)
+    shares = min(-(-2048 // heads), prompt // 64)
+    rest = heads * (prompt - 63) * (28 + 4 * rank)
+    room = binding.lessdec_workspace_bytes(d, prompt) - binding.lessdec_workspace_bytes(d, 63) - rest
+    assert shares > 1 and abs(room - shares * heads * rank * (head_dim + 1) * 8) < 16 * 256
+
+
 def test_product_does_not_import_the_oracle():
     pkg = os.path.join(ROOT, "paper_2402_09398_amd")
     for dirpath, _, files in os.walk(pkg):
