@@ -6,9 +6,16 @@ namespace lessdec {
 
 // Waves per SIMD the register allocation aims for (the K and V rows held in registers
 // take 4 VGPRs per iteration, the values reusing the keys' registers).
+// The loop: few units, or fp16 rows, request eight iterations ahead with four waves (six spilled); many units of fp32 rows cover
+// each other, and registers for requests only take waves away.  us of eight steps, D = 128, eight ahead with six waves, eight
+// with four, two with eight (one row at a time): fp32 256 units x 640 slots 467, 412, - (946); 1056 x 200 740, 592, 578 (690); 2048 x
+// 200 1088, 899, 864 (894); fp16 2048 x 400 1096, 981, 1015 (1133).
+template <typename T>
+constexpr int step_ahead(int w) { return w == 8 || sizeof(T) == 2 ? 8 : 2; }
+template <typename T>
 constexpr int step_waves_per_simd(int nit, int w)
 {
-  const int n = nit == 0 ? 6 : nit <= 2 ? 6 : nit <= 7 ? 5 : nit <= 11 ? 3 : 2;
+  const int n = nit == 0 ? (step_ahead<T>(w) == 8 ? 4 : 8) : nit <= 2 ? 6 : nit <= 7 ? 5 : nit <= 11 ? 3 : 2;
   return w == 4 ? n : n < w / 4 ? w / 4 : n / (w / 4) * (w / 4);         // whole blocks
 }
 
@@ -24,9 +31,9 @@ constexpr int step_waves_per_simd(int nit, int w)
 // after the scores, into the same registers.  Loads come back to a wave in issue order, so
 // anything the head of the kernel wants early is requested before the keys, and nothing
 // after the decisions waits on a load whose address depends on them.  NIT = 0 is the
-// looped form for any capacity, eight iterations' rows requested before the first is used.
+// looped form for any capacity, several iterations' rows requested before the first is used (step_ahead).
 // 256 units x 102 slots, D = 128, fp32: 14.6 us with four waves, 21 requests a wave for 13 iterations and the sum of a row's 32
-// lanes by LDS shuffles; 8.8 now.  In the loop, one row at a time, 400 slots took 75 us a step (maps included), 46 now.
+// lanes by LDS shuffles; 8.8 now.  In the loop, one row at a time, 400 slots took 82 us a step (maps included), 41 now.
 // Bound by the chain of requests, scores, softmax and values of a unit.
 //
 // Roles: wave 0 owns the scores (phase 2); wave 1 owns the low-rank side (phi(q), the
@@ -51,7 +58,7 @@ constexpr int step_waves_per_simd(int nit, int w)
 //          freed slot (Sec. 3.2); the discarded value row is left pending.
 // =====================================================================================
 template <typename T, int D, int NIT, int W>
-__global__ __launch_bounds__(64 * W, step_waves_per_simd(NIT, W)) void step_kernel(const StepArgs a)
+__global__ __launch_bounds__(64 * W, step_waves_per_simd<T>(NIT, W)) void step_kernel(const StepArgs a)
 {
   constexpr int kThreads = 64 * W;
   constexpr int EPL = Store<T>::kPerVec;   // elements per lane
@@ -148,7 +155,7 @@ __global__ __launch_bounds__(64 * W, step_waves_per_simd(NIT, W)) void step_kern
 
   // looped form: kAhead iterations' rows (of keys or values) are requested before the first of them is used; row m is the
   // appended pair's
-  constexpr int kAhead = 8;
+  constexpr int kAhead = step_ahead<T>(W);
   auto sweep = [&](const T *rows_at, const Vec appended, auto &&use) __attribute__((always_inline)) {
     const __amdgpu_buffer_rsrc_t rs =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(rows_at), 0, C * D * (int)sizeof(T), 0x00020000);
@@ -415,15 +422,17 @@ static hipError_t launch_step_t(const StepArgs &a, hipStream_t st)
   const unsigned grid = (unsigned)a.U;
   const int need = (a.C + 1 + RPB - 1) / RPB;            // row iterations of four waves to cover C + 1 rows
 #define LESSDEC_STEP(NIT, W) step_kernel<T, D, NIT, W><<<grid, 64 * W, lds, st>>>(a)
-  // Eight waves per unit where four would take more than eleven turns and there are few units: a unit's rows are then
-  // requested at once instead of in a loop, by twice the waves.  fp32, us of eight steps: 12 units x 200 slots, D = 128, 161
-  // against 226, 256 x 400 379 / 384, 512 x 200 341 / 398, 1280 x 300 915 / 910; D = 64 256 x 400 218 / 256, 512 x 300
-  // 268 / 249.  (Sixteen waves: 154 at 12 x 200, 613 against 470 at 256 x 640.)
-  if (need > 11 && grid <= (LPR == 32 ? 1024u : 384u)) {
-    const int turns = (need + 1) / 2;
+  // Eight waves per unit where four would take more than eleven turns and there are few units.  A block with many rows in
+  // registers leaves no room for a second one on its compute unit: past 256 units the loop, whose blocks come in twos, or, with few
+  // turns, four waves.  us of eight steps, fp32, D = 128: 256 units x 200 slots eight waves 230, four 258; 320 x 200 in
+  // registers 319, in the loop 274, four waves 317; 512 x 300 425, 378, 431; 512 x 400 in the loop 449, four waves 513; 768 x 200
+  // in registers 489, four waves 421; D = 64 448 x 640 393, 350, 427; fp16, D = 128 384 x 300 (ten turns) 319, 326, 309; 512 x
+  // 700 in the loop 474, four waves 497.  (Sixteen waves: 154 against 161 at 12 x 200, 613 against 470 at 256 x 640.)
+  const int turns = (need + 1) / 2;
+  if (need > 11 && grid <= (turns <= 11 ? 256u : 512u)) {
     if (turns <= 7) LESSDEC_STEP(7, 8);
     else if (turns <= 11) LESSDEC_STEP(11, 8);
-    else if (turns <= 21) LESSDEC_STEP(21, 8);
+    else if (turns <= 21 && grid <= 256) LESSDEC_STEP(21, 8);
     else LESSDEC_STEP(0, 8);
   } else if (need <= 2) LESSDEC_STEP(2, 4);
   else if (need <= 4) LESSDEC_STEP(4, 4);
