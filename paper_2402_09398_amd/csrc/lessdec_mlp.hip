@@ -162,13 +162,18 @@ bool mlp_mfma_supported(int dtype, int D, int Rp, int R)
   return dtype == LESSDEC_DTYPE_F16 && (D == 64 || D == 128) && Rp % 32 == 0 && Rp >= 32 && R <= 16;
 }
 
-hipError_t launch_mlp(const MlpArgs &a, hipStream_t st)
+// many rows per head and R' = 128, 256, 384 or 512: weights stay in registers, rows stream through
+bool mlp_weights_in_registers(const MlpArgs &a)
 {
   const long rows_head = (long)a.B * a.rpu;
-  // many rows per head and R' = 128, 256, 384 or 512: weights stay in registers, rows stream through
-  const int ngw = a.Rp % 128 == 0 ? a.Rp / 128 : 0;
-  const long nchunk = (rows_head + 15) / 16;
-  if (ngw >= 1 && ngw <= 4 && nchunk >= 64 && rows_head < (1L << 31) - 64) {
+  return a.Rp % 128 == 0 && a.Rp <= 512 && rows_head > 63 * 16 && rows_head < (1L << 31) - 64;
+}
+
+hipError_t launch_mlp(const MlpArgs &a, hipStream_t st)
+{
+  if (mlp_weights_in_registers(a)) {
+    const int ngw = a.Rp / 128;
+    const long nchunk = ((long)a.B * a.rpu + 15) / 16;
     long parts = 1024 / a.Hh;                              // about four workgroups per compute unit
     if (parts < 1) parts = 1;
     if (parts > nchunk / 8) parts = nchunk / 8;            // at least 8 chunks behind every weight load

@@ -527,7 +527,8 @@ static hipError_t launch_rows_t(const RowArgs &a, hipStream_t st)
       (const __half *)a.Q + q, K, (const __half *)a.V + kv, nu * a.G, a.G, a.P, digits, words, a.lse + rows, out, a.zero0 + u,      \
       a.zero1 + u, mk, n_maps ? *a.maps : MlpArgs{}, grid)
     __half *out = a.out != nullptr ? (__half *)a.out + q : nullptr;
-    const unsigned n_maps = a.maps && u == 0 ? mlp_psi_blocks(*a.maps, kPsiTiles) : 0;      // all units' with the first share
+    // (maps ride with at most 8192 workgroups of rows, whose keys are one share)
+    const unsigned n_maps = a.maps && u == 0 ? mlp_psi_blocks(*a.maps, kPsiTiles) : 0;
     if (a.masked) {
       if (out != nullptr) LESSDEC_ROWS(true, true, false); else LESSDEC_ROWS(false, true, false);
     } else if (n_maps) {
@@ -543,13 +544,27 @@ static hipError_t launch_rows_t(const RowArgs &a, hipStream_t st)
 }
 
 // Whether psi rides along: it needs nothing of the row pass and is bound by other instructions, so it fills what the longest
-// sweeps leave idle, and a launch is saved (us of a whole prompt phase, D = 128, psi in a launch of its own against riding along:
-// 32 units x 64 tokens 47.2 and 40.0, 32 x 777 151.8 and 130.2, 64 x 1000 269 and 234, 128 x 2000 1097 and 1041).  Past 8192
-// workgroups of rows the maps that keep a head's weights in registers win: 2048 x 512 1700 and 1760, 2048 x 1024 4530 and
-// 4610 (128 x 4 heads x 2048: 3160 and 3090).
-bool rows_f16_take_maps(unsigned U, int G, int P)
+// sweeps leave idle, and a launch is saved; but it reads a head's weights again for every 64 rows, where a launch of its own keeps them
+// in registers (other hidden widths have no such form: riding is 5 % and more faster there).  us of a whole prompt phase, psi
+// in a launch of its own against riding along, D = 128, R' = 512, rank 8 unless said:
+//   2048 blocks of maps        32 units x 64 tokens 47 and 40, 32 x 777 140 and 119, 64 x 1000 269 and 234, 2048 x 64 184 and 178
+//   4096, short sweeps         4096 x 64 349 and 353 (4096 x 40, 2560 blocks: 267 and 263), 1024 x 256 406 and 402; rank 4 334 and
+//                              352, 394 and 410; rank 16 389 and 385, 446 and 437; R' = 256 298 and 311, 360 and 370
+//   4096, 500 tokens           512 x 512 495 and 485; rank 4 489 and 491; R' = 256 454 and 453
+//   8192                       4096 x 128 629 and 648 (rank 4 621 and 667), 1024 x 512 884 and 901, 512 x 1000 1173 and 1161 (rank 4
+//                              1154 and 1174), 256 x 2000 1842 and 1806 (rank 4 1814 and 1816)
+//   8192, D = 64               4096 x 128 493 and 481, 1024 x 512 678 and 654; R' = 256 419 and 430, 607 and 604
+//   more than 8192 workgroups  2048 x 400 1227 and 1265, 2048 x 1024 4530 and 4610
+// (128 units x 4 heads x 500: 378 and 355, x 2000, 64 units: 1607 and 1550)
+bool rows_f16_take_maps(const MlpArgs &maps, unsigned U, int G)
 {
-  return (size_t)U * G * ((P + 16 * kPrefillWaves - 1) / (16 * kPrefillWaves)) <= 8192;
+  const int ngrp = (maps.rpu + 16 * kPrefillWaves - 1) / (16 * kPrefillWaves);
+  if ((size_t)U * G * ngrp > 8192) return false;
+  if (!mlp_weights_in_registers(maps)) return true;
+  unsigned most = ngrp >= 32 ? 8192 : ngrp >= 8 ? 4096 : 2048;
+  if (maps.D == 64 && (maps.Rp > 256 || ngrp > 8)) most = 8192;
+  if (maps.D == 128 && maps.Rp == 512 && maps.R % 8 == 0) most = ngrp > 8 ? 8192 : ngrp > 1 || maps.R > 8 ? 4096 : 3072;
+  return mlp_psi_blocks(maps, kPsiTiles) <= most;
 }
 
 hipError_t launch_rows_f16(const RowArgs &a, int D, hipStream_t st)
