@@ -12,6 +12,12 @@ __device__ inline unsigned lds_offset(const unsigned char *p) { return (unsigned
 // (readable from base on) and to are the same for the whole wave.  Written as asm because the compiler, which
 // cannot tell the buffers of a pipeline apart, would wait for every transfer before the next LDS read; nothing is
 // returned in registers.  The readers stand behind lds_arrived<..>() of the wave that loaded and a barrier.
+// (The wait states between a vector instruction that writes a scalar register and a load that reads it are the compiler's affair for
+// its own loads only: base, bytes and to come from scalar arithmetic, which needs none; a test reads the assembly.  m0 is a
+// reserved register, about which the compiler warns in a clobber list; it is named so that no value of its own is
+// expected to live there across the block.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 template <int BYTES>
 __device__ inline void lds_load(const void *base, unsigned bytes, int offset, unsigned char *to)
 {
@@ -19,10 +25,13 @@ __device__ inline void lds_load(const void *base, unsigned bytes, int offset, un
   const unsigned long long b = reinterpret_cast<unsigned long long>(base);
   const v4u rsrc = {(unsigned)b, (unsigned)(b >> 32) & 0xffffu, bytes, 0x00020000u};
   if constexpr (BYTES == 16)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" : : "s"(lds_offset(to)), "v"(offset), "s"(rsrc) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 : : "s"(lds_offset(to)), "v"(offset), "s"(rsrc) : "m0", "memory");
   else
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" : : "s"(lds_offset(to)), "v"(offset), "s"(rsrc) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
+                 : : "s"(lds_offset(to)), "v"(offset), "s"(rsrc) : "m0", "memory");
 }
+#pragma clang diagnostic pop
 // all but the wave's latest N memory operations have arrived
 template <int N>
 __device__ inline void lds_arrived()

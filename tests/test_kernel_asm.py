@@ -3,6 +3,9 @@ compiler makes of this repository's own files (CPU: hipcc cross-compiles for gfx
 
 * A matrix instruction may read a vector instruction's result only two wait states after it.  The compiler
   counts them for the instructions that it makes itself, not for those inside an asm block.
+* A load may read a scalar register that a vector instruction wrote only five wait states after it; again the compiler
+  counts them for its own loads only.  And a load from memory into the LDS takes its place there from m0, which an asm
+  block writes without the compiler's help.
 * A buffer load is in range where its vector offset lies below num_records less its scalar offset: a load
   that relies on reading zeros past the end keeps the scalar offset within num_records.
 """
@@ -67,6 +70,55 @@ def test_the_reader_of_wait_states():
     far = [near[0], "s_nop 1", near[2]]
     assert len(early_matrix_reads(near)) == 1 and not early_matrix_reads(far)
     assert early_matrix_reads([near[0], near[2]]) and not early_matrix_reads(["v_mov_b32_e32 v12, 0", near[2]])
+
+
+def scalars(operand):
+    """Scalar registers an operand names: s7, s[4:7], m0."""
+    m = re.fullmatch(r"s(?:(\d+)|\[(\d+):(\d+)\])", operand)
+    if not m:
+        return {operand} if operand == "m0" else set()
+    lo, hi = (m.group(1), m.group(1)) if m.group(1) else (m.group(2), m.group(3))
+    return set(range(int(lo), int(hi) + 1))
+
+
+SCALAR_WAIT_STATES = 5
+
+
+def scalar_hazards(lines):
+    """Loads and stores that read a scalar register too soon after a vector instruction wrote it, and instructions other than
+    an asm block's own that touch m0: (line number, text, cause)."""
+    found, recent, in_asm = [], [], False     # recent: (wait states since, registers written, text)
+    for n, line in enumerate(lines, 1):
+        in_asm = (in_asm or "#ASMSTART" in line) and "#ASMEND" not in line
+        text = line.split(";")[0].strip()
+        if not text or text.startswith(".") or text.endswith(":"):
+            continue                          # (a label: what fell through to it counts on)
+        op, _, rest = text.partition(" ")
+        operands = [x.strip().split(" ")[0] for x in re.split(r",\s*(?![^\[]*\])", rest)]
+        if not in_asm and "m0" in operands:
+            found.append((n, text, "m0"))
+        if op.startswith(("buffer_", "global_", "flat_", "scratch_")):
+            reads = set().union(*(scalars(x) for x in operands))
+            found += [(n, text, t) for waited, regs, t in recent if waited < SCALAR_WAIT_STATES and regs & reads]
+        states = int(operands[0], 0) + 1 if op == "s_nop" else 1
+        recent = [(waited + states, regs, t) for waited, regs, t in recent if waited + states < SCALAR_WAIT_STATES]
+        if op.startswith("v_") and scalars(operands[0]):
+            recent.append((0, scalars(operands[0]), text))
+    return found
+
+
+def test_the_reader_of_scalar_hazards():
+    load = "buffer_load_dwordx4 v3, s[12:15], 0 offen lds"
+    assert scalar_hazards(["v_readfirstlane_b32 s13, v1", "s_nop 3", load])
+    assert not scalar_hazards(["v_readfirstlane_b32 s13, v1", "s_nop 4", load]) and not scalar_hazards(["s_mov_b32 s13, s1", load])
+    assert scalar_hazards(["v_readlane_b32 s7, v9, 3", ";;#ASMSTART", "s_mov_b32 m0, s7", "s_nop 0", load, ";;#ASMEND"]) == []
+    assert scalar_hazards(["s_mov_b32 m0, s7"]) and scalar_hazards(["v_cmp_lt_i32_e64 s[14:15], v0, v1", load])
+
+
+@pytest.mark.parametrize("name", [s for s in hip_build.SOURCES if "lessdec_lds.h" in (hip_build.CSRC / s).read_text()])
+def test_loads_into_the_lds_read_settled_scalars(assembly, name):
+    lines = assembly(name)
+    assert any("lds" in x.split(";")[0] for x in lines) and scalar_hazards(lines) == []
 
 
 @pytest.mark.parametrize("name", [s for s in hip_build.SOURCES
