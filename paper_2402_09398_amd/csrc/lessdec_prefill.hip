@@ -21,7 +21,6 @@ namespace lessdec {
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
-typedef _Float16 v4h __attribute__((ext_vector_type(4)));
 
 template <typename T, int D>
 struct Chunk {
@@ -651,7 +650,6 @@ __global__ __launch_bounds__(64 * kPrefillWaves) void prefill_colpass_kernel(
 // two slots, a matrix instruction blocks about two) and by the clock that the card lowers meanwhile (2.1 GHz).
 // -------------------------------------------------------------------------------------
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
-typedef unsigned v4u __attribute__((ext_vector_type(4)));
 constexpr int kApproxQueries = 64; // queries per chunk
 template <int D, int KT>
 __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per_eu(3, 3))) void prefill_colapprox_kernel(

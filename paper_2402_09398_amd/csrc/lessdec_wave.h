@@ -74,14 +74,6 @@ __device__ inline double row_sum(double v)
   }
 }
 
-template <typename T>
-__device__ inline typename Store<T>::Vec load_vec_nt(const T *p)
-{
-  typename Store<T>::Vec v;
-  const u4v t = __builtin_nontemporal_load(reinterpret_cast<const u4v *>(p));
-  __builtin_memcpy(&v.raw, &t, 16);
-  return v;
-}
 // Stores of state that go through the L2 to memory as they are issued (system scope).  A line
 // that stays dirty in an L2 is written back when the kernel ends, before the next launch can
 // start: with 16 MB written per launch that takes 2.4 us after plain stores, 1.3 us after
