@@ -127,7 +127,13 @@ typedef struct lessdec_desc {
 
 /*
  * Bytes of scratch the calls need.  max_prompt = 0: enough for lessdec_step only;
- * otherwise enough for lessdec_prefill with prompts up to max_prompt tokens as well.
+ * otherwise enough for lessdec_prefill with prompts up to max_prompt tokens as well (the size never
+ * falls with max_prompt).  A prompt needs some 28 + 4 rank bytes a token of every unit (8 more for
+ * every further query head), with fp16 storage another 4 head_dim, 352 MiB of these at most (a unit
+ * longer than that: its own), with fp32 storage up to 64 MiB for the sums of the state; masked
+ * prompts (LESSDEC_FLAG_LAMBDA and _PROMPT_STEPWISE) 4 rank (q_per_kv + head_dim / 64) more.  2048 units of
+ * 1024 tokens (fp16, head_dim 128, rank 8): 478 MiB.  Layers of one shape can share a workspace
+ * (see lessdec_desc), so that a model holds it once.
  * Host only.  Returns 0 if the descriptor's shape fields are invalid.
  */
 size_t lessdec_workspace_bytes(const lessdec_desc *desc, int32_t max_prompt);

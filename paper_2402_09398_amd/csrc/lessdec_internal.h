@@ -122,11 +122,13 @@ hipError_t launch_fill_empty(float *parts, size_t count, hipStream_t st);
 hipError_t launch_reset(const lessdec_desc *d, hipStream_t st);
 
 // Digit planes of prompt keys: four bytes an element, a word per tile of 32 keys.  They live between the kernel that writes them
-// and the row pass, so units take turns in a part of the workspace of limited size: 640 MiB hold a million tokens of
-// D = 128 (a share of the work that fills the chip many times over), and a unit longer than that gets its own size.
+// and the row pass, so units take turns in a part of the workspace of limited size: 352 MiB hold 0.7 million tokens of
+// D = 128 (a share of the work that fills the chip many times over), and a unit longer than that gets its own size.  Whole prompt
+// phases, us, with 640, 352, 264 and 128 MiB: 2048 units x 1024 tokens 4490, 4500, 4519, 4699, 128 x 8192 10930, 10550, 10590, 10970,
+// 2048 x 700 2445, 2465, 2472, -, 320 x 2048 masked 1644, 1645, 1666, 1683.
 // The part's size is a limit in bytes and not a number of units, so that it never falls with P: a workspace for a prompt
 // holds every shorter one.
-constexpr size_t kDigitBytes = (size_t)640 << 20;
+constexpr size_t kDigitBytes = (size_t)352 << 20;
 inline size_t digit_bytes_unit(size_t P, size_t D) { return (P + 31) / 32 * (32 * D * 4 + 4); }
 inline size_t digit_bytes(size_t U, size_t P, size_t D)
 {

@@ -55,3 +55,27 @@ def test_values_without_digits(which, head_dim):
     rep.failures.extend(hz.check_every_unit(w, res, flags=FLAGS))
     print("\n" + rep.summary(), flush=True)
     assert rep.ok(), rep.failures[:10]
+
+
+def test_units_in_several_shares():
+    """More tokens than the digits' part of the workspace holds (0.7 million of D = 128): the first, middle and last units as
+    in a call of their own."""
+    import torch
+    batch, heads, p, d = 400, 32, 112, 128
+    g = torch.Generator(device="cuda").manual_seed(3)
+    full = {n: torch.randn(batch, heads, p, d, generator=g, device="cuda").half() for n in "QKV"}
+
+    def prefill(x):
+        gpu = hz.make_gpu(shape(p, batch=x["Q"].shape[0], heads=heads, n_recent=20), flags=FLAGS)
+        out = torch.empty_like(x["Q"])
+        gpu.prefill(x["Q"].contiguous(), x["K"].contiguous(), x["V"].contiguous(), out=out)
+        torch.cuda.synchronize()
+        return [t.reshape(x["Q"].shape[0], heads, *t.shape[1:]) if t.shape[0] != x["Q"].shape[0] else t
+                for t in (out, gpu.acc, gpu.pos, gpu.H, gpu.z)]
+
+    whole = prefill(full)
+    for part in (slice(0, 3), slice(197, 203), slice(397, 400)):
+        (out, acc, pos, H, z), (out1, acc1, pos1, H1, z1) = ([t[part] for t in whole], prefill({n: x[part] for n, x in full.items()}))
+        assert torch.equal(out, out1) and torch.equal(pos, pos1) and torch.equal(H, H1) and torch.equal(z, z1)
+        # column sums of at most p positive terms, which another number of units adds in another order
+        assert torch.allclose(acc, acc1, rtol=p * 2.0 ** -53, atol=0)

@@ -42,7 +42,7 @@ def test_scales_and_lowest_digits(kind, head_dim):
 
 
 def test_units_in_several_shares():
-    """More tokens than the digits' part of the workspace holds (about 1.3 million of D = 128): the first and the last units
+    """More tokens than the digits' part of the workspace holds (0.7 million of D = 128): the first and the last units
     as in a call of their own."""
     import torch
     batch, heads, p, d = 400, 32, 112, 128
