@@ -645,8 +645,9 @@ __global__ __launch_bounds__(64 * kPrefillWaves) void prefill_colpass_kernel(
 // at a time through the LDS, so that a query row crosses the L2 once per workgroup; the next query tile's
 // products stand beside this one's exponentials.  The chunks go straight into the LDS, two ahead of their use: with one ahead,
 // through registers, the sweep waited for memory wherever a chunk's work was shorter than a round trip, and the
-// registers held it to two waves a SIMD (three now).  717 -> 582 us for 2048 units x 1024 tokens, 1334 -> 1270 for 128 x
-// 8192, 601 -> 511 for 128 x 4 heads x 2048.  Bound by issue (an instruction in 83 % of the cycles: exponentials take
+// registers held it to two waves a SIMD (three now, for which the form of four key tiles and D = 128 keeps four registers in scratch
+// memory, 20 bytes a lane; without them, at two waves, 729, 1445 and 615 us).  717 -> 582 us for 2048 units x 1024 tokens,
+// 1334 -> 1270 for 128 x 8192, 601 -> 511 for 128 x 4 heads x 2048.  Bound by issue (an instruction in 83 % of the cycles: exponentials take
 // two slots, a matrix instruction blocks about two) and by the clock that the card lowers meanwhile (2.1 GHz).
 // -------------------------------------------------------------------------------------
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));

@@ -50,10 +50,10 @@ typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 // (psi(K) phi(Q)^T on fp64 matrix tiles, R / 4 instructions; values through the LDS as before).  m rises once to the integer
 // below log2 of an upper bound of the low-rank weights, phi(q) . max_j psi(k_j).  Leaves lse_t = m_t ln 2 + ln(sum of the
 // entries that H2O's scores are normalised by): all, or with the sparse-denominator flag the exponentials.
-// 320 units x 2048 tokens, window 158, rank 16: 568 us and 70 for the digits, 1158 with scores on fp64 matrix tiles.
+// 320 units x 2048 tokens, window 158, rank 16: 551 us and 72 for the digits, 1158 with scores on fp64 matrix tiles.
 //
-// 2048 units x 1024 tokens: 3600 us before, 2545 now and 270 for the digits (1.6 GB at 5.9 TB/s); 128 x 8192:
-// 11000, 8340 and 125; 32 x 777: 65, 51 and 6.
+// 2048 units x 1024 tokens: 3600 us before, 2480 now and 217 for the digits (1.34 GB at 6.2 TB/s), three shares of units; 128 x
+// 8192: 11000, 8030 and 109, two; 32 x 777: 65, 51 and 6.
 // -------------------------------------------------------------------------------------
 constexpr int kRowKeys = 32;
 constexpr double kSlack = 15.0;                           // weights up to 2^15: they fit a half
@@ -154,8 +154,9 @@ __global__ __launch_bounds__(64 * kPrefillWaves) __attribute__((amdgpu_waves_per
   const double cs = kLog2E / sqrt((double)D);             // q . k to base-2 units
 
   // Tile kt into the LDS: the workgroup's waves bring 1 KiB pieces, key digits as they lie, value rows with their 16-byte
-  // chunks permuted within a row (val_swizzle) so that the transposing reads meet no bank twice.  Rows past the
-  // prompt repeat the last one: they come after every query.
+  // chunks permuted within a row (val_swizzle) so that the four rows of a 16-lane group lie in different banks.  (Two groups,
+  // whose rows are four apart, still meet in them: two cycles more for each transposing read, 27 % of the cycles that the LDS is
+  // busy at 8192 tokens.)  Rows past the prompt repeat the last one: they come after every query.
   constexpr int RB = 2 * D, kRowsPer = 1024 / RB, CH = RB / 16;       // bytes, rows and chunks of a value piece
   auto load_tile = [&](int kt, unsigned char *key, unsigned char *val, bool keys) __attribute__((always_inline)) {
     int lane = l;
@@ -601,7 +602,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   const int32_t *li = list ? list + u * (size_t)P : nullptr;
   const int n = list ? count[u] : P, nblk = (P + 15) / 16;
   const double cs = kLog2E / sqrt((double)D);
-  // block of 16 digits [(kc, g)][key], the key's place turned by the block as in the row pass
+  // block of 16 digits [(kc, g)][key], the key's place turned by the block, so that the writes of one key meet different banks
   auto key_at = [](int t, int plane, int kc, int gg, int row) {
     return t * kTile + plane * (KC * 1024) + (kc * 4 + gg) * 256 + (row ^ (2 * (kc * 4 + gg))) * 16;
   };

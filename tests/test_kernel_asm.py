@@ -128,8 +128,8 @@ def test_matrix_instructions_wait_for_vector_results(assembly, name):
 
 
 def test_prompt_rows_past_the_end_are_in_the_range_check(assembly):
-    """The row pass reads a tile through a buffer of the rows that the prompt still has, one at least: constant
-    scalar offsets stay below a row of 64 halves, the others are clamped to the buffer's size."""
+    """The row pass reads a tile through a buffer of a whole tile, rows past the prompt clamped to the last one by the vector
+    offset; scalar offsets are constants below a row of 64 halves, or clamped themselves."""
     written, loads = {}, 0
     for line in assembly("lessdec_rows.hip"):
         op, _, rest = line.split(";")[0].strip().partition(" ")
