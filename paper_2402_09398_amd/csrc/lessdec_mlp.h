@@ -68,7 +68,7 @@ __device__ inline void mlp_activate(const v4f &h0, const v4f &h1, v8h &bhi, v8h 
   float x[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    x[i] = gelu_fast_f32(i < 4 ? h0[i] : h1[i - 4]);
+    x[i] = gelu_exp2_f32(i < 4 ? h0[i] : h1[i - 4]);
     asm("" : "+v"(x[i]));                                  // one fp32 value for both halves of the split
   }
 #pragma unroll

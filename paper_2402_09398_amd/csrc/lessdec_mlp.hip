@@ -27,14 +27,17 @@ __global__ __launch_bounds__(256) void mlp_pair_kernel(const MlpArgs a, const Ml
 // groups; after two chunks the block adds the four layer-2 sums through the LDS and finishes the
 // outputs as above (same arithmetic in the same order as mlp_psi_block: identical results).  The
 // next chunk's rows are requested before the current chunk's arithmetic.
-// Bound by vector instructions (17 per activation, two of them transcendental).  With one max, one
-// mixed-precision fma per low half, one barrier per 32 rows in place of three per 16, and layer 1 of the
-// next group issued between the activations of this one: 920 -> 756 us for 2048 units x 1024
-// tokens, 460 -> 391 for 128 x 8192 (R' = 512, R = 8).
+// Bound by vector instructions (12.5 per activation, one of them transcendental, where there were 17 and two) and the clock that
+// the card lowers under them (2.1 GHz).  With one max, one mixed-precision fma per low half, one barrier per 32 rows in place of
+// three per 16, and layer 1 of the next group issued between the activations of this one: 920 -> 756 us for 2048 units x 1024
+// tokens, 460 -> 391 for 128 x 8192 (R' = 512, R = 8).  Then (799 on another card) an activation without a reciprocal: 760; the
+// finish without divisions and W3's products requested together, and a row's unit found by a multiplication: 700.  (Four
+// waves a SIMD, eight waves of two groups each, rows by DMA through the LDS, the polynomial's constants as literals, which makes a
+// multiply-add 2.7 cycles there: 4 % fewer cycles at a clock 4 % lower, no gain.)
 // grid = Hh * parts (head fastest), every block a contiguous share of the head's chunks.
 template <int D, int NGW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void mlp_rows_kernel(const MlpArgs a,
-                                                                                                  int parts)
+                                                                                                  int parts, unsigned rpu_mul, int rpu_shift)
 {
   __shared__ float s_red[2][4][16][32 + 1];                // [pair of chunks, in turn][wave][r][row]
   __shared__ double s_h2[32][17];                          // [row][r], each row written and read by one wave
@@ -43,14 +46,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int h = (int)blockIdx.x % Hh, part = (int)blockIdx.x / Hh;
   const __half *W1 = a.W1 + (size_t)h * Rp * D;
   const __half *W2 = a.W2 + (size_t)h * R * Rp;
-  // 32-bit row arithmetic (the launcher checks that a head's rows fit): a 64-bit division per row
-  // would be a long instruction sequence
+  // 32-bit row arithmetic (the launcher checks that a head's rows fit) and a division by multiplication: rpu_mul = floor(2^(31 + s) /
+  // rpu) + 1 with s = rpu_shift = ceil(log2 rpu) gives i / rpu = i rpu_mul 2^-(31 + s) for every i below 2^31
   const unsigned rows_head = (unsigned)a.B * (unsigned)a.rpu, rpu = (unsigned)a.rpu;
   const unsigned nchunk = (rows_head + 15) / 16;
   const unsigned ch0 = (unsigned)((unsigned long)nchunk * part / parts);
   const unsigned ch1 = (unsigned)((unsigned long)nchunk * (part + 1) / parts);
   auto global_row = [&](unsigned i) -> size_t {
-    const unsigned bb = i / rpu, p = i - bb * rpu;
+    const unsigned bb = __umulhi(2 * i, rpu_mul) >> rpu_shift, p = i - bb * rpu;   // bb = i / rpu
     return ((size_t)bb * Hh + h) * rpu + p;
   };
   MlpTiles<D> w[NGW];
@@ -120,7 +123,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       if (r < R && i < rows_head) {
         double acc3 = 0.0;
         if (a.W3 != nullptr) {
-          for (int j = 0; j < R; ++j) acc3 = fma(s_h2[row][j], s_w3[r][j], acc3);
+          // (eight at a time, all requested before the first is used; past R both are zero)
+          for (int j = 0; j < nr; j += 8)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) acc3 = fma(s_h2[row][j + i], s_w3[r][j + i], acc3);
         } else {
           acc3 = s_h2[row][r];
         }
@@ -178,7 +184,10 @@ hipError_t launch_mlp(const MlpArgs &a, hipStream_t st)
     if (parts < 1) parts = 1;
     if (parts > nchunk / 8) parts = nchunk / 8;            // at least 8 chunks behind every weight load
     const unsigned grid = (unsigned)(a.Hh * parts);
-#define LESSDEC_MLP_ROWS(DD, NG) mlp_rows_kernel<DD, NG><<<grid, 256, 0, st>>>(a, (int)parts)
+    int shift = 0;
+    while ((1L << shift) < a.rpu) ++shift;
+    const unsigned mul = (unsigned)((1UL << (31 + shift)) / (unsigned long)a.rpu + 1);
+#define LESSDEC_MLP_ROWS(DD, NG) mlp_rows_kernel<DD, NG><<<grid, 256, 0, st>>>(a, (int)parts, mul, shift)
     if (a.D == 128) {
       if (ngw == 1) LESSDEC_MLP_ROWS(128, 1); else if (ngw == 2) LESSDEC_MLP_ROWS(128, 2);
       else if (ngw == 3) LESSDEC_MLP_ROWS(128, 3); else LESSDEC_MLP_ROWS(128, 4);
