@@ -74,6 +74,56 @@ __device__ inline double row_sum(double v)
   }
 }
 
+// x of the lane X away added, X = 8, 16 or 32: DPP or a lane swap, without a trip through the LDS.
+template <int X>
+__device__ inline float add_xor(float x)
+{
+  typedef unsigned v2u __attribute__((ext_vector_type(2)));
+  static_assert(X == 8 || X == 16 || X == 32, "");
+  const unsigned u = __float_as_uint(x);
+  if constexpr (X == 8) {
+    return x + __uint_as_float((unsigned)dpp_mov<0x128>((int)u));       // row_ror 8
+  } else {
+    const v2u p = X == 16 ? __builtin_bit_cast(v2u, __builtin_amdgcn_permlane16_swap(u, u, false, false))
+                          : __builtin_bit_cast(v2u, __builtin_amdgcn_permlane32_swap(u, u, false, false));
+    return __uint_as_float(p.x) + __uint_as_float(p.y);
+  }
+}
+// Half of a reduce-scatter: lanes whose bit X is clear get the pair's sum of `lo`, the others that of `hi`.
+template <int X>
+__device__ inline float scatter_add(float lo, float hi, int lane)
+{
+  typedef unsigned v2u __attribute__((ext_vector_type(2)));
+  static_assert(X == 8 || X == 16, "");
+  if constexpr (X == 8) {
+    const float send = lane & X ? lo : hi, keep = lane & X ? hi : lo;
+    return keep + __uint_as_float((unsigned)dpp_mov<0x128>((int)__float_as_uint(send)));
+  } else {
+    const v2u p = __builtin_bit_cast(v2u, __builtin_amdgcn_permlane16_swap(__float_as_uint(lo), __float_as_uint(hi), false, false));
+    return __uint_as_float(p.x) + __uint_as_float(p.y);
+  }
+}
+// Combines the 64 / LPR row groups' partial sums of the same eight columns: a lane ends with four of them (the upper four where its bit
+// LPR is set), summed over all groups, and with f summed over the groups that differ in more than that bit.
+template <int LPR>
+__device__ inline void combine_row_groups(float (&o)[8], float (&f)[4], int lane)
+{
+#pragma unroll
+  for (int i = 0; i < 4; ++i) o[i] = scatter_add<LPR>(o[i], o[i + 4], lane);
+  if constexpr (LPR == 8) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      o[i] = add_xor<16>(o[i]);
+      f[i] = add_xor<16>(f[i]);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    o[i] = add_xor<32>(o[i]);
+    f[i] = add_xor<32>(f[i]);
+  }
+}
+
 // Stores of state that go through the L2 to memory as they are issued (system scope).  A line
 // that stays dirty in an L2 is written back when the kernel ends, before the next launch can
 // start: with 16 MB written per launch that takes 2.4 us after plain stores, 1.3 us after

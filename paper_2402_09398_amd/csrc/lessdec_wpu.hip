@@ -1,6 +1,8 @@
 // Decode step (Algorithm 1), streaming form: one wave per unit.  The layer-2 sums of the step's
 // feature maps come from the feature-map jobs (lessdec_mlp.h): the first workgroups of this very
 // launch (FUSED) or the launch before it (lessdec_mlp.hip).
+#include <type_traits>
+
 #include "lessdec_mlp.h"
 #include "lessdec_wave.h"
 
@@ -18,9 +20,15 @@ constexpr int kWpuSpinLimit = 1 << 14;   // FUSED: polls of the feature-map entr
 // the XCD whose L2 holds the feature-map sums written for them).  The waves of a block share
 // nothing and never meet at a barrier; each is on its own from the first instruction.
 // (SPLIT, for launches with few units: the block is one unit and its waves take every nw-th
-// load of each stream.  They meet twice: when the scores are complete, after which each wave
-// works out phase 2 for itself and only the lead wave stores; and when the partial outputs
-// are complete, which the lead wave adds in wave order and finishes.)
+// load of each stream.  They meet twice: when the scores are complete, and when the partial outputs are, which one wave
+// adds in wave order and finishes.  In between every wave works out the exponentials for itself; the rest of phase 2 is
+// shared out, since one wave alone issues an instruction every nine cycles and a few hundred of them were half of the step:
+// waves 0 and 1 work out the denominator, then wave 0 phi(q) H and the output and wave 1 the bookkeeping, the choice of the
+// discarded pair and its stores; wave 2 finishes psi of the new key, wave 3 folds the pending pair into H and z.  What one
+// wave stores and another loads is back in its registers before they first meet.  32 units x 204 slots, a step: 13.5 ->
+// 10.3 us (entries asked for behind the keys, where a wave that came too early slept a microsecond, and shared out: 10.9;
+// exponentials and bookkeeping without branches, row groups combined by lane swaps, partial outputs read at once: 10.3);
+// 512 x 408 24.2 -> 23.5, 256 x 102 11.8 -> 9.9, 640 x 162 at rank 16 27.9 -> 24.0.)
 //
 // A cache row is LPR = D / 8 lanes of 16 bytes, one load instruction covers RPI = 64 / LPR
 // rows.  The rows of K and then of V pass through a ring of DEPTH registers per lane: each
@@ -73,7 +81,7 @@ constexpr int kWpuSpinLimit = 1 << 14;   // FUSED: polls of the feature-map entr
 // =====================================================================================
 template <int D, int NR2, int RM, int DEPTH, bool SPLIT, bool FUSED>
 __global__ __launch_bounds__((FUSED && !(SPLIT && NR2 > 2) ? kWpuFusedUnits : kWpuUnits) * kWave,
-                             FUSED && !(SPLIT && NR2 > 2) ? ((SPLIT || NR2 > 2 || RM > 8) ? 3 : 4) : 1) void wpu_step_kernel(
+                             FUSED ? ((SPLIT || NR2 > 2 || RM > 8) ? 3 : 4) : 1) void wpu_step_kernel(
     void *k_cache_, const void *q_, const void *k_, int crp_, int hb_, int xs_, int n_mlp_, const void *Wq1_,
     const void *Wk1_, const void *Wq2_, const StepArgs a)
 {
@@ -119,7 +127,11 @@ __global__ __launch_bounds__((FUSED && !(SPLIT && NR2 > 2) ? kWpuFusedUnits : kW
   // SPLIT: the waves of the block share one unit, wave w taking every nw-th load of each
   // stream; otherwise a wave is a unit.
   const int nw = SPLIT ? upb : 1, wv = SPLIT ? wave : 0;
-  const bool lead = !SPLIT || wave == 0;                     // the wave that writes the unit's state
+  constexpr bool kTailEarly = SPLIT && NR2 <= 4 && RM / (RPI / 2) <= 4;   // (below; else the registers do not reach)
+  // Who does what behind the scores (SPLIT: the parts of a step that its waves need not all work out; else the wave does
+  // everything): the output; the bookkeeping and the pair that goes in; psi of the new key; the fold into H and z.
+  const bool out_wave = !SPLIT || wave == 0, book_wave = !SPLIT || wave == 1;
+  const bool psi_wave = !SPLIT || wave == (nw > 2 ? 2 : 1), fold_wave = !SPLIT || wave == (kTailEarly ? (nw > 2 ? 3 : 1) : 0);
   const int bb = SPLIT ? chunk : chunk * upb + wave;
   if (bb >= B_) return;                                      // uniform over the unit's waves
   const int u = bb * Hh + h;
@@ -190,9 +202,7 @@ __global__ __launch_bounds__((FUSED && !(SPLIT && NR2 > 2) ? kWpuFusedUnits : kW
   const int m = n < C ? n : C;          // live slots are 0..m-1 (slots fill in order)
   const int rows = m + 1;               // + the appended pair (K', V' of Eq. 3)
   const bool full = (m == C);
-  // (accumulated scores and positions: a single wave asks for them in phase 2, two passes of the
-  // value stream before it needs them; waves that share a unit must have them before they meet,
-  // since the lead wave stores the new ones after that)
+  // (accumulated scores and positions are asked for in phase 2, ahead of the passes of the value stream before their use)
   double acc_pre[NR2];
   int pos_pre[NR2];
   auto request_scores = [&]() __attribute__((always_inline)) {
@@ -204,10 +214,34 @@ __global__ __launch_bounds__((FUSED && !(SPLIT && NR2 > 2) ? kWpuFusedUnits : kW
       pos_pre[i] = a.pos[idx];
     }
   };
-  if constexpr (SPLIT) request_scores();
   double z_lane = a.z[(size_t)u * R + rl];                   // lane r < R
   const float ppsi_lane = a.pend_psi[(size_t)u * R + rl];
   float psie_lane = a.psi[((size_t)u * C + (pend.slot >= 0 && pend.slot < C ? pend.slot : 0)) * R + rl];
+  // This lane's share of H and of the pending value row, wanted after the value stream: four
+  // consecutive columns (those the reduce-scatter of phase 3 leaves it with) of every NHB-th
+  // row, so that one 16-byte load per lane covers NHB whole rows of H per instruction.
+  // (A single wave asks behind the keys, FUSED inside phase 2, once the feature-map entries have given their registers back.
+  // Waves that share a unit must have before they meet what others store the new state of after that.)
+  constexpr int NHB = RPI / 2, HR = RM / NHB;
+  const int col0 = lr * EPL + ((lane & LPR) ? 4 : 0);
+  const int hb = lane / (2 * LPR);                           // which rows: r = NHB * i + hb
+  Vec vnv;
+  float4 hreg[HR];
+  uint2 pend_v_h;
+  auto request_pending = [&]() {
+    pend_v_h = *reinterpret_cast<const uint2 *>(reinterpret_cast<const T *>(a.pend_v) + (size_t)u * D + col0);
+  };
+  auto request_tail = [&]() {
+    vnv = load_vec<T>(vn + lr * EPL);
+#pragma unroll
+    for (int i = 0; i < HR; ++i) {
+      const int r = NHB * i + hb;
+      hreg[i] = *reinterpret_cast<const float4 *>(a.H + ((size_t)u * R + (r < R ? r : R - 1)) * D + col0);
+    }
+    if constexpr (!SPLIT) request_pending();
+  };
+  if constexpr (SPLIT) request_pending();
+  if constexpr (kTailEarly) request_tail();
   __builtin_amdgcn_sched_barrier(0);
 
   // The stream: position s < nitp is load s of K, position nitp + t is load t of V.
@@ -248,21 +282,22 @@ __global__ __launch_bounds__((FUSED && !(SPLIT && NR2 > 2) ? kWpuFusedUnits : kW
         __builtin_amdgcn_sched_barrier(0);
       }
     };
-    // Both feature maps from their layer-2 sums, and the entries handed back empty.
-    auto finish_maps = [&]() {
-      double sq = 0.0, sk = 0.0;
+    // The feature maps from their layer-2 sums.
+    auto finish_phi = [&]() {
+      double sq = 0.0;
 #pragma unroll
-      for (int p = 0; p < NP; ++p) {
-        if (p < nparts) {
-          sq += (double)pq[p];
-          sk += (double)pk[p];
-        }
-      }
-      for (int p = NP; p < nparts; ++p) {                  // hidden widths above 512 (never FUSED)
+      for (int p = 0; p < NP; ++p)
+        if (p < nparts) sq += (double)pq[p];
+      for (int p = NP; p < nparts; ++p)                    // hidden widths above 512 (never FUSED)
         sq += (double)a.mlp_parts[((size_t)u * 2 * nparts + p) * rp + rl];
-        sk += (double)a.mlp_parts[(((size_t)u * 2 + 1) * nparts + p) * rp + rl];
-      }
       f_lane = lane < R ? fabs(gelu_poly_f64(sq)) : 0.0;   // last activation of Eq. 1
+    };
+    auto finish_psi = [&]() {
+      double sk = 0.0;
+#pragma unroll
+      for (int p = 0; p < NP; ++p)
+        if (p < nparts) sk += (double)pk[p];
+      for (int p = NP; p < nparts; ++p) sk += (double)a.mlp_parts[(((size_t)u * 2 + 1) * nparts + p) * rp + rl];
       const double h2 = gelu_poly_f64(sk);                 // lane r < R; Eq. 2: |W3 gelu(.)|
       double acc3 = 0.0;
 #pragma unroll
@@ -274,49 +309,37 @@ __global__ __launch_bounds__((FUSED && !(SPLIT && NR2 > 2) ? kWpuFusedUnits : kW
       // The entries are requested before the last pass of the key stream and first looked at after
       // the sparse part of phase 2: that hides their way from memory.  (Asking a pass earlier
       // still keeps their sixteen registers live through two passes and makes the kernel spill.)
+      // (SPLIT: behind the last pass, which with few loads a wave is over before the jobs are; an entry that is not there yet
+      // costs another way to memory.  More than 256 rows: 188 us before the pass, 191 behind it for eight steps of 512 units x
+      // 408 slots; 13.6 and 12.8 a step for 128 x 326.)
       int base = 0;
       for (; base + DEPTH < nitp; base += DEPTH) key_pass(base);
-      request_parts();
+      if constexpr (!SPLIT || NR2 > 4) request_parts();
       key_pass(base);
+      if constexpr (SPLIT && NR2 <= 4) request_parts();
     } else {
       int base = 0;
       do {                                                 // nitp >= DEPTH
         key_pass(base);
         // The parts have been back for a while (they were requested before the loads this pass
         // re-issued): finish both feature maps here, where nothing is waiting for anything.
-        if (base == 0) finish_maps();
+        if (base == 0) {
+          if (out_wave || book_wave) finish_phi();
+          if (psi_wave) finish_psi();
+        }
       } while ((base += DEPTH) < nitp);
     }
 
-  // ---- requests behind the keys: what the value stream and the output want --------------------------
-  // This lane's share of H and of the pending value row, wanted after the value stream: four
-  // consecutive columns (those the reduce-scatter of phase 3 leaves it with) of every NHB-th
-  // row, so that one 16-byte load per lane covers NHB whole rows of H per instruction.
-  // (FUSED: requested inside phase 2, once the feature-map entries have given their registers back.)
-  constexpr int NHB = RPI / 2, HR = RM / NHB;
-  const int col0 = lr * EPL + ((lane & LPR) ? 4 : 0);
-  const int hb = lane / (2 * LPR);                           // which rows: r = NHB * i + hb
-  Vec vnv;
-  float4 hreg[HR];
-  uint2 pend_v_h;
-  auto request_tail = [&]() {
-    vnv = load_vec<T>(vn + lr * EPL);
-#pragma unroll
-    for (int i = 0; i < HR; ++i) {
-      const int r = NHB * i + hb;
-      hreg[i] = *reinterpret_cast<const float4 *>(a.H + ((size_t)u * R + (r < R ? r : R - 1)) * D + col0);
-    }
-    pend_v_h = *reinterpret_cast<const uint2 *>(reinterpret_cast<const T *>(a.pend_v) + (size_t)u * D + col0);
-  };
-  if constexpr (!FUSED) request_tail();
+  if constexpr (!FUSED && !SPLIT) request_tail();
   if constexpr (SPLIT) {
-    // Every wave works out phase 2 for itself from the shared scores; only the lead wave
-    // stores.  Its stores must not overtake another wave's loads of the same state: have
+    // What a wave stores must not overtake another wave's loads of the same state: have
     // those loads back before the waves meet (the value rows requested after them stay in
     // flight), then meet with the scores visible.
+    if constexpr (kTailEarly) {
 #pragma unroll
-    for (int i = 0; i < NR2; ++i) asm volatile("" ::"v"(acc_pre[i]), "v"(pos_pre[i]));
-    asm volatile("" ::"v"(z_lane), "v"(ppsi_lane), "v"(psie_lane));
+      for (int i = 0; i < HR; ++i) asm volatile("" ::"v"(hreg[i].x), "v"(hreg[i].y), "v"(hreg[i].z), "v"(hreg[i].w));
+    }
+    asm volatile("" ::"v"(pend_v_h.x), "v"(pend_v_h.y), "v"(z_lane), "v"(ppsi_lane), "v"(psie_lane));
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
@@ -339,21 +362,29 @@ __global__ __launch_bounds__((FUSED && !(SPLIT && NR2 > 2) ? kWpuFusedUnits : kW
 #pragma unroll
   for (int i = 0; i < NR2; ++i) {
     const int j = lane + i * kWave;
-    sc[i] = j < rows ? s_sc[j] : -__builtin_inf();
+    const double x = s_sc[j < rows ? j : 0];
+    sc[i] = j < rows ? x : -__builtin_inf();
     M = fmax(M, sc[i]);
   }
   M = wave_allreduce(M, OpMax{});
 #pragma unroll
+  for (int i = 0; i < NR2; ++i) sc[i] = exp_softmax_f64(sc[i] - M);      // without a branch: the rows' chains side by side
+#pragma unroll
   for (int i = 0; i < NR2; ++i) {
     const int j = lane + i * kWave;
-    sc[i] = j < rows ? exp_softmax_f64(sc[i] - M) : 0.0;
     if (j < rows) s_p[j] = (float)sc[i];
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
-  // second part: low-rank term and denominator
+  // second part: the pending fold of z (Eq. 5), low-rank term and denominator
+  auto fold_z = [&]() __attribute__((always_inline)) {
+    if (lane >= R) z_lane = 0.0;
+    if (!pend.fold) psie_lane = 0.f;
+    else if (pend.slot >= C) psie_lane = ppsi_lane;        // the previous step discarded its own pair
+    if (lane < R && pend.fold) z_lane += (double)psie_lane;
+  };
   auto denominators = [&]() __attribute__((always_inline)) {
     double S = 0.0;
 #pragma unroll
@@ -375,18 +406,17 @@ __global__ __launch_bounds__((FUSED && !(SPLIT && NR2 > 2) ? kWpuFusedUnits : kW
       // for whatever the loop body may have requested, which is everything in flight)
       bool have = have_all();
       for (int spin = 0; !have && spin < kWpuSpinLimit; ++spin) {
-        __builtin_amdgcn_s_sleep(32);
+        __builtin_amdgcn_s_sleep(SPLIT ? 4 : 32);
         request_parts();
         have = have_all();
       }
-      finish_maps();
-      request_tail();
+      if (psi_wave) finish_psi();
+      if (!out_wave && !book_wave) return;                 // (from this part)
+      finish_phi();
+      if constexpr (!SPLIT) request_tail();
     }
-    // pending fold of z (Eq. 5), then phi(q) z^T
-    if (lane >= R) z_lane = 0.0;
-    if (!pend.fold) psie_lane = 0.f;
-    else if (pend.slot >= C) psie_lane = ppsi_lane;        // the previous step discarded its own pair
-    if (lane < R && pend.fold) z_lane += (double)psie_lane;
+    if constexpr (SPLIT) request_scores();                   // (one wave stores the new ones, and looks at these)
+    if constexpr (SPLIT && !kTailEarly) request_tail();
     const double fz = wave_allreduce(f_lane * z_lane, OpAdd{});
     // den = phi(q) z^T + sum_j e^{s_j}, in whichever scaling cannot overflow:
     //   M > 0 (or no low-rank term): everything times e^{-M};  M <= 0: unscaled, e^{M} <= 1
@@ -403,7 +433,6 @@ __global__ __launch_bounds__((FUSED && !(SPLIT && NR2 > 2) ? kWpuFusedUnits : kW
     }
     ascale = pscale;
     if (a.flags & LESSDEC_FLAG_SPARSE_DENOM) ascale = 1.0 / S;
-    if constexpr (!SPLIT) request_scores();
   };
 
   // third part: H2O bookkeeping and the choice of the discarded pair; its value row is asked for
@@ -416,22 +445,17 @@ __global__ __launch_bounds__((FUSED && !(SPLIT && NR2 > 2) ? kWpuFusedUnits : kW
 #pragma unroll
     for (int i = 0; i < NR2; ++i) {
       const int j = lane + i * kWave;
-      if (j < rows) {
-        double na = sc[i] * ascale;
-        int pj = n;
-        if (j < m) {
-          na += acc_pre[i];
-          pj = pos_pre[i];
-        }
-        sc[i] = na;
-        if (full) {
-          // H2O: every pair that is not among the Nr most recent competes on its score;
-          // Lambda-masking: the first Nh tokens never leave and the oldest of the others does
-          const bool is_cand = (j < m) ? (pj <= n - a.Nr && (!lambda || pj >= a.Nh)) : (a.Nr == 0);
-          const Cand cnd{lambda ? 0.0 : na, pj, j};
-          if (is_cand && cand_less(cnd, best)) best = cnd;
-        }
-      }
+      const double na = sc[i] * ascale + (j < m ? acc_pre[i] : 0.0);
+      const int pj = j < m ? pos_pre[i] : n;
+      sc[i] = na;
+      // H2O: every pair that is not among the Nr most recent competes on its score;
+      // Lambda-masking: the first Nh tokens never leave and the oldest of the others does
+      const bool is_cand = (j < m) ? (pj <= n - a.Nr && (!lambda || pj >= a.Nh)) : (j == m && a.Nr == 0);
+      const Cand cnd{lambda ? 0.0 : na, pj, j};
+      const bool take = full && is_cand && cand_less(cnd, best);
+      best.acc = take ? cnd.acc : best.acc;
+      best.pos = take ? cnd.pos : best.pos;
+      best.slot = take ? cnd.slot : best.slot;
     }
     // argmin over (score, position): smallest score, then the oldest among equals
     if (full) {
@@ -445,12 +469,12 @@ __global__ __launch_bounds__((FUSED && !(SPLIT && NR2 > 2) ? kWpuFusedUnits : kW
     }
     const bool evict = eslot >= 0;                         // eslot == m: the new pair itself
     ins_slot = full ? ((evict && eslot < m) ? eslot : -1) : m;
-    {
-      // unconditional, from row 0 where no cached pair leaves
-      const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(vc, 0, C * D * (int)sizeof(T), 0x00020000);
-      const int er = (evict && eslot < m) ? eslot : 0;
-      pv_row = __builtin_amdgcn_raw_buffer_load_b128(rv, lr * 16, er * (D * (int)sizeof(T)), 0);
-    }
+  };
+  auto request_discarded = [&]() __attribute__((always_inline)) {
+    // unconditional, from row 0 where no cached pair leaves
+    const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(vc, 0, C * D * (int)sizeof(T), 0x00020000);
+    const int er = (eslot >= 0 && eslot < m) ? eslot : 0;
+    pv_row = __builtin_amdgcn_raw_buffer_load_b128(rv, lr * 16, er * (D * (int)sizeof(T)), 0);
   };
 
   // ---- phase 3: e^{s - M} . V as the value rows arrive ------------------------------------------------
@@ -505,17 +529,29 @@ __global__ __launch_bounds__((FUSED && !(SPLIT && NR2 > 2) ? kWpuFusedUnits : kW
   // range, which fetches nothing: the three passes always run, so that no load sits under a
   // condition.
   value_pass(0);
-  denominators();
+  fold_z();
+  if (out_wave || book_wave || (FUSED && psi_wave)) denominators();
+  if constexpr (!SPLIT) request_scores();
   value_pass(DEPTH);
-  bookkeeping();
+  if (book_wave) bookkeeping();
+  request_discarded();
   value_pass(2 * DEPTH);
-  fold_state();
+  if (out_wave || fold_wave) fold_state();
+  // the discarded pair's value row, parked for the next step's fold (before the insert overwrites the row it was read from;
+  // SPLIT: behind the last meeting, which would else wait for the row)
+  auto park = [&]() __attribute__((always_inline)) {
+    if (eslot >= 0 && rb == 0) {
+      uint4 row = vnv.raw;
+      if (eslot < m) __builtin_memcpy(&row, &pv_row, 16);
+      store_wt16(reinterpret_cast<T *>(a.pend_v) + (size_t)u * D, lr * EPL * (int)sizeof(T), row);
+    }
+  };
   // The unit's new state.  Its stores stand behind the last load that fetches anything: the memory
   // counter of a wave runs in order, so a store in mid-stream holds up every row requested after
   // it until the store has been acknowledged.  The rows of the last pass are requested before
-  // these stores and do not wait for them.  (SPLIT: the lead wave's.)
+  // these stores and do not wait for them.
   auto state_stores = [&]() __attribute__((always_inline)) {
-    if (pend.fold) {                                         // H with the pending pair folded in (Eq. 4)
+    if (fold_wave && pend.fold) {                            // H with the pending pair folded in (Eq. 4)
 #pragma unroll
       for (int i = 0; i < HR; ++i) {
         const int r = NHB * i + hb;
@@ -523,103 +559,95 @@ __global__ __launch_bounds__((FUSED && !(SPLIT && NR2 > 2) ? kWpuFusedUnits : kW
       }
     }
     if (lane < R) {
-      if (pend.fold) store_wt(a.z + (size_t)u * R + lane, z_lane);
-      if (pend.slot >= 0 && pend.slot < C) store_wt(a.psi + ((size_t)u * C + pend.slot) * R + lane, ppsi_lane);
-      store_wt(a.pend_psi + (size_t)u * R + lane, npsi_lane);
-    }
-#pragma unroll
-    for (int i = 0; i < NR2; ++i) {
-      const int j = lane + i * kWave;
-      if (j < m) {
-        if (j != ins_slot) store_wt(a.acc + (size_t)u * C + j, sc[i]);
-      } else if (j == m && ins_slot >= 0) {
-        store_wt(a.acc + (size_t)u * C + ins_slot, sc[i]);
-        store_wt(a.pos + (size_t)u * C + ins_slot, n);
+      if (fold_wave && pend.fold) store_wt(a.z + (size_t)u * R + lane, z_lane);
+      if (psi_wave) {
+        if (pend.slot >= 0 && pend.slot < C) store_wt(a.psi + ((size_t)u * C + pend.slot) * R + lane, ppsi_lane);
+        store_wt(a.pend_psi + (size_t)u * R + lane, npsi_lane);
       }
-    }
-    if (lane == 0) {
-      // what the next step has to finish: fold of the discarded pair and / or the slot write
-      store_wt(a.pend_slot + u, eslot >= 0 ? (eslot < m ? eslot : C) : (m | kPendNoFold));
-      if (a.evicted_pos) store_wt(a.evicted_pos + u, eslot >= 0 ? epos : -1);
-      store_wt(a.n_seen + u, n + 1);
     }
     if constexpr (!SPLIT) {
       // the feature-map entries go back empty (the unit's 2 * nparts entries lie together)
       for (int e = lane; e < 2 * nparts * (rp / 4); e += kWave)
         store_wt16(a.mlp_out + (size_t)u * 2 * nparts * rp, e * 16, uint4{kMlpEmpty, kMlpEmpty, kMlpEmpty, kMlpEmpty});
     }
-    // the discarded pair's value row, parked for the next step's fold (before the insert below
-    // overwrites the row it was read from)
-    if (eslot >= 0 && rb == 0) {
-      uint4 row = vnv.raw;
-      if (eslot < m) __builtin_memcpy(&row, &pv_row, 16);
-      store_wt16(reinterpret_cast<T *>(a.pend_v) + (size_t)u * D, lr * EPL * (int)sizeof(T), row);
+    if (!book_wave) return;
+#pragma unroll
+    for (int i = 0; i < NR2; ++i) {
+      // (the new pair's, row m, goes where it is put)
+      const int j = lane + i * kWave, to = j < m ? j : ins_slot;
+      if (j < m ? j != ins_slot : j == m && ins_slot >= 0) store_wt(a.acc + (size_t)u * C + to, sc[i]);
     }
+    if (lane == 0) {
+      // what the next step has to finish: fold of the discarded pair and / or the slot write
+      store_wt(a.pend_slot + u, eslot >= 0 ? (eslot < m ? eslot : C) : (m | kPendNoFold));
+      if (a.evicted_pos) store_wt(a.evicted_pos + u, eslot >= 0 ? epos : -1);
+      store_wt(a.n_seen + u, n + 1);
+      if (ins_slot >= 0) store_wt(a.pos + (size_t)u * C + ins_slot, n);
+    }
+    if constexpr (!SPLIT) park();
   };
   {
     int base = 3 * DEPTH;
     for (; base + DEPTH < nit; base += DEPTH) value_pass(base);
-    if (lead) state_stores();
+    state_stores();
     if (base < nit) value_pass(base);                        // the last pass requests nothing real
   }
   // the appended pair's value row
-  if (lead && rb == 0) {
+  if (out_wave && rb == 0) {
     const float p = s_p[m];
 #pragma unroll
     for (int i = 0; i < EPL; ++i) o[i] = fmaf(p, Store<T>::get(vnv, i), o[i]);
   }
-  {
-    // The RPI row groups hold partial sums of the same 8 columns.  First stage (partner at
-    // distance LPR): reduce-scatter, a lane keeps the four columns selected by its bit LPR;
-    // remaining stages: all-reduce, together with the partial phi(q) H of the row subsets.
-    {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const bool hi = lane & LPR;
-        const float send = hi ? o[i] : o[i + 4], keep = hi ? o[i + 4] : o[i];
-        o[i] = keep + __shfl_xor(send, LPR);
-      }
-#pragma unroll
-      for (int x = 2 * LPR; x < kWave; x *= 2) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          o[i] += __shfl_xor(o[i], x);
-          fh[i] += __shfl_xor(fh[i], x);
-        }
-      }
+  auto insert = [&]() __attribute__((always_inline)) {
+    if (ins_slot >= 0 && rb == 0) {
+      store_wt16(kc + (size_t)ins_slot * D, lr * EPL * (int)sizeof(T), knv.raw);
+      store_wt16(vc + (size_t)ins_slot * D, lr * EPL * (int)sizeof(T), vnv.raw);
     }
+  };
+  {
+    // The RPI row groups hold partial sums of the same 8 columns, the row subsets of H partial phi(q) H.
+    combine_row_groups<LPR>(o, fh, lane);
 
     if constexpr (SPLIT) {
-      // the waves' partial p . V meet in the LDS and the lead wave adds them in wave order
+      // the waves' partial p . V meet in the LDS and one wave adds them in wave order
       if (hb == 0) *reinterpret_cast<float4 *>(s_o + (size_t)wave * D + col0) = float4{o[0], o[1], o[2], o[3]};
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
       __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-      if (!lead) return;
-      const float4 first = *reinterpret_cast<const float4 *>(s_o + col0);
-      o[0] = first.x; o[1] = first.y; o[2] = first.z; o[3] = first.w;
-      for (int w = 1; w < nw; ++w) {
-        const float4 part = *reinterpret_cast<const float4 *>(s_o + (size_t)w * D + col0);
-        o[0] += part.x; o[1] += part.y; o[2] += part.z; o[3] += part.w;
+      // the feature-map entries go back empty, now that every wave of the unit has read them
+      if (psi_wave)
+        for (int e = lane; e < 2 * nparts * (rp / 4); e += kWave)
+          store_wt16(a.mlp_out + (size_t)u * 2 * nparts * rp, e * 16, uint4{kMlpEmpty, kMlpEmpty, kMlpEmpty, kMlpEmpty});
+      if (book_wave) {
+        park();
+        insert();
       }
+      if (!out_wave) return;
+      // (all requested before the first is used)
+      auto add_waves = [&](auto count) __attribute__((always_inline)) {
+        constexpr int N = decltype(count)::value;
+        float4 part[N];
+#pragma unroll
+        for (int w = 0; w < N; ++w) part[w] = *reinterpret_cast<const float4 *>(s_o + (size_t)w * D + col0);
+        o[0] = part[0].x; o[1] = part[0].y; o[2] = part[0].z; o[3] = part[0].w;
+#pragma unroll
+        for (int w = 1; w < N; ++w) {
+          o[0] += part[w].x; o[1] += part[w].y; o[2] += part[w].z; o[3] += part[w].w;
+        }
+      };
+      if (nw == 8) add_waves(std::integral_constant<int, 8>{});
+      else if (nw == 4) add_waves(std::integral_constant<int, 4>{});
+      else add_waves(std::integral_constant<int, 2>{});
     }
 
-    // ---- phase 4: output and the in-place insert (SPLIT: only the lead wave gets here) -------------
-    if constexpr (SPLIT) {
-      // the feature-map entries go back empty, now that every wave of the unit has read them
-      for (int e = lane; e < 2 * nparts * (rp / 4); e += kWave)
-        store_wt16(a.mlp_out + (size_t)u * 2 * nparts * rp, e * 16, uint4{kMlpEmpty, kMlpEmpty, kMlpEmpty, kMlpEmpty});
-    }
+    // ---- phase 4: output and the in-place insert ---------------------------------------------------
     if (hb == 0) {
       __half2 res[2];
       res[0] = __floats2half2_rn((float)(pscale * (double)o[0] + lscale * (double)fh[0]), (float)(pscale * (double)o[1] + lscale * (double)fh[1]));
       res[1] = __floats2half2_rn((float)(pscale * (double)o[2] + lscale * (double)fh[2]), (float)(pscale * (double)o[3] + lscale * (double)fh[3]));
       store_wt8(reinterpret_cast<T *>(a.out) + (size_t)u * xs_ + col0, *reinterpret_cast<const uint2 *>(res));
     }
-    if (ins_slot >= 0 && rb == 0) {
-      store_wt16(kc + (size_t)ins_slot * D, lr * EPL * (int)sizeof(T), knv.raw);
-      store_wt16(vc + (size_t)ins_slot * D, lr * EPL * (int)sizeof(T), vnv.raw);
-    }
+    if constexpr (!SPLIT) insert();
   }
 }
 
