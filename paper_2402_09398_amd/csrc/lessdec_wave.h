@@ -73,6 +73,39 @@ __device__ inline double row_sum(double v)
     return LPR == 32 ? add_other_row16(v) : v;
   }
 }
+// Sums of four values over the LPR lanes of a row: lane lr % 4 == h of the row gets that of v[h].  The first two stages halve
+// what is carried on: 27 vector instructions where four row_sum take 48; the same sums in the same order.
+template <int LPR>
+__device__ inline double row_sum4(const double (&v)[4], int lane)
+{
+  static_assert(LPR == 8 || LPR == 16, "");
+  const bool b0 = lane & 1, b1 = lane & 2;
+  const double s01 = (b0 ? v[1] : v[0]) + dpp_mov<0xB1>(b0 ? v[0] : v[1]);
+  const double s23 = (b0 ? v[3] : v[2]) + dpp_mov<0xB1>(b0 ? v[2] : v[3]);
+  double s = (b1 ? s23 : s01) + dpp_mov<0x4E>(b1 ? s01 : s23);
+  if constexpr (LPR == 16) {
+    s += dpp_mov<0x124>(s);
+    return s + dpp_mov<0x128>(s);
+  } else {
+    return s + dpp_mov<0x141>(dpp_mov<0x1B>(s));           // the lane four away: quad reversed, then row_half_mirror
+  }
+}
+// Sums of two values over the LPR lanes of a row: even lanes get a's, odd ones b's.  The first stage halves what is carried on;
+// the same sums in the same order as row_sum.
+template <int LPR>
+__device__ inline double row_sum2(double a, double b, int lane)
+{
+  static_assert(LPR == 8 || LPR == 16, "");
+  const bool odd = lane & 1;
+  double s = (odd ? b : a) + dpp_mov<0xB1>(odd ? a : b);
+  s += dpp_mov<0x4E>(s);
+  if constexpr (LPR == 16) {
+    s += dpp_mov<0x124>(s);
+    return s + dpp_mov<0x128>(s);
+  } else {
+    return s + dpp_mov<0x141>(dpp_mov<0x1B>(s));           // the lane four away: quad reversed, then row_half_mirror
+  }
+}
 
 // x of the lane X away added, X = 8, 16 or 32: DPP or a lane swap, without a trip through the LDS.
 template <int X>
@@ -121,6 +154,41 @@ __device__ inline void combine_row_groups(float (&o)[8], float (&f)[4], int lane
   for (int i = 0; i < 4; ++i) {
     o[i] = add_xor<32>(o[i]);
     f[i] = add_xor<32>(f[i]);
+  }
+}
+// Four heads' partial sums of the same eight columns in the 64 / LPR row groups: lanes 16 h .. 16 h + 15 end with head h's, summed
+// over all groups (LPR = 8: every column twice).
+template <int LPR>
+__device__ inline void combine_four_heads(const float (&o)[4][8], float (&r)[8])
+{
+  typedef unsigned v2u __attribute__((ext_vector_type(2)));
+  auto sum32 = [](float a, float b) {
+    const v2u p = __builtin_bit_cast(v2u, __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false));
+    return __uint_as_float(p.x) + __uint_as_float(p.y);
+  };
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const float even = sum32(o[0][i], o[2][i]), odd = sum32(o[1][i], o[3][i]);
+    r[i] = scatter_add<16>(even, odd, 0);
+    if constexpr (LPR == 8) r[i] = add_xor<8>(r[i]);
+  }
+}
+// Two heads' partial sums of the same eight columns in the 64 / LPR row groups: a lane ends with four of the columns (the upper
+// four where its bit LPR is set) of head lane / 32, summed over all groups.
+template <int LPR>
+__device__ inline void combine_two_heads(const float (&o)[2][8], float (&r)[4], int lane)
+{
+  typedef unsigned v2u __attribute__((ext_vector_type(2)));
+  float t[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const v2u p = __builtin_bit_cast(v2u, __builtin_amdgcn_permlane32_swap(__float_as_uint(o[0][i]), __float_as_uint(o[1][i]), false, false));
+    t[i] = __uint_as_float(p.x) + __uint_as_float(p.y);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    r[i] = scatter_add<LPR>(t[i], t[i + 4], lane);
+    if constexpr (LPR == 8) r[i] = add_xor<16>(r[i]);
   }
 }
 
