@@ -166,7 +166,7 @@ int lessdec_state_sync(const lessdec_desc *desc, void *hip_stream);
  * With LESSDEC_FLAG_PROMPT_STEPWISE the call is lessdec_state_reset followed by one
  * lessdec_step per prompt token t with rows Q[.,.,t,.], K[.,.,t,.], V[.,.,t,.] (bit for bit: on
  * the streaming path the steps read and write the rows where they lie in the prompt arrays, one
- * launch per token on large shapes; elsewhere rows are staged and a token takes three launches):
+ * launch per token on large shapes; elsewhere rows are staged and a token takes two more):
  * out[.,.,t,.] is then Eq. 3's output at token t, and the state afterwards is the state after
  * P steps (a fold may be pending).
  * With LESSDEC_FLAG_LAMBDA as well and P > n_heavy + n_recent the same results (outputs, slot

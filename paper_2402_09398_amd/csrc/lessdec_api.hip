@@ -122,6 +122,7 @@ StepArgs state_args(const lessdec_desc *desc, const Shape &s)
   a.f_phi = nullptr; a.f_phi32 = nullptr; a.f_psi = nullptr; a.mlp_parts = nullptr; a.mlp_out = nullptr;
   a.gqa_parts = nullptr;
   a.Wk3 = desc->Wk3; a.Wk2 = desc->Wk2;
+  a.map_sums = nullptr; a.map_parts = 0;
   return a;
 }
 
@@ -130,6 +131,15 @@ bool use_wpu(const lessdec_desc *desc, const Shape &s)
 {
   return s.G == 1 && desc->batch < 65536 && desc->heads < 65536 &&
          wpu_supported(desc->dtype, desc->head_dim, (int)s.C, desc->hidden, desc->rank);
+}
+
+// Any-shape path, one query head per unit: parts of the hidden layer whose sums the step finishes itself, which saves a launch
+// (256 units x 102 slots, fp32, a step: 21.8 us against 17.2); 0: the maps come complete.  Ranks up to 16, a lane each.
+int step_finishes_parts(const lessdec_desc *desc, const Shape &s, const Workspace &w)
+{
+  if (s.G > 1 || use_wpu(desc, s) || desc->rank > 16) return 0;
+  const int parts = featmap_step_parts(desc->batch, 2 * desc->heads, desc->hidden, desc->rank, w.off_gqa - w.off_parts);
+  return parts < 2 ? 0 : parts;
 }
 
 // Several query heads per unit on the streaming kernel, which finishes the feature maps itself
@@ -266,7 +276,7 @@ int step_features_impl(const lessdec_desc *desc, const void *q, const void *k, i
   fk.x = k; fk.W1 = desc->Wk1; fk.W2 = desc->Wk2; fk.W3 = desc->Wk3;
   fk.out = reinterpret_cast<float *>(ws + w.off_fpsi); fk.out_f64 = 0;
   return launch_featmap_step(fa, fk, desc->dtype, reinterpret_cast<double *>(ws + w.off_parts), w.off_gqa - w.off_parts,
-                             st) == hipSuccess ? LESSDEC_OK : LESSDEC_EHIP;
+                             step_finishes_parts(desc, s, w) == 0, st) == hipSuccess ? LESSDEC_OK : LESSDEC_EHIP;
 }
 
 int step_attend_impl(const lessdec_desc *desc, const void *q, const void *k, const void *v, void *out,
@@ -303,6 +313,8 @@ int step_attend_impl(const lessdec_desc *desc, const void *q, const void *k, con
   }
   a.f_phi = reinterpret_cast<double *>(ws + w.off_fphi);           // one block per unit
   a.f_psi = reinterpret_cast<float *>(ws + w.off_fpsi);
+  a.map_sums = reinterpret_cast<double *>(ws + w.off_parts);
+  a.map_parts = step_finishes_parts(desc, s, w);
   return launch_step(a, desc->dtype, desc->head_dim, st) == hipSuccess ? LESSDEC_OK : LESSDEC_EHIP;
 }
 
@@ -376,7 +388,7 @@ int lessdec_step_launches(const lessdec_desc *desc)
                ? 2 : gqa_head_blocks((long)s.U, (int)s.G) > 1 ? 3 : 2;
   if (use_wpu(desc, s))
     return wpu_fusable(desc->batch, desc->heads, desc->head_dim, (int)s.C, desc->hidden, desc->rank) ? 1 : 2;
-  return 3;                                                                 // feature maps (two launches), step
+  return step_finishes_parts(desc, s, carve(s, 0, desc->flags)) ? 2 : 3;     // feature maps (one or two launches), step
 }
 
 int lessdec_step_static(const lessdec_desc *desc, const void *q, const void *k, const void *v, void *out,

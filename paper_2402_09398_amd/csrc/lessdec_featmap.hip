@@ -20,9 +20,10 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 // activated tile is then directly the B operand of layer 2 (hidden units g + 4 v).  The waves' layer-2
 // sums meet in the LDS in wave order.  With one part the block finishes the map; a decode step, which has few
 // (head, 16 rows) pairs, spreads the hidden units over blocks that leave their sums (fp64) in the workspace, and
-// featmap_finish_kernel adds them in part order: the two launches that phi and psi took one each.
-// Bound by the fp64 matrix rate (66 cycles an instruction) and the erfc of the hidden units, about half and half.
-// 8 x 32 units, D = 128, R' = 512, fp32 storage: 10.8 + 4.1 us for both maps (11.5 + 4.8 with the weights of the second layer
+// the step's own kernel adds them (one query head per unit, ranks up to 16), or featmap_finish_kernel in part order.
+// Bound by the chain of requests, fp64 matrix products (66 cycles each) and activations of a wave.
+// 8 x 32 units, D = 128, R' = 512, fp32 storage: 9.5 us for both maps; 10.4 + 4.1 with the library's erfc in the activations and the
+// finishing launch, which the step has taken over (11.5 + 4.8 with the weights of the second layer
 // requested after the first's products, a branch around every activation and divisions ahead of the first request), against 82 with a hidden unit per
 // thread on the vector units and a block per (head, 8 rows).
 // =====================================================================================
@@ -195,24 +196,32 @@ hipError_t launch_featmap_generic(const FeatmapArgs &a, int dtype, hipStream_t s
   return hipGetLastError();
 }
 
-hipError_t launch_featmap_step(const FeatmapArgs &a, const FeatmapArgs &b, int dtype, double *sums, size_t bytes, hipStream_t st)
+int featmap_step_parts(int B, int heads, int Rp, int R, size_t bytes)
 {
   // Parts of 64 hidden units (a tile per wave) as far as their sums fit the scratch and until there are 512 blocks.
-  const size_t rows = (size_t)a.B * (a.Hh + b.Hh), per = rows * a.R * sizeof(double);
-  const long chunks = (long)(a.Hh + b.Hh) * ((a.B + 15) / 16);
-  long parts = (a.Rp + 63) / 64;
+  const size_t per = (size_t)B * heads * R * sizeof(double);
+  const long chunks = (long)heads * ((B + 15) / 16);
+  long parts = (Rp + 63) / 64;
   if (parts > (long)(bytes / per)) parts = (long)(bytes / per);
   if (parts > (512 + chunks - 1) / chunks) parts = (512 + chunks - 1) / chunks;
+  return (int)parts;
+}
+
+hipError_t launch_featmap_step(const FeatmapArgs &a, const FeatmapArgs &b, int dtype, double *sums, size_t bytes, bool finish,
+                               hipStream_t st)
+{
+  const size_t rows = (size_t)a.B * (a.Hh + b.Hh);
+  const int parts = featmap_step_parts(a.B, a.Hh + b.Hh, a.Rp, a.R, bytes);
   hipError_t e;
   if (parts < 2) {                                         // a launch per map
     if ((e = launch_featmap_generic(a, dtype, st)) != hipSuccess) return e;
     return launch_featmap_generic(b, dtype, st);
   }
-  featmap_launch(a, b, true, dtype, (int)parts, sums, st);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  featmap_launch(a, b, true, dtype, parts, sums, st);
+  if ((e = hipGetLastError()) != hipSuccess || !finish) return e;
   const unsigned grid = (unsigned)((rows + 3) / 4);
-  if (dtype == LESSDEC_DTYPE_F16) featmap_finish_kernel<__half><<<grid, 256, 0, st>>>(a, b, (int)parts, sums);
-  else featmap_finish_kernel<float><<<grid, 256, 0, st>>>(a, b, (int)parts, sums);
+  if (dtype == LESSDEC_DTYPE_F16) featmap_finish_kernel<__half><<<grid, 256, 0, st>>>(a, b, parts, sums);
+  else featmap_finish_kernel<float><<<grid, 256, 0, st>>>(a, b, parts, sums);
   return hipGetLastError();
 }
 

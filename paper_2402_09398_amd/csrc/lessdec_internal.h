@@ -20,8 +20,12 @@ struct FeatmapArgs {
   int D, Rp, R;
 };
 hipError_t launch_featmap_generic(const FeatmapArgs &a, int dtype, hipStream_t st);
-// both maps of a decode step (rpu = 1, the same rank, hidden width and head_dim): two launches; sums: scratch
-hipError_t launch_featmap_step(const FeatmapArgs &a, const FeatmapArgs &b, int dtype, double *sums, size_t bytes, hipStream_t st);
+// both maps of a decode step (rpu = 1, the same rank, hidden width and head_dim): two launches; sums: scratch.  finish = false:
+// the first launch alone, which leaves the sums of featmap_step_parts parts (2 or more)
+hipError_t launch_featmap_step(const FeatmapArgs &a, const FeatmapArgs &b, int dtype, double *sums, size_t bytes, bool finish,
+                               hipStream_t st);
+// parts that the hidden layer is spread over; heads: of both maps together; bytes: of the sums' scratch
+int featmap_step_parts(int B, int heads, int Rp, int R, size_t bytes);
 
 // Matrix-core psi (Eq. 2) for many rows: fp16 storage, D in {64,128}, R' a multiple of 32,
 // R <= 16.  Row convention as above; out is [rows, R] fp32.
@@ -92,6 +96,10 @@ struct StepArgs {
   float *mlp_out;        // the same array, for handing entries back empty (and, fused, for writing them)
   const void *Wk3;
   const void *Wk2;       // fused launch only (the other weight pointers are kernel arguments of their own)
+  // generic path, one query head per unit: layer-2 sums of both maps by parts, [phi rows, psi rows][map_parts][R], which the step
+  // adds up and finishes (launch_featmap_step left them); map_parts == 0: f_phi, f_psi are complete
+  const double *map_sums;
+  int map_parts;
 };
 hipError_t launch_step(const StepArgs &a, int dtype, int D, hipStream_t st);
 // several query heads per unit: q, out [U,G,D], f_phi [U,G,R]

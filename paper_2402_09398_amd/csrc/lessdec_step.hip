@@ -13,9 +13,11 @@ namespace lessdec {
 template <typename T>
 constexpr int step_ahead(int w) { return w == 8 || sizeof(T) == 2 ? 8 : 2; }
 template <typename T>
-constexpr int step_waves_per_simd(int nit, int w)
+constexpr int step_waves_per_simd(int nit, int w, bool parts)
 {
-  const int n = nit == 0 ? (step_ahead<T>(w) == 8 ? 4 : 8) : nit <= 2 ? 6 : nit <= 7 ? 5 : nit <= 11 ? 3 : 2;
+  // (with the maps' last activation in the kernel a wave less where the registers would not reach: a kernel that spills even
+  // eight bytes starts two microseconds later)
+  const int n = nit == 0 ? (step_ahead<T>(w) == 8 ? 4 : parts ? 6 : 8) : nit <= 2 ? 6 : nit <= 7 ? (parts ? 4 : 5) : nit <= 11 ? 3 : 2;
   return w == 4 ? n : n < w / 4 ? w / 4 : n / (w / 4) * (w / 4);         // whole blocks
 }
 
@@ -57,8 +59,9 @@ constexpr int step_waves_per_simd(int nit, int w)
 // Phase 4  column threads: out = p V + phi(q) H / den (Eq. 3); the new pair goes into the
 //          freed slot (Sec. 3.2); the discarded value row is left pending.
 // =====================================================================================
-template <typename T, int D, int NIT, int W>
-__global__ __launch_bounds__(64 * W, step_waves_per_simd<T>(NIT, W)) void step_kernel(const StepArgs a)
+// PARTS: the maps come as sums by parts (a.map_parts of them), which wave 1 finishes.
+template <typename T, int D, int NIT, int W, bool PARTS>
+__global__ __launch_bounds__(64 * W, step_waves_per_simd<T>(NIT, W, PARTS)) void step_kernel(const StepArgs a)
 {
   constexpr int kThreads = 64 * W;
   constexpr int EPL = Store<T>::kPerVec;   // elements per lane
@@ -115,8 +118,22 @@ __global__ __launch_bounds__(64 * W, step_waves_per_simd<T>(NIT, W)) void step_k
   } else if (wave == 1 && lane < R) {
     z_lane = a.z[(size_t)u * R + lane];
     ppsi_lane = a.pend_psi[(size_t)u * R + lane];
-    npsi_lane = a.f_psi[(size_t)u * R + lane];
-    f_lane = a.f_phi[(size_t)u * R + lane];
+    if (!PARTS) {
+      npsi_lane = a.f_psi[(size_t)u * R + lane];
+      f_lane = a.f_phi[(size_t)u * R + lane];
+    }
+  }
+  // PARTS: lanes r and 32 + r add up phi's sums of output r, 16 + r and 48 + r psi's, every other part each
+  constexpr int kParts = 4;
+  double part[kParts], h2 = 0.0;
+  const double *sums = nullptr;
+  if (PARTS && wave == 1) {
+    sums = a.map_sums + ((size_t)(lane & 16 ? a.U + u : u) * a.map_parts) * R + (lane % 16 < R ? lane % 16 : R - 1);
+#pragma unroll
+    for (int i = 0; i < kParts; ++i) {
+      const int p = 2 * i + lane / 32;
+      part[i] = sums[(size_t)(p < a.map_parts ? p : a.map_parts - 1) * R];
+    }
   }
   float hreg[16];                          // column threads: their column of H
   float pend_v_c = 0.f;
@@ -136,6 +153,16 @@ __global__ __launch_bounds__(64 * W, step_waves_per_simd<T>(NIT, W)) void step_k
     for (int it = 0; it < NIT; ++it) kbuf[it] = buffer_load_nt<T>(rk, tid * 16, it * kIterBytes);
   }
   __builtin_amdgcn_sched_barrier(0);
+  if (PARTS && wave == 1) {
+    // the maps' last activation while the keys are on their way; W3 later, where the other waves wait for the bookkeeping
+    double sum = 0.0;
+#pragma unroll
+    for (int i = 0; i < kParts; ++i)
+      if (2 * i + lane / 32 < a.map_parts) sum += part[i];
+    for (int p = 2 * kParts + lane / 32; p < a.map_parts; p += 2) sum += sums[(size_t)p * R];
+    h2 = gelu_f64(sum + __shfl_xor(sum, 32));
+    f_lane = lane < R ? fabs(h2) : 0.0;
+  }
   // psi of the pending discarded pair (address known only now; it returns behind the keys)
   float psie_lane = 0.f;
   if (wave == 1 && lane < R && pend.fold)
@@ -228,7 +255,7 @@ __global__ __launch_bounds__(64 * W, step_waves_per_simd<T>(NIT, W)) void step_k
         a.z[(size_t)u * R + lane] = z_lane;
       }
       if (pend.slot >= 0 && pend.slot < C) a.psi[((size_t)u * C + pend.slot) * R + lane] = ppsi_lane;
-      a.pend_psi[(size_t)u * R + lane] = npsi_lane;
+      if (!PARTS) a.pend_psi[(size_t)u * R + lane] = npsi_lane;
       s_f[lane] = (float)f_lane;
     }
     const double fz = wave_allreduce(f_lane * z_lane, OpAdd{});      // phi(q) z^T
@@ -325,6 +352,13 @@ __global__ __launch_bounds__(64 * W, step_waves_per_simd<T>(NIT, W)) void step_k
       if (a.evicted_pos) a.evicted_pos[u] = evict ? epos : -1;
       a.n_seen[u] = n + 1;
     }
+  } else if (PARTS && wave == 1) {
+    const T *w3 = reinterpret_cast<const T *>(a.Wk3) + ((size_t)(u % a.Hh) * R + (lane < R ? lane : R - 1)) * R;
+    double acc3 = 0.0;
+#pragma unroll
+    for (int j = 0; j < 16; ++j)
+      if (j < R) acc3 = fma(readlane_v(h2, 16 + j), (double)Store<T>::to_float(w3[j]), acc3);
+    if (lane < R) a.pend_psi[(size_t)u * R + lane] = (float)fabs(acc3);
   }
   __syncthreads();
 
@@ -421,7 +455,11 @@ static hipError_t launch_step_t(const StepArgs &a, hipStream_t st)
   const size_t lds = (size_t)(a.C + 1) * (sizeof(double) + sizeof(float));
   const unsigned grid = (unsigned)a.U;
   const int need = (a.C + 1 + RPB - 1) / RPB;            // row iterations of four waves to cover C + 1 rows
-#define LESSDEC_STEP(NIT, W) step_kernel<T, D, NIT, W><<<grid, 64 * W, lds, st>>>(a)
+#define LESSDEC_STEP(NIT, W)                                                         \
+  do {                                                                               \
+    if (a.map_parts) step_kernel<T, D, NIT, W, true><<<grid, 64 * W, lds, st>>>(a);  \
+    else step_kernel<T, D, NIT, W, false><<<grid, 64 * W, lds, st>>>(a);             \
+  } while (0)
   // Eight waves per unit where four would take more than eleven turns and there are few units.  A block with many rows in
   // registers leaves no room for a second one on its compute unit: past 256 units the loop, whose blocks come in twos, or, with few
   // turns, four waves.  us of eight steps, fp32, D = 128: 256 units x 200 slots eight waves 230, four 258; 320 x 200 in
