@@ -62,6 +62,10 @@ struct LdsCopies {
 // choice, fold of the discarded pair into H, z (Eq. 4, Eq. 5), in-place insert of the new pair
 // (Sec. 3.2).  s_inc holds the step's probabilities per pair summed over the heads; s_e is
 // scratch of the same size; s_cand THREADS entries.
+// Bound by latency: the loads are one round before the choice and one behind it (the pair that leaves: value row,
+// psi), and H's elements are spread over all threads.  In a launch of its own, 64 units x 204 slots, D = 64: 5.1 us,
+// against 6.5 with the choice as a tree over the LDS (a barrier per halving), H by the first D threads and every load
+// where it was used; a whole step of 71 heads 33.5 us, against 35.5.
 template <typename T, int D, int THREADS = 256>
 __device__ inline void gqa_finish_unit(const StepArgs &a, int u, int tid, double *s_e, const double *s_inc,
                                        Cand *s_cand, const LdsCopies<T> lds = LdsCopies<T>())
@@ -77,6 +81,29 @@ __device__ inline void gqa_finish_unit(const StepArgs &a, int u, int tid, double
   const T *vn = reinterpret_cast<const T *>(a.v) + (size_t)u * D;
   float *Hu = a.H + (size_t)u * R * D;
   double *zu = a.z + (size_t)u * R;
+  // requested before the choice, and before n_seen is needed, on which they do not depend: this thread's
+  // elements of H (a full unit folds the discarded pair into all of them), z, the scores and positions of the
+  // first pass, and the new pair's rows
+  constexpr int HB = 8;
+  const float *Hs = lds.H ? lds.H : Hu;
+  const int hn = R * D;
+  float h[HB];
+  double z_old = 0.0;
+  if (hn > 0) {
+#pragma unroll
+    for (int j = 0; j < HB; ++j) h[j] = Hs[tid + j * THREADS < hn ? tid + j * THREADS : hn - 1];
+    if (tid < R) z_old = zu[tid];
+  }
+  const int first = tid < C ? tid : C - 1;
+  const double acc_first = lds.acc ? lds.acc[first] : a.acc[(size_t)u * C + first];
+  const int pos_first = lds.pos ? lds.pos[first] : a.pos[(size_t)u * C + first];
+  T k_new = T(0.f), v_new = T(0.f);
+  float psi_new = 0.f;
+  if (tid < D) {
+    k_new = lds.k ? lds.k[(size_t)m * D + tid] : kn[tid];
+    v_new = lds.v ? lds.v[(size_t)m * D + tid] : vn[tid];
+  }
+  if (tid < R) psi_new = a.f_psi[(size_t)u * R + tid];
   // accumulated scores; eviction candidate of this thread's rows
   const bool lambda = (a.flags & LESSDEC_FLAG_LAMBDA) != 0;
   Cand best = cand_none();
@@ -84,8 +111,8 @@ __device__ inline void gqa_finish_unit(const StepArgs &a, int u, int tid, double
     double na = s_inc[r];
     int pj = n;
     if (r < m) {
-      na += lds.acc ? lds.acc[r] : a.acc[(size_t)u * C + r];
-      pj = lds.pos ? lds.pos[r] : a.pos[(size_t)u * C + r];
+      na += r == tid ? acc_first : lds.acc ? lds.acc[r] : a.acc[(size_t)u * C + r];
+      pj = r == tid ? pos_first : lds.pos ? lds.pos[r] : a.pos[(size_t)u * C + r];
     }
     s_e[r] = na;
     if (full) {
@@ -94,40 +121,47 @@ __device__ inline void gqa_finish_unit(const StepArgs &a, int u, int tid, double
       if (is_cand && cand_less(cnd, best)) best = cnd;
     }
   }
-  s_cand[tid] = best;
+  // the smallest score, then the oldest among equals: of a wave by lane exchanges, of the waves through the LDS
+  constexpr int NW = THREADS / kWave;
+  const double amin = wave_allreduce(best.acc, OpMin{});
+  const int pmin = wave_allreduce(best.acc == amin ? best.pos : INT_MAX, OpMinI{});
+  const unsigned long long who = __ballot(best.acc == amin && best.pos == pmin && best.slot >= 0);
+  if ((tid & (kWave - 1)) == 0) s_cand[tid / kWave] = cand_none();
+  if (who != 0ull && (tid & (kWave - 1)) == __ffsll((long long)who) - 1) s_cand[tid / kWave] = best;
   __syncthreads();
-  for (int o = THREADS / 2; o > 0; o >>= 1) {
-    if (tid < o && cand_less(s_cand[tid + o], s_cand[tid])) s_cand[tid] = s_cand[tid + o];
-    __syncthreads();
-  }
-  const Cand win = s_cand[0];
+  Cand win = s_cand[0];
+#pragma unroll
+  for (int w = 1; w < NW; ++w)
+    if (cand_less(s_cand[w], win)) win = s_cand[w];
   const int eslot = full ? win.slot : -1;                    // eslot == m: the new pair itself
   const bool evict = eslot >= 0;
   const int ins_slot = full ? ((evict && eslot < m) ? eslot : -1) : m;
 
   // fold of the discarded pair into H, z (Eq. 4, Eq. 5), before its row is overwritten; the
-  // pair's psi goes through the LDS and H's column is requested eight rows at a time
+  // pair's value row and psi go through the LDS
   if (evict) {
-    const float *pe = eslot < m ? a.psi + ((size_t)u * C + eslot) * R : a.f_psi + (size_t)u * R;
-    float *s_pe = reinterpret_cast<float *>(s_cand + 1);     // s_cand[0] has been read; [1..] is free
-    double ve = 0.0;
+    float *s_ve = reinterpret_cast<float *>(s_cand + NW);    // behind the waves' candidates: [D], then psi [R]
+    float *s_pe = s_ve + D;
     if (tid < D)
-      ve = (double)Store<T>::to_float(lds.v ? lds.v[(size_t)eslot * D + tid]
-                                            : (eslot < m ? vc[(size_t)eslot * D + tid] : vn[tid]));
-    if (tid < R) s_pe[tid] = pe[tid];
+      s_ve[tid] = Store<T>::to_float(
+          lds.v ? lds.v[(size_t)eslot * D + tid] : (eslot < m ? vc[(size_t)eslot * D + tid] : v_new));
+    if (tid < R) s_pe[tid] = eslot < m ? a.psi[((size_t)u * C + eslot) * R + tid] : psi_new;
     __syncthreads();
-    if (tid < D) {
-      for (int r0 = 0; r0 < R; r0 += 8) {
-        float h[8];
+    for (int e0 = 0; e0 < hn; e0 += HB * THREADS) {
+      if (e0 > 0) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) h[j] = (lds.H ? lds.H : Hu)[(size_t)(r0 + j < R ? r0 + j : R - 1) * D + tid];
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-          if (r0 + j < R) Hu[(size_t)(r0 + j) * D + tid] = (float)fma((double)s_pe[r0 + j], ve, (double)h[j]);
+        for (int j = 0; j < HB; ++j) {
+          const int e = e0 + tid + j * THREADS;
+          h[j] = Hs[e < hn ? e : hn - 1];
+        }
       }
-    } else if (tid - D < R) {
-      zu[tid - D] += (double)s_pe[tid - D];
+#pragma unroll
+      for (int j = 0; j < HB; ++j) {
+        const int e = e0 + tid + j * THREADS;
+        if (e < hn) Hu[e] = (float)fma((double)s_pe[e / D], (double)s_ve[e % D], (double)h[j]);
+      }
     }
+    if (tid < R) zu[tid] = z_old + (double)s_pe[tid];
   }
   __syncthreads();
   // scores of the pairs that stay, and the new pair into its slot (Sec. 3.2: in place)
@@ -135,10 +169,10 @@ __device__ inline void gqa_finish_unit(const StepArgs &a, int u, int tid, double
     if (r != ins_slot) a.acc[(size_t)u * C + r] = s_e[r];
   if (ins_slot >= 0) {
     if (tid < D) {
-      kc[(size_t)ins_slot * D + tid] = lds.k ? lds.k[(size_t)m * D + tid] : kn[tid];
-      vc[(size_t)ins_slot * D + tid] = lds.v ? lds.v[(size_t)m * D + tid] : vn[tid];
+      kc[(size_t)ins_slot * D + tid] = k_new;
+      vc[(size_t)ins_slot * D + tid] = v_new;
     }
-    if (tid < R) a.psi[((size_t)u * C + ins_slot) * R + tid] = a.f_psi[(size_t)u * R + tid];
+    if (tid < R) a.psi[((size_t)u * C + ins_slot) * R + tid] = psi_new;
     if (tid == 0) {
       a.acc[(size_t)u * C + ins_slot] = s_e[m];
       a.pos[(size_t)u * C + ins_slot] = n;
@@ -430,13 +464,18 @@ __global__ __launch_bounds__(256) void gqa_finish_kernel(const StepArgs a, int n
   const int u = (int)blockIdx.x, tid = threadIdx.x;
   const int rows_cap = a.C + 2;
   double *s_e = dyn, *s_inc = dyn + rows_cap;
-  const int n = sane_n_seen(a.n_seen[u]);
-  const int rows = (n < a.C ? n : a.C) + 1;
-  for (int r = tid; r < rows; r += 256) {
-    double p[kGqaMaxHeadBlocks];
+  // the first pass's sums are requested before n_seen says how many of them the blocks wrote
+  double p[kGqaMaxHeadBlocks];
+  auto request = [&](int r) __attribute__((always_inline)) {
 #pragma unroll
     for (int hb = 0; hb < kGqaMaxHeadBlocks; ++hb)
       p[hb] = a.gqa_parts[((size_t)u * nhb + (hb < nhb ? hb : nhb - 1)) * rows_cap + r];
+  };
+  request(tid < rows_cap ? tid : rows_cap - 1);
+  const int n = sane_n_seen(a.n_seen[u]);
+  const int rows = (n < a.C ? n : a.C) + 1;
+  for (int r = tid; r < rows; r += 256) {
+    if (r != tid) request(r);
     double v = 0.0;
 #pragma unroll
     for (int hb = 0; hb < kGqaMaxHeadBlocks; ++hb)
