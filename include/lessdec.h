@@ -196,7 +196,7 @@ int lessdec_prefill(const lessdec_desc *desc, const void *Q, const void *K, cons
  * prescribes.  With LESSDEC_FLAG_LAMBDA the discarded pair is instead the oldest one that is
  * neither among the first n_heavy tokens of the sequence nor among the n_recent most recent.
  * With q_per_kv = G > 1: q and out are [B,Hh,G,D] (k, v stay [B,Hh,D]).  Up to 8 query heads
- * with fp16 storage run on a streaming kernel (a block per unit, a wave per query head) that
+ * with fp16 storage run on a streaming kernel (a block per unit, a wave per two or four query heads) that
  * leaves the discarded pair pending like the single-head path; other shapes on a plain kernel
  * that folds the discarded pair at once.
  */
