@@ -546,24 +546,32 @@ static hipError_t launch_rows_t(const RowArgs &a, hipStream_t st)
 // Whether psi rides along: it needs nothing of the row pass and is bound by other instructions, so it fills what the longest
 // sweeps leave idle, and a launch is saved; but it reads a head's weights again for every 64 rows, where a launch of its own keeps them
 // in registers (other hidden widths have no such form: riding is 5 % and more faster there).  us of a whole prompt phase, psi
-// in a launch of its own against riding along, D = 128, R' = 512, rank 8 unless said:
-//   2048 blocks of maps        32 units x 64 tokens 47 and 40, 32 x 777 140 and 119, 64 x 1000 269 and 234, 2048 x 64 184 and 178
-//   4096, short sweeps         4096 x 64 349 and 353 (4096 x 40, 2560 blocks: 267 and 263), 1024 x 256 406 and 402; rank 4 334 and
-//                              352, 394 and 410; rank 16 389 and 385, 446 and 437; R' = 256 298 and 311, 360 and 370
-//   4096, 500 tokens           512 x 512 495 and 485; rank 4 489 and 491; R' = 256 454 and 453
-//   8192                       4096 x 128 629 and 648 (rank 4 621 and 667), 1024 x 512 884 and 901, 512 x 1000 1173 and 1161 (rank 4
-//                              1154 and 1174), 256 x 2000 1842 and 1806 (rank 4 1814 and 1816)
-//   8192, D = 64               4096 x 128 493 and 481, 1024 x 512 678 and 654; R' = 256 419 and 430, 607 and 604
-//   more than 8192 workgroups  2048 x 400 1227 and 1265, 2048 x 1024 4530 and 4610
-// (128 units x 4 heads x 500: 378 and 355, x 2000, 64 units: 1607 and 1550)
+// in a launch of its own against riding along, units x tokens, R' = 512, rank 8 unless said:
+//   2048 blocks of maps     2048 x 64 193 and 192, 2560 x 40 (1600 blocks) 195 and 186
+//   2560                    1280 x 128 239 and 238, 640 x 256 at rank 16 307 and 303
+//   3072, short sweeps      3072 x 64 268 and 276, 1536 x 128 273 and 278, 768 x 256 313 and 317
+//   4096, short sweeps      4096 x 64 340 and 352, 2048 x 128 330 and 342, 1024 x 256 388 and 397; rank 16 431 and 437; rank 4 384 and
+//                           403; R' = 256 353 and 364
+//   4096, 500 tokens        512 x 512 484 and 481; rank 16 523 and 519; rank 4 479 and 485; R' = 256 448 and 446
+//   4096, long sweeps       256 x 1000 632 and 612 (rank 4 627 and 616), 128 x 2000 971 and 929
+//   6144, long sweeps       384 x 1000 906 and 903 (rank 16 967 and 960; rank 4 898 and 910); R' = 256, 320 x 1100, 819 and 808
+//   8192                    4096 x 128 605 and 648, 1024 x 512 859 and 893, 512 x 1000 1152 and 1163 (rank 16 1220 and 1228), 256 x 2000
+//                           1827 and 1831
+//   D = 64: 2048            2048 x 64 140 and 132
+//   4096                    2048 x 128 248 and 246, 1024 x 256 288 and 286, 512 x 512 361 and 350, 256 x 1000 474 and 448
+//   8192                    4096 x 128 454 and 465, 1024 x 512 639 and 641 (R' = 256 585 and 587), 512 x 1000 860 and 847
+//   more than 8192 workgroups  2048 x 400 1227 and 1265, 2048 x 1024 4530 and 4610 (both with a longer activation, 17 instructions for 12.5)
+// (256 units x 4 heads x 500: 646 and 627)
 bool rows_f16_take_maps(const MlpArgs &maps, unsigned U, int G)
 {
   const int ngrp = (maps.rpu + 16 * kPrefillWaves - 1) / (16 * kPrefillWaves);
   if ((size_t)U * G * ngrp > 8192) return false;
   if (!mlp_weights_in_registers(maps)) return true;
-  unsigned most = ngrp >= 32 ? 8192 : ngrp >= 8 ? 4096 : 2048;
-  if (maps.D == 64 && (maps.Rp > 256 || ngrp > 8)) most = 8192;
-  if (maps.D == 128 && maps.Rp == 512 && maps.R % 8 == 0) most = ngrp > 8 ? 8192 : ngrp > 1 || maps.R > 8 ? 4096 : 3072;
+  const bool full = maps.R % 8 == 0;                      // of a block's columns of features none is padding
+  unsigned most;
+  if (maps.D == 64) most = ngrp > 8 ? 8192 : ngrp == 8 || maps.Rp > 256 ? 4096 : 2048;
+  else if (ngrp >= 8) most = ngrp > 8 && full ? 6144 : 4096;
+  else most = full && maps.Rp == 512 ? 2560 : 2048;
   return mlp_psi_blocks(maps, kPsiTiles) <= most;
 }
 
