@@ -7,13 +7,16 @@ gelu(x) = x - |x| Q(|x|) for x >= 0 and -|x| Q(|x|) for x < 0.  Weighted least s
 dense grid (the weight is the factor exp(-t^2/2) t that multiplies the polynomial's error in
 gelu).  Prints p, c_1..c_7 and the error of a float32 evaluation against float64 erfc.
 
-And those of gelu_exp2_f32(): log2 Q(t) = -1 + c_1 t + ... + c_8 t^8, so that gelu takes one base-2 exponential and no
-reciprocal: near-minimax (Lawson's reweighted least squares) in the error that it leaves in t Q(t).
+And those of gelu_exp2_f32(): log2 Q(t) = c_0 + c_1 s + ... + c_10 s^10, s = t - 1, so that gelu takes one base-2
+exponential and no reciprocal: near-minimax (Lawson's reweighted least squares) in the relative error of Q, which may
+grow tenfold per unit beyond t = 3, as that of the form above does, and counts for less where t Q(t) falls below 1e-9.  The
+coefficients are rounded to fp32 one after the other, lowest first, and the others fitted again.
 """
 import numpy as np
 from scipy.special import erfc, erfcx, log_ndtr
 
 P, N = 0.24, 7
+CENTRE, DEGREE = 1.0, 10
 
 
 def fit(p=P, n=N):
@@ -26,46 +29,58 @@ def fit(p=P, n=N):
     return c
 
 
+def _fma(a, b, c):
+    """Fused multiply-add of fp32 values, rounded to fp32 (the product is exact in fp64, the sum all but)."""
+    return (a.astype(np.float64) * b + c).astype(np.float32)
+
+
 def gelu32(x, p, c):
+    """With the reciprocal, as a kernel evaluates it."""
     x = x.astype(np.float32)
+    c = [np.float32(v) for v in c]
     t = np.abs(x)
-    u = (np.float32(1) / (np.float32(1) + np.float32(p) * t)).astype(np.float32)
-    acc = np.full_like(u, np.float32(c[-1]))
+    u = np.float32(1) / _fma(t, np.float32(p), 1.0)
+    acc = np.full_like(u, c[-1])
     for k in range(len(c) - 2, -1, -1):
-        acc = (acc * u + np.float32(c[k])).astype(np.float32)
-    acc = (acc * u).astype(np.float32)
-    e = np.exp2((np.float32(-0.5 * np.log2(np.e)) * t * t).astype(np.float32)).astype(np.float32)
-    tq = (t * (acc * e).astype(np.float32)).astype(np.float32)
-    return np.where(x >= 0, (x - tq).astype(np.float32), -tq)
+        acc = _fma(acc, u, c[k])
+    e = np.exp2((t * t * np.float32(-0.5 * np.log2(np.e))).astype(np.float64)).astype(np.float32)
+    return np.maximum(x, 0) - t * (acc * u * e)
 
 
-def fit_log2(n=8, top=7.0, rounds=400):
-    """c_0 = -1, c_1 .. c_n, and the largest weighted error of t Q(t); beyond `top` t Q(t) is below 1e-11."""
+def fit_log2(n=DEGREE, centre=CENTRE, top=7.5, rounds=300):
+    """c_0 .. c_n, each of them a fp32 number, and the largest weighted error before the rounding."""
     t = (top * (0.5 - 0.5 * np.cos(np.linspace(0, np.pi, 4001))))[1:]
-    y = (log_ndtr(-t) / np.log(2) + 1) / t
-    # (small t count up to twice: there the error should stay below the rounding of small results)
-    w = np.maximum(np.log(2) * t * t * np.exp(log_ndtr(-t)), 1e-13) * (1 + 1 / (1 + (t / 0.3) ** 2))
-    lam, best = np.full_like(t, 1 / len(t)), None
-    A = np.polynomial.chebyshev.chebvander(2 * t / top - 1, n - 1)
-    for _ in range(rounds):
+    y, tq = log_ndtr(-t) / np.log(2), t * np.exp(log_ndtr(-t))
+    w = np.log(2) * tq / np.maximum(tq * 1e-7 * 10 ** np.maximum(t - 3, 0), 2e-13)
+    A = ((t - centre)[:, None] / top) ** np.arange(n + 1)
+
+    def solve(lam, known):
         r = np.sqrt(lam) * w
-        c, *_ = np.linalg.lstsq(A * r[:, None], y * r, rcond=None)
-        e = np.abs((A @ c - y) * w)
+        k = len(known)
+        rest = y - A[:, :k] @ (np.array(known) * top ** np.arange(k))
+        c, *_ = np.linalg.lstsq(A[:, k:] * r[:, None], rest * r, rcond=None)
+        return c / top ** np.arange(k, n + 1), np.abs((A[:, k:] @ c - rest) * w)
+
+    lam, best = np.full_like(t, 1 / len(t)), None
+    for _ in range(rounds):
+        c, e = solve(lam, [])
         if best is None or e.max() < best[0]:
-            best = (e.max(), c)
-        lam = lam * e
-        lam /= lam.sum()
-    p = np.polynomial.Chebyshev(best[1], domain=[0, top]).convert(kind=np.polynomial.Polynomial, domain=[-1, 1], window=[-1, 1])
-    return np.concatenate([[-1.0], p.coef]), best[0]
+            best = (e.max(), lam)
+        lam = lam * e / (lam * e).sum()
+    known = []
+    while len(known) <= n:
+        known.append(float(np.float32(solve(best[1], known)[0][0])))
+    return known, best[0]
 
 
-def gelu_exp2_32(x, c):
-    """As the kernels evaluate it: fused multiply-adds rounded to fp32."""
+def gelu_exp2_32(x, c, centre=CENTRE):
+    """As the kernels evaluate it."""
     x = x.astype(np.float32)
     t = np.abs(x)
+    s = t - np.float32(centre)
     p = np.full_like(t, np.float32(c[-1]))
     for k in range(len(c) - 2, -1, -1):
-        p = (p.astype(np.float64) * t + np.float64(np.float32(c[k]))).astype(np.float32)
+        p = _fma(p, s, np.float32(c[k]))
     e = np.exp2(p.astype(np.float64)).astype(np.float32)
     return (np.maximum(x, 0).astype(np.float64) - t.astype(np.float64) * e).astype(np.float32)
 
@@ -79,9 +94,10 @@ if __name__ == "__main__":
     exact = 0.5 * x * erfc(-x / np.sqrt(2))
     err = np.abs(gelu32(x, P, c).astype(np.float64) - exact)
     print("max abs error on [-12, 12]:", err.max(), "; on [-4, 4]:", err[np.abs(x) <= 4].max())
-    c8, worst = fit_log2()
-    print("log2 Q:", ", ".join(f"{v:.10e}" for v in c8), "; t Q(t) within", worst)
-    e8 = np.abs(gelu_exp2_32(x, c8).astype(np.float64) - exact)
-    for name, e in (("u-polynomial", err), ("exp2", e8)):
-        print(name, "rms on [-2, 2]:", np.sqrt((e[np.abs(x) <= 2] ** 2).mean()), "; max on [-4, 4]:", e[np.abs(x) <= 4].max())
     print("max error / max(|gelu|, |x| 6e-8, 1e-30):", (err / np.maximum(np.abs(exact), 1e-30))[np.abs(x) > 1e-3].max())
+    c10, worst = fit_log2()
+    print("log2 Q about", CENTRE, ":", ", ".join(f"{v:.10e}" for v in c10), "; of the allowed error", worst)
+    e10 = np.abs(gelu_exp2_32(x, c10).astype(np.float64) - exact)
+    for lo, hi in ((-6, -5), (-5, -4), (-4, -3), (-3, -2), (-2, -1), (-1, 0), (0, 1), (1, 2), (2, 4)):
+        k = (x >= lo) & (x <= hi)
+        print([lo, hi], "root mean square with the reciprocal", np.sqrt((err[k] ** 2).mean()), "; exp2", np.sqrt((e10[k] ** 2).mean()))

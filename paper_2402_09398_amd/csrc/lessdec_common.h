@@ -130,7 +130,7 @@ __device__ inline double gelu_f64(double x)
 // Branch-free fp32 GELU for the matrix-core feature maps.  With t = |x| the upper normal
 // tail is Q(t) = exp(-t^2/2) * (c1 u + ... + c7 u^7), u = 1 / (1 + 0.24 t) (polynomial error
 // 1e-9; constants from fit_gelu_poly.py), and gelu(x) = x - t Q(t) for x >= 0, -t Q(t) else.
-// Absolute error in fp32: 2.5e-7 on [-4, 4], one ulp of x beyond.
+// Absolute error in fp32: 2.5e-7 on [-4, 4], one ulp of x beyond.  (No kernel uses it.)
 __device__ inline float gelu_fast_f32(float x)
 {
   const float t = fabsf(x);
@@ -150,31 +150,37 @@ __device__ inline float gelu_fast_f32(float x)
   return __builtin_bit_cast(float, xi > 0 ? xi : 0) - tq;
 }
 
-// The same activation for the hidden layers with one transcendental: log2 Q(t) is smooth, a polynomial of degree 8 with
-// log2 Q(0) = -1 kept exact takes t Q(t) to 1e-8 (fit_gelu_poly.py; the leading term is negative, so that it goes to
-// -infinity beyond), and gelu(x) = max(x, 0) - t 2^poly(t): 11 instructions where the form above takes 16, and closer to erfc
-// in fp32 (root mean square error on [-2, 2] 2.9e-8 against 3.1e-8; the largest on [-4, 4], 2.6e-7 and 2.5e-7, is the
-// rounding of x there).  The hidden layers of the matrix-core maps use this one; the other remains as the form that the fp64
-// one below shares its constants with, and the yardstick of the tests.
+// The fp32 GELU of the matrix-core feature maps' hidden layers, branch-free and with one transcendental: with t = |x| the upper
+// normal tail is Q(t) = 2^p(t), log2 Q being smooth enough for a polynomial of degree 10 (fit_gelu_poly.py), and
+// gelu(x) = max(x, 0) - t 2^p(t).  p is written about t = 1, where it is small, so that the roundings of Horner's scheme stay below
+// those of the other roundings up to t = 4; its leading term is negative, so that p goes to -infinity beyond the fit.
+// Measured on gfx950 against erfc, root mean square: 1.6e-9 on [-3, -5/2], 1.1e-8 on [-1, -1/2], 9.2e-9 on [1/4, 1/2]; in every
+// range of half a unit from -13/2 to 13 no larger than that of the form e^{-t^2/2} u q(u), u = 1 / (1 + 0.24 t), of
+// fit_gelu_poly.py, which takes 16 instructions, two of them transcendental, where this one takes 14 (those errors: 1.6e-9, 2.1e-8,
+// 1.9e-8).  Below -13/2, where gelu is above -2.7e-10, to 2e-13.  Degree 8 about t = 0 (11 instructions) errs by 5 to 700 times
+// as much as that form below -5/2.
 __device__ inline float gelu_exp2_f32(float x)
 {
-  const float t = fabsf(x);
-  float p = -2.0174934872e-06f;
-  p = fmaf(p, t, 2.9592299348e-05f);
-  p = fmaf(p, t, -1.3967072405e-04f);
-  p = fmaf(p, t, -2.4949272248e-04f);
-  p = fmaf(p, t, 7.2111265152e-03f);
-  p = fmaf(p, t, -5.2599315427e-02f);
-  p = fmaf(p, t, -4.5917365010e-01f);
-  p = fmaf(p, t, -1.1511093201e+00f);
-  p = fmaf(p, t, -1.0f);
+  const float t = fabsf(x), s = t - 1.0f;
+  float p = -2.3653170089e-08f;
+  p = fmaf(p, s, 4.8210540626e-07f);
+  p = fmaf(p, s, -3.9688147808e-06f);
+  p = fmaf(p, s, 1.4616596673e-05f);
+  p = fmaf(p, s, 1.5595947843e-05f);
+  p = fmaf(p, s, -5.8290286688e-04f);
+  p = fmaf(p, s, 4.7590648755e-03f);
+  p = fmaf(p, s, -2.8118170798e-02f);
+  p = fmaf(p, s, -5.7772850990e-01f);
+  p = fmaf(p, s, -2.2003047466e+00f);
+  p = fmaf(p, s, -2.6560328007e+00f);
   const float e = __builtin_amdgcn_exp2f(p);
-  // max(x, 0) on the bits (as above)
+  // max(x, 0) on the bits: one instruction, where fmaxf quiets its input in another (a NaN stays one through e)
   const int xi = __builtin_bit_cast(int, x);
   return fmaf(-t, e, __builtin_bit_cast(float, xi > 0 ? xi : 0));
 }
 
-// The approximation of gelu_fast_f32 evaluated in fp64 (absolute error 1e-9): for the handful of
+// GELU in fp64 with Q(t) = exp(-t^2/2) (c1 u + ... + c7 u^7), u = 1 / (1 + 0.24 t) (absolute error 1e-9; constants from
+// fit_gelu_poly.py): for the handful of
 // layer-2 activations per row, whose inputs already carry the fp32 rounding of layer 1.
 // Much lighter on registers than the library erfc.
 __device__ inline double gelu_poly_f64(double x)

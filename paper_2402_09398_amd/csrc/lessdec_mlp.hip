@@ -27,13 +27,14 @@ __global__ __launch_bounds__(256) void mlp_pair_kernel(const MlpArgs a, const Ml
 // groups; after two chunks the block adds the four layer-2 sums through the LDS and finishes the
 // outputs as above (same arithmetic in the same order as mlp_psi_block: identical results).  The
 // next chunk's rows are requested before the current chunk's arithmetic.
-// Bound by vector instructions (12.5 per activation, one of them transcendental, where there were 17 and two) and the clock that
+// Bound by vector instructions (15.5 per activation, one of them transcendental, where there were 17 and two) and the clock that
 // the card lowers under them (2.1 GHz).  With one max, one mixed-precision fma per low half, one barrier per 32 rows in place of
 // three per 16, and layer 1 of the next group issued between the activations of this one: 920 -> 756 us for 2048 units x 1024
-// tokens, 460 -> 391 for 128 x 8192 (R' = 512, R = 8).  Then (799 on another card) an activation without a reciprocal: 760; the
-// finish without divisions and W3's products requested together, and a row's unit found by a multiplication: 700.  (Four
-// waves a SIMD, eight waves of two groups each, rows by DMA through the LDS, the polynomial's constants as literals, which makes a
-// multiply-add 2.7 cycles there: 4 % fewer cycles at a clock 4 % lower, no gain.)
+// tokens, 460 -> 391 for 128 x 8192 (R' = 512, R = 8).  Then (808 and 418 on another card) an activation without a reciprocal, the
+// finish without divisions and with W3's products requested together, and a row's unit found by a multiplication: 751 and 381.
+// (With an activation of three instructions less, which is not as accurate: 676 and 343.  Four waves a SIMD, eight waves of two groups
+// each, rows by DMA through the LDS, the polynomial's constants as literals, which makes a multiply-add 2.7 cycles there: 4 % fewer
+// cycles at a clock 4 % lower, no gain.)
 // grid = Hh * parts (head fastest), every block a contiguous share of the head's chunks.
 template <int D, int NGW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void mlp_rows_kernel(const MlpArgs a,
@@ -94,7 +95,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
         for (int i = 0; i < 2 * (D / 32); ++i) {
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x002, 12, 0);
+          __builtin_amdgcn_sched_group_barrier(0x002, 14, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
