@@ -1,9 +1,11 @@
-"""Derives the constants of gelu_f64() in lessdec_common.h.
+"""Derives the constants of gelu_f64() and exp_parts_f64() in lessdec_common.h.
 
 Upper tail of the standard normal, t >= 0: Q(t) = exp(-t^2 / 2) u q(u) with u = 1 / (1 + p t).  exp(t^2/2) Q(t) is smooth and slowly
 decaying, so that a polynomial q of degree 16, interpolated at the Chebyshev points of u over 0 <= t <= 8 and written about
 a point in the middle (which keeps the coefficients near 1 and their rounding small), takes t Q(t) to 1.1e-17 with the
 coefficients rounded to fp64.  All in 50 digits; beyond t = 8 t Q(t) is below 1e-14 and decays faster than q errs.
+
+e^r for |r| <= ln 2 / 2: 1 + r + r^2/2 + r^3 p(r), p of degree 8, interpolated at the Chebyshev points.
 """
 import math
 from decimal import Decimal, getcontext
@@ -61,8 +63,33 @@ def tail(t, coefficients):
     return t * u * q * e, t * scaled_tail(t) * e
 
 
+def fit_exp(degree=11, known=3):
+    """Coefficients of r^0 .. r^degree, as floats; the first `known` are those of the series."""
+    half, n = Decimal(2).ln() / 2 * Decimal("1.0001"), degree - known + 1
+    rs = [half * Decimal(math.cos(math.pi * (2 * i + 1) / (2 * n))) for i in range(n)]
+    c = [sum(r ** k / math.factorial(k + known) for k in range(40)) for r in rs]
+    for j in range(1, n):                                   # divided differences
+        for i in range(n - 1, j - 1, -1):
+            c[i] = (c[i] - c[i - 1]) / (rs[i] - rs[i - j])
+    poly = [c[-1]]
+    for i in range(n - 2, -1, -1):                          # Newton's form to powers
+        poly = [c[i] - poly[0] * rs[i]] + [poly[k] - poly[k + 1] * rs[i] for k in range(len(poly) - 1)] + [poly[-1]]
+    return [1 / math.factorial(k) for k in range(known)] + [float(v) for v in poly]
+
+
+def exp_error(r, coefficients):
+    """Relative error of e^r from these coefficients, exactly evaluated."""
+    r, p = Decimal(r), Decimal(0)
+    for v in reversed(coefficients):
+        p = p * r + Decimal(v)
+    return float(p / r.exp() - 1)
+
+
 if __name__ == "__main__":
     rounded = [float(v) for v in fit()]
     for k, v in enumerate(rounded):
         print(f"q{k} = {v:.17e}")
     print("t Q(t) within", max(abs(float(a - b)) for a, b in (tail(0.03 * i, rounded) for i in range(300))))
+    for k, v in enumerate(fit_exp()):
+        print(f"e{k} = {v:.17e}")
+    print("e^r within", max(abs(exp_error(0.34658 * i / 100, fit_exp())) for i in range(-100, 101)))

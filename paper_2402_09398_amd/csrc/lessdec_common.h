@@ -75,6 +75,27 @@ __device__ inline double exp_softmax_f64(double x)
   return x > -708.0 ? __builtin_ldexp(p, (int)n) : 0.0;
 }
 
+// e^s for s <= 0 to fp64, as 2^n times the value returned: s = n ln 2 + r with |r| <= ln 2 / 2, 1 + r + r^2/2 + r^3 times a
+// polynomial of degree 8 (fit_gelu_f64.py; to 3.3e-17 relatively, with two constants and steps less than the Taylor polynomial).
+__device__ inline double exp_parts_f64(double s, double &n)
+{
+  n = __builtin_rint(s * 1.44269504088896338700e+00);
+  double r = fma(n, -6.93147180369123816490e-01, s);
+  r = fma(n, -1.90821492927058770002e-10, r);
+  double e = 2.50955546771111123e-08;
+  e = fma(e, r, 2.76138068615382899e-07);
+  e = fma(e, r, 2.75572800670169807e-06);
+  e = fma(e, r, 2.48015363886907663e-05);
+  e = fma(e, r, 1.98412698543386110e-04);
+  e = fma(e, r, 1.38888889058815424e-03);
+  e = fma(e, r, 8.33333333333215534e-03);
+  e = fma(e, r, 4.16666666666513572e-02);
+  e = fma(e, r, 1.66666666666666657e-01);
+  e = fma(e, r, 0.5);
+  e = fma(e, r, 1.0);
+  return fma(e, r, 1.0);
+}
+
 // GELU, x * Phi(x) (Sec. 3.2 names GELU as the activation of both feature maps), to fp64: with t = |x| the upper normal tail is
 // Q(t) = exp(-t^2/2) u q(u), u = 1 / (1 + 0.2 t), q a polynomial of degree 16 about u = 0.6875 (interpolated in 50 digits,
 // fit_gelu_f64.py: t Q(t) to 1.1e-17), and gelu(x) = x - t Q(t) or -t Q(t).  Within a unit in the last place of max(|x|, 1 / 4);
@@ -180,13 +201,13 @@ __device__ inline float gelu_exp2_f32(float x)
 }
 
 // GELU in fp64 with Q(t) = exp(-t^2/2) (c1 u + ... + c7 u^7), u = 1 / (1 + 0.24 t) (absolute error 1e-9; constants from
-// fit_gelu_poly.py): for the handful of
-// layer-2 activations per row, whose inputs already carry the fp32 rounding of layer 1.
-// Much lighter on registers than the library erfc.
+// fit_gelu_poly.py): for the handful of layer-2 activations per row, whose inputs already carry the fp32 rounding of
+// layer 1.  Evaluated to fp64 (within 6e-16 of the same formula with the library's exponential and a division, relatively),
+// and much lighter on registers than the library erfc.
 __device__ inline double gelu_poly_f64(double x)
 {
   const double t = fabs(x), d = fma(0.24, t, 1.0);
-  // 1 / d by two Newton steps: d >= 1 needs none of the scaling and fixing of a division
+  // 1 / d to fp64 by two Newton steps: d >= 1 needs none of the scaling and fixing of a division
   double u = __builtin_amdgcn_rcp(d);
   u = fma(fma(-d, u, 1.0), u, u);
   u = fma(fma(-d, u, 1.0), u, u);
@@ -198,7 +219,10 @@ __device__ inline double gelu_poly_f64(double x)
   a = fma(a, u, 1.5460257740e-01);
   a = fma(a, u, 8.9645194151e-02);
   a *= u;
-  const double tq = t * (a * exp_softmax_f64(-0.5 * t * t));
+  // exp(-t^2/2); 0 below the smallest fp64 number (and where t is infinite, which has no n)
+  double n;
+  const double s = -0.5 * t * t, e = exp_parts_f64(s, n);
+  const double tq = t * (a * (s > -746.0 ? __builtin_ldexp(e, (int)n) : 0.0));
   return x >= 0.0 ? x - tq : -tq;
 }
 

@@ -32,14 +32,29 @@ def horner(text, name, arg):
     return [first] + [float(x) for x in re.findall(rf"{name} = fmaf?\({name}, {arg}, {number}\);", text)]
 
 
+def _with_callees(names):
+    """These functions and the header's own that they call, callees first."""
+    src = (CSRC / "lessdec_common.h").read_text()
+    known = re.findall(r"^__device__ inline \w+ (\w+)\(", src, re.M)
+    out = []
+
+    def add(name):
+        for other in known:
+            if other != name and re.search(rf"\b{other}\(", body(name)):
+                add(other)
+        if name not in out:
+            out.append(name)
+    for n in names:
+        add(n)
+    return out
+
+
 def on_host(*names):
-    """name -> function of an array, for the header's functions of one argument; the others are what those call, in order."""
+    """name -> function of an array, for functions of one argument."""
+    kinds = {n: body(n).split("inline ")[1].split()[0] for n in names}
     with tempfile.TemporaryDirectory() as tmp:
-        text = SHIMS + "".join(body(n) for n in names)
-        kinds = {n: body(n).split("inline ")[1].split()[0] for n in names}
-        unary = [n for n in names if "," not in body(n).split(")")[0]]
-        for n in unary:
-            t = kinds[n]
+        text = SHIMS + "".join(body(n) for n in _with_callees(names))
+        for n, t in kinds.items():
             text += f'extern "C" void run_{n}(const {t} *x, {t} *y, long n) {{ for (long i = 0; i < n; ++i) y[i] = {n}(x[i]); }}\n'
         (Path(tmp) / "f.cpp").write_text(text)
         subprocess.run(["g++", "-std=c++17", "-O2", "-ffp-contract=off", "-fPIC", "-shared", "-o", f"{tmp}/f.so", f"{tmp}/f.cpp"],
@@ -55,4 +70,4 @@ def on_host(*names):
             getattr(lib, f"run_{n}")(x.ctypes.data_as(ctypes.c_void_p), y.ctypes.data_as(ctypes.c_void_p), ctypes.c_long(x.size))
             return y
         return call
-    return {n: caller(n) for n in unary}
+    return {n: caller(n) for n in names}

@@ -9,6 +9,8 @@ from pathlib import Path
 import numpy as np
 from scipy.special import erfc
 
+from tests.header_on_host import body, horner, on_host
+
 CSRC = Path(__file__).resolve().parents[1] / "paper_2402_09398_amd" / "csrc"
 
 
@@ -51,14 +53,33 @@ def test_fp32_evaluation_error():
 
 
 def test_fp64_evaluation_error():
-    p, horner = _header_constants("gelu_poly_f64")
+    gelu = on_host("gelu_poly_f64")["gelu_poly_f64"]
     x = np.linspace(-12, 12, 400001)
-    t = np.abs(x)
-    u = 1.0 / (1.0 + p * t)
-    a = np.full_like(u, horner[0])
-    for c in horner[1:]:
-        a = a * u + c
-    a = a * u
-    tq = t * (a * np.exp(-0.5 * t * t))
-    got = np.where(x >= 0, x - tq, -tq)
-    assert np.abs(got - 0.5 * x * erfc(-x / np.sqrt(2))).max() < 2e-9
+    assert np.abs(gelu(x) - 0.5 * x * erfc(-x / np.sqrt(2))).max() < 2e-9
+    assert np.isnan(gelu(np.array([np.nan, -np.inf]))).all() and (gelu(np.array([40.0, 1e300, -1e300])) == [40.0, 1e300, 0.0]).all()
+
+
+def test_fp64_evaluation_is_to_fp64():
+    """Nothing but roundings between the kernels' evaluation and the formula itself (in more digits): a few units of 2^-53 from the
+    polynomial, the exponential and the products, and 2^-53 t^2 / 2 from rounding the exponent."""
+    p, constants = _header_constants("gelu_poly_f64")
+    x = -np.linspace(0.01, 37, 100001)                              # where gelu is the tail alone
+    t = -x.astype(np.longdouble)
+    u = 1 / (1 + np.longdouble(p) * t)
+    a = np.zeros_like(u)
+    for c in constants:
+        a = a * u + np.longdouble(c)
+    want = -t * (a * u * np.exp(-t * t / 2))
+    got = on_host("gelu_poly_f64")["gelu_poly_f64"](x)
+    assert (np.abs(got - want) <= np.abs(want) * (10 + t * t) * 2.0 ** -53).all()
+
+
+def test_exponential_constants():
+    spec = importlib.util.spec_from_file_location("fit_gelu_f64", CSRC / "fit_gelu_f64.py")
+    fit = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(fit)
+    c = horner(body("exp_parts_f64"), "e", "r")[::-1]
+    c = [1.0] + c                                                   # (the last step is the function's result)
+    assert len(c) == 12 and c[:3] == [1.0, 1.0, 0.5]
+    np.testing.assert_allclose(c, fit.fit_exp(), rtol=1e-9, atol=0)  # (the points are cosines of a math library)
+    assert max(abs(fit.exp_error(0.34658 * i / 100, c)) for i in range(-100, 101)) < 4e-17
