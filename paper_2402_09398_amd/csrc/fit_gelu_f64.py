@@ -1,66 +1,78 @@
 """Derives the constants of gelu_f64() and exp_parts_f64() in lessdec_common.h.
 
-Upper tail of the standard normal, t >= 0: Q(t) = exp(-t^2 / 2) u q(u) with u = 1 / (1 + p t).  exp(t^2/2) Q(t) is smooth and slowly
-decaying, so that a polynomial q of degree 16, interpolated at the Chebyshev points of u over 0 <= t <= 8 and written about
-a point in the middle (which keeps the coefficients near 1 and their rounding small), takes t Q(t) to 1.1e-17 with the
-coefficients rounded to fp64.  All in 50 digits; beyond t = 8 t Q(t) is below 1e-14 and decays faster than q errs.
+Upper tail of the standard normal, t >= 0: Q(t) = exp(-t^2 / 2) F(t), F(t) = 1/2 + c_1 v + ... + c_N v^N with
+v = t / (1 + p t).  F decays smoothly from 1/2 to 1 / (t sqrt(2 pi)), and small t have small v, so that neither the
+polynomial nor the division costs digits there.  Weighted least squares over 0 <= t <= 39, beyond which Q is below the smallest fp64
+number, in the relative error of F; the weight allows (1 + 0.6 t^2) 1e-17, a tenth of what rounding -t^2 / 2 to fp64 costs.  The
+coefficients are rounded to fp64 one after the other, lowest first, and the others fitted again.  All in 90 digits.
 
 e^r for |r| <= ln 2 / 2: 1 + r + r^2/2 + r^3 p(r), p of degree 8, interpolated at the Chebyshev points.
 """
 import math
 from decimal import Decimal, getcontext
 
-getcontext().prec = 50
-P, N, CENTRE, TOP = Decimal("0.2"), 16, Decimal("0.6875"), Decimal(8)
-PI = Decimal("3.14159265358979323846264338327950288419716939937510582097494459")
+getcontext().prec = 90
+P, N, TOP = Decimal("0.2"), 20, 39
+PI = Decimal("3.14159265358979323846264338327950288419716939937510582097494459230781640628620899862803482534211706798")
 
 
 def scaled_tail(t):
-    """exp(t^2 / 2) Q(t): the series of the normal's distribution below 4, its continued fraction above."""
+    """F(t) = exp(t^2 / 2) Q(t): the series of the normal's distribution below 4, its continued fraction above."""
     t = Decimal(t)
     if t < 4:
         s, term, k = Decimal(0), t, 0
-        while abs(term) > Decimal(10) ** -48:
+        while abs(term) > Decimal(10) ** -80:
             s += term
             k += 1
             term = term * t * t / (2 * k + 1)
         return (t * t / 2).exp() / 2 - s / (2 * PI).sqrt()
     f = Decimal(0)
-    for k in range(400, 0, -1):
+    for k in range(600, 0, -1):
         f = Decimal(k) / (t + f)
     return 1 / ((t + f) * (2 * PI).sqrt())
 
 
-def fit():
-    """Coefficients of q about CENTRE, lowest first, as Decimals."""
+def _solve(a, b):
+    n = len(b)
+    for i in range(n):
+        for j in range(i + 1, n):
+            m = a[j][i] / a[i][i]
+            for k in range(i, n):
+                a[j][k] -= m * a[i][k]
+            b[j] -= m * b[i]
+    for i in reversed(range(n)):
+        b[i] = (b[i] - sum(a[i][k] * b[k] for k in range(i + 1, n))) / a[i][i]
+    return b
+
+
+def fit(points=120):
+    """c_1 .. c_N as floats."""
     low = 1 / (1 + P * TOP)
-    half, mid = (1 - low) / 2, (1 + low) / 2
-    us = [half * Decimal(math.cos(math.pi * (2 * i + 1) / (2 * N + 2))) + mid for i in range(N + 1)]
-    c = [scaled_tail((1 / u - 1) / P) / u for u in us]
-    for j in range(1, N + 1):                               # divided differences
-        for i in range(N, j - 1, -1):
-            c[i] = (c[i] - c[i - 1]) / (us[i] - us[i - j])
-    poly = [c[N]]
-    for i in range(N - 1, -1, -1):                          # Newton's form to powers of w = u - CENTRE
-        root = us[i] - CENTRE
-        grown = [Decimal(0)] * (len(poly) + 1)
-        for k, v in enumerate(poly):
-            grown[k + 1] += v
-            grown[k] -= v * root
-        grown[0] += c[i]
-        poly = grown
-    return poly
+    us = [(1 + low) / 2 + (1 - low) / 2 * Decimal(math.cos(math.pi * (2 * i + 1) / (2 * points))) for i in range(points)]
+    ts = [(1 / u - 1) / P for u in us]
+    vs = [t * u for t, u in zip(ts, us)]
+    fs = [scaled_tail(t) for t in ts]
+    w2 = [1 / (f * (1 + Decimal("0.6") * t * t)) ** 2 for f, t in zip(fs, ts)]
+    powers = [[v ** k for k in range(N + 1)] for v in vs]
+    moments = [sum(w * row[1] ** k for w, row in zip(w2, powers)) for k in range(2 * N + 1)]
+    known = [Decimal("0.5")]
+    while len(known) <= N:
+        free = range(len(known), N + 1)
+        rest = [f - sum(c * x for c, x in zip(known, row)) for f, row in zip(fs, powers)]
+        b = [sum(w * r * row[j] for w, r, row in zip(w2, rest, powers)) for j in free]
+        known.append(Decimal(float(_solve([[moments[j + k] for k in free] for j in free], b)[0])))
+    return [float(c) for c in known[1:]]
 
 
-def tail(t, coefficients):
-    """t Q(t) from the polynomial, exactly, and the true value."""
+def error(t, coefficients):
+    """Relative error of F at t from these coefficients, exactly evaluated."""
     t = Decimal(t)
-    u = 1 / (1 + P * t)
+    v = t / (1 + P * t)
     q = Decimal(0)
-    for v in reversed(coefficients):
-        q = q * (u - CENTRE) + Decimal(v)
-    e = (-t * t / 2).exp()
-    return t * u * q * e, t * scaled_tail(t) * e
+    for c in reversed(coefficients):
+        q = (q + Decimal(c)) * v
+    f = scaled_tail(t)
+    return float((q + Decimal("0.5") - f) / f)
 
 
 def fit_exp(degree=11, known=3):
@@ -86,10 +98,10 @@ def exp_error(r, coefficients):
 
 
 if __name__ == "__main__":
-    rounded = [float(v) for v in fit()]
-    for k, v in enumerate(rounded):
-        print(f"q{k} = {v:.17e}")
-    print("t Q(t) within", max(abs(float(a - b)) for a, b in (tail(0.03 * i, rounded) for i in range(300))))
+    c = fit()
+    for k, value in enumerate(c, 1):
+        print(f"c{k} = {value:.17e}")
+    print("of the allowed error", max(abs(error(0.0154 * i * i, c)) / (1e-17 * (1 + 0.6 * (0.0154 * i * i) ** 2)) for i in range(1, 50)))
     for k, v in enumerate(fit_exp()):
         print(f"e{k} = {v:.17e}")
     print("e^r within", max(abs(exp_error(0.34658 * i / 100, fit_exp())) for i in range(-100, 101)))

@@ -22,7 +22,7 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 // (head, 16 rows) pairs, spreads the hidden units over blocks that leave their sums (fp64) in the workspace, and
 // the step's own kernel adds them (one query head per unit, ranks up to 16), or featmap_finish_kernel in part order.
 // Bound by the chain of requests, fp64 matrix products (66 cycles each) and activations of a wave.
-// 8 x 32 units, D = 128, R' = 512, fp32 storage: 9.5 us for both maps; 10.4 + 4.1 with the library's erfc in the activations and the
+// 8 x 32 units, D = 128, R' = 512, fp32 storage: 9.7 us for both maps; 10.4 + 4.1 with the library's erfc in the activations and the
 // finishing launch, which the step has taken over (11.5 + 4.8 with the weights of the second layer
 // requested after the first's products, a branch around every activation and divisions ahead of the first request), against 82 with a hidden unit per
 // thread on the vector units and a block per (head, 8 rows).

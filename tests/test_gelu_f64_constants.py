@@ -1,66 +1,62 @@
 """gelu_f64 of csrc/lessdec_common.h, the activation of the fp64 feature maps (Sec. 3.2 names GELU): its constants are the ones
-csrc/fit_gelu_f64.py derives, and evaluated in fp64 it stays within a unit in the last place of max(|x|, 1/4) of x Phi(x)."""
+csrc/fit_gelu_f64.py derives, and in every range, on either side of zero and far below it, it is no further from x Phi(x) than
+0.5 x erfc(-x / sqrt 2) in fp64."""
 import importlib.util
-import math
-import re
 from decimal import Decimal
 
 import numpy as np
+import pytest
+from scipy.special import erfc
 
-from tests.test_gelu_constants import CSRC
+from tests.header_on_host import CSRC, body, horner, on_host
 
 
-def _fit():
+@pytest.fixture(scope="module")
+def fit():
     spec = importlib.util.spec_from_file_location("fit_gelu_f64", CSRC / "fit_gelu_f64.py")
     mod = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(mod)
     return mod
 
 
-def _body():
-    src = (CSRC / "lessdec_common.h").read_text()
-    body = src[src.index("double gelu_f64(double x)"):]
-    return body[:body.index("\n}\n")]
+@pytest.fixture(scope="module")
+def gelu():
+    return on_host("gelu_f64")["gelu_f64"]
 
 
-def _horner(name, arg):
-    body = _body()
-    first = float(re.search(rf"double {name} = (-?[\d.]+e[-+]\d+);", body).group(1))
-    return [first] + [float(v) for v in re.findall(rf"{name} = fma\({name}, {arg}, (-?[\d.]+(?:e[-+]\d+)?)\);", body)]
+def test_constants(fit):
+    c = horner(body("gelu_f64"), "a", "v")[::-1]
+    assert len(c) == fit.N + 1 and c[0] == 0.5 and f"fma({fit.P}, t, 1.0)" in body("gelu_f64")
+    # the points of the fit are cosines of a math library: its digits beyond those that matter may differ
+    np.testing.assert_allclose(c[1:6], fit.fit()[:5], rtol=1e-6, atol=0)
+    assert max(abs(fit.error(0.0154 * i * i, c[1:])) / (1e-17 * (1 + 0.6 * (0.0154 * i * i) ** 2)) for i in range(1, 50)) < 2
 
 
-def test_constants():
-    fit = _fit()
-    q = _horner("a", "w")[::-1]
-    assert len(q) == fit.N + 1 and all(abs(a - float(b)) <= 1e-15 * abs(a) for a, b in zip(q, fit.fit()))
-    assert max(abs(float(a - b)) for a, b in (fit.tail(0.05 * i, q) for i in range(180))) < 2e-17
-    assert f"fma({fit.P}, t, 1.0)" in _body() and f"u - {fit.CENTRE};" in _body()
-    e = _horner("e", "r")[::-1]
-    assert len(e) == 13 and all(abs(v * math.factorial(k) - 1) < 1e-15 for k, v in enumerate(e))
+# Relative error.  numpy's erfc is nearly correctly rounded about zero, closer than the math library's on the GPU (1.0e-16 on
+# [1/10, 1/2], 1.1e-16 on [-1/2, -1/10]): there the bound is that one's root mean square, elsewhere the form in fp64 here.
+RANGES = [(-36, -20, None), (-20, -9, None), (-9, -5, None), (-5, -3, None), (-3, -2, None), (-2, -1, None), (-1, -0.5, 1.37e-16),
+          (-0.5, -0.1, 1.05e-16), (-0.1, -1e-3, 0.99e-16), (-1e-3, 0, 1.08e-16), (0, 1e-3, 1.37e-16), (1e-3, 0.1, 1.22e-16),
+          (0.1, 0.5, 1.02e-16), (0.5, 1, 0.77e-16), (1, 2, None), (2, 4, None), (4, 12, None)]
 
 
-def test_evaluation_error():
-    fit = _fit()
-    wide = np.longdouble
+@pytest.mark.parametrize("lo,hi,bound", RANGES, ids=lambda v: str(v))
+def test_no_further_off_than_the_library_form(fit, gelu, lo, hi, bound):
+    x = np.random.default_rng(3).uniform(lo, hi, 400)
 
-    def fma(a, b, c):
-        return np.float64(wide(a) * wide(b) + wide(c))
+    def true(v):
+        t = Decimal(abs(v))
+        tail = t * fit.scaled_tail(t) * (-t * t / 2).exp()
+        return Decimal(v) - tail if v > 0 else -tail
+    want = [true(float(v)) for v in x]
+    rms = lambda y: np.sqrt(np.mean([float((Decimal(float(a)) - b) / b) ** 2 for a, b in zip(y, want)]))  # noqa: E731
+    if bound is None:
+        bound = rms(0.5 * x * erfc(-x * 0.70710678118654752440))
+    # 400 samples give a root mean square to a few percent
+    assert rms(gelu(x)) <= 1.05 * bound
 
-    q, p = _horner("a", "w"), _horner("e", "r")
-    for x in np.concatenate([np.linspace(-9, 9, 361), [1e-3, -1e-3, 0.0]]):
-        t = np.float64(abs(x))
-        u = np.float64(1) / fma(0.2, t, 1.0)
-        a, w = q[0], u - 0.6875
-        for v in q[1:]:
-            a = fma(a, w, v)
-        s = -0.5 * t * t
-        n = np.rint(s * 1.44269504088896338700e+00)
-        r = fma(n, -1.90821492927058770002e-10, fma(n, -6.93147180369123816490e-01, s))
-        e = p[0]
-        for v in p[1:]:
-            e = fma(e, r, v)
-        tq = t * (a * u * np.ldexp(e, int(n)))
-        got = x - tq if x >= 0 else -tq
-        true = fit.tail(float(t), [0.0])[1] if t > 0 else Decimal(0)
-        want = Decimal(float(x)) - true if x >= 0 else -true
-        assert abs(float(Decimal(float(got)) - want)) <= 2.3e-16 * max(abs(x), 0.25), x
+
+def test_far_out_and_no_numbers(gelu):
+    x = np.array([0.0, 13.0, 39.9, 40.0, 1e10, 1e300, np.inf])
+    np.testing.assert_array_equal(gelu(x), x)
+    assert (gelu(-x[3:6]) == 0).all() and -1e-313 < gelu(np.array([-38.0]))[0] < 0
+    assert np.isnan(gelu(np.array([-np.inf, np.nan]))).all()
