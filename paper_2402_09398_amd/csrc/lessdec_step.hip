@@ -15,9 +15,12 @@ constexpr int step_ahead(int w) { return w == 8 || sizeof(T) == 2 ? 8 : 2; }
 template <typename T>
 constexpr int step_waves_per_simd(int nit, int w, bool parts)
 {
-  // (with the maps' last activation in the kernel a wave less where the registers would not reach: a kernel that spills even
-  // eight bytes starts two microseconds later)
-  const int n = nit == 0 ? (step_ahead<T>(w) == 8 ? 4 : parts ? 6 : 8) : nit <= 2 ? 6 : nit <= 7 ? (parts ? 4 : 5) : nit <= 11 ? 3 : 2;
+  // The loop's small blocks live from many waves: eight a SIMD also with the maps' last activation in the kernel, for which the compiler
+  // has to be held to 80 scalar registers (a SIMD has 800, given out in sixteens, and sixteen more to every wave).  With 85 of
+  // them, seven waves: 2048 units x 1000 slots, fp32, 380 us a step without the activation, 428; with eight 373.
+  // With the activation, fp16 forms of up to seven turns take a wave less: a kernel that spills even eight bytes starts two
+  // microseconds later.
+  const int n = nit == 0 ? (step_ahead<T>(w) == 8 ? 4 : 8) : nit <= 4 ? 6 : nit <= 7 ? (parts && sizeof(T) == 2 ? 4 : 5) : nit <= 11 ? 3 : 2;
   return w == 4 ? n : n < w / 4 ? w / 4 : n / (w / 4) * (w / 4);         // whole blocks
 }
 

@@ -141,3 +141,37 @@ def test_prompt_rows_past_the_end_are_in_the_range_check(assembly):
         elif op.startswith("s_") and operands[0].startswith("s"):
             written[operands[0]] = op
     assert loads
+
+
+def resident_waves(lines):
+    """kernel -> (waves a SIMD holds of it, scratch bytes): vector registers by the compiler's own count; a SIMD's 800 scalar registers
+    are given out in sixteens, with sixteen more to every wave."""
+    found, name, scalar, scratch = {}, None, 0, 0
+    for line in lines:
+        word = line.split()
+        if len(word) == 2 and word[0] == ".amdhsa_kernel":
+            name = word[1]
+        elif line.startswith("; TotalNumSgprs:"):
+            scalar = int(word[-1])
+        elif line.startswith("; ScratchSize:"):
+            scratch = int(word[-1])
+        elif line.startswith("; Occupancy:"):
+            found[name] = (min(int(word[-1]), 800 // ((scalar + 15) // 16 * 16 + 16)), scratch)
+    return found
+
+
+def test_the_step_that_finishes_the_maps_keeps_its_waves(assembly):
+    """The any-shape step with the maps' last activation in it has as many waves a SIMD as without, and no scratch memory."""
+    waves = {k: v for k, v in resident_waves(assembly("lessdec_step.hip")).items() if "11step_kernel" in k}
+    compared = 0
+    for kernel, (n, scratch) in waves.items():
+        m = re.search(r"step_kernelI(f|6__half)Li(\d+)ELi(\d+)ELi(\d+)ELb1E", kernel)
+        if not m:
+            continue
+        storage, d, turns, w = m.group(1), *map(int, m.groups()[1:])
+        without, spilled = waves[kernel.replace("ELb1E", "ELb0E")]
+        assert scratch <= spilled, kernel
+        if storage == "f" or turns != 7:              # (fp16, seven turns: see step_waves_per_simd)
+            assert n >= without, (kernel, n, without)
+            compared += 1
+    assert compared >= 20
