@@ -426,7 +426,10 @@ __global__ __launch_bounds__(kGqsMaxHeads * kWave, FUSED ? 4 : 1) void gqs_step_
     Cand best = cand_none();
 #pragma unroll
     for (int i = 0; i < NR2; ++i) na_[i] = 0.0;
-    for (int h = 0; h < G; ++h) {                            // in head order
+    // In head order, four at a time: eight of four rows a lane are more registers than anything else here needs, and left 129 to 256
+    // rows two waves a SIMD where three fit (2048 units x 4 heads x 150 slots 62.5 us a step, now 54.5; D = 64 49.4 and 40.2).
+#pragma unroll 4
+    for (int h = 0; h < G; ++h) {
 #pragma unroll
       for (int i = 0; i < NR2; ++i) {
         const int j = lane + i * kWave;
@@ -590,9 +593,9 @@ template <int D, int RM>
 static hipError_t launch_step_gqs_h(const StepArgs &a, int G, hipStream_t st, const MlpPartsArgs *fm)
 {
   // Four heads a wave (a row is widened once for them, a stream is a quarter of the rows) where that leaves none idle, or the
-  // launch is small.  A step, four against two: 512 units x 4 heads x 400 slots 31.3 and 39.2, 16 x 4 x 204 18.2 and 20.9, 1024 x
-  // 4 x 102 at rank 16 32.6 and 35.2, 512 x 8 x 150 34.9 and 38.4; of 3 heads 256 x 102 14.4 and 15.6, 1024 x 60 22.7 and 21.6;
-  // 96 x 5 x 150 19.5 and 20.7, 512 x 6 x 102 26.7 and 23.9.  (The one launch has the registers for two, and its shapes
+  // launch is small.  A step, four against two: 512 units x 4 heads x 400 slots 33.0 and 41.8, 16 x 4 x 204 17.3 and 20.6, 1024 x
+  // 4 x 102 at rank 16 32.8 and 35.1, 512 x 8 x 150 33.1 and 36.7; of 3 heads 256 x 102 13.6 and 14.9, 1024 x 60 23.1 and 22.3;
+  // 96 x 5 x 150 18.5 and 20.6, 512 x 6 x 102 27.2 and 24.5.  (The one launch has the registers for two, and its shapes
   // take two as two launches as well: the same bits either way.)
   const bool four = !gqs_fusable(D, a.C, a.Rp, a.R, G) && G > 2 && (G % 4 == 0 || (long)a.U * (G > 4 ? 8 : 4) <= kGqsFourWaves);
   return four ? launch_step_gqs_t<D, RM, 4>(a, G, st, fm) : launch_step_gqs_t<D, RM, 2>(a, G, st, fm);
@@ -601,7 +604,9 @@ static hipError_t launch_step_gqs_h(const StepArgs &a, int G, hipStream_t st, co
 hipError_t launch_step_gqs(const StepArgs &a, int G, int D, hipStream_t st, const MlpPartsArgs *fm)
 {
   if (fm && !gqs_fusable(D, a.C, a.Rp, a.R, G)) return hipErrorInvalidValue;
-  if (D == 64) return launch_step_gqs_h<64, 16>(a, G, st, fm);
+  // (Up to rank 8 with that many rows of H and W3: at D = 64 the form for 16 of them holds three waves a SIMD, this one four, without which
+  // 1024 units of three heads do not run at once; x 30 slots 19.6 against 15.8 us a step, x 60 20.8 against 17.2.)
+  if (D == 64) return a.R <= 8 ? launch_step_gqs_h<64, 8>(a, G, st, fm) : launch_step_gqs_h<64, 16>(a, G, st, fm);
   return a.R <= 8 ? launch_step_gqs_h<128, 8>(a, G, st, fm) : launch_step_gqs_h<128, 16>(a, G, st, fm);
 }
 
