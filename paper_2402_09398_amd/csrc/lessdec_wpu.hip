@@ -283,21 +283,17 @@ __global__ __launch_bounds__((FUSED && !(SPLIT && NR2 > 2) ? kWpuFusedUnits : kW
       }
     };
     // The feature maps from their layer-2 sums.
-    auto finish_phi = [&]() {
-      double sq = 0.0;
+    auto sum_parts = [&](const float (&x)[NP]) {             // in part order
+      double sum = 0.0;
 #pragma unroll
       for (int p = 0; p < NP; ++p)
-        if (p < nparts) sq += (double)pq[p];
-      for (int p = NP; p < nparts; ++p)                    // hidden widths above 512 (never FUSED)
-        sq += (double)a.mlp_parts[((size_t)u * 2 * nparts + p) * rp + rl];
+        if (p < nparts) sum += (double)x[p];
+      return sum;
+    };
+    auto finish_phi = [&](double sq) {
       f_lane = lane < R ? fabs(gelu_poly_f64(sq)) : 0.0;   // last activation of Eq. 1
     };
-    auto finish_psi = [&]() {
-      double sk = 0.0;
-#pragma unroll
-      for (int p = 0; p < NP; ++p)
-        if (p < nparts) sk += (double)pk[p];
-      for (int p = NP; p < nparts; ++p) sk += (double)a.mlp_parts[(((size_t)u * 2 + 1) * nparts + p) * rp + rl];
+    auto finish_psi = [&](double sk) {
       const double h2 = gelu_poly_f64(sk);                 // lane r < R; Eq. 2: |W3 gelu(.)|
       double acc3 = 0.0;
 #pragma unroll
@@ -318,16 +314,52 @@ __global__ __launch_bounds__((FUSED && !(SPLIT && NR2 > 2) ? kWpuFusedUnits : kW
       key_pass(base);
       if constexpr (SPLIT && NR2 <= 4) request_parts();
     } else {
-      int base = 0;
-      do {                                                 // nitp >= DEPTH
-        key_pass(base);
-        // The parts have been back for a while (they were requested before the loads this pass
-        // re-issued): finish both feature maps here, where nothing is waiting for anything.
-        if (base == 0) {
-          if (out_wave || book_wave) finish_phi();
-          if (psi_wave) finish_psi();
+      // The parts are back behind the first pass (they were requested before the loads that it re-issues).
+      double sq = 0.0, sk = 0.0;
+      auto add_parts = [&]() {
+        sq = sum_parts(pq);
+        sk = sum_parts(pk);
+        // Hidden widths above 512: four more of both maps at a time, since whoever looks at one waits for all that is in flight.  (Part by
+        // part, 1024 units x 102 slots at R' = 2048 take 30.8 us a step, map by map as well 33.3; so 27.1.)
+        constexpr int kMore = 4;
+        for (int first = NP; first < nparts; first += kMore) {
+          const float *eq = a.mlp_parts + ((size_t)u * 2 * nparts + first) * rp, *ek = eq + (size_t)nparts * rp;
+          float xq[kMore], xk[kMore];
+#pragma unroll
+          for (int p = 0; p < kMore; ++p) {
+            const unsigned at = (unsigned)((first + p < nparts ? p : 0) * rp + rl);
+            xq[p] = eq[at];
+            xk[p] = ek[at];
+          }
+#pragma unroll
+          for (int p = 0; p < kMore; ++p) {
+            if (first + p < nparts) {
+              sq += (double)xq[p];
+              sk += (double)xk[p];
+            }
+          }
         }
-      } while ((base += DEPTH) < nitp);
+      };
+      auto finish_maps = [&]() {
+        if (out_wave || book_wave) finish_phi(sq);
+        if (psi_wave) finish_psi(sk);
+      };
+      // Outside the loop: inside, the constants of the activations take thirty registers all through it.  Waves that share a unit, short of
+      // others to run beside them, finish the maps while the rows of the first pass's requests are on their way; a wave per unit, of
+      // which there are many, has no copy of a pass for that (which costs it thirteen registers).
+      int base = 0;
+      if constexpr (SPLIT) {
+        key_pass(0);                                       // nitp >= DEPTH
+        add_parts();
+        finish_maps();
+        for (base = DEPTH; base < nitp; base += DEPTH) key_pass(base);
+      } else {
+        do {
+          key_pass(base);
+          if (base == 0) add_parts();
+        } while ((base += DEPTH) < nitp);
+        finish_maps();
+      }
     }
 
   if constexpr (!FUSED && !SPLIT) request_tail();
@@ -410,9 +442,9 @@ __global__ __launch_bounds__((FUSED && !(SPLIT && NR2 > 2) ? kWpuFusedUnits : kW
         request_parts();
         have = have_all();
       }
-      if (psi_wave) finish_psi();
+      if (psi_wave) finish_psi(sum_parts(pk));
       if (!out_wave && !book_wave) return;                 // (from this part)
-      finish_phi();
+      finish_phi(sum_parts(pq));
       if constexpr (!SPLIT) request_tail();
     }
     if constexpr (SPLIT) request_scores();                   // (one wave stores the new ones, and looks at these)
