@@ -39,11 +39,10 @@ constexpr int kGqsParts = 8;        // feature maps taken as parts up to this ma
 // and hand their results to the attention waves through the exchange array, as in the one-wave-
 // per-unit kernel (wpu_step_kernel): an entry no job has written yet holds kMlpEmpty, jobs write
 // through with device-scope stores, waves read with device-scope loads, ask again while any entry
-// is empty (bounded by kGqsSpinLimit polls, then the NaNs of the empty entries show in the unit's
+// is empty (bounded by poll_limit, then the NaNs of the empty entries show in the unit's
 // outputs), and hand the entries back empty with their other stores.  Workgroups are dispatched in
 // index order and a job waits for nothing, so no cycle of waits exists.  A job is four waves: a
 // block of four query heads runs one job, a block of eight two.
-constexpr int kGqsSpinLimit = 1 << 14;
 // GH: query heads of a wave, and waves that share a unit's rows
 template <int D, int NR2, int RM, int DEPTH, int GH, bool FUSED>
 __global__ __launch_bounds__(kGqsMaxHeads * kWave, FUSED ? 4 : 1) void gqs_step_kernel(
@@ -298,8 +297,9 @@ __global__ __launch_bounds__(kGqsMaxHeads * kWave, FUSED ? 4 : 1) void gqs_step_
         return __all(missing == 0u) != 0;
       };
       bool have = have_all();
-      for (int spin = 0; !have && spin < kGqsSpinLimit; ++spin) {
-        __builtin_amdgcn_s_sleep(4);
+      constexpr int kSleep = 4;
+      for (int spin = 0; !have && spin < poll_limit(kSleep); ++spin) {
+        __builtin_amdgcn_s_sleep(kSleep);
         request_parts();
         have = have_all();
       }

@@ -9,6 +9,10 @@ namespace lessdec {
 
 typedef unsigned int u4v __attribute__((ext_vector_type(4)));
 
+// Polls of the feature-map entries, with s_sleep(sleep) of 64 x sleep cycles ahead of each, before a wave gives up: the sleeps alone add
+// up to 2^25 cycles (16 ms at 2.1 GHz), however short one of them is; the ways to memory come on top.
+constexpr int poll_limit(int sleep) { return (1 << 19) / sleep; }
+
 // ---- cross-lane helpers (DPP within 16-lane rows, readlane across rows) -------------------
 template <int CTRL>
 __device__ inline int dpp_mov(int x)

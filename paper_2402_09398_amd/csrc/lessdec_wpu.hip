@@ -12,7 +12,6 @@ constexpr int kWpuUnits = 8;        // units (waves) per block, at most
 constexpr int kWpuMaxRows = 512;    // C + 1 at most
 constexpr int kWpuSplitWaves = 3072; // a unit's rows are split over more waves while the launch stays below this many
 constexpr int kWpuFusedUnits = 4;   // FUSED: units (waves) per block, the size of a feature-map job
-constexpr int kWpuSpinLimit = 1 << 14;   // FUSED: polls of the feature-map entries before a wave gives up
 
 // =====================================================================================
 // A block is up to 8 waves = 8 units that share a head (4 when FUSED): consecutive batch rows of
@@ -76,7 +75,7 @@ constexpr int kWpuSpinLimit = 1 << 14;   // FUSED: polls of the feature-map entr
 // while any is still empty, and puts kMlpEmpty back with its other stores, so that the array is
 // all empty again when the step ends.  (The form that gets its entries from a launch before it,
 // !FUSED, empties them as well: either form can follow the other on one workspace.)  A wave that
-// has polled kWpuSpinLimit times gives up and computes with the empty entries, which are NaN: the
+// has polled poll_limit times gives up and computes with the empty entries, which are NaN: the
 // outputs of its unit then show it.
 // =====================================================================================
 template <int D, int NR2, int RM, int DEPTH, bool SPLIT, bool FUSED>
@@ -437,8 +436,9 @@ __global__ __launch_bounds__((FUSED && !(SPLIT && NR2 > 2) ? kWpuFusedUnits : kW
       // (the first look stands outside the loop: a look at the loop's head would have to wait
       // for whatever the loop body may have requested, which is everything in flight)
       bool have = have_all();
-      for (int spin = 0; !have && spin < kWpuSpinLimit; ++spin) {
-        __builtin_amdgcn_s_sleep(SPLIT ? 4 : 32);
+      constexpr int kSleep = SPLIT ? 4 : 32;
+      for (int spin = 0; !have && spin < poll_limit(kSleep); ++spin) {
+        __builtin_amdgcn_s_sleep(kSleep);
         request_parts();
         have = have_all();
       }

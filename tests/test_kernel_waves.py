@@ -17,3 +17,21 @@ def test_query_heads_that_share_a_unit(assembly):  # noqa: F811
             assert n >= (3 if rows == 4 else 4) and scratch == 0, (kernel, n, scratch)
             seen.add((d, rows, heads))
     assert len(seen) == 6
+
+
+def test_a_wave_waits_for_its_entries_as_long_at_any_interval(assembly):  # noqa: F811
+    """Every loop that asks for feature-map entries of its own launch sleeps 2^14 x 32 x 64 cycles before the wave gives up, give or take two
+    polls, and is bounded."""
+    loops = 0
+    for source in ("lessdec_wpu.hip", "lessdec_gqs.hip"):
+        lines = assembly(source)
+        for at, line in enumerate(lines):
+            if (sleep := re.match(r"\s*s_sleep (\d+)", line)) is None:
+                continue
+            end = next(i for i in range(at, len(lines)) if "s_cbranch" in lines[i])
+            bound = [int(m.group(1), 0) for x in lines[at:end] if (m := re.match(r"\s*s_cmpk?_gt_u32 s\d+, (\w+)", x))]
+            assert len(bound) == 1, (source, at)
+            cycles = 64 * int(sleep.group(1)) * bound[0]
+            assert abs(cycles - 2 ** 25) <= 2 * 64 * int(sleep.group(1)), (source, at, cycles)
+            loops += 1
+    assert loops >= 8
