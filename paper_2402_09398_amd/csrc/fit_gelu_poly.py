@@ -1,11 +1,12 @@
-"""Derives the constants of gelu_fast_f32() in lessdec_common.h.
+"""Derives the constants of gelu_poly_f64() in lessdec_common.h.
 
 Upper tail of the standard normal, Q(t) = 0.5 erfc(t / sqrt 2), t >= 0, is written as
 Q(t) = exp(-t^2 / 2) * sum_{k=1..7} c_k u^k with u = 1 / (1 + p t): exp(t^2/2) Q(t) is a smooth,
 slowly decaying function of t and a low-degree polynomial in u captures it to 1e-9.  Then
 gelu(x) = x - |x| Q(|x|) for x >= 0 and -|x| Q(|x|) for x < 0.  Weighted least squares on a
 dense grid (the weight is the factor exp(-t^2/2) t that multiplies the polynomial's error in
-gelu).  Prints p, c_1..c_7 and the error of a float32 evaluation against float64 erfc.
+gelu).  Prints p, c_1..c_7 and the error of a float32 evaluation against float64 erfc, the measure
+of the form below.
 
 And those of gelu_exp2_f32(): log2 Q(t) = c_0 + c_1 s + ... + c_10 s^10, s = t - 1, so that gelu takes one base-2
 exponential and no reciprocal: near-minimax (Lawson's reweighted least squares) in the relative error of Q, which may
@@ -35,7 +36,7 @@ def _fma(a, b, c):
 
 
 def gelu32(x, p, c):
-    """With the reciprocal, as a kernel evaluates it."""
+    """With the reciprocal, in fp32: what gelu_exp2_f32 is measured by."""
     x = x.astype(np.float32)
     c = [np.float32(v) for v in c]
     t = np.abs(x)

@@ -139,29 +139,6 @@ __device__ inline double gelu_f64(double x)
   return t < 40.0 ? near : x >= 0.0 ? x : x * 0.0;
 }
 
-// Branch-free fp32 GELU for the matrix-core feature maps.  With t = |x| the upper normal
-// tail is Q(t) = exp(-t^2/2) * (c1 u + ... + c7 u^7), u = 1 / (1 + 0.24 t) (polynomial error
-// 1e-9; constants from fit_gelu_poly.py), and gelu(x) = x - t Q(t) for x >= 0, -t Q(t) else.
-// Absolute error in fp32: 2.5e-7 on [-4, 4], one ulp of x beyond.  (No kernel uses it.)
-__device__ inline float gelu_fast_f32(float x)
-{
-  const float t = fabsf(x);
-  const float u = __builtin_amdgcn_rcpf(fmaf(0.24f, t, 1.0f));
-  float a = -1.2459717568e-01f;
-  a = fmaf(a, u, 5.5222350684e-01f);
-  a = fmaf(a, u, -6.4138824846e-01f);
-  a = fmaf(a, u, 6.2064721284e-01f);
-  a = fmaf(a, u, -1.5113306584e-01f);
-  a = fmaf(a, u, 1.5460257740e-01f);
-  a = fmaf(a, u, 8.9645194151e-02f);
-  a *= u;
-  const float e = __builtin_amdgcn_exp2f(t * t * -0.72134752044448170368f);   // exp(-t^2/2)
-  const float tq = t * (a * e);
-  // max(x, 0) on the bits: one instruction, where fmaxf quiets its input in another (a NaN stays one through tq)
-  const int xi = __builtin_bit_cast(int, x);
-  return __builtin_bit_cast(float, xi > 0 ? xi : 0) - tq;
-}
-
 // The fp32 GELU of the matrix-core feature maps' hidden layers, branch-free and with one transcendental: with t = |x| the upper
 // normal tail is Q(t) = 2^p(t), log2 Q being smooth enough for a polynomial of degree 10 (fit_gelu_poly.py), and
 // gelu(x) = max(x, 0) - t 2^p(t).  p is written about t = 1, where it is small, so that the roundings of Horner's scheme stay below
