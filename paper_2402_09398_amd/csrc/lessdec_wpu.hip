@@ -742,6 +742,7 @@ static hipError_t launch_step_wpu_s(const StepArgs &a, int upb, hipStream_t st, 
   } while (0)
   if (rows <= 2 * kWave) LESSDEC_WPU_LAUNCH(2);
   else if (rows <= 4 * kWave) LESSDEC_WPU_LAUNCH(4);
+  else if constexpr (FUSED && !SPLIT) return hipErrorInvalidValue;   // (wpu_fusable: not with so many rows)
   else LESSDEC_WPU_LAUNCH(kWpuMaxRows / kWave);
 #undef LESSDEC_WPU_LAUNCH
   return hipGetLastError();

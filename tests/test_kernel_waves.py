@@ -35,3 +35,11 @@ def test_a_wave_waits_for_its_entries_as_long_at_any_interval(assembly):  # noqa
             assert abs(cycles - 2 ** 25) <= 2 * 64 * int(sleep.group(1)), (source, at, cycles)
             loops += 1
     assert loops >= 8
+
+
+def test_every_form_of_the_streaming_step_can_be_launched(assembly):  # noqa: F811
+    """A wave per unit with the maps in the launch: no more than 256 rows, head_dim 128."""
+    forms = {tuple(map(int, m.groups())) for x in assembly("lessdec_wpu.hip")
+             if (m := re.search(r"\.amdhsa_kernel \S*wpu_step_kernelILi(\d+)ELi(\d+)ELi(\d+)ELi\d+ELb(\d)ELb(\d)E", x))}
+    assert {(d, rows) for d, rows, _, split, fused in forms if fused and not split} == {(128, 2), (128, 4)}
+    assert {rows for _, rows, _, split, fused in forms if not fused} == {2, 4, 8}
