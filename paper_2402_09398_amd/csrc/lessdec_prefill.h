@@ -58,7 +58,7 @@ struct RowArgs {
   const MaskedArgs *masked;  // or NULL: all causal pairs
   const MlpArgs *maps;       // psi of the keys in the same launch (rows_f16_take_maps), or NULL
 };
-bool rows_f16_take_maps(const MlpArgs &maps, unsigned U, int G);
+bool rows_f16_take_maps(const MlpArgs &maps);
 hipError_t launch_rows_f16(const RowArgs &a, int D, hipStream_t st);
 // list == nullptr: every column
 hipError_t launch_columns_f16(const void *Q, const void *K, unsigned U, int G, int P, int D, const double *lse,

@@ -1412,7 +1412,7 @@ static hipError_t launch_prefill_t(const PrefillArgs &a, hipStream_t st)
   fm.x = (const __half *)a.K; fm.W1 = (const __half *)d->Wk1; fm.W2 = (const __half *)d->Wk2;
   fm.W3 = (const __half *)d->Wk3; fm.out = a.psi_all;
   const bool matrix_maps = mlp_mfma_supported(d->dtype, d->head_dim, d->hidden, d->rank);
-  const bool maps_ride = matrix_maps && !masked && rows_f16_take_maps(fm, U, G);
+  const bool maps_ride = matrix_maps && !masked && rows_f16_take_maps(fm);
   auto key_features = [&]() -> hipError_t {
     if (matrix_maps) return launch_mlp(fm, st);
     FeatmapArgs fa;

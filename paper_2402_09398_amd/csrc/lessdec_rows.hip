@@ -527,7 +527,7 @@ static hipError_t launch_rows_t(const RowArgs &a, hipStream_t st)
       (const __half *)a.Q + q, K, (const __half *)a.V + kv, nu * a.G, a.G, a.P, digits, words, a.lse + rows, out, a.zero0 + u,      \
       a.zero1 + u, mk, n_maps ? *a.maps : MlpArgs{}, grid)
     __half *out = a.out != nullptr ? (__half *)a.out + q : nullptr;
-    // (maps ride with at most 8192 workgroups of rows, whose keys are one share)
+    // (maps, of all keys, ride with the first share: they need nothing of its digits)
     const unsigned n_maps = a.maps && u == 0 ? mlp_psi_blocks(*a.maps, kPsiTiles) : 0;
     if (a.masked) {
       if (out != nullptr) LESSDEC_ROWS(true, true, false); else LESSDEC_ROWS(false, true, false);
@@ -545,34 +545,41 @@ static hipError_t launch_rows_t(const RowArgs &a, hipStream_t st)
 
 // Whether psi rides along: it needs nothing of the row pass and is bound by other instructions, so it fills what the longest
 // sweeps leave idle, and a launch is saved; but it reads a head's weights again for every 64 rows, where a launch of its own keeps them
-// in registers (other hidden widths have no such form: riding is 5 % and more faster there).  us of a whole prompt phase, psi
-// in a launch of its own against riding along, units x tokens, R' = 512, rank 8 unless said:
-//   2048 blocks of maps     2048 x 64 193 and 192, 2560 x 40 (1600 blocks) 195 and 186
-//   2560                    1280 x 128 239 and 238, 640 x 256 at rank 16 307 and 303
-//   3072, short sweeps      3072 x 64 268 and 276, 1536 x 128 273 and 278, 768 x 256 313 and 317
-//   4096, short sweeps      4096 x 64 340 and 352, 2048 x 128 330 and 342, 1024 x 256 388 and 397; rank 16 431 and 437; rank 4 384 and
-//                           403; R' = 256 353 and 364
-//   4096, 500 tokens        512 x 512 484 and 481; rank 16 523 and 519; rank 4 479 and 485; R' = 256 448 and 446
-//   4096, long sweeps       256 x 1000 632 and 612 (rank 4 627 and 616), 128 x 2000 971 and 929
-//   6144, long sweeps       384 x 1000 906 and 903 (rank 16 967 and 960; rank 4 898 and 910); R' = 256, 320 x 1100, 819 and 808
-//   8192                    4096 x 128 605 and 648, 1024 x 512 859 and 893, 512 x 1000 1152 and 1163 (rank 16 1220 and 1228), 256 x 2000
-//                           1827 and 1831
-//   D = 64: 2048            2048 x 64 140 and 132
-//   4096                    2048 x 128 248 and 246, 1024 x 256 288 and 286, 512 x 512 361 and 350, 256 x 1000 474 and 448
-//   8192                    4096 x 128 454 and 465, 1024 x 512 639 and 641 (R' = 256 585 and 587), 512 x 1000 860 and 847
-//   more than 8192 workgroups  2048 x 400 1227 and 1265, 2048 x 1024 4530 and 4610 (both with a longer activation, 17 instructions for 12.5)
-// (256 units x 4 heads x 500: 646 and 627)
-bool rows_f16_take_maps(const MlpArgs &maps, unsigned U, int G)
+// in registers.  So it rides up to a number of workgroups of maps that grows with the sweeps' length, and that is smaller where the launch
+// of its own has less to lose: narrower weights, and ranks whose blocks of eight features hold padding.  How many query heads share the
+// unit makes no difference to that number.  Gain in percent of a whole prompt phase with psi riding along over psi in a launch of its own, by
+// workgroups of 64 rows in a sweep; "|": the line.
+//   D = 128, R' = 512, rank 8 and 16, 2048 + 256 a workgroup of the sweep:
+//     1   2048 1.3 | 3072 -1.7, 4096 -2.8, 8192 -5.3            rank 16: 2048 2.1 | 2560 0.3, 3072 -1.5, 4096 -2.8
+//     2   2048 2.7, 2560 0.1 | 3072 -0.7, 4096 -2.8             rank 16: 2048 3.0 | 4096 -1.9
+//     4   2048 3.4, 3072 0.1 | 4096 -1.6, 8192 -3.5             rank 16: 2048 3.8, 3072 0.1 | 4096 -1.3
+//     8   2048 7.8, 3072 3.7, 4096 1.1 | 6144 -0.6, 8192 -2.0   rank 16: 2048 7.6, 4096 1.4 | 8192 -2.4
+//     16  2048 10.0, 4096 2.6, 6144 0.7 to 1.6 | 8192 -0.5, 12288 -2.2
+//     32  2048 10.6, 4096 4.2, 8192 0.8, 10240 0.1 | 12288 -0.6        rank 16: 4096 4.5, 8192 0.7
+//     64  8192 1.5 | 12288 -0.5          128  8192 0.6 | 12288 -1.0, 16384 0.2
+//   others of D = 128, 1536 + 256 (R' = 256; rank 4; R' = 128):
+//     1   | 2048 -1.6; -1.5; -0.6, 3072 -3.4; -4.5; -2.5        2   2048 0.0; -0.2; 0.9 | 2560 -2.6; -2.7
+//     4   2048 2.1; 1.0; 2.4, 2560 0.0; -0.9; 1.0 | 3072 -1.8; -2.6; -0.6
+//     8   2048 6.6; 5.5; 7.5 | 4096 0.0; -1.2; 1.6, 8192 -2.9; -4.8; -0.9
+//     16  | 6144 0.6; -0.4, 10240 -1.3; -3.1                    32  2048 7.0; 10.5; 5.5, 8192 0.8; -0.1; 1.5 | 10240 -0.1; -0.7
+//   D = 64, R' = 512, rank 8 and 16, 6144 + 512:
+//     1   2048 5.7, 4096 1.6 | 8192 -0.4, 12288 -1.1 (rank 16: 8.0, 5.2 | 2.9)     4   2048 6.6, 8192 0.6 | 12288 -0.1
+//     8   2048 10.8, 8192 2.0 | 12288 1.0                       32  8192 3.2, 12288 1.9
+//   others of D = 64, 2560 + 512 (R' = 256; rank 4; R' = 128):
+//     1   2048 3.2; 2.7; 2.1 | 4096 -1.4; -1.0; -1.5            4   2048 4.2; 4.7; 2.7, 4096 0.1; 0.5; -0.4 | 8192 -2.8; -2.4; -3.2
+//     8   4096 3.8; 3.9; 3.9 | 8192 -0.8; -0.3; -0.6            16  8192 1.2 | 12288 -0.2      32  8192 2.4; 2.1; 2.7, 12288 2.2
+// With 2, 4 and 8 query heads, D = 128: 4096 in sweeps of 32 2.5, 2.2, -; 2048 in sweeps of 8 5.3, 2.9, 1.9; 8192 in sweeps of 16 -0.2, 0.3.
+// Other hidden widths, and few rows of a head, have no such form: riding is faster at every number with D = 128 (R' = 96, 320, 1024: 2.7 to
+// 5.6 at 4096 and 8192, 1.1 to 3.0 at 16384 and 24576), with D = 64 up to 8192 (16384: R' = 96 -1.1, R' = 1024 -2.4).
+bool rows_f16_take_maps(const MlpArgs &maps)
 {
-  const int ngrp = (maps.rpu + 16 * kPrefillWaves - 1) / (16 * kPrefillWaves);
-  if ((size_t)U * G * ngrp > 8192) return false;
-  if (!mlp_weights_in_registers(maps)) return true;
-  const bool full = maps.R % 8 == 0;                      // of a block's columns of features none is padding
-  unsigned most;
-  if (maps.D == 64) most = ngrp > 8 ? 8192 : ngrp == 8 || maps.Rp > 256 ? 4096 : 2048;
-  else if (ngrp >= 8) most = ngrp > 8 && full ? 6144 : 4096;
-  else most = full && maps.Rp == 512 ? 2560 : 2048;
-  return mlp_psi_blocks(maps, kPsiTiles) <= most;
+  const unsigned blocks = mlp_psi_blocks(maps, kPsiTiles);
+  if (!mlp_weights_in_registers(maps)) return maps.D == 128 || blocks <= 8192;
+  const unsigned sweep = (unsigned)((maps.rpu + 16 * kPrefillWaves - 1) / (16 * kPrefillWaves));
+  const bool whole = maps.Rp > 384 && maps.R % 8 == 0;     // the widest weights, no padding among a block's features
+  const unsigned most = maps.D == 128 ? (whole ? 2048 : 1536) + 256 * sweep : (whole ? 6144 : 2560) + 512 * sweep;
+  const unsigned measured = maps.D == 128 ? 10240 : 12288;
+  return blocks <= (most < measured ? most : measured);
 }
 
 hipError_t launch_rows_f16(const RowArgs &a, int D, hipStream_t st)

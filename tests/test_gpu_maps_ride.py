@@ -6,19 +6,21 @@ the rule's line.
 import pytest
 
 from tests import harness as hz
+from tests.maps_rule import rides
 from tests.test_gpu_digits import shape
 
 pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("head_dim,rank,hidden,heads,prompt,batches", [
-    (128, 4, 128, 8, 64, (256, 257)),                    # 2048 blocks of 64 rows ride, more do not
-    (128, 8, 512, 16, 130, (126, 127)),                  # 4096 at R' = 512 and rank 8, ragged rows
-    (128, 12, 512, 8, 500, (64, 66)),                    # 4096 with sweeps of eight workgroups
-    (64, 8, 256, 8, 70, (234, 235)),
+    (128, 4, 128, 8, 64, (224, 225)),                    # one workgroup a sweep
+    (128, 8, 512, 16, 130, (86, 87)),                    # the widest weights, ragged rows
+    (128, 12, 512, 8, 500, (57, 58)),                    # features with padding, sweeps of eight workgroups
+    (64, 8, 256, 8, 70, (409, 410)),
 ])
 def test_both_sides_of_the_line(head_dim, rank, hidden, heads, prompt, batches):
     import torch
+    assert [rides(b, heads, prompt, head_dim, hidden, rank) for b in batches] == [True, False]
     g = torch.Generator(device="cuda").manual_seed(4)
     x = {n: torch.randn(max(batches), heads, prompt, head_dim, generator=g, device="cuda").half() for n in "QKV"}
     res = []
