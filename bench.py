@@ -291,7 +291,7 @@ def main():
                      "kernel": ("wpu_step_kernel" + (" (one launch per step: feature-map jobs and attention waves)"
                                                      if one_launch else " + mlp_parts_kernel (two launches per step)")
                                 if w.q_per_kv == 1 else
-                                ("gqs_step_kernel (one launch per step: feature-map jobs and a wave per two or four query heads)"
+                                ("gqs_step_kernel (one launch per step: feature-map jobs; two or four waves share as many query heads and split the rows)"
                                  if launches == 1 else f"grouped-head step kernel + feature-map kernel ({launches} launches per step)")),
                      "launches_per_step": launches,
                      "bytes_per_launch": bytes_per_step, "ms_per_launch": ms_per_step,

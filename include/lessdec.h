@@ -196,8 +196,8 @@ int lessdec_prefill(const lessdec_desc *desc, const void *Q, const void *K, cons
  * prescribes.  With LESSDEC_FLAG_LAMBDA the discarded pair is instead the oldest one that is
  * neither among the first n_heavy tokens of the sequence nor among the n_recent most recent.
  * With q_per_kv = G > 1: q and out are [B,Hh,G,D] (k, v stay [B,Hh,D]).  Up to 8 query heads
- * with fp16 storage run on a streaming kernel (a block per unit, a wave per two or four query heads) that
- * leaves the discarded pair pending like the single-head path; other shapes on a plain kernel
+ * with fp16 storage run on a streaming kernel (a block per unit; two or four waves share two or four query heads and
+ * split the unit's rows between them) that leaves the discarded pair pending like the single-head path; other shapes on a plain kernel
  * that folds the discarded pair at once.
  */
 int lessdec_step(const lessdec_desc *desc, const void *q, const void *k, const void *v,

@@ -107,8 +107,8 @@ hipError_t launch_step_gqa(const StepArgs &a, int G, int dtype, int D, hipStream
 constexpr int kGqaMaxHeadBlocks = 8;
 int gqa_head_blocks(long units, int G);
 hipError_t launch_state_sync(const StepArgs &a, int dtype, int D, hipStream_t st);
-// several query heads per unit, streaming form: one block per unit, a wave per two or four query heads
-// (lessdec_gqs.hip); leaves the discarded pair pending like the single-head streaming path
+// several query heads per unit, streaming form: one block per unit, two or four waves share two or four query heads and split the
+// unit's rows (lessdec_gqs.hip); leaves the discarded pair pending like the single-head streaming path
 bool gqs_supported(int dtype, int D, int C, int R, int G);
 // whether that kernel finishes the feature maps itself from the parts of launch_mlp_parts_gq
 // (StepArgs::mlp_parts set) instead of taking them complete (f_phi32, f_psi)

@@ -22,9 +22,14 @@ constexpr int kWpuFusedUnits = 4;   // FUSED: units (waves) per block, the size 
 // load of each stream.  They meet twice: when the scores are complete, and when the partial outputs are, which one wave
 // adds in wave order and finishes.  In between every wave works out the exponentials for itself; the rest of phase 2 is
 // shared out, since one wave alone issues an instruction every nine cycles and a few hundred of them were half of the step:
-// waves 0 and 1 work out the denominator, then wave 0 phi(q) H and the output and wave 1 the bookkeeping, the choice of the
-// discarded pair and its stores; wave 2 finishes psi of the new key, wave 3 folds the pending pair into H and z.  What one
-// wave stores and another loads is back in its registers before they first meet.  32 units x 204 slots, a step: 13.5 ->
+//   waves 0 and 1  the denominator; then wave 0 phi(q) H and the output, wave 1 the bookkeeping, the choice of the discarded
+//                  pair and the stores of both
+//   psi of the new key and its stores  wave 2; wave 1 where there are two
+//   the pending pair folded into H and z, and their stores  kTailEarly: wave 3, wave 1 where there are two; else (rank above 8
+//                  at D = 128, or more than 256 rows: no registers for H through the keys) wave 0
+// What a wave stores, every other wave that uses it has back in its registers before they first meet (H, z, psi of the
+// pending slot, the pending value row), or no other wave uses: accumulated scores and positions, requested behind that meeting, only
+// wave 1, H without kTailEarly only wave 0.  The entries go back empty behind the second meeting.  32 units x 204 slots, a step: 13.5 ->
 // 10.3 us (entries asked for behind the keys, where a wave that came too early slept a microsecond, and shared out: 10.9;
 // exponentials and bookkeeping without branches, row groups combined by lane swaps, partial outputs read at once: 10.3);
 // 512 x 408 24.2 -> 23.5, 256 x 102 11.8 -> 9.9, 640 x 162 at rank 16 27.9 -> 24.0.)
@@ -71,9 +76,9 @@ constexpr int kWpuFusedUnits = 4;   // FUSED: units (waves) per block, the size 
 // The layer-2 sums travel through the exchange array as 32-bit entries, written through by the
 // jobs and read with device-scope loads.  An entry that no job has written yet holds kMlpEmpty:
 // an attention wave requests its entries before the last pass of the key stream (by then the jobs
-// are normally long done), looks at them after the first pass of the value stream, asks again
-// while any is still empty, and puts kMlpEmpty back with its other stores, so that the array is
-// all empty again when the step ends.  (The form that gets its entries from a launch before it,
+// are normally long done; SPLIT with up to 256 rows: behind it), looks at them after the first pass of the value stream,
+// asks again while any is still empty, and puts kMlpEmpty back with its other stores (SPLIT: the wave of psi, behind the waves'
+// last meeting), so that the array is all empty again when the step ends.  (The form that gets its entries from a launch before it,
 // !FUSED, empties them as well: either form can follow the other on one workspace.)  A wave that
 // has polled poll_limit times gives up and computes with the empty entries, which are NaN: the
 // outputs of its unit then show it.
@@ -220,7 +225,8 @@ __global__ __launch_bounds__((FUSED && !(SPLIT && NR2 > 2) ? kWpuFusedUnits : kW
   // consecutive columns (those the reduce-scatter of phase 3 leaves it with) of every NHB-th
   // row, so that one 16-byte load per lane covers NHB whole rows of H per instruction.
   // (A single wave asks behind the keys, FUSED inside phase 2, once the feature-map entries have given their registers back.
-  // Waves that share a unit must have before they meet what others store the new state of after that.)
+  // Waves that share a unit ask with kTailEarly here, to have H back before they meet, since one wave then stores what two use; else
+  // with the denominator, where wave 0 alone uses and stores it.)
   constexpr int NHB = RPI / 2, HR = RM / NHB;
   const int col0 = lr * EPL + ((lane & LPR) ? 4 : 0);
   const int hb = lane / (2 * LPR);                           // which rows: r = NHB * i + hb
@@ -364,8 +370,8 @@ __global__ __launch_bounds__((FUSED && !(SPLIT && NR2 > 2) ? kWpuFusedUnits : kW
   if constexpr (!FUSED && !SPLIT) request_tail();
   if constexpr (SPLIT) {
     // What a wave stores must not overtake another wave's loads of the same state: have
-    // those loads back before the waves meet (the value rows requested after them stay in
-    // flight), then meet with the scores visible.
+    // the loads whose values a wave uses and another stores back before the waves meet (the value rows requested after
+    // them stay in flight), then meet with the scores visible.
     if constexpr (kTailEarly) {
 #pragma unroll
       for (int i = 0; i < HR; ++i) asm volatile("" ::"v"(hreg[i].x), "v"(hreg[i].y), "v"(hreg[i].z), "v"(hreg[i].w));
