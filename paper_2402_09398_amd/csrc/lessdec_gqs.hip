@@ -45,7 +45,7 @@ constexpr int kGqsParts = 8;        // feature maps taken as parts up to this ma
 // block of four query heads runs one job, a block of eight two.
 // GH: query heads of a wave, and waves that share a unit's rows
 template <int D, int NR2, int RM, int DEPTH, int GH, bool FUSED>
-__global__ __launch_bounds__(kGqsMaxHeads * kWave, FUSED ? 4 : 1) void gqs_step_kernel(
+__global__ __launch_bounds__(kGqsMaxHeads * kWave, FUSED || DEPTH == 4 ? 4 : 1) void gqs_step_kernel(
     void *k_cache_, const void *q_, const void *k_, int C_, int G_, int n_mlp, const void *Wq1_, const void *Wk1_,
     const void *Wq2_, const StepArgs a)
 {
@@ -579,12 +579,16 @@ static hipError_t launch_step_gqs_t(const StepArgs &a, int G, hipStream_t st, co
     }
   }
   const unsigned grid = (unsigned)a.U;
-#define LESSDEC_GQS_LAUNCH(NR2)                                                                                   \
-  gqs_step_kernel<D, NR2, RM, kDepth, GH, false><<<grid, block, lds, st>>>(a.k_cache, a.q, a.k, a.C, G, 0, nullptr, nullptr, \
-                                                                           nullptr, a)
-  if (rows <= 2 * kWave) LESSDEC_GQS_LAUNCH(2);
-  else if (rows <= 4 * kWave) LESSDEC_GQS_LAUNCH(4);
-  else LESSDEC_GQS_LAUNCH(kGqsMaxRows / kWave);
+  // (Ranks above 8 at D = 64, two heads a wave, few rows: a ring of four leaves the registers for four waves a SIMD, where seven deep three
+  // are there and 880 units of three heads do not run at once.  x 41 slots 26.0 against 23.3 us a step; 2000 x 2 x 41 29.2 and 24.7, 4000 x
+  // 2 x 120 55.8 and 50.9, 1200 x 6 x 120 67.9 and 51.6.)
+  constexpr int kFewDepth = D == 64 && RM == 16 && GH == 2 ? 4 : kDepth;
+#define LESSDEC_GQS_LAUNCH(NR2, DEPTH)                                                                            \
+  gqs_step_kernel<D, NR2, RM, DEPTH, GH, false><<<grid, block, lds, st>>>(a.k_cache, a.q, a.k, a.C, G, 0, nullptr, nullptr, \
+                                                                          nullptr, a)
+  if (rows <= 2 * kWave) LESSDEC_GQS_LAUNCH(2, kFewDepth);
+  else if (rows <= 4 * kWave) LESSDEC_GQS_LAUNCH(4, kDepth);
+  else LESSDEC_GQS_LAUNCH(kGqsMaxRows / kWave, kDepth);
 #undef LESSDEC_GQS_LAUNCH
   return hipGetLastError();
 }

@@ -22,3 +22,13 @@ def test_many_units():
     w = shape((65, 4), 3, 150, head_dim=64, steps=4)
     rep = hz.run_workload(w, [0, 5, w.units - 1])
     assert rep.ok(), rep.failures[:10]
+
+
+@pytest.mark.parametrize("g", [2, 3, 5, 6])
+@pytest.mark.parametrize("slots,rank", [(3, 9), (33, 16), (63, 12), (64, 16), (65, 10), (126, 16)])
+def test_ring_of_four(g, slots, rank):
+    """Ranks above 8 and up to 128 rows: two heads a wave in most of these; 32 rows of a unit make a pass of a wave of two."""
+    w = shape((65, 4) if g > 2 else (2, 3), g, slots, rank=rank, head_dim=64, steps=5)
+    rep = hz.run_workload(w, sorted({0, 1, w.units // 2, w.units - 1}))
+    print("\n" + rep.summary(), flush=True)
+    assert rep.ok(), rep.failures[:10]

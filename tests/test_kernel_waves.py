@@ -5,7 +5,7 @@ from tests.test_kernel_asm import assembly, resident_waves  # noqa: F401  (a fix
 
 
 def test_query_heads_that_share_a_unit(assembly):  # noqa: F811
-    """Two launches, rank up to 8: three waves for 129 to 256 rows, as many as a wave per head and row had; four for fewer rows and two heads a
+    """Two launches; rank up to 8, and any rank at D = 64 with two heads a wave and up to 128 rows: three waves for 129 to 256 rows, as many as a wave per head and row had; four for fewer rows and two heads a
     wave, so that the blocks of 1024 units are there at once."""
     seen = set()
     for kernel, (n, scratch) in resident_waves(assembly("lessdec_gqs.hip")).items():
@@ -13,10 +13,10 @@ def test_query_heads_that_share_a_unit(assembly):  # noqa: F811
         if not m:
             continue
         d, rows, rank, heads = map(int, m.groups())
-        if rank == 8 and (rows == 4 or (rows == 2 and heads == 2)):
+        if (rank == 8 and (rows == 4 or (rows == 2 and heads == 2))) or (d, rows, heads) == (64, 2, 2):
             assert n >= (3 if rows == 4 else 4) and scratch == 0, (kernel, n, scratch)
-            seen.add((d, rows, heads))
-    assert len(seen) == 6
+            seen.add((d, rows, heads, rank))
+    assert len(seen) == 7
 
 
 def test_a_wave_waits_for_its_entries_as_long_at_any_interval(assembly):  # noqa: F811
