@@ -442,7 +442,9 @@ __global__ __launch_bounds__((FUSED && !(SPLIT && NR2 > 2) ? kWpuFusedUnits : kW
       // (the first look stands outside the loop: a look at the loop's head would have to wait
       // for whatever the loop body may have requested, which is everything in flight)
       bool have = have_all();
-      constexpr int kSleep = SPLIT ? 4 : 32;
+      // (Small caches, whose waves are here before the jobs are done, a step: 1344 units x 6 slots 13.4 us asleep for 2048 cycles at a
+      // time, 12.6 for 256; 1408 x 8 15.4 and 14.0; 1920 x 120 at rank 16 39.7 and 38.0; 2048 x 102, whose waves find them, 26.6 and 26.7.)
+      constexpr int kSleep = 4;
       for (int spin = 0; !have && spin < poll_limit(kSleep); ++spin) {
         __builtin_amdgcn_s_sleep(kSleep);
         request_parts();

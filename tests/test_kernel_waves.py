@@ -21,7 +21,7 @@ def test_query_heads_that_share_a_unit(assembly):  # noqa: F811
 
 def test_a_wave_waits_for_its_entries_as_long_at_any_interval(assembly):  # noqa: F811
     """Every loop that asks for feature-map entries of its own launch sleeps 2^14 x 32 x 64 cycles before the wave gives up, give or take two
-    polls, and is bounded."""
+    polls, and is bounded; no sleep is longer than 256 cycles, which is what a wave may come too late by."""
     loops = 0
     for source in ("lessdec_wpu.hip", "lessdec_gqs.hip"):
         lines = assembly(source)
@@ -31,6 +31,7 @@ def test_a_wave_waits_for_its_entries_as_long_at_any_interval(assembly):  # noqa
             end = next(i for i in range(at, len(lines)) if "s_cbranch" in lines[i])
             bound = [int(m.group(1), 0) for x in lines[at:end] if (m := re.match(r"\s*s_cmpk?_gt_u32 s\d+, (\w+)", x))]
             assert len(bound) == 1, (source, at)
+            assert int(sleep.group(1)) <= 4, (source, at)
             cycles = 64 * int(sleep.group(1)) * bound[0]
             assert abs(cycles - 2 ** 25) <= 2 * 64 * int(sleep.group(1)), (source, at, cycles)
             loops += 1
